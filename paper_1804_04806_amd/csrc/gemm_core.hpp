@@ -62,7 +62,8 @@ struct Tile {
     static constexpr int WN = BN / (32 * WAVES_N);
     static constexpr int LDA = BM + kPad, LDB = BN + kPad;
     static constexpr int LDS_FLOATS = kBK * (LDA + LDB);
-    static_assert(WAVES_M * WAVES_N == 4, "four wavefronts per workgroup");
+    static constexpr int THREADS = 64 * WAVES_M * WAVES_N;
+    static_assert(THREADS == 256 || THREADS == 512, "four or eight wavefronts per workgroup");
     static_assert(WM >= 1 && WN >= 1, "tile too small for the wave layout");
 };
 
@@ -216,13 +217,13 @@ struct GatherParams {
 // NOMASK: every tap of every tile position lies inside the tensor (a layer without padding): the
 // per-thread offset is used as it is, and a row past the end of the reduction is pushed out of
 // range through the scalar offset: no vector instruction per element at all.
-template <int TD, bool SMALL, class E = float, bool NOMASK = false>
+template <int TD, bool SMALL, class E = float, bool NOMASK = false, int NTHR = kThreads>
 struct GatherNLaneT : NoSetup {
     static constexpr uint32_t EB = Elem<E>::kBytes;
     static constexpr bool kBf16 = std::is_same<E, bf16>::value;
     static std::string name() { return std::string(NOMASK ? "GatherNLane<no padding>" : SMALL ? "GatherNLane<taps<=31>" : "GatherNLane<taps>31>") + Elem<E>::tag(); }
     static_assert(TD >= 64, "a wave must cover one reduction row");
-    static constexpr int RP = kThreads / TD;  // reduction rows per pass
+    static constexpr int RP = NTHR / TD;  // reduction rows per pass
     static constexpr int NE = kBK / RP;       // elements per thread per step
     static constexpr int LD = TD + kPad;
     // A thread takes a block of NE consecutive rows of the step (NE*row0 + i): their decode is
@@ -404,12 +405,12 @@ struct KLaneParams {
 // Dense matrix, element (kk, j) = t[kk*row_stride + j*col_stride]  (operand limit 2 GiB).
 // One VGPR of address state: the thread's (kl, c0) offset; the step and the position index i enter
 // as scalar offsets.
-template <int TD, class E = float>
+template <int TD, class E = float, int NTHR = kThreads>
 struct KLane0T : NoSetup {
     static constexpr uint32_t EB = Elem<E>::kBytes;
     static constexpr bool kBf16 = std::is_same<E, bf16>::value;
     static std::string name() { return std::string("KLane0") + Elem<E>::tag(); }
-    static constexpr int CP = kThreads / kBK;  // tile positions per pass (16)
+    static constexpr int CP = NTHR / kBK;  // tile positions per pass (16)
     static constexpr int NE = TD / CP;
     static constexpr int LD = TD + kPad;
     struct Regs { float r[NE]; };
@@ -663,12 +664,12 @@ struct PhaseFilterKLaneT : NoSetup {
 // The x loader reuses the pixel decode its peer (the dy loader of the same step) has just done.
 // NOMASK (x of a layer without padding: every tap of every pixel is inside the image): no masks, one
 // address addition per element.
-template <int TD, bool WINDOW, class E = float, bool NOMASK = false>
+template <int TD, bool WINDOW, class E = float, bool NOMASK = false, int NTHR = kThreads>
 struct PixelKLane : NoSetup {
     static constexpr uint32_t EB = Elem<E>::kBytes;
     static constexpr bool kBf16 = std::is_same<E, bf16>::value;
     static std::string name() { return std::string(!WINDOW ? "PixelKLane<dy>" : NOMASK ? "PixelKLane<x, no padding>" : "PixelKLane<x>") + Elem<E>::tag(); }
-    static constexpr int CP = kThreads / kBK;
+    static constexpr int CP = NTHR / kBK;
     static constexpr int NE = TD / CP;
     static constexpr int LD = TD + kPad;
     static constexpr int NV = WINDOW ? NE : 1;
@@ -765,7 +766,7 @@ template <int TD> using XKLaneFree = PixelKLane<TD, true, float, true>;
 // it refilled when they are used up), instead of once per step per thread.  Per step a thread then reads its entry (two LDS reads for x, one for dy) and spends three
 // vector instructions per x element (mask shift, address add, merge) and none per dy element.
 constexpr int kTabRows = 1024;
-constexpr int kTabCap = kTabRows + 2 * kBK;  // the pipeline looks two steps past the chunk's end
+constexpr int kTabCap = kTabRows + 3 * kBK;  // the pipelines look two or three steps past the chunk's end
 
 struct PixelTable {
     uint32_t dy_off[kTabCap];   // byte offset of (n, a, b) in dy, or kOob for rows past the end
@@ -773,12 +774,12 @@ struct PixelTable {
     uint32_t tapmask[kTabCap];  // bit r*S+s set = tap outside the image; bit 31 always set
 };
 
-template <int TD, class E = float>
+template <int TD, class E = float, int NTHR = kThreads>
 struct PixelTabX {
     static constexpr uint32_t EB = Elem<E>::kBytes;
     static constexpr bool kBf16 = std::is_same<E, bf16>::value;
     static std::string name() { return std::string("PixelTab<x>") + Elem<E>::tag(); }
-    static constexpr int CP = kThreads / kBK;
+    static constexpr int CP = NTHR / kBK;
     static constexpr int NE = TD / CP;
     static constexpr int LD = TD + kPad;
     typedef PixelTable Shared;
@@ -828,7 +829,7 @@ struct PixelTabX {
         k_begin_ = k_begin;
         const KLaneParams &q = *peer.p;
 #pragma unroll 1
-        for (int e = threadIdx.x; e < kTabCap; e += kThreads) {
+        for (int e = threadIdx.x; e < kTabCap; e += NTHR) {
             const int kk = k_begin + e;
             uint32_t n, rest, a, b;
             p->grid_hw.divmod((uint32_t)kk, n, rest);
@@ -868,12 +869,12 @@ struct PixelTabX {
     }
 };
 
-template <int TD, class E = float>
+template <int TD, class E = float, int NTHR = kThreads>
 struct PixelTabDy : NoSetup {
     static constexpr uint32_t EB = Elem<E>::kBytes;
     static constexpr bool kBf16 = std::is_same<E, bf16>::value;
     static std::string name() { return std::string("PixelTab<dy>") + Elem<E>::tag(); }
-    static constexpr int CP = kThreads / kBK;
+    static constexpr int CP = NTHR / kBK;
     static constexpr int NE = TD / CP;
     static constexpr int LD = TD + kPad;
     struct Regs { float r[NE]; };
@@ -1245,6 +1246,131 @@ __device__ __forceinline__ void write_tile(const typename Epi::Params &pe, const
 }
 
 // ---- the kernel --------------------------------------------------------------------------------
+// acc = A[m0.., k_begin..k_end) * B[k_begin..k_end), n0..] on the fp32 matrix pipe, for the whole workgroup.
+// INTERLEAVED: how a wave's MFMA tiles along M share its rows (see write_tile).  The parameters come by value: through
+// references the compiler keeps branches on them inside the main loop (32-row BackwardData 15.4 -> 18.5 us).
+template <class T, class ALoader, class BLoader, bool INTERLEAVED = true, class AParams, class BParams>
+__device__ __forceinline__ void fp32_tile(const AParams pa, const BParams pb, float (&lds)[2][T::LDS_FLOATS],
+                                          typename ALoader::Shared &sha, typename BLoader::Shared &shb, int m0, int M,
+                                          int n0, int N, int k_begin, int k_end, int wm0, int wn0, int l32, int lhi,
+                                          f32x16 (&acc)[T::WM][T::WN])
+{
+    ALoader la;
+    BLoader lb;
+    la.init(pa, m0, M);
+    lb.init(pb, n0, N);
+    la.setup(sha, k_begin, k_end, lb);
+    lb.setup(shb, k_begin, k_end, la);
+    if constexpr (ALoader::kHasShared || BLoader::kHasShared) __syncthreads();
+
+#pragma unroll
+    for (int i = 0; i < T::WM; ++i)
+#pragma unroll
+        for (int j = 0; j < T::WN; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+
+    typename ALoader::Regs ra;
+    typename BLoader::Regs rb;
+
+    // Software pipeline, two tiles deep with one register set: during step s (MFMAs on tile s from
+    // one LDS buffer) the registers holding tile s+1, loaded during step s-1, are written to the
+    // other LDS buffer and immediately reloaded with tile s+2.  That work is dealt out over the 8
+    // k-pairs of the step, so that each wave always has MFMAs in flight while it issues its loads
+    // and LDS writes (a wave that issued them in one block would leave the matrix pipe idle unless
+    // another wave happened to be in its MFMA phase).
+    constexpr int NA = ALoader::NE, NB = BLoader::NE, kGroups = kBK / 2;
+    // wave row of MFMA row r of tile i = kRowMul * r + kTileMul * i
+    constexpr int kRowMul = INTERLEAVED ? T::WM : 1, kTileMul = INTERLEAVED ? 1 : 32;
+    la.prep(k_begin, k_end, lb);
+    lb.prep(k_begin, k_end, la);
+#pragma unroll
+    for (int i = 0; i < NA; ++i) la.load(i, ra.r);
+#pragma unroll
+    for (int i = 0; i < NB; ++i) lb.load(i, rb.r);
+#pragma unroll
+    for (int i = 0; i < NA; ++i) la.store(lds[0], i, ra.r);
+#pragma unroll
+    for (int i = 0; i < NB; ++i) lb.store(lds[0] + kBK * T::LDA, i, rb.r);
+    la.prep(k_begin + kBK, k_end, lb);
+    lb.prep(k_begin + kBK, k_end, la);
+#pragma unroll
+    for (int i = 0; i < NA; ++i) la.load(i, ra.r);
+#pragma unroll
+    for (int i = 0; i < NB; ++i) lb.load(i, rb.r);
+    __syncthreads();
+
+    int buf = 0;
+    for (int k0 = k_begin; k0 < k_end; k0 += kBK) {
+        if constexpr (ALoader::kHasShared || BLoader::kHasShared) {
+            // LDS tables hold kTabRows reduction rows (plus the two tiles of lookahead, already
+            // fetched from the old contents): refill them at every multiple of that
+            if (k0 != k_begin && ((k0 - k_begin) & (kTabRows - 1)) == 0) {
+                __syncthreads();
+                la.setup(sha, k0, k_end, lb);
+                lb.setup(shb, k0, k_end, la);
+                __syncthreads();
+            }
+        }
+        // the lane's operands of row 0; every other read is an immediate offset from here (an address of its own would
+        // be computed behind an MFMA, which a vector instruction waits for)
+        const float *Al = lds[buf] + (lhi * T::LDA + wm0 + kRowMul * l32);
+        const float *Bl = lds[buf] + (kBK * T::LDA + lhi * T::LDB + wn0 + l32);
+        float *An = lds[buf ^ 1];
+        float *Bn = lds[buf ^ 1] + kBK * T::LDA;
+        // operands of the next k-pair are read from LDS before the MFMAs of the current one issue
+        float a[2][T::WM], b[2][T::WN];
+#pragma unroll
+        for (int i = 0; i < T::WM; ++i) a[0][i] = Al[kTileMul * i];
+#pragma unroll
+        for (int j = 0; j < T::WN; ++j) b[0][j] = Bl[j * 32];
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_setprio(UCD_MFMA_PRIO);  // a wave inside its MFMA run keeps the pipe
+#pragma unroll
+        for (int kk = 0; kk < kBK; kk += 2) {
+            const int g = kk >> 1, cur = g & 1, nxt = cur ^ 1;
+            constexpr int NM = T::WM * T::WN;
+            // each piece of memory work issues behind one MFMA, in the shadow of its 16 passes
+#pragma unroll
+            for (int m = 0; m < NM; ++m) {
+                const int mi = m / T::WN, mj = m % T::WN;
+                acc[mi][mj] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[cur][mi], b[cur][mj], acc[mi][mj], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (m == 0 && kk == 0) {  // per-step loader state, needed by the loads further down
+                    la.prep(k0 + 2 * kBK, k_end, lb);
+                    lb.prep(k0 + 2 * kBK, k_end, la);
+                }
+                if (m == 0 && kk + 2 < kBK) {
+#pragma unroll
+                    for (int i = 0; i < T::WM; ++i) a[nxt][i] = Al[(kk + 2) * T::LDA + kTileMul * i];
+#pragma unroll
+                    for (int j = 0; j < T::WN; ++j) b[nxt][j] = Bl[(kk + 2) * T::LDB + j * 32];
+                }
+                if (m == 1 % NM) {
+#pragma unroll
+                    for (int i = 0; i < NA; ++i)
+                        if (i * kGroups / NA == g) {
+                            la.store(An, i, ra.r);
+                            la.load(i, ra.r);
+                        }
+                }
+                if (m == 2 % NM) {
+#pragma unroll
+                    for (int i = 0; i < NB; ++i)
+                        if (i * kGroups / NB == g) {
+                            lb.store(Bn, i, rb.r);
+                            lb.load(i, rb.r);
+                        }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        __builtin_amdgcn_s_setprio(0);
+        __syncthreads();
+        buf ^= 1;
+    }
+}
+
 // grid.x = tiles_m * tiles_n (XCD-remapped), grid.y = reduction splits (chunk `k_chunk`, a multiple
 // of BK), grid.z = batch of independent GEMMs (loaders/epilogue see pointers advanced by the
 // given element strides).
@@ -1289,118 +1415,8 @@ __global__ __launch_bounds__(kThreads) void gemm_kernel(AParams pa, BParams pb, 
         const int m0 = wi.m0, n0 = wi.n0, k_begin = wi.k_begin, k_end = wi.k_end;
         const bool accumulate = wi.accumulate;
 
-        ALoader la;
-        BLoader lb;
-        la.init(pa, m0, M);
-        lb.init(pb, n0, N);
-        la.setup(sha, k_begin, k_end, lb);
-        lb.setup(shb, k_begin, k_end, la);
-        if constexpr (ALoader::kHasShared || BLoader::kHasShared) __syncthreads();
-
         f32x16 acc[T::WM][T::WN];
-#pragma unroll
-        for (int i = 0; i < T::WM; ++i)
-#pragma unroll
-            for (int j = 0; j < T::WN; ++j)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-
-        typename ALoader::Regs ra;
-        typename BLoader::Regs rb;
-
-        // Software pipeline, two tiles deep with one register set: during step s (MFMAs on tile s from
-        // one LDS buffer) the registers holding tile s+1, loaded during step s-1, are written to the
-        // other LDS buffer and immediately reloaded with tile s+2.  That work is dealt out over the 8
-        // k-pairs of the step, so that each wave always has MFMAs in flight while it issues its loads
-        // and LDS writes (a wave that issued them in one block would leave the matrix pipe idle unless
-        // another wave happened to be in its MFMA phase).
-        constexpr int NA = ALoader::NE, NB = BLoader::NE, kGroups = kBK / 2;
-        la.prep(k_begin, k_end, lb);
-        lb.prep(k_begin, k_end, la);
-#pragma unroll
-        for (int i = 0; i < NA; ++i) la.load(i, ra.r);
-#pragma unroll
-        for (int i = 0; i < NB; ++i) lb.load(i, rb.r);
-#pragma unroll
-        for (int i = 0; i < NA; ++i) la.store(lds[0], i, ra.r);
-#pragma unroll
-        for (int i = 0; i < NB; ++i) lb.store(lds[0] + kBK * T::LDA, i, rb.r);
-        la.prep(k_begin + kBK, k_end, lb);
-        lb.prep(k_begin + kBK, k_end, la);
-#pragma unroll
-        for (int i = 0; i < NA; ++i) la.load(i, ra.r);
-#pragma unroll
-        for (int i = 0; i < NB; ++i) lb.load(i, rb.r);
-        __syncthreads();
-
-        int buf = 0;
-        for (int k0 = k_begin; k0 < k_end; k0 += kBK) {
-            if constexpr (ALoader::kHasShared || BLoader::kHasShared) {
-                // LDS tables hold kTabRows reduction rows (plus the two tiles of lookahead, already
-                // fetched from the old contents): refill them at every multiple of that
-                if (k0 != k_begin && ((k0 - k_begin) & (kTabRows - 1)) == 0) {
-                    __syncthreads();
-                    la.setup(sha, k0, k_end, lb);
-                    lb.setup(shb, k0, k_end, la);
-                    __syncthreads();
-                }
-            }
-            const float *As = lds[buf];
-            const float *Bs = lds[buf] + kBK * T::LDA;
-            float *An = lds[buf ^ 1];
-            float *Bn = lds[buf ^ 1] + kBK * T::LDA;
-            // operands of the next k-pair are read from LDS before the MFMAs of the current one issue
-            float a[2][T::WM], b[2][T::WN];
-#pragma unroll
-            for (int i = 0; i < T::WM; ++i) a[0][i] = As[lhi * T::LDA + wm0 + T::WM * l32 + i];
-#pragma unroll
-            for (int j = 0; j < T::WN; ++j) b[0][j] = Bs[lhi * T::LDB + wn0 + j * 32 + l32];
-            __builtin_amdgcn_sched_barrier(0);
-            __builtin_amdgcn_s_setprio(UCD_MFMA_PRIO);  // a wave inside its MFMA run keeps the pipe
-#pragma unroll
-            for (int kk = 0; kk < kBK; kk += 2) {
-                const int g = kk >> 1, cur = g & 1, nxt = cur ^ 1;
-                constexpr int NM = T::WM * T::WN;
-                // each piece of memory work issues behind one MFMA, in the shadow of its 16 passes
-#pragma unroll
-                for (int m = 0; m < NM; ++m) {
-                    const int mi = m / T::WN, mj = m % T::WN;
-                    acc[mi][mj] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[cur][mi], b[cur][mj], acc[mi][mj], 0, 0, 0);
-                    __builtin_amdgcn_sched_barrier(0);
-                    if (m == 0 && kk == 0) {  // per-step loader state, needed by the loads further down
-                        la.prep(k0 + 2 * kBK, k_end, lb);
-                        lb.prep(k0 + 2 * kBK, k_end, la);
-                    }
-                    if (m == 0 && kk + 2 < kBK) {
-#pragma unroll
-                        for (int i = 0; i < T::WM; ++i) a[nxt][i] = As[(kk + 2 + lhi) * T::LDA + wm0 + T::WM * l32 + i];
-#pragma unroll
-                        for (int j = 0; j < T::WN; ++j) b[nxt][j] = Bs[(kk + 2 + lhi) * T::LDB + wn0 + j * 32 + l32];
-                    }
-                    if (m == 1 % NM) {
-#pragma unroll
-                        for (int i = 0; i < NA; ++i)
-                            if (i * kGroups / NA == g) {
-                                la.store(An, i, ra.r);
-                                la.load(i, ra.r);
-                            }
-                    }
-                    if (m == 2 % NM) {
-#pragma unroll
-                        for (int i = 0; i < NB; ++i)
-                            if (i * kGroups / NB == g) {
-                                lb.store(Bn, i, rb.r);
-                                lb.load(i, rb.r);
-                            }
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-            __builtin_amdgcn_s_setprio(0);
-            __syncthreads();
-            buf ^= 1;
-        }
-
+        fp32_tile<T, ALoader, BLoader>(pa, pb, lds, sha, shb, m0, M, n0, N, k_begin, k_end, wm0, wn0, l32, lhi, acc);
         write_tile<T, Epi>(pe, acc, M, N, m0, n0, wm0, wn0, l32, lhi, accumulate);
         if (!tail_wg || !next_tail_item<T>(wi, tail_it, tail_end, whole_tiles, tail.ksteps, tiles_m, Kd)) break;
     }
@@ -1966,17 +1982,17 @@ __global__ __launch_bounds__(kThreads) void gemm_kernel_bf16v(AParams pa, BParam
 
 // Zero-fills the outputs of the last `tail_tiles` tiles through the epilogue's own index mapping.
 template <class T, class Epi>
-__global__ __launch_bounds__(kThreads) void zero_tiles_kernel(typename Epi::Params pe, int M, int N, int tiles_m,
+__global__ __launch_bounds__(T::THREADS) void zero_tiles_kernel(typename Epi::Params pe, int M, int N, int tiles_m,
                                                               int tiles_n, int tail_tiles)
 {
     const int t = tiles_m * tiles_n - tail_tiles + (int)blockIdx.x;
     const int m0 = (t % tiles_m) * T::BM, n0 = (t / tiles_m) * T::BN;
-    static_assert(kThreads % T::BN == 0, "a row of the tile per thread group");
+    static_assert(T::THREADS % T::BN == 0, "a row of the tile per thread group");
     const int col = n0 + (int)threadIdx.x % T::BN;  // lanes along the columns: contiguous stores
     if (col >= N) return;
     Epi epi;
     if (!epi.prep(pe, col)) return;
-    for (int r = threadIdx.x / T::BN; r < T::BM; r += kThreads / T::BN) {
+    for (int r = threadIdx.x / T::BN; r < T::BM; r += T::THREADS / T::BN) {
         const int row = m0 + r;
         if (row < M) epi.store(pe, row, 0.f);
     }

@@ -3,6 +3,7 @@
 #include <string>
 
 #include "gemm_core.hpp"
+#include "gemm_split.hpp"
 #include "kernels.h"
 
 namespace ucd {
@@ -54,10 +55,12 @@ template <class T, template <int> class AL, template <int> class BL, class Epi, 
 hipError_t launch_tile(const AP &pa, const BP &pb, const typename Epi::Params &pe, const GemmShape &g,
                        hipStream_t s)
 {
-    constexpr bool kVecLoads = vec_run<BL<T::BN>>(0);  // the bf16 kernel with vector operand loads
+    constexpr bool kVecLoads = vec_run<BL<loader_tag_n<T>()>>(0);  // the bf16 kernel with vector operand loads
     // both operands bf16 tensors: the kernel on the bf16 matrix pipe (single GEMMs only)
-    constexpr bool kBf16Mfma = AL<T::BM>::kBf16 && BL<T::BN>::kBf16;
-    if (kBf16Mfma && g.batch != 1) return hipErrorInvalidValue;
+    constexpr bool kBf16Mfma = AL<loader_tag_m<T>()>::kBf16 && BL<loader_tag_n<T>()>::kBf16;
+    // fp32 operands on the bf16 matrix pipe (single GEMMs only)
+    constexpr bool kSplit = split_loader<AL<loader_tag_m<T>()>>(0) && split_loader<BL<loader_tag_n<T>()>>(0);
+    if ((kBf16Mfma || kSplit) && g.batch != 1) return hipErrorInvalidValue;
     const int tiles_m = (g.M + T::BM - 1) / T::BM, tiles_n = (g.N + T::BN - 1) / T::BN;
     if (tiles_m <= 0 || tiles_n <= 0) return hipSuccess;
     int k_chunk;
@@ -74,7 +77,7 @@ hipError_t launch_tile(const AP &pa, const BP &pb, const typename Epi::Params &p
         const long tiles = (long)tiles_m * tiles_n;
         const int kCUs = device_cus();
         const int over = (int)(tiles % kCUs);
-        if (g.tail_split && splits == 1 && g.batch == 1 && tiles >= 2 * kCUs && over > 0 && over <= kTailMaxTiles * kCUs / 256) {
+        if (g.tail_split && splits == 1 && g.batch == 1 && tiles >= (T::THREADS == 512 ? 1 : 2) * kCUs && over > 0 && over <= kTailMaxTiles * kCUs / 256) {
             const int ksteps = (g.Kd + kBK - 1) / kBK;
             const long steps = (long)over * ksteps;
             long wgs = steps / kTailMinSteps;
@@ -90,8 +93,9 @@ hipError_t launch_tile(const AP &pa, const BP &pb, const typename Epi::Params &p
     dim3 grid(gx, (unsigned)splits, (unsigned)g.batch);
     if (LaunchLog *log = launch_log()) {
         if (tail.tiles) log->add("zero_tiles_kernel");
-        log->add(std::string(kVecLoads ? "gemm_kernel_bf16v<Tile<" : kBf16Mfma ? "gemm_kernel_bf16<Tile<" : "gemm_kernel<Tile<") + std::to_string(T::BM) + "x" + std::to_string(T::BN) + ">," +
-                 AL<T::BM>::name() + "," + BL<T::BN>::name() + "," + Epi::name() + "> tiles=" +
+        log->add(std::string(kVecLoads ? "gemm_kernel_bf16v<Tile<" : kBf16Mfma ? "gemm_kernel_bf16<Tile<"
+                                       : kSplit ? "gemm_kernel_split<Tile<" : "gemm_kernel<Tile<") + std::to_string(T::BM) + "x" + std::to_string(T::BN) + ">," +
+                 AL<loader_tag_m<T>()>::name() + "," + BL<loader_tag_n<T>()>::name() + "," + Epi::name() + "> tiles=" +
                  std::to_string(tiles_m * tiles_n) + " splits=" + std::to_string(splits) + " batch=" +
                  std::to_string(g.batch) + " M=" + std::to_string(g.M) + " N=" + std::to_string(g.N) + " K=" +
                  std::to_string(g.Kd) +
@@ -99,18 +103,21 @@ hipError_t launch_tile(const AP &pa, const BP &pb, const typename Epi::Params &p
         return hipSuccess;
     }
     if (tail.tiles) {
-        zero_tiles_kernel<T, Epi><<<(unsigned)tail.tiles, kThreads, 0, s>>>(pe, g.M, g.N, tiles_m, tiles_n, tail.tiles);
+        zero_tiles_kernel<T, Epi><<<(unsigned)tail.tiles, T::THREADS, 0, s>>>(pe, g.M, g.N, tiles_m, tiles_n, tail.tiles);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     if constexpr (kVecLoads)
-        gemm_kernel_bf16v<T, AL<T::BM>, BL<T::BN>, Epi, AP, BP><<<grid, kThreads, 0, s>>>(
+        gemm_kernel_bf16v<T, AL<loader_tag_m<T>()>, BL<loader_tag_n<T>()>, Epi, AP, BP><<<grid, kThreads, 0, s>>>(
             pa, pb, pe, g.M, g.N, g.Kd, k_chunk, tiles_m, tiles_n);
     else if constexpr (kBf16Mfma)
-        gemm_kernel_bf16<T, AL<T::BM>, BL<T::BN>, Epi, AP, BP><<<grid, kThreads, 0, s>>>(
+        gemm_kernel_bf16<T, AL<loader_tag_m<T>()>, BL<loader_tag_n<T>()>, Epi, AP, BP><<<grid, kThreads, 0, s>>>(
             pa, pb, pe, g.M, g.N, g.Kd, k_chunk, tiles_m, tiles_n);
+    else if constexpr (kSplit)
+        gemm_kernel_split<T, AL<loader_tag_m<T>()>, BL<loader_tag_n<T>()>, Epi, AP, BP><<<grid, T::THREADS, 0, s>>>(
+            pa, pb, pe, g.M, g.N, g.Kd, k_chunk, tiles_m, tiles_n, tail);
     else
-        gemm_kernel<T, AL<T::BM>, BL<T::BN>, Epi, AP, BP><<<grid, kThreads, 0, s>>>(
+        gemm_kernel<T, AL<loader_tag_m<T>()>, BL<loader_tag_n<T>()>, Epi, AP, BP><<<grid, kThreads, 0, s>>>(
             pa, pb, pe, g.M, g.N, g.Kd, k_chunk, tiles_m, tiles_n, g.a_batch, g.b_batch, g.c_batch, tail);
     return hipGetLastError();
 }
@@ -153,11 +160,45 @@ inline TilePick pick_tile(int M, int N, bool rows96, long mult)
     return t;
 }
 
+// 128 x 256 tiles on eight waves (one workgroup per CU) instead of 128 x 128 on four (two per CU), for the split
+// kernel: a third less staging per MFMA.  With few reduction steps per tile the second resident workgroup's
+// overlap of one's start and the other's end is worth more; and the tiles have to fill most CUs.
+// Measured (us, 128x256 / 128x128): 96->256 5x5 27x27 1090 / 1180, 384->384 3x3 13x13 531 / 583, 64->128 3x3/2 56x56
+// (576 rows) 98 / 107, 128->512 1x1 28x28 (128 rows) 131 / 114; b = 256, 256, 128, 128.
+inline bool wide_shape(int M, int N)
+{
+    return pick_rows(M, true) == 128 && (N + 255) / 256 * 256 <= (N + 127) / 128 * 128 * 17 / 16;
+}
+inline bool wide_tiles_pay(const GemmShape &g)
+{
+    const long tiles = (long)((g.M + 127) / 128) * ((g.N + 255) / 256) * (g.splits < 1 ? 1 : g.splits);
+    const int rows = g.Kd / (g.splits < 1 ? 1 : g.splits);
+    return wide_shape(g.M, g.N) && rows >= 320 && tiles >= device_cus() * 3 / 4;
+}
+// the fp32 kernel's loaders for the operands of split loaders
+template <template <int> class AL>
+struct FallbackOf {
+    template <int TD> using L = typename AL<TD>::Fallback;
+};
+template <class L>
+constexpr auto wide_loader(int) -> decltype(L::kWideTiles) { return L::kWideTiles; }
+template <class L>
+constexpr bool wide_loader(...) { return false; }
+
 template <template <int> class AL, template <int> class BL, class Epi, bool ROWS96 = false, class AP, class BP>
 hipError_t launch_gemm(const AP &pa, const BP &pb, const typename Epi::Params &pe, const GemmShape &g,
                        hipStream_t s)
 {
     const TilePick t = pick_tile(g.M, g.N, ROWS96, (long)(g.splits < 1 ? 1 : g.splits) * g.batch);
+    if constexpr (wide_loader<AL<128>>(0) && wide_loader<BL<128>>(0)) {
+        if (t.bm == 128 && t.bn == 128 && wide_tiles_pay(g)) return launch_tile<Tile<128, 256, 2, 4>, AL, BL, Epi>(pa, pb, pe, g, s);
+    }
+    if constexpr (split_loader<AL<32>>(0) && split_loader<BL<128>>(0)) {
+        // 32 rows: an element of B is split for a single MFMA tile, which costs more vector time than the fp32
+        // instructions take (32 output channels, 144 rows, 16 workgroups: 10.7 against 9.7 us)
+        if (t.bm == 32)
+            return launch_tile<Tile<32, 128, 1, 4>, FallbackOf<AL>::template L, FallbackOf<BL>::template L, Epi>(pa, pb, pe, g, s);
+    }
     if (t.bm == 32) return launch_tile<Tile<32, 128, 1, 4>, AL, BL, Epi>(pa, pb, pe, g, s);
     if (t.bm == 64) {
         if (t.bn == 64) return launch_tile<Tile<64, 64, 2, 2>, AL, BL, Epi>(pa, pb, pe, g, s);

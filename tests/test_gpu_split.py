@@ -1,0 +1,82 @@
+"""fp32 GEMMs on the bf16 matrix pipe (three-way split operands): edges of its tiles, loaders and range handling.
+
+Bounds.  A product of two split operands leaves out terms below 2^-24 of it and accumulates in fp32; over n
+rows the worst relative L2 error that fp32 accumulation in chunks allows is a few 2^-24 * sqrt(n), and the
+kernel is built to stay below what the fp32 matrix instructions give (3e-7 to 1e-6 on these shapes): 1e-6."""
+import numpy as np
+import pytest
+
+from paper_1804_04806_amd import ucd
+from paper_1804_04806_amd.synth import Shape
+from hip_helpers import inputs, rel_l2, run_hip, run_oracle
+
+pytestmark = pytest.mark.gpu
+
+I, MIRROR = ucd.ALGO_IMPLICIT, ucd.ALGO_IMPLICIT_MIRROR
+
+SHAPES = [
+    # Forward / mirrored BackwardData: output channels around each tile height (64, 96, 128; 256 columns),
+    # reductions that end inside a 16-row step, inside a 4-row load and inside a 64-row window
+    Shape(2, 37, 9, 11, 34, 3, 3, 1, 1), Shape(2, 33, 8, 8, 33, 1, 1, 1, 0), Shape(1, 21, 12, 12, 65, 3, 3, 1, 1),
+    Shape(3, 5, 31, 30, 96, 11, 11, 4, 0), Shape(2, 9, 20, 20, 97, 7, 7, 2, 3), Shape(2, 3, 14, 14, 129, 5, 5, 1, 2),
+    Shape(24, 64, 33, 33, 128, 3, 3, 1, 1), Shape(33, 67, 40, 40, 250, 2, 2, 1, 0),
+    # BackwardFilter: images whose pixel count is 1, 2 or 3 above a multiple of 4, one row or column of pixels,
+    # strides 1 to 3, outputs narrower and wider than the input, more than 31 taps, more rows than the pixel table
+    Shape(5, 17, 13, 13, 40, 3, 3, 1, 1), Shape(7, 9, 7, 7, 50, 3, 3, 1, 2), Shape(9, 6, 1, 25, 33, 1, 3, 1, 0),
+    Shape(3, 8, 25, 1, 70, 3, 1, 1, 0), Shape(4, 19, 18, 15, 130, 3, 3, 2, 1), Shape(2, 11, 23, 22, 64, 7, 7, 2, 3),
+    Shape(3, 10, 17, 19, 96, 7, 7, 1, 3), Shape(2, 12, 20, 21, 61, 3, 3, 3, 0), Shape(1, 1, 6, 5, 33, 2, 2, 1, 1),
+    Shape(2, 260, 9, 9, 256, 1, 1, 1, 0),
+]
+
+
+def _id(s):
+    return f"n{s.N}c{s.C}h{s.H}w{s.W}k{s.K}r{s.R}s{s.S}st{s.stride}p{s.pad}"
+
+
+def _runs(s):
+    """Operations whose GEMM has more than 32 rows: those run on the split kernel."""
+    runs = [(ucd.FWD, I), (ucd.BWD_FILTER, I)] if s.K > 32 else []
+    if s.C > 32 and s.stride == 1 and s.pad <= min(s.R, s.S) - 1:
+        runs.append((ucd.BWD_DATA, MIRROR))
+    return runs
+
+
+@pytest.mark.parametrize("s", SHAPES, ids=_id)
+def test_split_gemm_edges(s):
+    x, w, dy = inputs(s, seed=7)
+    for op, algo in _runs(s):
+        assert "gemm_kernel_split" in ucd.ucd_describe_micro(ucd.layer(s), op, algo, s.N)[0]
+        got = run_hip(s, op, [(algo, s.N)], x=x, w=w, dy=dy)
+        ref = run_oracle(s, op, x=x, w=w, dy=dy)
+        assert rel_l2(got, ref) <= 1e-6, (ucd.OP_NAMES[op], rel_l2(got, ref))
+
+
+@pytest.mark.parametrize("s", [SHAPES[1], SHAPES[6], SHAPES[7], SHAPES[10], SHAPES[11]], ids=_id)
+def test_split_gemm_not_finite(s):
+    """Infinities and NaN come out where, and as, fp32 arithmetic gives them; the other outputs stay exact."""
+    x, w, dy = inputs(s, seed=8)
+    finite_dy = dy.copy()
+    x[0, 0, 0, 0], x[-1, -1, -1, -1], dy[0, -1, 0, 0], dy[-1, 0, -1, -1] = np.inf, np.nan, -np.inf, np.nan
+    x[0, 1, 0, 0] = 3.3e38  # finite, but infinite when rounded to bf16
+    for op, algo in _runs(s):
+        # BackwardFilter's kernels multiply dy with the padding's zeros, the oracle skips them
+        g = finite_dy if op == ucd.BWD_FILTER and s.pad else dy
+        got = run_hip(s, op, [(algo, s.N)], x=x, w=w, dy=g).astype(np.float64)
+        ref = run_oracle(s, op, x=x, w=w, dy=g)
+        ref = np.where(np.abs(ref) > np.finfo(np.float32).max, np.sign(ref) * np.inf, ref)
+        fine = np.isfinite(ref)
+        assert not fine.all() and fine.any()
+        assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isposinf(got), np.isposinf(ref))
+        assert np.array_equal(np.isneginf(got), np.isneginf(ref))
+        assert rel_l2(got[fine], ref[fine]) <= 1e-6
+
+
+@pytest.mark.parametrize("scale", [1e-37, 1e-30, 1e30])
+def test_split_gemm_range(scale):
+    """Operands so small that their low parts leave bf16's range, and large ones."""
+    s = SHAPES[8]
+    x, w, dy = inputs(s, seed=9)
+    for op, algo in _runs(s):
+        xs, dys = (x * np.float32(scale), dy) if op != ucd.BWD_DATA else (x, dy * np.float32(scale))
+        got = run_hip(s, op, [(algo, s.N)], x=xs, w=w, dy=dys)
+        assert rel_l2(got, run_oracle(s, op, x=xs, w=w, dy=dys)) <= 1e-6, ucd.OP_NAMES[op]
