@@ -36,6 +36,7 @@ sys.path.insert(0, ROOT)
 METRIC = "conv ms/iter (fwd+bwdData+bwdFilter) @64MB workspace; TFLOP/s, % MFMA peak"
 FP32_MFMA_PEAK_TFLOPS = 157.3   # MI355X dense fp32 matrix peak: 256 CU x 2.4 GHz x 256 flop/clk/CU
 BF16_MFMA_PEAK_TFLOPS = 2500.0  # dense bf16 matrix peak (16x the fp32 rate); kernels named gemm_kernel_bf16
+SPLIT_PEAK_TFLOPS = BF16_MFMA_PEAK_TFLOPS / 6  # fp32 products as six bf16 ones; kernels named *_split*
 WS_LIMIT = 64 << 20
 
 # HBM bytes (fetched + written) per matrix flop of the kernels of the default workload's planned
@@ -338,7 +339,8 @@ def dominant_kernel_roofline(torch, ucd, states, plans, ws, reps, traffic_table=
              for k, g in sorted(groups.items(), key=lambda kv: -kv[1]["ms"])]
     name, g = max(groups.items(), key=lambda kv: kv[1]["ms"])
     achieved = g["flops"] / (g["ms"] * 1e-3) / 1e12
-    peak = BF16_MFMA_PEAK_TFLOPS if name.startswith("gemm_kernel_bf16") else FP32_MFMA_PEAK_TFLOPS
+    peak = (BF16_MFMA_PEAK_TFLOPS if name.startswith("gemm_kernel_bf16") else
+            SPLIT_PEAK_TFLOPS if "_split" in name.split("<")[0] else FP32_MFMA_PEAK_TFLOPS)
     roof = {"bound": "mfma", "kernel": name, "achieved": round(achieved, 2), "peak": peak,
             "unit": "TFLOP/s", "frac": round(achieved / peak, 4),
             "traffic": None,

@@ -189,13 +189,16 @@ size_t winograd_ws_bytes(const Dims &d, int op, int b, int mt)
 // U[xi][ci][co] = (G g G^T)[xi], one thread per (ci, co) filter; pads co up to Mo4 with zeros.
 template <class E, int MT>
 __global__ __launch_bounds__(256) void wino_filter_kernel(const void *__restrict__ w, float *__restrict__ U, int Ci,
-                                                          int Co, int Mo4, int transposed, int Cpad)
+                                                          int Co, int Mo4, int transposed, int Cpad, bool cells)
 {
-    // a plane of U has Cpad >= Ci rows; rows past Ci are written as zeros
+    // a plane of U has Cpad >= Ci rows; rows past Ci are written as zeros.  cells: [ci / 8][co][ci % 8] instead
+    // of [ci][co] (Cpad a multiple of 8)
     constexpr int A = Wino<MT>::A;
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= Cpad * Mo4) return;
-    const int ci = i / Mo4, co = i - ci * Mo4;
+    // threads in the order of U's elements: a plane's stores are contiguous
+    const int row = cells ? i >> 3 : i;
+    const int co = row % Mo4, ci = cells ? row / Mo4 * 8 + (i & 7) : row / Mo4;
     float t[A][3];  // G g, column by column
 #pragma unroll
     for (int s = 0; s < 3; ++s) {
@@ -227,11 +230,12 @@ __global__ __launch_bounds__(256) void wino_filter_kernel(const void *__restrict
 template <class E>
 __global__ __launch_bounds__(256) void wino_phase_filter_kernel(const void *__restrict__ w, float *__restrict__ U,
                                                                 int K, int C, int R, int S, int sh, int sw, int Mo4,
-                                                                int Cpad)
+                                                                int Cpad, bool cells)
 {
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= Cpad * Mo4) return;
-    const int k = i / Mo4, co = i - k * Mo4;
+    const int row = cells ? i >> 3 : i;
+    const int co = row % Mo4, k = cells ? row / Mo4 * 8 + (i & 7) : row / Mo4;
     const int c = co / (sh * sw), pr = co / sw % sh, pc = co % sw;
     const bool live = k < K && c < C;
     float t[4][3];  // G g, column by column
@@ -359,7 +363,7 @@ static hipError_t winograd_run(const Dims &d, int op, int b, const void *in, con
     } else if (log) log->add("wino_filter_kernel");
     else
         wino_filter_kernel<E, MT><<<(unsigned)((g.Ci * g.Mo4 + 255) / 256), 256, 0, s>>>(w, U, g.Ci, g.Co, g.Mo4,
-                                                                                      g.transposed ? 1 : 0, g.Ci);
+                                                                                      g.transposed ? 1 : 0, g.Ci, false);
     hipError_t e = log ? hipSuccess : hipGetLastError();
     if (e != hipSuccess) return e;
 
@@ -1167,6 +1171,10 @@ __global__ __launch_bounds__(512) void wino_fused_bf16_kernel(FusedBf16Params p)
     }
 }
 
+}  // namespace ucd
+#include "wino_split.hpp"
+namespace ucd {
+
 static int fused_ci_pad(const WinoGeom &g) { return (g.Ci + kFuC - 1) / kFuC * kFuC; }
 
 size_t winograd_fused_ws_bytes(const Dims &d, int op)
@@ -1187,6 +1195,13 @@ static hipError_t winograd_fused_run(const Dims &d, int op, int b, const void *i
     static const bool bf16_fp32 = getenv("UCD_FUSED_BF16_FP32") != nullptr;
     const bool bf16_pipe = std::is_same_v<E, bf16> && !bf16_fp32 && g.Hi * g.Wi >= 4;
     const int ci_pad16 = (g.Ci + kBfC - 1) / kBfC * kBfC;
+    static const bool elementwise = getenv("UCD_FUSED_ELEMENTWISE") != nullptr;
+    static const bool fp32_pipe = getenv("UCD_FUSED_FP32") != nullptr;
+    const bool rows = std::is_same_v<E, float> && !elementwise && g.pad_w <= 2;
+    // fp32 tensors with at least 32 input channels: three-way split operands on the bf16 matrix pipe (wino_split.hpp;
+    // UCD_FUSED_FP32=1 in the environment keeps the fp32 instructions).  A rule on the layer alone: micro-batches
+    // of one call share U, whose layout differs.
+    const bool split = rows && !fp32_pipe && g.Ci >= 32;
     if (filter_ready) {
         // U of this filter is still in the workspace from the previous micro-batch
     } else if (log) log->add(phased ? "wino_phase_filter_kernel" : bf16_pipe ? "wino_filter_bf16_kernel" : "wino_filter_kernel");
@@ -1198,10 +1213,10 @@ static hipError_t winograd_fused_run(const Dims &d, int op, int b, const void *i
             w, (uint16_t *)ws, g.Ci, g.Co, g.Mo4, g.transposed ? 1 : 0, ci_pad16);
     else if (phased)
         wino_phase_filter_kernel<E><<<(unsigned)((fused_ci_pad(g) * g.Mo4 + 255) / 256), 256, 0, s>>>(
-            w, ws, d.K, d.C, d.R, d.S, d.sh, d.sw, g.Mo4, fused_ci_pad(g));
+            w, ws, d.K, d.C, d.R, d.S, d.sh, d.sw, g.Mo4, fused_ci_pad(g), split);
     else
         wino_filter_kernel<E, 2><<<(unsigned)((fused_ci_pad(g) * g.Mo4 + 255) / 256), 256, 0, s>>>(
-            w, ws, g.Ci, g.Co, g.Mo4, g.transposed ? 1 : 0, fused_ci_pad(g));
+            w, ws, g.Ci, g.Co, g.Mo4, g.transposed ? 1 : 0, fused_ci_pad(g), split);
     hipError_t e = log ? hipSuccess : hipGetLastError();
     if (e != hipSuccess) return e;
     if (bf16_pipe) {
@@ -1235,17 +1250,27 @@ static hipError_t winograd_fused_run(const Dims &d, int op, int b, const void *i
     // row-vector patch loads: fp32 tensors (UCD_FUSED_ELEMENTWISE=1 in the environment keeps the
     // element-wise loads, for comparison).  With them, the 128 x 32 block wherever 128-channel blocks
     // cover the output channels with no more padding than 64-channel ones (UCD_FUSED_NARROW=1: never).
-    static const bool elementwise = getenv("UCD_FUSED_ELEMENTWISE") != nullptr;
     static const bool narrow = getenv("UCD_FUSED_NARROW") != nullptr;
-    const bool rows = std::is_same_v<E, float> && !elementwise && g.pad_w <= 2;
-    const bool wide = rows && !phased && !narrow && (g.Co + 127) / 128 * 2 <= (g.Co + 63) / 64;
+    const bool wide = rows && !split && !phased && !narrow && (g.Co + 127) / 128 * 2 <= (g.Co + 63) / 64;
     const int kblock = wide ? 128 : kFuK, tblock = wide ? 32 : kFuT;
     p.k_blocks = (g.Co + kblock - 1) / kblock;
     const unsigned blocks = (unsigned)(p.k_blocks * ((p.n_tiles + tblock - 1) / tblock));
     if (log) {
-        log->add(std::string(phased ? "wino_fused_kernel<phases>" : "wino_fused_kernel") + " blocks=" +
+        log->add(std::string(split ? (phased ? "wino_fused_split_kernel<phases>" : "wino_fused_split_kernel")
+                                   : phased ? "wino_fused_kernel<phases>" : "wino_fused_kernel") + " blocks=" +
                  std::to_string(blocks) + " gemm_flops=" + std::to_string(2.0 * 16 * g.Co * (double)p.n_tiles * g.Ci));
         return hipSuccess;
+    }
+    if constexpr (std::is_same_v<E, float>) {
+        if (split) {
+            const bool odd = g.Wi % 2 != 0;
+            if (phased) wino_fused_split_kernel<2, false, true><<<blocks, 512, 0, s>>>(p);
+            else if (g.pad_w == 0) wino_fused_split_kernel<0, false, false><<<blocks, 512, 0, s>>>(p);
+            else if (g.pad_w == 2) wino_fused_split_kernel<2, false, false><<<blocks, 512, 0, s>>>(p);
+            else if (odd) wino_fused_split_kernel<1, true, false><<<blocks, 512, 0, s>>>(p);
+            else wino_fused_split_kernel<1, false, false><<<blocks, 512, 0, s>>>(p);
+            return hipGetLastError();
+        }
     }
     if (phased) {
         if (rows) wino_fused_kernel<float, 2, false, true><<<blocks, 256, 0, s>>>(p);

@@ -80,3 +80,56 @@ def test_split_gemm_range(scale):
         xs, dys = (x * np.float32(scale), dy) if op != ucd.BWD_DATA else (x, dy * np.float32(scale))
         got = run_hip(s, op, [(algo, s.N)], x=xs, w=w, dy=dys)
         assert rel_l2(got, run_oracle(s, op, x=xs, w=w, dy=dys)) <= 1e-6, ucd.OP_NAMES[op]
+
+
+# ---- fused Winograd F(2x2,3x3), at least 32 input channels ----------------------------------------------------------
+WF = ucd.ALGO_WINOGRAD_FUSED
+WINO_SHAPES = [
+    # input channels around the 16-channel step and the 8-channel blocks of the transformed filter, output channels
+    # around the 64-channel block, tiles around the 64-tile block, odd and even widths, paddings 0 to 2
+    Shape(1, 32, 6, 6, 64, 3, 3, 1, 1), Shape(3, 33, 13, 13, 65, 3, 3, 1, 1), Shape(2, 40, 9, 16, 31, 3, 3, 1, 0),
+    Shape(2, 47, 10, 7, 130, 3, 3, 1, 2), Shape(5, 56, 8, 11, 3, 3, 3, 1, 1), Shape(1, 100, 17, 16, 96, 3, 3, 1, 1),
+    Shape(3, 64, 5, 4, 37, 3, 3, 1, 2), Shape(2, 36, 3, 3, 40, 3, 3, 1, 1),
+]
+PHASE_SHAPES = [Shape(2, 3, 31, 35, 48, 11, 11, 4, 0), Shape(1, 9, 22, 17, 33, 5, 5, 2, 2), Shape(2, 4, 23, 23, 40, 7, 7, 3, 1)]
+
+
+def _wino_runs(s):
+    return ([(ucd.FWD, s)] if s.C >= 32 and s.stride == 1 else []) + ([(ucd.BWD_DATA, s)] if s.K >= 32 else [])
+
+
+@pytest.mark.parametrize("s", WINO_SHAPES + PHASE_SHAPES, ids=_id)
+def test_split_winograd_edges(s):
+    """Bound: Winograd's transforms amplify the operands' rounding by less than 4 (their matrices have entries 0, 1
+    and 1/2 and at most three terms a row), so 4 times the direct kernels' bound; measured 2e-7 to 6e-7."""
+    x, w, dy = inputs(s, seed=17)
+    for op, _ in _wino_runs(s):
+        assert "wino_fused_split_kernel" in ucd.ucd_describe_micro(ucd.layer(s), op, WF, s.N)[0]
+        for parts in ([s.N], [1] * s.N):
+            got = run_hip(s, op, [(WF, b) for b in parts], x=x, w=w, dy=dy)
+            ref = run_oracle(s, op, x=x, w=w, dy=dy)
+            assert rel_l2(got, ref) <= 4e-6, (ucd.OP_NAMES[op], parts, rel_l2(got, ref))
+
+
+@pytest.mark.parametrize("s", [WINO_SHAPES[1], WINO_SHAPES[2], PHASE_SHAPES[1]], ids=_id)
+def test_split_winograd_not_finite(s):
+    """What arithmetic makes not finite is not finite, and blocks that hold such values are otherwise as exact as the
+    rest: only outputs within a tile's reach of the pixel may differ from the oracle's."""
+    x, w, dy = inputs(s, seed=18)
+    t = dy if s.stride > 1 else x
+    t[0, 1, 2, 2], t[-1, -1, 0, 0] = np.inf, np.nan
+    op = ucd.BWD_DATA if s.stride > 1 else ucd.FWD
+    got = run_hip(s, op, [(WF, s.N)], x=x, w=w, dy=dy).astype(np.float64)
+    ref = run_oracle(s, op, x=x, w=w, dy=dy)
+    assert not np.isfinite(got[~np.isfinite(ref)]).any()
+    far = np.isfinite(got)
+    assert far.mean() > 0.3 and rel_l2(got[far], ref[far]) <= 4e-6
+
+
+@pytest.mark.parametrize("scale", [1e-36, 1e-30, 1e30])
+def test_split_winograd_range(scale):
+    s = WINO_SHAPES[1]
+    x, w, dy = inputs(s, seed=19)
+    x = x * np.float32(scale)
+    got = run_hip(s, ucd.FWD, [(WF, s.N)], x=x, w=w, dy=dy)
+    assert rel_l2(got, run_oracle(s, ucd.FWD, x=x, w=w, dy=dy)) <= 4e-6
