@@ -20,10 +20,11 @@ int filter_splits(int M, int N, int Kd, int batch)
     return best_fill(tiles, want, (want + 1) / 2, want * 2 < cap ? want * 2 : cap, slots);
 }
 
-// The same for the split kernel, whose 128-column workgroups fit a CU twice and whose 256-column ones once.
-static int split_kernel_filter_splits(int M, int N, int Kd)
+// The same for the kernels that read runs of four pixels: two workgroups fit a CU (one of the 256-column ones of the
+// split kernel, three of 64 x 64 tiles).
+static int quad_filter_splits(int M, int N, int Kd, bool wide_tiles)
 {
-    const bool wide = wide_shape(M, N);
+    const bool wide = wide_tiles && wide_shape(M, N);
     const TilePick shape = pick_tile(M, N, true, 1 << 20);
     const long tiles = wide ? (long)((M + 127) / 128) * ((N + 255) / 256) : shape.blocks(M, N, 1);
     const long slots = (wide ? 1l : shape.bm * shape.bn <= 64 * 64 ? 3l : 2l) * device_cus();
@@ -67,32 +68,62 @@ __global__ void reduce_partials_kernel(const float *part, int splits, size_t pla
     }
 }
 
-// fp32 tensors: the split kernel, masks by padding and tap count (see QuadXT)
-template <class Epi>
+// bf16 tensors: runs of four pixels (gemm_kernel_bf16q) or element by element (gemm_kernel_bf16).  The runs have to be
+// whole in nearly every wave of 64 rows: images of a multiple of four pixels (13x13, 384 channels: 343 against 283 us;
+// 14x14, 256 channels: 127 against 158), whose rows are one after the other in x as well or of a multiple of four pixels
+// themselves.  Column stride 1, or 2 where its two loads still pay (4: 454 against 224 us, 11x11 first layer; 2 with
+// border masks and few taps: 85 against 77, 64 -> 128 channels 56x56; 1x1 stride 2: 106 against 169).  Short reductions
+// do not pay for the table of a 64-row step (196 rows: 11.7 against 10.9 us).  b = 256, 128 for the strided ones.
+static bool bf16_quads_pay(const Dims &d, int Kd)
+{
+    if (Kd < 2048 || d.P * d.Q % 4 != 0) return false;
+    const bool masked = d.ph != 0 || d.pw != 0, even_rows = d.Q % 4 == 0;
+    if (d.sw == 1) return even_rows || (d.Q == d.W && d.sh == 1);
+    return d.sw == 2 && even_rows && (!masked || d.R * d.S > 31);
+}
+
+// Operands in runs of four pixels, masks by padding and tap count (see QuadXT, QuadHalfX); fp32 tensors on the split
+// kernel, bf16 tensors on theirs.
+template <class E, class Epi>
 static hipError_t launch_filter_gemm(const Dims &d, const KLaneParams &pa, const KLaneParams &pb,
                                      const typename Epi::Params &pe, const GemmShape &g, hipStream_t s)
 {
-    const bool two = d.sw == 2;
-    if (d.ph == 0 && d.pw == 0)
-        return two ? launch_gemm<QuadDyFree, QuadXFree2, Epi, true>(pa, pb, pe, g, s)
-                   : launch_gemm<QuadDyFree, QuadXFree, Epi, true>(pa, pb, pe, g, s);
-    if (d.R * d.S <= 31)
-        return two ? launch_gemm<QuadDy, QuadX2, Epi, true>(pa, pb, pe, g, s)
-                   : launch_gemm<QuadDy, QuadX, Epi, true>(pa, pb, pe, g, s);
-    return two ? launch_gemm<QuadDyFree, QuadXBig2, Epi, true>(pa, pb, pe, g, s)
-               : launch_gemm<QuadDyFree, QuadXBig, Epi, true>(pa, pb, pe, g, s);
+    const bool two = d.sw == 2, free = d.ph == 0 && d.pw == 0, few = d.R * d.S <= 31;
+    if constexpr (std::is_same<E, float>::value) {
+        if (free)
+            return two ? launch_gemm<QuadDyFree, QuadXFree2, Epi, true>(pa, pb, pe, g, s)
+                       : launch_gemm<QuadDyFree, QuadXFree, Epi, true>(pa, pb, pe, g, s);
+        if (few)
+            return two ? launch_gemm<QuadDy, QuadX2, Epi, true>(pa, pb, pe, g, s)
+                       : launch_gemm<QuadDy, QuadX, Epi, true>(pa, pb, pe, g, s);
+        return two ? launch_gemm<QuadDyFree, QuadXBig2, Epi, true>(pa, pb, pe, g, s)
+                   : launch_gemm<QuadDyFree, QuadXBig, Epi, true>(pa, pb, pe, g, s);
+    } else {
+        typedef Loaders<E> L;
+        if (!bf16_quads_pay(d, g.Kd)) {
+            if (few) return launch_gemm<L::template DyTab, L::template XTab, Epi, true>(pa, pb, pe, g, s);
+            if (free) return launch_gemm<L::template DyKLane, L::template XKLaneFree, Epi, true>(pa, pb, pe, g, s);
+            return launch_gemm<L::template DyKLane, L::template XKLane, Epi, true>(pa, pb, pe, g, s);
+        }
+        if (free)
+            return two ? launch_gemm<QuadHalfDy, QuadHalfXFree2, Epi, true>(pa, pb, pe, g, s)
+                       : launch_gemm<QuadHalfDy, QuadHalfXFree, Epi, true>(pa, pb, pe, g, s);
+        if (few) return launch_gemm<QuadHalfDy, QuadHalfXTab, Epi, true>(pa, pb, pe, g, s);
+        return two ? launch_gemm<QuadHalfDy, QuadHalfXBig2, Epi, true>(pa, pb, pe, g, s)
+                   : launch_gemm<QuadHalfDy, QuadHalfXBig, Epi, true>(pa, pb, pe, g, s);
+    }
 }
 
 template <class E>
 static hipError_t implicit_bwd_filter_t(const Dims &d, int b, const void *x, const void *dy, float *dw, float beta,
                                         float *ws, hipStream_t s)
 {
-    typedef Loaders<E> L;
+    constexpr bool F32 = std::is_same<E, float>::value;
     hipError_t e;
     GemmShape g{d.K, d.crs(), b * d.P * d.Q};
     g.splits = d.det ? det_filter_splits(d, b)
-               : std::is_same<E, float>::value && g.M > 32 ? split_kernel_filter_splits(g.M, g.N, g.Kd)
-                                               : filter_splits(g.M, g.N, g.Kd);
+               : (F32 ? g.M > 32 : bf16_quads_pay(d, g.Kd)) ? quad_filter_splits(g.M, g.N, g.Kd, F32)
+                                                            : filter_splits(g.M, g.N, g.Kd);
     const bool partials = d.det && g.splits > 1;
     if (!partials && beta == 0.f && (e = fill_zero(dw, (size_t)d.K * d.crs(), s)) != hipSuccess) return e;
     KLaneParams pa{};
@@ -112,11 +143,7 @@ static hipError_t implicit_bwd_filter_t(const Dims &d, int b, const void *x, con
     if (partials) {
         const size_t plane = (size_t)d.K * d.crs();
         EpiPartialParams pp{ws, d.crs(), (long)plane};
-        if constexpr (std::is_same<E, float>::value)
-            e = launch_filter_gemm<EpiPartial>(d, pa, pb, pp, g, s);
-        else
-            e = d.R * d.S <= 31 ? launch_gemm<L::template DyTab, L::template XTab, EpiPartial, true>(pa, pb, pp, g, s)
-                                : launch_gemm<L::template DyKLane, L::template XKLane, EpiPartial, true>(pa, pb, pp, g, s);
+        e = launch_filter_gemm<E, EpiPartial>(d, pa, pb, pp, g, s);
         if (e != hipSuccess) return e;
         if (LaunchLog *log = launch_log()) {
             log->add("reduce_partials_kernel");
@@ -128,15 +155,7 @@ static hipError_t implicit_bwd_filter_t(const Dims &d, int b, const void *x, con
         return hipGetLastError();
     }
     EpiDenseParams pe{dw, d.crs()};
-    if constexpr (std::is_same<E, float>::value) {
-        return launch_filter_gemm<EpiAtomic>(d, pa, pb, pe, g, s);
-    } else {
-        // filters of at most 31 taps: per-row state in an LDS table; without padding every tap of every pixel is inside x
-        const bool tab = d.R * d.S <= 31, free = d.ph == 0 && d.pw == 0;
-        if (tab) return launch_gemm<L::template DyTab, L::template XTab, EpiAtomic, true>(pa, pb, pe, g, s);
-        if (free) return launch_gemm<L::template DyKLane, L::template XKLaneFree, EpiAtomic, true>(pa, pb, pe, g, s);
-        return launch_gemm<L::template DyKLane, L::template XKLane, EpiAtomic, true>(pa, pb, pe, g, s);
-    }
+    return launch_filter_gemm<E, EpiAtomic>(d, pa, pb, pe, g, s);
 }
 
 hipError_t implicit_bwd_filter(const Dims &d, int b, const void *x, const void *dy, float *dw, float beta,

@@ -4,6 +4,7 @@
 
 #include "gemm_core.hpp"
 #include "gemm_split.hpp"
+#include "gemm_bf16_quads.hpp"
 #include "kernels.h"
 
 namespace ucd {
@@ -65,7 +66,9 @@ hipError_t launch_tile(const AP &pa, const BP &pb, const typename Epi::Params &p
     if (tiles_m <= 0 || tiles_n <= 0) return hipSuccess;
     int k_chunk;
     int splits = effective_splits(g.Kd, g.splits, k_chunk);
-    if (kVecLoads) {  // that kernel's steps are kDeepBK rows
+    constexpr bool kQuadLoads = quad_loader<AL<loader_tag_m<T>()>>(0) && quad_loader<BL<loader_tag_n<T>()>>(0);
+    static_assert(kDeepBK == kQuadBK, "one step length for both deep kernels");
+    if (kVecLoads || kQuadLoads) {  // those kernels' steps are kDeepBK rows
         k_chunk = (k_chunk + kDeepBK - 1) / kDeepBK * kDeepBK;
         splits = g.Kd > 0 ? (g.Kd + k_chunk - 1) / k_chunk : 1;
     }
@@ -93,7 +96,7 @@ hipError_t launch_tile(const AP &pa, const BP &pb, const typename Epi::Params &p
     dim3 grid(gx, (unsigned)splits, (unsigned)g.batch);
     if (LaunchLog *log = launch_log()) {
         if (tail.tiles) log->add("zero_tiles_kernel");
-        log->add(std::string(kVecLoads ? "gemm_kernel_bf16v<Tile<" : kBf16Mfma ? "gemm_kernel_bf16<Tile<"
+        log->add(std::string(kVecLoads ? "gemm_kernel_bf16v<Tile<" : kQuadLoads ? "gemm_kernel_bf16q<Tile<" : kBf16Mfma ? "gemm_kernel_bf16<Tile<"
                                        : kSplit ? "gemm_kernel_split<Tile<" : "gemm_kernel<Tile<") + std::to_string(T::BM) + "x" + std::to_string(T::BN) + ">," +
                  AL<loader_tag_m<T>()>::name() + "," + BL<loader_tag_n<T>()>::name() + "," + Epi::name() + "> tiles=" +
                  std::to_string(tiles_m * tiles_n) + " splits=" + std::to_string(splits) + " batch=" +
@@ -109,6 +112,9 @@ hipError_t launch_tile(const AP &pa, const BP &pb, const typename Epi::Params &p
     }
     if constexpr (kVecLoads)
         gemm_kernel_bf16v<T, AL<loader_tag_m<T>()>, BL<loader_tag_n<T>()>, Epi, AP, BP><<<grid, kThreads, 0, s>>>(
+            pa, pb, pe, g.M, g.N, g.Kd, k_chunk, tiles_m, tiles_n);
+    else if constexpr (kQuadLoads)
+        gemm_kernel_bf16q<T, AL<loader_tag_m<T>()>, BL<loader_tag_n<T>()>, Epi, AP, BP><<<grid, kThreads, 0, s>>>(
             pa, pb, pe, g.M, g.N, g.Kd, k_chunk, tiles_m, tiles_n);
     else if constexpr (kBf16Mfma)
         gemm_kernel_bf16<T, AL<loader_tag_m<T>()>, BL<loader_tag_n<T>()>, Epi, AP, BP><<<grid, kThreads, 0, s>>>(

@@ -170,3 +170,25 @@ def test_bf16_plan_on_device_and_execute():
             out = torch.empty(s.w_shape, dtype=torch.float32, device=dev)
             ucd.ucd_conv_bwd_filter(plan, xb, dyb, out, 0.0, ws)
             assert rel_l2(out.cpu().numpy(), ref) <= 1e-5
+
+
+# BackwardFilter in runs of four pixels (64-row steps): images of a multiple of four pixels, rows that are and are not,
+# no padding / border masks / more than 31 taps, column strides 1 and 2, tile heights 32 to 128, reductions that end
+# inside a step and run past the pixel table's 256 rows; and the neighbouring shapes that stay element by element
+QUAD_SHAPES = [
+    (Shape(11, 9, 14, 14, 40, 3, 3, 1, 1), True), (Shape(5, 17, 20, 21, 33, 1, 1, 1, 0), True),
+    (Shape(40, 5, 10, 9, 100, 3, 3, 1, 0), False), (Shape(6, 3, 45, 41, 64, 7, 7, 2, 3), False),
+    (Shape(6, 3, 47, 48, 97, 7, 7, 2, 3), True), (Shape(9, 20, 32, 31, 130, 1, 1, 2, 0), True),
+    (Shape(40, 7, 8, 8, 30, 5, 5, 1, 2), True), (Shape(13, 6, 13, 13, 50, 3, 3, 1, 1), False),
+    (Shape(40, 4, 11, 11, 20, 6, 6, 1, 1), True),
+]
+
+
+@pytest.mark.parametrize("s,runs", QUAD_SHAPES, ids=lambda v: str(v))
+def test_bf16_bwd_filter_runs_of_pixels(s, runs):
+    """dw is fp32 and products of bf16 values are exact, so only fp32 summation differs: the file's 1e-5."""
+    bits, (x, w, dy) = bf16_inputs(s, seed=21)
+    text = ucd.ucd_describe_micro(ucd.layer(s, dtype=1), ucd.BWD_FILTER, ucd.ALGO_IMPLICIT, s.N)[0]
+    assert ("gemm_kernel_bf16q" in text) == runs, text
+    got = run_hip_bf16(s, ucd.BWD_FILTER, [(ucd.ALGO_IMPLICIT, s.N)], bits)
+    assert rel_l2(got, run_oracle(s, ucd.BWD_FILTER, x=x, w=w, dy=dy)) <= 1e-5
