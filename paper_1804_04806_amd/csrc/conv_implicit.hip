@@ -97,9 +97,16 @@ static hipError_t implicit_fwd_t(const Dims &d, int b, const void *x, const void
     // (filters of more than one tap: 1x1 layers are bound by memory, not by the loader)
     const bool free = d.ph == 0 && d.pw == 0 && d.R * d.S > 1;
     if constexpr (F32) {
-        if (free) return launch_gemm<CellK32T, GatherCellFree, EpiNCHW, true>(pa, pb, pe, g, s);
-        if (d.R * d.S <= 31) return launch_gemm<CellK32T, GatherCell, EpiNCHW, true>(pa, pb, pe, g, s);
-        return launch_gemm<CellK32T, GatherCellBig, EpiNCHW, true>(pa, pb, pe, g, s);
+        // 1x1 layers with short reductions stay on the fp32 kernel: a tile's start and end outweigh its steps, and the
+        // split kernel's cost more.  b = 80, 24x74, us split / fp32: 64 output channels, 64 rows 27.2 / 23.9, 96 rows
+        // 31.8 / 29.5, 128 rows 35.8 / 35.8; 128 and 186 output channels, 48 rows 38 / 36 and 51 / 45, 64 rows 41 / 41
+        // and 56 / 53, 80 rows 44 / 46 and 60 / 60, 96 rows 47 / 52 and 65 / 68.
+        if (d.R * d.S > 1 || g.Kd >= (g.M <= 64 ? 128 : 80)) {
+            if (free) return launch_gemm<CellK32T, GatherCellFree, EpiNCHW, true>(pa, pb, pe, g, s);
+            if (d.R * d.S <= 31) return launch_gemm<CellK32T, GatherCell, EpiNCHW, true>(pa, pb, pe, g, s);
+            return launch_gemm<CellK32T, GatherCellBig, EpiNCHW, true>(pa, pb, pe, g, s);
+        }
+        return launch_gemm<L::template KLane0, L::template GatherNLane, EpiNCHW, true>(pa, pb, pe, g, s);
     } else {
         if (free) return launch_gemm<L::template KLane0, L::template GatherNLaneFree, EpiNCHWT<E>, true>(pa, pb, pe, g, s);
         if (d.R * d.S <= 31) return launch_gemm<L::template KLane0, L::template GatherNLane, EpiNCHWT<E>, true>(pa, pb, pe, g, s);

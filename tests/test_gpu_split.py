@@ -19,6 +19,7 @@ SHAPES = [
     # reductions that end inside a 16-row step, inside a 4-row load and inside a 64-row window
     Shape(2, 37, 9, 11, 34, 3, 3, 1, 1), Shape(2, 33, 8, 8, 33, 1, 1, 1, 0), Shape(1, 21, 12, 12, 65, 3, 3, 1, 1),
     Shape(3, 5, 31, 30, 96, 11, 11, 4, 0), Shape(2, 9, 20, 20, 97, 7, 7, 2, 3), Shape(2, 3, 14, 14, 129, 5, 5, 1, 2),
+    Shape(2, 128, 9, 7, 64, 1, 1, 1, 0), Shape(3, 80, 11, 6, 127, 1, 1, 1, 0), Shape(2, 79, 8, 8, 65, 1, 1, 1, 0),
     Shape(24, 64, 33, 33, 128, 3, 3, 1, 1), Shape(33, 67, 40, 40, 250, 2, 2, 1, 0),
     # BackwardFilter: images whose pixel count is 1, 2 or 3 above a multiple of 4, one row or column of pixels,
     # strides 1 to 3, outputs narrower and wider than the input, more than 31 taps, more rows than the pixel table
@@ -45,13 +46,15 @@ def _runs(s):
 def test_split_gemm_edges(s):
     x, w, dy = inputs(s, seed=7)
     for op, algo in _runs(s):
-        assert "gemm_kernel_split" in ucd.ucd_describe_micro(ucd.layer(s), op, algo, s.N)[0]
+        rows, outs = (s.C, s.K) if op == ucd.FWD else (s.K, s.C)
+        short = op != ucd.BWD_FILTER and s.R * s.S == 1 and rows < (128 if outs <= 64 else 80)
+        assert ("gemm_kernel_split" in ucd.ucd_describe_micro(ucd.layer(s), op, algo, s.N)[0]) != short
         got = run_hip(s, op, [(algo, s.N)], x=x, w=w, dy=dy)
         ref = run_oracle(s, op, x=x, w=w, dy=dy)
         assert rel_l2(got, ref) <= 1e-6, (ucd.OP_NAMES[op], rel_l2(got, ref))
 
 
-@pytest.mark.parametrize("s", [SHAPES[1], SHAPES[6], SHAPES[7], SHAPES[10], SHAPES[11]], ids=_id)
+@pytest.mark.parametrize("s", [SHAPES[6], SHAPES[9], SHAPES[10], SHAPES[13], SHAPES[14]], ids=_id)
 def test_split_gemm_not_finite(s):
     """Infinities and NaN come out where, and as, fp32 arithmetic gives them; the other outputs stay exact."""
     x, w, dy = inputs(s, seed=8)
@@ -74,7 +77,7 @@ def test_split_gemm_not_finite(s):
 @pytest.mark.parametrize("scale", [1e-37, 1e-30, 1e30])
 def test_split_gemm_range(scale):
     """Operands so small that their low parts leave bf16's range, and large ones."""
-    s = SHAPES[8]
+    s = SHAPES[11]
     x, w, dy = inputs(s, seed=9)
     for op, algo in _runs(s):
         xs, dys = (x * np.float32(scale), dy) if op != ucd.BWD_DATA else (x, dy * np.float32(scale))
