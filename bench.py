@@ -47,6 +47,7 @@ WS_LIMIT = 64 << 20
 # `traffic` = this figure x the flops per launch of the step being timed: the planner does not
 # pick the same micro-batch sizes every run, and a kernel's traffic follows its size.
 MEASURED_TRAFFIC_BYTES_PER_FLOP = {
+    "wino_fused_split_kernel": 529.8e6 / 59.19e9,  # conv4 Forward, 256 samples, launched alone
     "wino5_fused_kernel": 735.6e6 / 87.77e9,
     "wino_fused_filter_kernel": 569.6e6 / 46.04e9,
     "wino5_fused_filter_kernel": 913.4e6 / 90.6e9,
