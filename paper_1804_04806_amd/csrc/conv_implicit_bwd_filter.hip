@@ -74,10 +74,14 @@ __global__ void reduce_partials_kernel(const float *part, int splits, size_t pla
 // themselves.  Column stride 1, or 2 where its two loads still pay (4: 454 against 224 us, 11x11 first layer; 2 with
 // border masks and few taps: 85 against 77, 64 -> 128 channels 56x56; 1x1 stride 2: 106 against 169).  Short reductions
 // do not pay for the table of a 64-row step (196 rows: 11.7 against 10.9 us).  b = 256, 128 for the strided ones.
+// Padded filters of more than 31 taps need two masks per pixel, whose table pays later still (us, runs / element by
+// element, rows): 11x11 on 8x7 2408 18.6 / 16.2, 38528 66.5 / 90.5; 11x11 on 16x16 11008 83.9 / 79.5; 7x7/2 on 48x48
+// 18432 17.3 / 14.5, on 96x96 73728 33.0 / 34.1; 7x7 on 24x24 4608 11.1 / 10.5, 73728 59.4 / 88.6.
 static bool bf16_quads_pay(const Dims &d, int Kd)
 {
     if (Kd < 2048 || d.P * d.Q % 4 != 0) return false;
     const bool masked = d.ph != 0 || d.pw != 0, even_rows = d.Q % 4 == 0;
+    if (masked && d.R * d.S > 31 && Kd < 32768) return false;
     if (d.sw == 1) return even_rows || (d.Q == d.W && d.sh == 1);
     return d.sw == 2 && even_rows && (!masked || d.R * d.S > 31);
 }

@@ -178,9 +178,9 @@ def test_bf16_plan_on_device_and_execute():
 QUAD_SHAPES = [
     (Shape(11, 9, 14, 14, 40, 3, 3, 1, 1), True), (Shape(5, 17, 20, 21, 33, 1, 1, 1, 0), True),
     (Shape(40, 5, 10, 9, 100, 3, 3, 1, 0), False), (Shape(6, 3, 45, 41, 64, 7, 7, 2, 3), False),
-    (Shape(6, 3, 47, 48, 97, 7, 7, 2, 3), True), (Shape(9, 20, 32, 31, 130, 1, 1, 2, 0), True),
+    (Shape(60, 3, 47, 48, 97, 7, 7, 2, 3), True), (Shape(9, 20, 32, 31, 130, 1, 1, 2, 0), True),
     (Shape(40, 7, 8, 8, 30, 5, 5, 1, 2), True), (Shape(13, 6, 13, 13, 50, 3, 3, 1, 1), False),
-    (Shape(40, 4, 11, 11, 20, 6, 6, 1, 1), True),
+    (Shape(520, 4, 11, 11, 20, 6, 6, 1, 1), True), (Shape(6, 3, 47, 48, 97, 7, 7, 2, 3), False),
 ]
 
 
