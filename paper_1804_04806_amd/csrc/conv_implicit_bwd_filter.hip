@@ -36,26 +36,6 @@ static int quad_filter_splits(int M, int N, int Kd, bool wide_tiles)
     return best_fill(tiles, want, (want + 1) / 2, want * 2 < cap ? want * 2 : cap, slots);
 }
 
-// Reproducible BackwardFilter: at most this much workspace holds the reduction chunks' partial
-// results (one K x CRS plane per chunk); a filter too large for several planes gets fewer, longer chunks.
-constexpr size_t kDetPartialCap = (size_t)32 << 20;
-
-static int det_filter_splits(const Dims &d, int b)
-{
-    const int Kd = b * d.P * d.Q;
-    long want = filter_splits(d.K, d.crs(), Kd);
-    const long cap = (long)(kDetPartialCap / ((size_t)4 * d.K * d.crs()));
-    if (want > cap) want = cap;
-    int chunk;
-    return effective_splits(Kd, (int)(want < 1 ? 1 : want), chunk);
-}
-
-size_t implicit_det_ws_bytes(const Dims &d, int b)
-{
-    const int splits = det_filter_splits(d, b);
-    return splits > 1 ? (size_t)4 * splits * d.K * d.crs() : 0;  // one chunk: a single addition per element
-}
-
 // dw = beta * dw + part[0] + part[1] + ... in that order
 __global__ void reduce_partials_kernel(const float *part, int splits, size_t plane, float *dw, float beta, size_t n)
 {
@@ -84,6 +64,28 @@ static bool bf16_quads_pay(const Dims &d, int Kd)
     if (masked && d.R * d.S > 31 && Kd < 32768) return false;
     if (d.sw == 1) return even_rows || (d.Q == d.W && d.sh == 1);
     return d.sw == 2 && even_rows && (!masked || d.R * d.S > 31);
+}
+
+// Reproducible BackwardFilter: at most this much workspace holds the reduction chunks' partial
+// results (one K x CRS plane per chunk); a filter too large for several planes gets fewer, longer chunks.
+constexpr size_t kDetPartialCap = (size_t)32 << 20;
+
+// The planes that the launch writes, the sum reads and ucd_workspace_size prices.
+static int det_filter_splits(const Dims &d, int b)
+{
+    const int Kd = b * d.P * d.Q;
+    long want = filter_splits(d.K, d.crs(), Kd);
+    const long cap = (long)(kDetPartialCap / ((size_t)4 * d.K * d.crs()));
+    if (want > cap) want = cap;
+    int chunk;
+    const int step = d.dtype == 1 && bf16_quads_pay(d, Kd) ? kQuadBK : kBK;  // of the kernel that will run
+    return effective_splits(Kd, (int)(want < 1 ? 1 : want), chunk, step);
+}
+
+size_t implicit_det_ws_bytes(const Dims &d, int b)
+{
+    const int splits = det_filter_splits(d, b);
+    return splits > 1 ? (size_t)4 * splits * d.K * d.crs() : 0;  // one chunk: a single addition per element
 }
 
 // Operands in runs of four pixels, masks by padding and tap count (see QuadXT, QuadHalfX); fp32 tensors on the split

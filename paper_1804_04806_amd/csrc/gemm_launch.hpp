@@ -42,13 +42,14 @@ inline int device_cus()
 constexpr int kTailMinSteps = 8;    // a tail workgroup's run has at least this many reduction steps (of BK rows)
 constexpr int kTailMaxTiles = 224;  // a last round fuller than this is left alone
 
-// Reduction chunks are whole steps of BK rows: the chunk length for a requested split count, and the
-// number of chunks that really results.
-inline int effective_splits(int Kd, int want, int &k_chunk)
+// Reduction chunks are whole steps of the kernel that runs (`step` rows: kBK, or kDeepBK of the deep bf16
+// kernels): the chunk length for a requested split count, and the number of chunks that really results (asked
+// for which it gives that number again: whoever prices or sums the chunks and the launch agree).
+inline int effective_splits(int Kd, int want, int &k_chunk, int step = kBK)
 {
     if (want < 1) want = 1;
-    k_chunk = ((Kd + want - 1) / want + kBK - 1) / kBK * kBK;
-    if (k_chunk < kBK) k_chunk = kBK;
+    k_chunk = ((Kd + want - 1) / want + step - 1) / step * step;
+    if (k_chunk < step) k_chunk = step;
     return Kd > 0 ? (Kd + k_chunk - 1) / k_chunk : 1;
 }
 
@@ -64,14 +65,10 @@ hipError_t launch_tile(const AP &pa, const BP &pb, const typename Epi::Params &p
     if ((kBf16Mfma || kSplit) && g.batch != 1) return hipErrorInvalidValue;
     const int tiles_m = (g.M + T::BM - 1) / T::BM, tiles_n = (g.N + T::BN - 1) / T::BN;
     if (tiles_m <= 0 || tiles_n <= 0) return hipSuccess;
-    int k_chunk;
-    int splits = effective_splits(g.Kd, g.splits, k_chunk);
     constexpr bool kQuadLoads = quad_loader<AL<loader_tag_m<T>()>>(0) && quad_loader<BL<loader_tag_n<T>()>>(0);
-    static_assert(kDeepBK == kQuadBK, "one step length for both deep kernels");
-    if (kVecLoads || kQuadLoads) {  // those kernels' steps are kDeepBK rows
-        k_chunk = (k_chunk + kDeepBK - 1) / kDeepBK * kDeepBK;
-        splits = g.Kd > 0 ? (g.Kd + k_chunk - 1) / k_chunk : 1;
-    }
+    constexpr int kStep = kQuadLoads ? kQuadBK : kVecLoads ? kDeepBK : kBK;
+    int k_chunk;
+    const int splits = effective_splits(g.Kd, g.splits, k_chunk, kStep);
     // Tail spreading (see TailSplit): when an unsplit GEMM's tile count is not a multiple of the CU
     // count, the reduction steps of the tiles beyond the last multiple are dealt out evenly to (up to)
     // one workgroup per CU, so that every CU gets the same work.

@@ -1,5 +1,6 @@
 """The C-ABI library loads without a GPU and exports every symbol include/*.h declares."""
 import ctypes
+import itertools
 import os
 import re
 
@@ -151,3 +152,25 @@ def test_reproducible_mode_workspace_sizes():
     finally:
         assert ucd.ucd_set_deterministic(0) == 1
     assert [[ucd.ucd_workspace_size(L, op, a, 64) for a in range(ucd.N_ALGO)] for op in range(3)] == before
+
+
+def test_reproducible_backward_filter_prices_the_planes_it_launches():
+    """One K*C*R*S plane per reduction chunk, for both element types: the bytes that ucd_workspace_size reports
+    are those of the `splits=` planes that the launch writes (and the sum that follows reads), no more and no fewer."""
+    planes_of = {}
+    assert ucd.ucd_set_deterministic(1) == 0
+    try:
+        for dtype in (0, 1):
+            for n, h, w, c, k, r, stride, pad in itertools.product((1, 8, 32), (13, 28), (14, 28), (16, 65), (24, 64, 130),
+                                                                  (1, 3, 7), (1, 2), (0, 1)):
+                L = ucd.layer(N=n, C=c, H=h, W=w, K=k, R=r, S=r, pad_h=pad, pad_w=pad, stride_h=stride,
+                              stride_w=stride, dtype=dtype)
+                text = ucd.ucd_describe_micro(L, ucd.BWD_FILTER, ucd.ALGO_IMPLICIT, n)[0]
+                need = ucd.ucd_workspace_size(L, ucd.BWD_FILTER, ucd.ALGO_IMPLICIT, n)
+                planes = int(re.search(r"splits=(\d+)", text).group(1))
+                assert need == (4 * planes * k * c * r * r if "reduce_partials_kernel" in text else 0), text
+                assert ("reduce_partials_kernel" in text) == (planes > 1), text
+                planes_of.setdefault("bf16q" in text, set()).add(planes)
+    finally:
+        assert ucd.ucd_set_deterministic(0) == 1
+    assert all(len(v) > 3 for v in planes_of.values()) and len(planes_of) == 2   # both kernels, many chunk counts

@@ -8,6 +8,7 @@ import pytest
 from paper_1804_04806_amd import ucd
 from paper_1804_04806_amd.synth import Shape
 from hip_helpers import inputs, l2_tol, rel_l2, run_hip, run_oracle
+from test_gpu_bf16 import bf16_inputs, run_hip_bf16
 
 pytestmark = pytest.mark.gpu
 
@@ -123,3 +124,25 @@ def test_reproducible_mode_plans_and_runs_a_layer(deterministic):
             res.append(outs[op].cpu().numpy())
         assert np.array_equal(res[0], res[1])
         assert rel_l2(res[0], run_oracle(s, op, x=x, w=w, dy=dy)) <= l2_tol(plan.micro)
+
+
+# bf16 BackwardFilter: layers whose reduction chunks are counted in 64 rows (runs of four pixels) and in 16
+HALF = [(LONG, True), (Shape(33, 20, 14, 14, 64, 3, 3, 1, 1, "b33"), True), (Shape(12, 24, 32, 31, 70, 1, 1, 2, 0, "s2"), True),
+        (Shape(40, 17, 13, 13, 40, 3, 3, 1, 1, "odd-images"), False)]
+
+
+@pytest.mark.parametrize("s,runs", HALF, ids=lambda v: getattr(v, "name", str(v)))
+def test_reproducible_bf16_backward_filter(deterministic, s, runs):
+    """Every plane that is summed has been written (the workspace starts as NaN); products of bf16 values are
+    exact and dw is fp32, so the fp32 bound holds."""
+    text = ucd.ucd_describe_micro(ucd.layer(s, dtype=1), ucd.BWD_FILTER, ucd.ALGO_IMPLICIT, s.N)[0]
+    assert ("gemm_kernel_bf16q" in text) == runs and "reduce_partials_kernel" in text, text
+    bits, (x, w, dy) = bf16_inputs(s, seed=35)
+    dw0 = np.random.default_rng(6).standard_normal(s.w_shape).astype(np.float32)
+    for parts in ([s.N], [s.N - 3, 3]):
+        for beta in (0.0, 1.0):
+            ref = run_oracle(s, ucd.BWD_FILTER, x=x, dy=dy, beta=beta, dw0=dw0 if beta else None)
+            got = [run_hip_bf16(s, ucd.BWD_FILTER, [(ucd.ALGO_IMPLICIT, b) for b in parts], bits, beta=beta,
+                                dw0=dw0 if beta else None) for _ in range(2)]
+            assert np.array_equal(got[0], got[1])
+            assert rel_l2(got[0], ref) <= 1e-5, (parts, beta, rel_l2(got[0], ref))
