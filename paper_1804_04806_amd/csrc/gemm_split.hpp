@@ -13,10 +13,14 @@
 // normal weights: 1.5e-7; one accumulator for all six 4.9e-7; fp32 instructions 4.2e-7.  16384 rows: 7.2e-7 /
 // 1.9e-6 / 1.6e-6).  Splitting by truncation instead of rounding is biased (1.8e-5 on positive operands).
 //
-// Range.  An infinity (or a value that rounds to one in bf16) splits into inf - inf, and below about 2^-110
-// the low parts are lost to bf16's exponent range.  A workgroup therefore looks at its finished accumulators:
-// where one is not finite, or smaller than 2^-104 and not zero, it computes its tile again with the fp32
-// instructions (fp32_tile), so that infinities, NaN and tiny operands give what they always gave.
+// Range.  With all three parts rounded to nearest, x = h + m + l exactly (the last remainder has at most 7 bits)
+// unless x lies so low (below 2^-102) that the remainder ends under bf16's smallest step, 2^-133, and that can be seen
+// in it: its low 16 bits are no longer zero.  Those bits are collected while the operands are split (one v_or3 per two
+// values).  An infinity, or a value that rounds to one in bf16, splits into inf - inf and leaves sums that are not
+// finite; and sums below 2^-104 may have lost products below fp32's range.  A workgroup that finds any of the three
+// after its last step computes its tile again with the fp32 instructions (fp32_tile), so that infinities, NaN and
+// tiny operands give what they always gave, whatever they are multiplied with (such a tile costs both: 384 channels
+// 3x3 13x13 b = 256, 560 us, all of it recomputed 1450).
 #pragma once
 #include "gemm_core.hpp"
 
@@ -30,7 +34,8 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b)
     asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
     return r;
 }
-__device__ __forceinline__ void split_pair(float a, float b, uint32_t &h, uint32_t &m, uint32_t &l)
+// `rest` collects the bits of the last remainders: its low half is zero as long as every split is exact (see Range)
+__device__ __forceinline__ void split_pair(float a, float b, uint32_t &h, uint32_t &m, uint32_t &l, uint32_t &rest)
 {
     h = pack_bf16(a, b);
     a -= __uint_as_float(h << 16);
@@ -38,6 +43,8 @@ __device__ __forceinline__ void split_pair(float a, float b, uint32_t &h, uint32
     m = pack_bf16(a, b);
     a -= __uint_as_float(m << 16);
     b -= __uint_as_float(m & 0xFFFF0000u);
+    // an instruction in its place: the compiler would keep the remainders in registers and combine them later
+    asm("v_or3_b32 %0, %0, %1, %2" : "+v"(rest) : "v"(a), "v"(b));
     l = pack_bf16(a, b);
 }
 
@@ -411,11 +418,12 @@ struct SplitStage {
     static constexpr int NE = L::NE, NP = NE / 2, RR = L::kRows;
     static_assert(RR == 8 || RR == 4, "runs of 4 or 8 rows");
     uint32_t part[3][RR / 2];
+    uint32_t rest = 0;
 
     __device__ __forceinline__ void stage_pair(char *buf, int q, const L &ld, const typename L::Regs &g)
     {
         const int k = q % (RR / 2);
-        split_pair(ld.value(2 * q, g), ld.value(2 * q + 1, g), part[0][k], part[1][k], part[2][k]);
+        split_pair(ld.value(2 * q, g), ld.value(2 * q + 1, g), part[0][k], part[1][k], part[2][k], rest);
         if (k + 1 < RR / 2) return;
         const int j = q / (RR / 2), row = ld.erow0();
         if (!ld.has_run(j)) return;
@@ -596,7 +604,7 @@ __global__ __launch_bounds__(T::THREADS, 2) void gemm_kernel_split(AParams pa, B
             o_wr = t;
         }
 
-        bool redo = false;
+        bool redo = ((sa.rest | sb.rest) & 0xFFFFu) != 0;
 #pragma unroll
         for (int i = 0; i < WM; ++i)
 #pragma unroll

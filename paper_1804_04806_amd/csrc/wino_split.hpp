@@ -29,10 +29,10 @@ constexpr int kWsC = 16;   // input channels per step
 // One lane's MFMA operand in three parts, and a quarter of its making: values 2i and 2i + 1 of eight
 struct SplitCell {
     u32x4 part[3];
-    __device__ __forceinline__ void pair(int i, const float (&v)[8])
+    __device__ __forceinline__ void pair(int i, const float (&v)[8], uint32_t &rest)
     {
         uint32_t h, m, l;
-        split_pair(v[2 * i], v[2 * i + 1], h, m, l);
+        split_pair(v[2 * i], v[2 * i + 1], h, m, l, rest);
         part[0][i] = h; part[1][i] = m; part[2][i] = l;
     }
     __device__ __forceinline__ bf16x8 operand(int pl) const { return __builtin_bit_cast(bf16x8, part[pl]); }
@@ -266,6 +266,7 @@ __global__ __launch_bounds__(512, 2) void wino_fused_split_kernel(FusedParams p)
     // together and then wait for the matrix pipe together; it measured 1-2 % slower with long reductions and 4 %
     // faster on 64 channels.)
     SplitCell a0, a1, b0, b1;
+    uint32_t rest = 0;
     float vv[8];
     auto read_v = [&](const float *vr, int q, int tt) __attribute__((always_inline)) {
         const f32x4 x = *reinterpret_cast<const f32x4 *>(vr + v_get0 + (64 * q + 32 * tt) * kWsC);
@@ -296,12 +297,12 @@ __global__ __launch_bounds__(512, 2) void wino_fused_split_kernel(FusedParams p)
     }
     fetch_patch(kWsC, 0);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) a0.pair(i, ur[0]);
+    for (int i = 0; i < 4; ++i) a0.pair(i, ur[0], rest);
     fetch_u(0, 1, 0);
     __syncthreads();
     read_v(vbuf, 0, 0);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) b0.pair(i, vv);
+    for (int i = 0; i < 4; ++i) b0.pair(i, vv, rest);
 
     int cur = 0;
     for (int c0 = 0; c0 < g.Ci; c0 += kWsC) {
@@ -324,12 +325,12 @@ __global__ __launch_bounds__(512, 2) void wino_fused_split_kernel(FusedParams p)
             };
             read_v(vr, q, 1);
             group(acc[q][0][0], a0, b0, [&](int m) __attribute__((always_inline)) {
-                if (m >= 2) b1.pair(m - 2, vv);
+                if (m >= 2) b1.pair(m - 2, vv, rest);
                 if (m == 0) finish_patch();
                 if (m == 1) column_transform();
             });
             group(acc[q][0][1], a0, b1, [&](int m) __attribute__((always_inline)) {
-                if (m < 4) a1.pair(m, ur[1]);
+                if (m < 4) a1.pair(m, ur[1], rest);
                 if (m == 4) fetch_u(c_next, q ^ 1, 1);
                 if (m == 4) put_row(vw, q, 0);
                 if (m == 5) put_row(vw, q, 1);
@@ -337,7 +338,7 @@ __global__ __launch_bounds__(512, 2) void wino_fused_split_kernel(FusedParams p)
             group(acc[q][1][0], a1, b0, [&](int m) __attribute__((always_inline)) {
                 if (m == 0) put_row(vw, q, 2);
                 if (m == 1) put_row(vw, q, 3);
-                if (m >= 2) a0.pair(m - 2, ur[0]);
+                if (m >= 2) a0.pair(m - 2, ur[0], rest);
                 if (m == 5) fetch_u(c0 + kWsC, q, 0);
             });
             if (q == 1) __syncthreads();   // the next step's V is complete, and this step's has been read
@@ -347,7 +348,7 @@ __global__ __launch_bounds__(512, 2) void wino_fused_split_kernel(FusedParams p)
                     fetch_row(q == 0 ? c0 + kWsC : c0 + 2 * kWsC, q ^ 1, 2 * m);
                     fetch_row(q == 0 ? c0 + kWsC : c0 + 2 * kWsC, q ^ 1, 2 * m + 1);
                 }
-                if (m >= 2) b0.pair(m - 2, vv);
+                if (m >= 2) b0.pair(m - 2, vv, rest);
             });
         };
         half(std::integral_constant<int, 0>{});
@@ -356,7 +357,7 @@ __global__ __launch_bounds__(512, 2) void wino_fused_split_kernel(FusedParams p)
     }
 
     // range check as in gemm_kernel_split
-    bool redo = false;
+    bool redo = (rest & 0xFFFFu) != 0;
 #pragma unroll
     for (int q = 0; q < 2; ++q)
 #pragma unroll

@@ -74,15 +74,42 @@ def test_split_gemm_not_finite(s):
         assert rel_l2(got[fine], ref[fine]) <= 1e-6
 
 
-@pytest.mark.parametrize("scale", [1e-37, 1e-30, 1e30])
-def test_split_gemm_range(scale):
-    """Operands so small that their low parts leave bf16's range, and large ones."""
+# Operands whose low parts leave bf16's range (below 2^-102) or that vanish in it (below 2^-134: denormals), the other
+# operand near 1 or so large that the results are ordinary numbers, and large ones.  fp32 operands of any size are
+# exact inputs; the partner keeps results above 2^-110, where fp32 sums of a few 2^-149 steps still meet the bound.
+RANGES = [(1e-37, 1.0), (1e-30, 1.0), (1e30, 1.0), (2.0 ** -116, 2.0 ** 30), (2.0 ** -124, 2.0 ** 40), (2.0 ** -136, 2.0 ** 60)]
+
+
+@pytest.mark.parametrize("scale,partner", RANGES)
+def test_split_gemm_range(scale, partner):
     s = SHAPES[11]
     x, w, dy = inputs(s, seed=9)
     for op, algo in _runs(s):
-        xs, dys = (x * np.float32(scale), dy) if op != ucd.BWD_DATA else (x, dy * np.float32(scale))
-        got = run_hip(s, op, [(algo, s.N)], x=xs, w=w, dy=dys)
-        assert rel_l2(got, run_oracle(s, op, x=xs, w=w, dy=dys)) <= 1e-6, ucd.OP_NAMES[op]
+        for first in (True, False):   # which operand is the small one
+            a, b = np.float32(scale if first else partner), np.float32(partner if first else scale)
+            xs, ws, dys = (x * a, w * b, dy) if op == ucd.FWD else (x, w * b, dy * a) if op == ucd.BWD_DATA else (x * b, w, dy * a)
+            got = run_hip(s, op, [(algo, s.N)], x=xs, w=ws, dy=dys)
+            ref = run_oracle(s, op, x=xs, w=ws, dy=dys)
+            assert rel_l2(got, ref) <= 1e-6, (ucd.OP_NAMES[op], first, rel_l2(got, ref))
+
+
+@pytest.mark.parametrize("s", [SHAPES[9], SHAPES[11], SHAPES[13]], ids=_id)
+def test_split_gemm_small_parts(s):
+    """One image, one output channel or one input channel far below bf16's range among ordinary ones, whose results
+    are compared by themselves."""
+    x, w, dy = inputs(s, seed=10)
+    tiny = np.float32(2.0 ** -130)
+    x[0] *= tiny
+    w[1] *= tiny
+    dy[:, 2] *= tiny
+    up = np.float32(2.0 ** 40)
+    for op, algo in _runs(s):
+        xs, ws, dys = (x, w * up, dy) if op == ucd.FWD else (x, w * up, dy) if op == ucd.BWD_DATA else (x * up, w, dy)
+        got = run_hip(s, op, [(algo, s.N)], x=xs, w=ws, dy=dys)
+        ref = run_oracle(s, op, x=xs, w=ws, dy=dys)
+        parts = {ucd.FWD: [(0, 0), (0, 3), (1, 3)], ucd.BWD_DATA: [(0,), (1,)], ucd.BWD_FILTER: [(2,), (3,)]}[op]
+        for at in parts:
+            assert rel_l2(got[at], ref[at]) <= 1e-6, (ucd.OP_NAMES[op], at, rel_l2(got[at], ref[at]))
 
 
 # ---- fused Winograd F(2x2,3x3), at least 32 input channels ----------------------------------------------------------
@@ -129,10 +156,16 @@ def test_split_winograd_not_finite(s):
     assert far.mean() > 0.3 and rel_l2(got[far], ref[far]) <= 4e-6
 
 
-@pytest.mark.parametrize("scale", [1e-36, 1e-30, 1e30])
-def test_split_winograd_range(scale):
-    s = WINO_SHAPES[1]
+@pytest.mark.parametrize("scale,partner", RANGES)
+@pytest.mark.parametrize("s", [WINO_SHAPES[1], PHASE_SHAPES[0]], ids=_id)
+def test_split_winograd_range(s, scale, partner):
+    """The filter's transform is fp32 arithmetic of its own (halves and sums), whose results have steps of 2^-149: a
+    filter of that size is off by up to one such step before it is multiplied, which is added to the bound."""
     x, w, dy = inputs(s, seed=19)
-    x = x * np.float32(scale)
-    got = run_hip(s, ucd.FWD, [(WF, s.N)], x=x, w=w, dy=dy)
-    assert rel_l2(got, run_oracle(s, ucd.FWD, x=x, w=w, dy=dy)) <= 4e-6
+    op = ucd.BWD_DATA if s.stride > 1 else ucd.FWD
+    for first in (True, False):
+        a, b = np.float32(scale if first else partner), np.float32(partner if first else scale)
+        got = run_hip(s, op, [(WF, s.N)], x=x * a, w=w * b, dy=dy * a)
+        ref = run_oracle(s, op, x=x * a, w=w * b, dy=dy * a)
+        step = 2.0 ** -149 / np.sqrt(np.mean(np.square((w * b).astype(np.float64))))
+        assert rel_l2(got, ref) <= 4e-6 + step, (first, rel_l2(got, ref))
