@@ -368,64 +368,47 @@ __global__ __launch_bounds__(512, 2) void wino_fused_split_kernel(FusedParams p)
                 for (int e = 0; e < 16; ++e)
                     redo |= __builtin_amdgcn_classf(acc[q][i][j][e], 0x297) |
                             __builtin_amdgcn_classf(acc[q][i][j][e] * 0x1p-22f, 0x090);
-    const int h0 = 2 * (int)th, w0 = 2 * (int)tw;
     if (__syncthreads_or(redo)) {
-        // the same sums in fp32: four output channels of tile `lane` at a time
+        // the same sums with the fp32 instructions, one step after the other: MFMA e takes channel e of the lower half
+        // wave's eight and of the upper half's (every block recomputed, 384 -> 384 13x13 b = 256: 1000 us, against 410
+        // without and 525 of wino_fused_kernel)
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) acc[q][i][j][e] = 0.f;
 #pragma unroll 1
-        for (int ct = 0; ct < 2; ++ct) {
-            const int kq = k0 + 32 * ct + 4 * wave;
-            float m[4][16];
+        for (int c0 = 0; c0 < g.Ci; c0 += kWsC) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int x = 0; x < 16; ++x) m[i][x] = 0.f;
-#pragma unroll 1
-            for (int c = 0; c < g.Ci; ++c) {
-                float q[16], tr[16];
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-#pragma unroll
-                    for (int s = 0; s < 4; ++s) {
-                        const int h = h0 - g.pad_h + r, w = w0 - g.pad_w + s;
-                        const bool ok = live && (unsigned)h < (unsigned)g.Hi && (unsigned)w < (unsigned)g.Wi;
-                        q[4 * r + s] = Elem<float>::load(rin, ok ? 4u * (uint32_t)((((int)n_img * g.Ci + c) * g.Hi + h) * g.Wi + w) : kOob, 0);
-                    }
-#pragma unroll
-                for (int s = 0; s < 4; ++s) {
-                    tr[s] = q[s] - q[8 + s]; tr[4 + s] = q[4 + s] + q[8 + s];
-                    tr[8 + s] = q[8 + s] - q[4 + s]; tr[12 + s] = q[4 + s] - q[12 + s];
-                }
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const float a0 = tr[4 * r], a1 = tr[4 * r + 1], a2 = tr[4 * r + 2], a3 = tr[4 * r + 3];
-                    tr[4 * r] = a0 - a2; tr[4 * r + 1] = a1 + a2; tr[4 * r + 2] = a2 - a1; tr[4 * r + 3] = a1 - a3;
-                }
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int x = 0; x < 16; ++x) {
-                        const uint32_t at = (uint32_t)x * u_plane + 4u * (uint32_t)(((c >> 3) * g.Mo4 + kq + i) * 8 + (c & 7));
-                        m[i][x] += Elem<float>::load(ru, kq + i < g.Mo4 ? at : kOob, 0) * tr[x];
-                    }
+            for (int h = 0; h < 2; ++h) {
+                fetch_patch(c0, h);
+                store_v(vbuf, h);
             }
-            float o[4][2][2];
+            __syncthreads();
+            const bool in_plane = c0 + 8 * lhi < p.ci_pad;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                float y[2][4];
+            for (int q = 0; q < 2; ++q) {
 #pragma unroll
-                for (int s = 0; s < 4; ++s) {
-                    y[0][s] = m[i][s] + m[i][4 + s] + m[i][8 + s];
-                    y[1][s] = m[i][4 + s] - m[i][8 + s] - m[i][12 + s];
+                for (int ct = 0; ct < 2; ++ct) {
+                    fetch_u(c0, q, ct);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) ur[ct][e] = in_plane ? ur[ct][e] : 0.f;
                 }
 #pragma unroll
-                for (int r = 0; r < 2; ++r) {
-                    o[i][r][0] = y[r][0] + y[r][1] + y[r][2];
-                    o[i][r][1] = y[r][1] - y[r][2] - y[r][3];
+                for (int tt = 0; tt < 2; ++tt) {
+                    read_v(vbuf, q, tt);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+#pragma unroll
+                        for (int ct = 0; ct < 2; ++ct)
+                            acc[q][ct][tt] = __builtin_amdgcn_mfma_f32_32x32x2f32(ur[ct][e], vv[e], acc[q][ct][tt], 0, 0, 0);
                 }
             }
-            if (live) wino_store4<PHASED>(p, n_img, h0, w0, kq, o);
+            __syncthreads();
         }
-        return;
     }
 
     // Output transform.  Along the columns a wave has two of its row's four points: wave 2i the terms m0 + m1 and
@@ -460,7 +443,7 @@ __global__ __launch_bounds__(512, 2) void wino_fused_split_kernel(FusedParams p)
                 o[i][0][c] = t[0] + t[1] + t[2];
                 o[i][1][c] = t[1] - t[2] - t[3];
             }
-        if (live) wino_store4<PHASED>(p, n_img, h0, w0, k0 + 32 * ct + 4 * wave, o);
+        if (live) wino_store4<PHASED>(p, n_img, 2 * (int)th, 2 * (int)tw, k0 + 32 * ct + 4 * wave, o);
     }
 }
 
