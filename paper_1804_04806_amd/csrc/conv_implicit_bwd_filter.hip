@@ -20,11 +20,35 @@ int filter_splits(int M, int N, int Kd, int batch)
     return best_fill(tiles, want, (want + 1) / 2, want * 2 < cap ? want * 2 : cap, slots);
 }
 
-// The same for the kernels that read runs of four pixels: two workgroups fit a CU (one of the 256-column ones of the
-// split kernel, three of 64 x 64 tiles).
-static int quad_filter_splits(int M, int N, int Kd, bool wide_tiles)
+// The same for gemm_kernel_bf16q: the count whose rounds of workgroups take least, a workgroup's start and end (pixel
+// table, first loads, atomics) costing as much as kStart of its 64-row steps.  Filling the last round best, as above,
+// took two short rounds for one long one (us, before / now: 128 -> 128 3x3 56x56 b = 16, 112 / 56 chunks, 76 / 53;
+// 64 -> 64 3x3 32x32 b = 64, 38 / 28).
+static int bf16q_filter_splits(int M, int N, int Kd)
 {
-    const bool wide = wide_tiles && wide_shape(M, N);
+    constexpr long kStart = 6;
+    const TilePick shape = pick_tile(M, N, true, 1 << 20);
+    const int bn = shape.bm == 32 || shape.bm == 96 ? 128 : shape.bn;  // those exist with 128 columns only
+    const long tiles = (long)((M + shape.bm - 1) / shape.bm) * ((N + bn - 1) / bn);
+    const long slots = (shape.bm * bn <= 64 * 64 ? 3l : 2l) * device_cus();
+    // the atomics of a 128-row tile cost as much as eight steps (1x1 128 -> 256 56x56 b = 16: chunks of 256 rows 33 us,
+    // of 512 rows 25), where that leaves a quarter of the CUs a workgroup (1x1 128 -> 128 14x14 b = 16: 10.0 us with 256
+    // rows, 11.4 with 512)
+    const int least = shape.bm == 128 && tiles * (Kd / 512) >= device_cus() / 4 ? 512 : 256;
+    const long cap = Kd / least < 1 ? 1 : Kd / least;
+    long best = 1, best_cost = 0;
+    for (long c = 1; c <= cap && c <= 4 * slots / tiles + 1; ++c) {
+        const long steps = (Kd + c * kQuadBK - 1) / (c * kQuadBK);
+        const long cost = (tiles * c + slots - 1) / slots * (steps + kStart);
+        if (c == 1 || cost < best_cost) { best = c; best_cost = cost; }
+    }
+    return (int)best;
+}
+
+// The same for the split kernel: two workgroups fit a CU, one of 256 columns, three of 64 x 64 tiles.
+static int quad_filter_splits(int M, int N, int Kd)
+{
+    const bool wide = wide_shape(M, N);
     const TilePick shape = pick_tile(M, N, true, 1 << 20);
     const long tiles = wide ? (long)((M + 127) / 128) * ((N + 255) / 256) : shape.blocks(M, N, 1);
     const long slots = (wide ? 1l : shape.bm * shape.bn <= 64 * 64 ? 3l : 2l) * device_cus();
@@ -56,11 +80,17 @@ __global__ void reduce_partials_kernel(const float *part, int splits, size_t pla
 // do not pay for the table of a 64-row step (196 rows: 11.7 against 10.9 us).  b = 256, 128 for the strided ones.
 // Padded filters of more than 31 taps need two masks per pixel, whose table pays later still (us, runs / element by
 // element, rows): 11x11 on 8x7 2408 18.6 / 16.2, 38528 66.5 / 90.5; 11x11 on 16x16 11008 83.9 / 79.5; 7x7/2 on 48x48
-// 18432 17.3 / 14.5, on 96x96 73728 33.0 / 34.1; 7x7 on 24x24 4608 11.1 / 10.5, 73728 59.4 / 88.6.
+// 18432 17.3 / 14.5, on 96x96 73728 31.1 / 33.0; 7x7 on 24x24 4608 11.1 / 10.5, 73728 59.4 / 88.6.
+// A tile of 96 or 128 rows that has at most 64 columns keeps the element-wise kernel up to 131072 rows (3 -> 256 3x3 32x32
+// b = 64 26.3 / 22.7, 32 -> 256 1x1 56x56 b = 16 19.3 / 15.4; 3 -> 128 3x3 56x56 b = 64, 200704 rows 41 / 46).
 static bool bf16_quads_pay(const Dims &d, int Kd)
 {
     if (Kd < 2048 || d.P * d.Q % 4 != 0) return false;
     const bool masked = d.ph != 0 || d.pw != 0, even_rows = d.Q % 4 == 0;
+    // tiles of 96 and more rows whose columns are mostly padding
+    if (d.crs() <= 64 && (masked || Kd >= 32768) && Kd < 131072 &&
+        pick_tile(d.K, d.crs(), true, bf16q_filter_splits(d.K, d.crs(), Kd)).bm >= 96)
+        return false;
     if (masked && d.R * d.S > 31 && Kd < 32768) return false;
     if (d.sw == 1) return even_rows || (d.Q == d.W && d.sh == 1);
     return d.sw == 2 && even_rows && (!masked || d.R * d.S > 31);
@@ -128,8 +158,9 @@ static hipError_t implicit_bwd_filter_t(const Dims &d, int b, const void *x, con
     hipError_t e;
     GemmShape g{d.K, d.crs(), b * d.P * d.Q};
     g.splits = d.det ? det_filter_splits(d, b)
-               : (F32 ? g.M > 32 : bf16_quads_pay(d, g.Kd)) ? quad_filter_splits(g.M, g.N, g.Kd, F32)
-                                                            : filter_splits(g.M, g.N, g.Kd);
+               : F32 && g.M > 32 ? quad_filter_splits(g.M, g.N, g.Kd)
+               : !F32 && bf16_quads_pay(d, g.Kd) ? bf16q_filter_splits(g.M, g.N, g.Kd)
+                                                 : filter_splits(g.M, g.N, g.Kd);
     const bool partials = d.det && g.splits > 1;
     if (!partials && beta == 0.f && (e = fill_zero(dw, (size_t)d.K * d.crs(), s)) != hipSuccess) return e;
     KLaneParams pa{};

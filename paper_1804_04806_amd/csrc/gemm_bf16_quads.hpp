@@ -20,7 +20,7 @@ namespace ucd {
 constexpr int kQuadBK = 64;
 
 struct PixelQuadTable {
-    static constexpr int kTabRows = 256, kCap = kTabRows + 3 * kQuadBK;
+    static constexpr int kTabRows = 256, kCap = kTabRows + 2 * kQuadBK;  // the pipeline looks two steps ahead
     uint32_t dy_off[kCap];  // byte offset of (n, a, b) in dy, kOob past the end
     uint32_t x_off[kCap];   // byte offset (signed) of the window origin in x
     uint32_t ok_a[kCap];    // MODE 1: bit r*S+s set = tap inside the image; MODE 2: bit r, of the window's rows
@@ -112,13 +112,18 @@ struct QuadHalfX : QuadHalf<TD> {
 #pragma unroll 1
         for (int e = threadIdx.x; e < PixelQuadTable::kCap; e += kThreads) {
             const int kk = k_begin + e;
+            if (kk >= k_end) {
+                sh.dy_off[e] = sh.x_off[e] = kOob;
+                if constexpr (MODE != 0) sh.ok_a[e] = 0u;
+                if constexpr (MODE == 2) sh.ok_b[e] = 0u;
+                continue;
+            }
             uint32_t n, rest, a, b;
             g.grid_hw.divmod((uint32_t)kk, n, rest);
             g.grid_w.divmod(rest, a, b);
             const int hb = (int)a * g.mul_h + g.add_h, wb = (int)b * g.mul_w + g.add_w;
-            const bool live = kk < k_end;
-            sh.dy_off[e] = live ? 2u * (uint32_t)((int)n * peer.p->n_stride + (int)rest) : kOob;
-            sh.x_off[e] = MODE != 0 || live ? 2u * (uint32_t)((int)n * g.n_stride + hb * g.Wt + wb) : kOob;
+            sh.dy_off[e] = 2u * (uint32_t)((int)n * peer.p->n_stride + (int)rest);
+            sh.x_off[e] = 2u * (uint32_t)((int)n * g.n_stride + hb * g.Wt + wb);
             if constexpr (MODE != 0) {
                 uint32_t okh = 0, okw = 0;
 #pragma unroll 1
@@ -127,7 +132,7 @@ struct QuadHalfX : QuadHalf<TD> {
 #pragma unroll 1
                 for (int r = 0; r < g.n_tap_h; ++r)
                     if ((unsigned)(hb + r) < (unsigned)g.Ht) okh |= MODE == 1 ? okw << (r * g.n_tap_w) : 1u << r;
-                sh.ok_a[e] = live ? okh : 0u;
+                sh.ok_a[e] = okh;
                 if constexpr (MODE == 2) sh.ok_b[e] = okw;
             }
         }
@@ -284,8 +289,10 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel_bf16q(AParams pa, BPa
     lb.fetch(k_begin, rb, la);
     la.template stage<H::PA>(lds[0], ra);
     lb.template stage<H::PB>(lds[0] + H::A_BYTES, rb);
-    la.fetch(k_begin + kQuadBK, ra, lb);
-    lb.fetch(k_begin + kQuadBK, rb, la);
+    if (k_begin + kQuadBK < k_end) {
+        la.fetch(k_begin + kQuadBK, ra, lb);
+        lb.fetch(k_begin + kQuadBK, rb, la);
+    }
     __syncthreads();
 
     int buf = 0;
@@ -308,6 +315,9 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel_bf16q(AParams pa, BPa
                 b[slot][j] = __builtin_bit_cast(
                     bf16x8, *reinterpret_cast<const u32x4 *>(cur + H::A_BYTES + ((2 * u + lhi) * H::PB + wn0 + 32 * j + l32) * 16));
         };
+        // behind the chunk's end nothing is loaded: a short chunk would spend a good part of its loads there (what the
+        // registers hold then is staged once more and not multiplied)
+        const bool more = k0 + 2 * kQuadBK < k_end;
         read_ops(0, 0);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -321,11 +331,11 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel_bf16q(AParams pa, BPa
             // the registers hold the next tile: to the other buffer, and loaded with the one after it
             if (u == 0) {
                 la.template stage<H::PA>(nxt, ra);
-                la.fetch(k0 + 2 * kQuadBK, ra, lb);
+                if (more) la.fetch(k0 + 2 * kQuadBK, ra, lb);
             }
             if (u == 1) {
                 lb.template stage<H::PB>(nxt + H::A_BYTES, rb);
-                lb.fetch(k0 + 2 * kQuadBK, rb, la);
+                if (more) lb.fetch(k0 + 2 * kQuadBK, rb, la);
             }
             __builtin_amdgcn_sched_barrier(0);
         }

@@ -174,3 +174,21 @@ def test_reproducible_backward_filter_prices_the_planes_it_launches():
     finally:
         assert ucd.ucd_set_deterministic(0) == 1
     assert all(len(v) > 3 for v in planes_of.values()) and len(planes_of) == 2   # both kernels, many chunk counts
+
+
+def _bwd_filter_launch(n, c, hw, k, r, stride=1):
+    L = ucd.layer(N=n, C=c, H=hw, W=hw, K=k, R=r, S=r, pad_h=r // 2, pad_w=r // 2, stride_h=stride, stride_w=stride, dtype=1)
+    text = ucd.ucd_describe_micro(L, ucd.BWD_FILTER, ucd.ALGO_IMPLICIT, n)[0]
+    return text, int(re.search(r"tiles=(\d+)", text).group(1)) * int(re.search(r"splits=(\d+)", text).group(1))
+
+
+def test_bf16_backward_filter_launch_rules():
+    """Workgroups of the kernel that reads runs of pixels: one round of two per CU (three of 64 x 64 and 32 x 128 tiles),
+    not a second one of half as long chunks; and wide tiles that are mostly padding stay with the element-wise kernel."""
+    for case, most in (((16, 128, 56, 128, 3), 512), ((64, 128, 32, 128, 3), 512), ((64, 64, 32, 64, 3), 768),
+                       ((64, 32, 32, 24, 5), 768), ((64, 32, 56, 32, 3), 768), ((16, 128, 56, 256, 1), 512)):
+        text, wgs = _bwd_filter_launch(*case)
+        assert "gemm_kernel_bf16q" in text and 0.7 * most <= wgs <= most, (case, wgs, text)
+    for case in ((64, 3, 32, 256, 3), (32, 3, 56, 96, 3), (16, 32, 56, 192, 1)):
+        text, _ = _bwd_filter_launch(*case)
+        assert "gemm_kernel_bf16<" in text, (case, text)

@@ -127,7 +127,7 @@ def test_reproducible_mode_plans_and_runs_a_layer(deterministic):
 
 
 # bf16 BackwardFilter: layers whose reduction chunks are counted in 64 rows (runs of four pixels) and in 16
-HALF = [(LONG, True), (Shape(33, 20, 14, 14, 64, 3, 3, 1, 1, "b33"), True), (Shape(12, 24, 32, 31, 70, 1, 1, 2, 0, "s2"), True),
+HALF = [(LONG, True), (Shape(33, 20, 14, 14, 64, 3, 3, 1, 1, "b33"), True), (Shape(12, 80, 32, 31, 70, 1, 1, 2, 0, "s2"), True),
         (Shape(40, 17, 13, 13, 40, 3, 3, 1, 1, "odd-images"), False)]
 
 
