@@ -62,6 +62,23 @@ static hipError_t implicit_fwd_bf16_vec(const Dims &d, int b, const void *x, con
     return launch_gemm<Loaders<bf16>::KLane0, RunNLaneMaskedBig, EpiNCHWT<bf16>, true>(pa, pb, pe, g, s);
 }
 
+// Whether the split kernel is the faster one for an unsplit Forward GEMM.  With short reductions a tile's start and end
+// outweigh its steps, and the split kernel's cost more.  The fp32 kernel decodes taps, so layers with several cross
+// earlier than 1x1 ones; it also loses more to rows of 128 than to 64.  Its time / the split kernel's:
+//   one round of workgroups (tiles of 64 rows): 1x1 128 rows 0.93, 256 0.97, 512 1.00; 3x3 144 0.94, 7x7 196 0.99
+//   up to 64 output channels: 1x1 96 rows 0.93, 128 1.00 (b = 80, 24x74); 3x3 on 56x56 b = 32: 27 0.80, 72 0.93, 108 0.98,
+//   144 1.05 (3 -> 64 on 224x224, b = 8: 35 us / 50 us); 7x7 147 0.97, 196 1.01
+//   tiles of 96 rows: 3x3 27 0.80, 72 0.95, 90 0.98, 108 1.02; of 128 rows: 27 0.91 to 1.00, 36 1.03, 72 1.12
+//   more than 64 output channels, 1x1: 64 rows 0.95 to 1.00, 80 1.00 to 1.05
+static bool split_forward_pays(const GemmShape &g, int taps)
+{
+    const TilePick t = pick_tile(g.M, g.N, true, 1);
+    if (t.bm != 96 && t.blocks(g.M, g.N, 1) <= device_cus()) return g.Kd >= (taps == 1 ? 384 : 200);
+    if (g.M <= 64) return g.Kd >= (taps > 31 ? 196 : 128);
+    if (taps == 1) return g.Kd >= 80;
+    return g.Kd >= (pick_rows(g.M, true) == 96 ? 96 : 36);
+}
+
 template <class E>
 static hipError_t implicit_fwd_t(const Dims &d, int b, const void *x, const void *w, void *y, hipStream_t s)
 {
@@ -97,21 +114,15 @@ static hipError_t implicit_fwd_t(const Dims &d, int b, const void *x, const void
     // (filters of more than one tap: 1x1 layers are bound by memory, not by the loader)
     const bool free = d.ph == 0 && d.pw == 0 && d.R * d.S > 1;
     if constexpr (F32) {
-        // 1x1 layers with short reductions stay on the fp32 kernel: a tile's start and end outweigh its steps, and the
-        // split kernel's cost more.  b = 80, 24x74, us split / fp32: 64 output channels, 64 rows 27.2 / 23.9, 96 rows
-        // 31.8 / 29.5, 128 rows 35.8 / 35.8; 128 and 186 output channels, 48 rows 38 / 36 and 51 / 45, 64 rows 41 / 41
-        // and 56 / 53, 80 rows 44 / 46 and 60 / 60, 96 rows 47 / 52 and 65 / 68.
-        if (d.R * d.S > 1 || g.Kd >= (g.M <= 64 ? 128 : 80)) {
+        if (split_forward_pays(g, d.R * d.S)) {
             if (free) return launch_gemm<CellK32T, GatherCellFree, EpiNCHW, true>(pa, pb, pe, g, s);
             if (d.R * d.S <= 31) return launch_gemm<CellK32T, GatherCell, EpiNCHW, true>(pa, pb, pe, g, s);
             return launch_gemm<CellK32T, GatherCellBig, EpiNCHW, true>(pa, pb, pe, g, s);
         }
-        return launch_gemm<L::template KLane0, L::template GatherNLane, EpiNCHW, true>(pa, pb, pe, g, s);
-    } else {
-        if (free) return launch_gemm<L::template KLane0, L::template GatherNLaneFree, EpiNCHWT<E>, true>(pa, pb, pe, g, s);
-        if (d.R * d.S <= 31) return launch_gemm<L::template KLane0, L::template GatherNLane, EpiNCHWT<E>, true>(pa, pb, pe, g, s);
-        return launch_gemm<L::template KLane0, L::template GatherNLaneBig, EpiNCHWT<E>, true>(pa, pb, pe, g, s);
     }
+    if (free) return launch_gemm<L::template KLane0, L::template GatherNLaneFree, EpiNCHWT<E>, true>(pa, pb, pe, g, s);
+    if (d.R * d.S <= 31) return launch_gemm<L::template KLane0, L::template GatherNLane, EpiNCHWT<E>, true>(pa, pb, pe, g, s);
+    return launch_gemm<L::template KLane0, L::template GatherNLaneBig, EpiNCHWT<E>, true>(pa, pb, pe, g, s);
 }
 
 hipError_t implicit_fwd(const Dims &d, int b, const void *x, const void *w, void *y, hipStream_t s)

@@ -192,3 +192,15 @@ def test_bf16_backward_filter_launch_rules():
     for case in ((64, 3, 32, 256, 3), (32, 3, 56, 96, 3), (16, 32, 56, 192, 1)):
         text, _ = _bwd_filter_launch(*case)
         assert "gemm_kernel_bf16<" in text, (case, text)
+
+
+def test_fp32_forward_short_reductions_stay_on_the_fp32_kernel():
+    """Layers whose tiles have few reduction steps, by which kernel they run (the split kernel's tiles start and end
+    slower): first layers, small launches, and the same layers with more input channels."""
+    def kernel(n, c, hw, k, r):
+        L = ucd.layer(N=n, C=c, H=hw, W=hw, K=k, R=r, S=r, pad_h=r // 2, pad_w=r // 2)
+        return ucd.ucd_describe_micro(L, ucd.FWD, ucd.ALGO_IMPLICIT, n)[0].split("gemm_kernel")[1].split("<")[0]
+    for case in ((8, 3, 224, 64, 3), (32, 1, 56, 96, 5), (32, 8, 56, 40, 3), (2, 16, 28, 128, 3), (8, 192, 14, 64, 1)):
+        assert kernel(*case) == "", case
+    for case in ((8, 16, 224, 64, 3), (32, 16, 56, 96, 3), (32, 8, 56, 128, 3), (2, 32, 28, 128, 3), (8, 512, 14, 64, 1)):
+        assert kernel(*case) == "_split", case
