@@ -3,6 +3,8 @@
 Bounds.  A product of two split operands leaves out terms below 2^-24 of it and accumulates in fp32; over n
 rows the worst relative L2 error that fp32 accumulation in chunks allows is a few 2^-24 * sqrt(n), and the
 kernel is built to stay below what the fp32 matrix instructions give (3e-7 to 1e-6 on these shapes): 1e-6."""
+import re
+
 import numpy as np
 import pytest
 
@@ -29,6 +31,10 @@ SHAPES = [
     # the same heights with reductions long enough for the split kernel in launches of one round of workgroups
     Shape(1, 23, 12, 12, 65, 3, 3, 1, 1), Shape(2, 9, 14, 14, 129, 5, 5, 1, 2), Shape(2, 387, 9, 7, 64, 1, 1, 1, 0),
     Shape(3, 401, 11, 6, 127, 1, 1, 1, 0), Shape(2, 390, 8, 8, 65, 1, 1, 1, 0),
+    # 128 x 256 tiles on eight waves: output channels just under 256, pixels just over a multiple of 256, filters of
+    # nearly 512 columns; border masks, none, and more than 31 taps; column strides 1 and 2
+    Shape(61, 56, 20, 21, 250, 3, 3, 1, 1), Shape(61, 56, 22, 23, 250, 3, 3, 1, 0), Shape(61, 10, 20, 21, 250, 7, 7, 1, 3),
+    Shape(61, 56, 40, 41, 250, 3, 3, 2, 1), Shape(61, 56, 41, 43, 250, 3, 3, 2, 0), Shape(61, 10, 40, 41, 250, 7, 7, 2, 3),
 ]
 
 
@@ -56,7 +62,25 @@ def test_split_gemm_edges(s):
         assert rel_l2(got, ref) <= 1e-6, (ucd.OP_NAMES[op], rel_l2(got, ref))
 
 
-@pytest.mark.parametrize("s", [SHAPES[i] for i in (6, 9, 10, 13, 14, 0, 24)], ids=_id)
+def test_shapes_reach_every_tile_and_loader():
+    """Which kernels the shapes above run is the launch rules' choice: every tile of the split kernel with every
+    operand loader that it takes for such tiles has to be among them."""
+    seen = set()
+    for s in SHAPES:
+        for op, algo in _runs(s):
+            text = ucd.ucd_describe_micro(ucd.layer(s), op, algo, s.N)[0]
+            if "gemm_kernel_split" in text:
+                tile = re.search(r"Tile<(\w+)>", text).group(1)
+                taps = "free" if s.pad == 0 and s.R * s.S > 1 else "big" if s.R * s.S > 31 else "few"
+                seen.add((tile, "pixels" if op != ucd.BWD_FILTER else f"filter stride {min(s.stride, 3)}", taps))
+    for tile in ("64x64", "64x128", "96x128", "128x64", "128x128", "128x256"):
+        assert any(t == tile for t, _, _ in seen), (tile, sorted(seen))
+    for taps in ("few", "free", "big"):
+        assert ("128x256", "pixels", taps) in seen and ("128x256", "filter stride 1", taps) in seen, sorted(seen)
+        assert ("128x256", "filter stride 2", taps) in seen, sorted(seen)
+
+
+@pytest.mark.parametrize("s", [SHAPES[i] for i in (6, 9, 10, 13, 14, 0, 24, 26)], ids=_id)
 def test_split_gemm_not_finite(s):
     """Infinities and NaN come out where, and as, fp32 arithmetic gives them; the other outputs stay exact."""
     x, w, dy = inputs(s, seed=8)
@@ -95,7 +119,7 @@ def test_split_gemm_range(s, scale, partner):
             assert rel_l2(got, ref) <= 1e-6, (ucd.OP_NAMES[op], first, rel_l2(got, ref))
 
 
-@pytest.mark.parametrize("s", [SHAPES[i] for i in (0, 9, 11, 13)], ids=_id)
+@pytest.mark.parametrize("s", [SHAPES[i] for i in (0, 9, 11, 13, 26)], ids=_id)
 def test_split_gemm_small_parts(s):
     """One image, one output channel or one input channel far below bf16's range among ordinary ones, whose results
     are compared by themselves."""
