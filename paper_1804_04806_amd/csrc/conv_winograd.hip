@@ -1199,9 +1199,12 @@ static hipError_t winograd_fused_run(const Dims &d, int op, int b, const void *i
     static const bool fp32_pipe = getenv("UCD_FUSED_FP32") != nullptr;
     const bool rows = std::is_same_v<E, float> && !elementwise && g.pad_w <= 2;
     // fp32 tensors with at least 32 input channels: three-way split operands on the bf16 matrix pipe (wino_split.hpp;
-    // UCD_FUSED_FP32=1 in the environment keeps the fp32 instructions).  A rule on the layer alone: micro-batches
-    // of one call share U, whose layout differs.
-    const bool split = rows && !fp32_pipe && g.Ci >= 32;
+    // UCD_FUSED_FP32=1 in the environment keeps the fp32 instructions).  With more than 64 output channels from 41 on:
+    // up to there wino_fused_kernel's 8-channel steps pad less and its 128 x 32 blocks load less (us, split / fp32
+    // kernel, 56x56 b = 32: 40 -> 128 channels 78 / 70, 32 -> 256 113 / 104, 44 -> 128 76 / 74; 14x14 b = 64: 40 -> 128
+    // 22 / 21, 44 -> 128 21 / 22; 40 -> 64 21 / 21).  A rule on the layer alone: micro-batches of one call share U, whose
+    // layout differs.
+    const bool split = rows && !fp32_pipe && g.Ci >= (phased || g.Co <= 64 ? 32 : 41);
     if (filter_ready) {
         // U of this filter is still in the workspace from the previous micro-batch
     } else if (log) log->add(phased ? "wino_phase_filter_kernel" : bf16_pipe ? "wino_filter_bf16_kernel" : "wino_filter_kernel");

@@ -204,3 +204,14 @@ def test_fp32_forward_short_reductions_stay_on_the_fp32_kernel():
         assert kernel(*case) == "", case
     for case in ((8, 16, 224, 64, 3), (32, 16, 56, 96, 3), (32, 8, 56, 128, 3), (2, 32, 28, 128, 3), (8, 512, 14, 64, 1)):
         assert kernel(*case) == "_split", case
+
+
+def test_fused_winograd_kernel_by_channels():
+    """fp32 layers of few input channels: the split kernel from 32 on, with more than 64 output channels from 41 on."""
+    def split(c, k, op=ucd.FWD):
+        L = ucd.layer(N=8, C=c, H=28, W=28, K=k, R=3, S=3, pad_h=1, pad_w=1)
+        return "wino_fused_split_kernel" in ucd.ucd_describe_micro(L, op, ucd.ALGO_WINOGRAD_FUSED, 8)[0]
+    assert [split(c, 64) for c in (31, 32, 40)] == [False, True, True]
+    assert [split(c, 128) for c in (32, 40, 41)] == [False, False, True]
+    assert [split(k, c, ucd.BWD_DATA) for c, k in ((128, 40), (41, 128))] == [True, True]
+    assert not split(128, 40, ucd.BWD_DATA)

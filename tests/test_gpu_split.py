@@ -138,20 +138,23 @@ def test_split_gemm_small_parts(s):
             assert rel_l2(got[at], ref[at]) <= 1e-6, (ucd.OP_NAMES[op], at, rel_l2(got[at], ref[at]))
 
 
-# ---- fused Winograd F(2x2,3x3), at least 32 input channels ----------------------------------------------------------
+# ---- fused Winograd F(2x2,3x3) ----------------------------------------------------------
 WF = ucd.ALGO_WINOGRAD_FUSED
 WINO_SHAPES = [
     # input channels around the 16-channel step and the 8-channel blocks of the transformed filter, output channels
     # around the 64-channel block, tiles around the 64-tile block, odd and even widths, paddings 0 to 2
-    Shape(1, 32, 6, 6, 64, 3, 3, 1, 1), Shape(3, 33, 13, 13, 65, 3, 3, 1, 1), Shape(2, 40, 9, 16, 31, 3, 3, 1, 0),
+    Shape(1, 32, 6, 6, 64, 3, 3, 1, 1), Shape(3, 49, 13, 13, 65, 3, 3, 1, 1), Shape(2, 40, 9, 16, 31, 3, 3, 1, 0),
     Shape(2, 47, 10, 7, 130, 3, 3, 1, 2), Shape(5, 56, 8, 11, 3, 3, 3, 1, 1), Shape(1, 100, 17, 16, 96, 3, 3, 1, 1),
     Shape(3, 64, 5, 4, 37, 3, 3, 1, 2), Shape(2, 36, 3, 3, 40, 3, 3, 1, 1),
+    Shape(3, 33, 13, 13, 63, 3, 3, 1, 1), Shape(2, 41, 7, 7, 66, 3, 3, 1, 1),
 ]
 PHASE_SHAPES = [Shape(2, 3, 31, 35, 48, 11, 11, 4, 0), Shape(1, 9, 22, 17, 33, 5, 5, 2, 2), Shape(2, 4, 23, 23, 40, 7, 7, 3, 1)]
 
 
 def _wino_runs(s):
-    return ([(ucd.FWD, s)] if s.C >= 32 and s.stride == 1 else []) + ([(ucd.BWD_DATA, s)] if s.K >= 32 else [])
+    """Operations on the split kernel: 32 input channels, 41 with more than 64 output channels."""
+    return ([(ucd.FWD, s)] if s.C >= (32 if s.K <= 64 else 41) and s.stride == 1 else []) + \
+           ([(ucd.BWD_DATA, s)] if s.K >= (32 if s.C <= 64 or s.stride > 1 else 41) else [])
 
 
 @pytest.mark.parametrize("s", WINO_SHAPES + PHASE_SHAPES, ids=_id)
