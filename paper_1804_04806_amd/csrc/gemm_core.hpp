@@ -1354,6 +1354,10 @@ __device__ __forceinline__ void fp32_tile(const AParams pa, const BParams pb, fl
                             la.load(i, ra.r);
                         }
                 }
+                // With one MFMA per k-pair A's and B's writes stand together; joined into one instruction behind A's
+                // reload they would keep A's old registers alive, and the loop would end in copies of the new ones,
+                // waiting for every load in flight
+                if constexpr (NM == 1) __builtin_amdgcn_sched_barrier(0);
                 if (m == 2 % NM) {
 #pragma unroll
                     for (int i = 0; i < NB; ++i)
