@@ -118,14 +118,42 @@ size_t implicit_det_ws_bytes(const Dims &d, int b)
     return splits > 1 ? (size_t)4 * splits * d.K * d.crs() : 0;  // one chunk: a single addition per element
 }
 
-// Operands in runs of four pixels, masks by padding and tap count (see QuadXT, QuadHalfX); fp32 tensors on the split
-// kernel, bf16 tensors on theirs.
+// Whether the split kernel is the faster one for fp32 tensors.  Below 33 output channels it is not (see launch_gemm).
+// Where its runs of four pixels break (rows of other than a multiple of four pixels under a column stride of 2, other
+// strides, padding), or two masks per pixel are needed, it loads element by element or builds a dearer table, which
+// pays from a number of multiplications on.  Time of the fp32 kernel / of this one by millions of multiplications:
+// column stride 2, runs broken, up to 31 taps: 100 0.92 to 1.0, 200 to 400 0.92 to 0.99, 400 to 800 0.99 to 1.08;
+// padded filters of more taps, broken 100 0.85, 800 0.90 to 1.02, 1600 0.82 to 1.12, more 1.14 to 1.25; not broken 100
+// 0.91 to 0.95, 200 to 400 0.97 to 1.14.  All other layers 0.95 to 1.5.
+static bool split_filter_pays(const Dims &d, int Kd)
+{
+    if (d.K <= 32) return false;
+    // tiles of 96 and more rows most of whose columns are padding, in one round of workgroups (3 -> 128 3x3 32x32 b = 64
+    // 29 / 33 us)
+    if (d.crs() <= 32 && Kd < 131072 && pick_tile(d.K, d.crs(), true, quad_filter_splits(d.K, d.crs(), Kd)).bm >= 96) return false;
+    const double mul = (double)d.K * d.crs() * Kd;
+    const bool masked = d.ph != 0 || d.pw != 0, big = masked && d.R * d.S > 31;
+    const bool whole = d.sw == 1 || (d.sw == 2 && d.Q % 4 == 0);
+    if (whole) return !big || mul >= 2e8;
+    if (big) return mul >= 1.6e9;
+    return (d.sw > 2 && !masked) || mul >= 4e8;
+}
+
+// Operands in runs of four pixels, masks by padding and tap count (see QuadXT, QuadHalfX): fp32 tensors on the split
+// kernel, bf16 tensors on theirs; or element by element.
 template <class E, class Epi>
 static hipError_t launch_filter_gemm(const Dims &d, const KLaneParams &pa, const KLaneParams &pb,
                                      const typename Epi::Params &pe, const GemmShape &g, hipStream_t s)
 {
     const bool two = d.sw == 2, free = d.ph == 0 && d.pw == 0, few = d.R * d.S <= 31;
-    if constexpr (std::is_same<E, float>::value) {
+    typedef Loaders<E> L;
+    constexpr bool F32 = std::is_same<E, float>::value;
+    if (F32 ? !split_filter_pays(d, g.Kd) : !bf16_quads_pay(d, g.Kd)) {
+        if (few) return launch_gemm<L::template DyTab, L::template XTab, Epi, true>(pa, pb, pe, g, s);
+        if (free) return launch_gemm<L::template DyKLane, L::template XKLaneFree, Epi, true>(pa, pb, pe, g, s);
+        return launch_gemm<L::template DyKLane, L::template XKLane, Epi, true>(pa, pb, pe, g, s);
+    }
+    if constexpr (F32) {
         if (free)
             return two ? launch_gemm<QuadDyFree, QuadXFree2, Epi, true>(pa, pb, pe, g, s)
                        : launch_gemm<QuadDyFree, QuadXFree, Epi, true>(pa, pb, pe, g, s);
@@ -135,12 +163,6 @@ static hipError_t launch_filter_gemm(const Dims &d, const KLaneParams &pa, const
         return two ? launch_gemm<QuadDyFree, QuadXBig2, Epi, true>(pa, pb, pe, g, s)
                    : launch_gemm<QuadDyFree, QuadXBig, Epi, true>(pa, pb, pe, g, s);
     } else {
-        typedef Loaders<E> L;
-        if (!bf16_quads_pay(d, g.Kd)) {
-            if (few) return launch_gemm<L::template DyTab, L::template XTab, Epi, true>(pa, pb, pe, g, s);
-            if (free) return launch_gemm<L::template DyKLane, L::template XKLaneFree, Epi, true>(pa, pb, pe, g, s);
-            return launch_gemm<L::template DyKLane, L::template XKLane, Epi, true>(pa, pb, pe, g, s);
-        }
         if (free)
             return two ? launch_gemm<QuadHalfDy, QuadHalfXFree2, Epi, true>(pa, pb, pe, g, s)
                        : launch_gemm<QuadHalfDy, QuadHalfXFree, Epi, true>(pa, pb, pe, g, s);
@@ -158,7 +180,7 @@ static hipError_t implicit_bwd_filter_t(const Dims &d, int b, const void *x, con
     hipError_t e;
     GemmShape g{d.K, d.crs(), b * d.P * d.Q};
     g.splits = d.det ? det_filter_splits(d, b)
-               : F32 && g.M > 32 ? quad_filter_splits(g.M, g.N, g.Kd)
+               : F32 && split_filter_pays(d, g.Kd) ? quad_filter_splits(g.M, g.N, g.Kd)
                : !F32 && bf16_quads_pay(d, g.Kd) ? bf16q_filter_splits(g.M, g.N, g.Kd)
                                                  : filter_splits(g.M, g.N, g.Kd);
     const bool partials = d.det && g.splits > 1;

@@ -201,8 +201,9 @@ hipError_t launch_gemm(const AP &pa, const BP &pb, const typename Epi::Params &p
         // instructions take (32 output channels, 144 rows, 16 workgroups: 10.7 against 9.7 us)
         if (t.bm == 32)
             return launch_tile<Tile<32, 128, 1, 4>, FallbackOf<AL>::template L, FallbackOf<BL>::template L, Epi>(pa, pb, pe, g, s);
+    } else {
+        if (t.bm == 32) return launch_tile<Tile<32, 128, 1, 4>, AL, BL, Epi>(pa, pb, pe, g, s);
     }
-    if (t.bm == 32) return launch_tile<Tile<32, 128, 1, 4>, AL, BL, Epi>(pa, pb, pe, g, s);
     if (t.bm == 64) {
         if (t.bn == 64) return launch_tile<Tile<64, 64, 2, 2>, AL, BL, Epi>(pa, pb, pe, g, s);
         return launch_tile<Tile<64, 128, 2, 2>, AL, BL, Epi>(pa, pb, pe, g, s);
