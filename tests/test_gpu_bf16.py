@@ -158,18 +158,20 @@ def test_bf16_plan_on_device_and_execute():
                             dw_scratch if op == ucd.BWD_FILTER else wb.clone(), scratch_y, ws)
         assert sum(b for _, b in plan.micro) == s.N
         ref = run_oracle(s, op, x=x, w=w, dy=dy)
+        # the planner takes what it measures as fastest: the bound is that of the algorithms in the plan
+        slack = 3e-2 if any(a == ucd.ALGO_WINOGRAD_FUSED for a, _ in plan.micro) else 1e-5
         if op == ucd.FWD:
             out = torch.empty(s.y_shape, dtype=torch.bfloat16, device=dev)
             ucd.ucd_conv_fwd(plan, xb, wb, out, ws)
-            check_bf16_output(out.float().cpu().numpy(), ref, "fwd")
+            check_bf16_output(out.float().cpu().numpy(), ref, "fwd", slack=slack)
         elif op == ucd.BWD_DATA:
             out = torch.empty(s.x_shape, dtype=torch.bfloat16, device=dev)
             ucd.ucd_conv_bwd_data(plan, dyb, wb, out, ws)
-            check_bf16_output(out.float().cpu().numpy(), ref, "bwd_data")
+            check_bf16_output(out.float().cpu().numpy(), ref, "bwd_data", slack=slack)
         else:
             out = torch.empty(s.w_shape, dtype=torch.float32, device=dev)
             ucd.ucd_conv_bwd_filter(plan, xb, dyb, out, 0.0, ws)
-            assert rel_l2(out.cpu().numpy(), ref) <= 1e-5
+            assert rel_l2(out.cpu().numpy(), ref) <= l2_tol(plan.micro)
 
 
 # BackwardFilter in runs of four pixels (64-row steps): images of a multiple of four pixels, rows that are and are not,
