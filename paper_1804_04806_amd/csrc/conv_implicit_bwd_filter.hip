@@ -122,21 +122,21 @@ size_t implicit_det_ws_bytes(const Dims &d, int b)
 // Where its runs of four pixels break (rows of other than a multiple of four pixels under a column stride of 2, other
 // strides, padding), or two masks per pixel are needed, it loads element by element or builds a dearer table, which
 // pays from a number of multiplications on.  Time of the fp32 kernel / of this one by millions of multiplications:
-// column stride 2, runs broken, up to 31 taps: 100 0.92 to 1.0, 200 to 400 0.92 to 0.99, 400 to 800 0.99 to 1.08;
-// padded filters of more taps, broken 100 0.85, 800 0.90 to 1.02, 1600 0.82 to 1.12, more 1.14 to 1.25; not broken 100
-// 0.91 to 0.95, 200 to 400 0.97 to 1.14.  All other layers 0.95 to 1.5.
+// column stride 2, runs broken, up to 31 taps: 100 0.92 to 1.0, 200 to 400 0.92 to 0.99 (unpadded 0.94 to 1.02), 400 to 800
+// 0.99 to 1.08; padded filters of more taps, broken 100 0.85, 800 0.90 to 1.02, 1100 0.82, 1260 1.06 to 1.12, more 1.14 to
+// 1.25; not broken 100 to 180 0.91 to 0.95, 200 to 400 0.97 to 1.14, tiles of 96 rows 180 1.10.  Tiles of 96 rows, which the fp32 kernel cannot
+// make smaller in small launches, 1.05 in all but padded filters of many taps.  All other layers 0.95 to 1.5.
 static bool split_filter_pays(const Dims &d, int Kd)
 {
     if (d.K <= 32) return false;
-    // tiles of 96 and more rows most of whose columns are padding, in one round of workgroups (3 -> 128 3x3 32x32 b = 64
-    // 29 / 33 us)
-    if (d.crs() <= 32 && Kd < 131072 && pick_tile(d.K, d.crs(), true, quad_filter_splits(d.K, d.crs(), Kd)).bm >= 96) return false;
     const double mul = (double)d.K * d.crs() * Kd;
     const bool masked = d.ph != 0 || d.pw != 0, big = masked && d.R * d.S > 31;
     const bool whole = d.sw == 1 || (d.sw == 2 && d.Q % 4 == 0);
-    if (whole) return !big || mul >= 2e8;
-    if (big) return mul >= 1.6e9;
-    return (d.sw > 2 && !masked) || mul >= 4e8;
+    const bool rows96 = pick_rows(d.K, true) == 96;
+    if (big) return mul >= (!whole ? 1.2e9 : rows96 ? 1.5e8 : 2e8);
+    if (whole || rows96) return true;
+    if (!masked) return d.sw > 2 || mul >= 3e8;
+    return mul >= 4e8;
 }
 
 // Operands in runs of four pixels, masks by padding and tap count (see QuadXT, QuadHalfX): fp32 tensors on the split
@@ -149,7 +149,9 @@ static hipError_t launch_filter_gemm(const Dims &d, const KLaneParams &pa, const
     typedef Loaders<E> L;
     constexpr bool F32 = std::is_same<E, float>::value;
     if (F32 ? !split_filter_pays(d, g.Kd) : !bf16_quads_pay(d, g.Kd)) {
-        if (few) return launch_gemm<L::template DyTab, L::template XTab, Epi, true>(pa, pb, pe, g, s);
+        // fp32: without padding the loader without masks or table is the faster one for few taps too (us, table / this:
+        // 64 -> 32 3x3 56x56 b = 64 98 / 87, 64 -> 24 3x3/2 28x28 16.2 / 14.5)
+        if (few && !(F32 && free)) return launch_gemm<L::template DyTab, L::template XTab, Epi, true>(pa, pb, pe, g, s);
         if (free) return launch_gemm<L::template DyKLane, L::template XKLaneFree, Epi, true>(pa, pb, pe, g, s);
         return launch_gemm<L::template DyKLane, L::template XKLane, Epi, true>(pa, pb, pe, g, s);
     }

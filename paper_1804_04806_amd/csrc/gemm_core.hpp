@@ -766,7 +766,7 @@ template <int TD> using XKLaneFree = PixelKLane<TD, true, float, true>;
 // it refilled when they are used up), instead of once per step per thread.  Per step a thread then reads its entry (two LDS reads for x, one for dy) and spends three
 // vector instructions per x element (mask shift, address add, merge) and none per dy element.
 constexpr int kTabRows = 1024;
-constexpr int kTabCap = kTabRows + 3 * kBK;  // the pipelines look two or three steps past the chunk's end
+constexpr int kTabCap = kTabRows + 2 * kBK;  // the pipelines look two steps ahead
 
 struct PixelTable {
     uint32_t dy_off[kTabCap];   // byte offset of (n, a, b) in dy, or kOob for rows past the end

@@ -82,7 +82,7 @@ struct CellK32T : NoSetup {
     static constexpr bool kBf16 = false, kSplit = true, kWideTiles = true;
     static constexpr int TD = tile_extent(TDX), NTHR = tile_threads(TDX);
     typedef KLane0T<TD, float, NTHR> Fallback;
-    static std::string name() { return "KLane0"; }
+    static std::string name() { return "CellK32"; }
     static constexpr int NE = TD * 2 * 4 >= NTHR * 3 ? 8 : 4;
     static constexpr int TPP = kBK / NE;  // threads per position
     struct Regs { float r[NE]; };
@@ -126,6 +126,7 @@ template <int TDX, bool SMALL, bool NOMASK = false>
 struct GatherCellT : GatherNLaneT<tile_extent(TDX), SMALL, float, NOMASK, tile_threads(TDX)> {
     typedef GatherNLaneT<tile_extent(TDX), SMALL, float, NOMASK, tile_threads(TDX)> Base;
     typedef Base Fallback;
+    static std::string name() { return NOMASK ? "GatherCell<no padding>" : SMALL ? "GatherCell<taps<=31>" : "GatherCell<taps>31>"; }
     static constexpr bool kSplit = true;
     static constexpr bool kWideTiles = true;
     static constexpr int NE = Base::NE, kRows = NE, kLoad = 1;

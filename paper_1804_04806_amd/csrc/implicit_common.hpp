@@ -8,12 +8,14 @@
 
 namespace ucd {
 
-// A CU holds several of these workgroups at once (four of the Forward / BackwardData kernels,
-// three of the BackwardFilter ones, by registers and LDS) and needs them all to keep its matrix
-// pipes busy; workgroups of one launch take equally long, so a launch proceeds in rounds of
-// 256 x resident workgroups, and a last round that is nearly empty costs as much as a full one
-// (measured: the time of a Forward launch is flat from 769 to 1024 tiles).  Split counts are
-// chosen so that the workgroup count fills its rounds.
+// Split counts are chosen so that the workgroup count fills its rounds of 256 x resident workgroups: workgroups of one
+// launch take equally long, and a last round that is nearly empty costs as much as a full one (fp32 kernel, measured:
+// the time of a Forward launch is flat from 769 to 1024 tiles).  A CU holds four workgroups of the fp32 and bf16 Forward
+// / BackwardData kernels and three of the BackwardFilter ones, by registers and LDS, and needs them all to keep its
+// matrix pipes busy.  The split kernel's Forward launches use the same counts although two of its workgroups fit a CU (one
+// of 128 x 256 tiles): over 144 deep layers (1 to 32 images of 7x7 to 28x28) none takes longer than the fp32 kernel
+// with them and the mean is 1.04 times as fast.  The BackwardFilter kernels that read runs of pixels have counts of
+// their own.
 inline long slots_output() { return 4l * device_cus(); }
 inline long slots_filter() { return 3l * device_cus(); }
 
@@ -41,7 +43,7 @@ inline int best_fill(long tiles, long want, long lo, long hi, long slots)
 // Forward / BackwardData write each output once, so normally one workgroup owns a whole
 // reduction.  When the output has too few tiles to give every CU several workgroups (deep
 // layers: many channels, few pixels), the reduction is split as well and the partial results meet
-// through atomics in a zero-filled output.  Chunks keep at least 512 reduction rows.
+// through atomics in a zero-filled output.  Chunks keep at least 512 reduction rows (measured with the fp32 kernel).
 inline int output_splits(int M, int N, int Kd, bool fp32_out)
 {
     if (!fp32_out) return 1;  // bf16 outputs cannot be accumulated with atomics (nor may reproducible runs)

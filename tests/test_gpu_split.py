@@ -59,7 +59,7 @@ def test_split_gemm_edges(s):
         rows = (s.C if op == ucd.FWD else s.K) * s.R * s.S
         split = "gemm_kernel_split" in ucd.ucd_describe_micro(ucd.layer(s), op, algo, s.N)[0]
         if op == ucd.BWD_FILTER:  # strided layers and padded ones of many taps: from a number of multiplications on
-            assert split or (s.K * s.C * s.R * s.S * s.N * s.P * s.Q < 1.6e9 and (s.stride > 1 or s.R * s.S > 31)) or s.C * s.R * s.S <= 32
+            assert split or (s.K * s.C * s.R * s.S * s.N * s.P * s.Q < 1.6e9 and (s.stride > 1 or s.R * s.S > 31))
         else:
             assert split or rows < 384   # short reductions stay on the fp32 kernel
         got = run_hip(s, op, [(algo, s.N)], x=x, w=w, dy=dy)
