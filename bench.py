@@ -47,7 +47,13 @@ WS_LIMIT = 64 << 20
 # `traffic` = this figure x the flops per launch of the step being timed: the planner does not
 # pick the same micro-batch sizes every run, and a kernel's traffic follows its size.
 MEASURED_TRAFFIC_BYTES_PER_FLOP = {
-    "wino_fused_split_kernel": 529.8e6 / 59.19e9,  # conv4 Forward, 256 samples, launched alone
+    # the split kernels: conv4 Forward, conv1 BackwardData, conv2 and conv1 BackwardFilter, conv1 Forward, 256 samples,
+    # launched alone
+    "wino_fused_split_kernel": 529.8e6 / 59.19e9,
+    "wino_fused_split_kernel<phases>": 470.5e6 / 31.38e9,
+    "gemm_kernel_split<Tile<128x256>,PixelTab<dy,quads>,PixelTab<x,quads>,EpiAtomic>": 440.7e6 / 229.3e9,
+    "gemm_kernel_split<Tile<96x128>,PixelTab<dy,quads>,PixelTab<x,quads,no padding>,EpiAtomic>": 647.5e6 / 53.97e9,
+    "gemm_kernel_split<Tile<96x128>,CellK32,GatherCell<no padding>,EpiNCHW>": 479.9e6 / 53.97e9,
     "wino5_fused_kernel": 735.6e6 / 87.77e9,
     "wino_fused_filter_kernel": 569.6e6 / 46.04e9,
     "wino5_fused_filter_kernel": 913.4e6 / 90.6e9,

@@ -166,8 +166,9 @@ inline TilePick pick_tile(int M, int N, bool rows96, long mult)
 // 128 x 256 tiles on eight waves (one workgroup per CU) instead of 128 x 128 on four (two per CU), for the split
 // kernel: a third less staging per MFMA.  With few reduction steps per tile the second resident workgroup's
 // overlap of one's start and the other's end is worth more; and the tiles have to fill most CUs.
-// Measured (us, 128x256 / 128x128): 96->256 5x5 27x27 1090 / 1180, 384->384 3x3 13x13 531 / 583, 64->128 3x3/2 56x56
-// (576 rows) 98 / 107, 128->512 1x1 28x28 (128 rows) 131 / 114; b = 256, 256, 128, 128.
+// Measured (us, 128x256 / 128x128; before the operands were checked, which adds up to 2 % to both): 96->256 5x5 27x27
+// 1090 / 1180, 384->384 3x3 13x13 531 / 583, 64->128 3x3/2 56x56 (576 rows) 98 / 107, 128->512 1x1 28x28 (128 rows)
+// 131 / 114; b = 256, 256, 128, 128.
 inline bool wide_shape(int M, int N)
 {
     return pick_rows(M, true) == 128 && (N + 255) / 256 * 256 <= (N + 127) / 128 * 128 * 17 / 16;

@@ -7,19 +7,20 @@
 // it crosses LDS as one fp32 word and is split in the reader's registers, once; U is read by its one wave straight
 // from the workspace in operand order (blocks of 8 input channels, [point][Ci / 8][Mo4][8]) and never enters LDS.
 // With the 32 x 32 quarter blocks of wino_fused_kernel each value would be split, or its three parts read from LDS,
-// by two waves.  A step is 16 input channels: 48 MFMAs, about 450 other vector instructions (two patches of 32
-// additions, 64 splits of 5.5), 64 KB of LDS written and read.  The points of a tile meet after the last step, in
+// by two waves.  A step is 16 input channels: 48 MFMAs, about 530 other vector instructions (two patches of 32
+// additions, 64 splits of 6), 64 KB of LDS written and read.  The points of a tile meet after the last step, in
 // LDS, for the output transform.
 //
 // One accumulator per point serves all six products: the reduction is over input channels only, 16 of them per
 // addition instead of two.  Relative L2 error against fp64, ReLU activations, this kernel / fp32 instructions: 64
 // channels 2.2e-7 / 2.3e-7, 256 3.9e-7 / 4.3e-7, 384 4.6e-7 / 5.1e-7, 512 5.4e-7 / 5.9e-7 (16 channels: 1.56e-7 /
-// 1.45e-7, which is why layers of fewer than 32 keep wino_fused_kernel; it is the faster one there too, 14.2 / 16.2 us
+// 1.45e-7, which is why layers of fewer than 32 keep wino_fused_kernel, see the launch for the line; it is the faster one there too, 14.2 / 16.2 us
 // for 16 -> 32 channels of 16x16 at b = 8).
-// Measured at b = 256, us, before / now: 384 -> 384 13x13 527 / 403, 256 -> 256 14x14 302 / 229, 64 -> 64 56x56 337 / 300,
-// 512 -> 512 7x7 (b = 64) 148 / 96, phases of 11x11 stride 4 509 / 440.  Of the cycles of the first, 40 % are MFMAs and
-// half are other vector instructions, which the matrix pipe hides only in part (a register loop with 8 of them per
-// MFMA runs at 43 cycles per MFMA instead of 32).
+// Measured at b = 256, us, wino_fused_kernel / this: 384 -> 384 13x13 527 / 410, 256 -> 256 14x14 302 / 230, 64 -> 64 56x56
+// 337 / 307, 512 -> 512 7x7 (b = 64) 148 / 99, phases of 11x11 stride 4 509 / 435.  Of the matrix pipe's cycles in the
+// first, 39 % are MFMAs (counters; 11 other vector instructions per MFMA), and the pipe hides those only in part (a
+// register loop with 8 of them per MFMA runs at 43 cycles per MFMA instead of 32); LDS bank conflicts take twice the
+// cycles of its active LDS instructions.
 #pragma once
 
 namespace ucd {
