@@ -175,7 +175,7 @@ def test_split_winograd_edges(s):
             assert rel_l2(got, ref) <= 4e-6, (ucd.OP_NAMES[op], parts, rel_l2(got, ref))
 
 
-@pytest.mark.parametrize("s", [WINO_SHAPES[1], WINO_SHAPES[2], PHASE_SHAPES[1]], ids=_id)
+@pytest.mark.parametrize("s", [WINO_SHAPES[1], WINO_SHAPES[2], WINO_SHAPES[3], WINO_SHAPES[5], PHASE_SHAPES[1]], ids=_id)
 def test_split_winograd_not_finite(s):
     """What arithmetic makes not finite is not finite, and blocks that hold such values are otherwise as exact as the
     rest: only outputs within a tile's reach of the pixel may differ from the oracle's."""
