@@ -129,6 +129,10 @@ size_t implicit_det_ws_bytes(const Dims &d, int b)
 static bool split_filter_pays(const Dims &d, int Kd)
 {
     if (d.K <= 32) return false;
+    // one tile of 96 or 128 rows, most of its columns padding, in about a round of workgroups: with fewer chunks the tiles
+    // get smaller, with more the steps outweigh the start (us, fp32 / split: 3 -> 128 3x3, 50176 rows 22.0 / 22.1, 65536 29 /
+    // 34, 100352 36 / 40)
+    if (d.K > 64 && d.K <= 128 && d.crs() <= 32 && Kd >= 65536 && Kd < 131072) return false;
     const double mul = (double)d.K * d.crs() * Kd;
     const bool masked = d.ph != 0 || d.pw != 0, big = masked && d.R * d.S > 31;
     const bool whole = d.sw == 1 || (d.sw == 2 && d.Q % 4 == 0);
