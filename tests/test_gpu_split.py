@@ -17,7 +17,8 @@ pytestmark = pytest.mark.gpu
 I, MIRROR = ucd.ALGO_IMPLICIT, ucd.ALGO_IMPLICIT_MIRROR
 
 SHAPES = [
-    # Forward / mirrored BackwardData: output channels around each tile height (64, 96, 128), reductions that end inside a 16-row step, inside a 4-row load and inside a 64-row window
+    # Forward / mirrored BackwardData: output channels around each tile height (64, 96, 128), reductions that end
+    # inside a 16-row step, inside a 4-row load and inside a 64-row window
     Shape(2, 37, 9, 11, 34, 3, 3, 1, 1), Shape(2, 33, 8, 8, 33, 1, 1, 1, 0), Shape(1, 21, 12, 12, 65, 3, 3, 1, 1),
     Shape(3, 5, 31, 30, 96, 11, 11, 4, 0), Shape(2, 9, 20, 20, 97, 7, 7, 2, 3), Shape(2, 3, 14, 14, 129, 5, 5, 1, 2),
     Shape(2, 128, 9, 7, 64, 1, 1, 1, 0), Shape(3, 80, 11, 6, 127, 1, 1, 1, 0), Shape(2, 79, 8, 8, 65, 1, 1, 1, 0),
