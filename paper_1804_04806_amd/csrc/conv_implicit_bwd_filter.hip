@@ -226,6 +226,7 @@ static hipError_t implicit_bwd_filter_t(const Dims &d, int b, const void *x, con
 hipError_t implicit_bwd_filter(const Dims &d, int b, const void *x, const void *dy, float *dw, float beta,
                                float *ws, hipStream_t s)
 {
+    if (small_pays(d, 2, b)) return small_conv(d, 2, b, x, dy, dw, beta, s);
     return d.dtype == 1 ? implicit_bwd_filter_t<bf16>(d, b, x, dy, dw, beta, ws, s)
                         : implicit_bwd_filter_t<float>(d, b, x, dy, dw, beta, ws, s);
 }

@@ -36,6 +36,11 @@ hipError_t winograd5_fused(const Dims &d, int op, int b, const void *in, const v
 hipError_t winograd5_fused_filter(const Dims &d, int b, const void *x, const void *dy, float *dw, float beta, float *ws,
                                   hipStream_t s);
 
+// zero-workspace implicit GEMM of layers with a few microseconds of work (conv_small.hip): whether it is the one to
+// take, and (a, bsrc, out) = (x, w, y) | (dy, w, dx) | (x, dy, dw)
+bool small_pays(const Dims &d, int op, int b);
+hipError_t small_conv(const Dims &d, int op, int b, const void *a, const void *bsrc, void *out, float beta, hipStream_t s);
+
 // zero-workspace implicit GEMM
 hipError_t implicit_fwd(const Dims &d, int b, const void *x, const void *w, void *y, hipStream_t s);
 hipError_t implicit_bwd_data(const Dims &d, int b, const void *dy, const void *w, void *dx, hipStream_t s);
