@@ -128,8 +128,9 @@ def _nbytes(t):
 
 def _stream(stream):
     if stream is None:
+        # the raw handle: building a torch.cuda.Stream object for it costs more than a small layer's launch
         import torch
-        return torch.cuda.current_stream().cuda_stream
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
