@@ -41,6 +41,10 @@ hipError_t winograd5_fused_filter(const Dims &d, int b, const void *x, const voi
 bool small_pays(const Dims &d, int op, int b);
 hipError_t small_conv(const Dims &d, int op, int b, const void *a, const void *bsrc, void *out, float beta, hipStream_t s);
 
+// BackwardData of fp32 layers over a window in LDS (conv_halo.hip), zero workspace
+bool halo_pays(const Dims &d, int b);
+hipError_t halo_bwd_data(const Dims &d, int b, const void *dy, const void *w, void *dx, hipStream_t s);
+
 // zero-workspace implicit GEMM
 hipError_t implicit_fwd(const Dims &d, int b, const void *x, const void *w, void *y, hipStream_t s);
 hipError_t implicit_bwd_data(const Dims &d, int b, const void *dy, const void *w, void *dx, hipStream_t s);

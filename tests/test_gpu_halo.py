@@ -1,0 +1,64 @@
+"""conv_halo_kernel (BackwardData over a window in LDS): edges of its tiles of channels and positions, chunks of 16 channels
+that the last one does not fill, column blocks, tiles over several images, paddings of either parity, values out of range."""
+import numpy as np
+import pytest
+
+from paper_1804_04806_amd import ucd
+from paper_1804_04806_amd.synth import Shape
+from hip_helpers import inputs, rel_l2, run_hip, run_oracle
+
+pytestmark = pytest.mark.gpu
+
+I, D = ucd.ALGO_IMPLICIT, ucd.BWD_DATA
+
+SHAPES = [
+    # column stride 2: channels around the tile of 64, 17 to 65 output channels, positions over one and many images, rows
+    # and columns odd and even, blocks of columns (the last one ragged), filters with fewer and more rows than columns
+    Shape(20, 24, 14, 14, 400, 3, 3, 2, 1), Shape(31, 63, 13, 11, 65, 3, 3, 2, 0), Shape(5, 65, 29, 31, 33, 3, 3, 2, 2),
+    Shape(2, 130, 26, 71, 50, 3, 3, 2, 1), Shape(40, 40, 7, 9, 400, 3, 3, 2, 1), Shape(1, 64, 61, 150, 47, 2, 3, 2, 1),
+    Shape(6, 33, 40, 41, 17, 6, 3, 2, 1), Shape(60, 70, 8, 7, 130, 3, 3, 2, 1), Shape(9, 100, 20, 23, 64, 5, 5, 2, 2),
+    Shape(9, 64, 21, 22, 49, 5, 5, 2, 1), Shape(4, 100, 31, 52, 150, 4, 5, 2, 3), Shape(30, 96, 12, 13, 130, 5, 5, 2, 0),
+    # stride 1: tiles of 128 and of 64 channels
+    Shape(101, 100, 20, 21, 20, 3, 3, 1, 1), Shape(85, 120, 23, 22, 37, 4, 3, 1, 0), Shape(61, 56, 28, 27, 17, 5, 5, 1, 2),
+]
+
+
+def _id(s):
+    return f"n{s.N}c{s.C}h{s.H}w{s.W}k{s.K}r{s.R}s{s.S}st{s.stride}p{s.pad}"
+
+
+def _run(s, w, dy, parts=None):
+    assert parts or "gemm_kernel_split_halo" in ucd.ucd_describe_micro(ucd.layer(s), D, I, s.N)[0]
+    return run_hip(s, D, [(I, b) for b in parts or [s.N]], w=w, dy=dy)
+
+
+@pytest.mark.parametrize("s", SHAPES, ids=_id)
+def test_halo_edges(s):
+    _, w, dy = inputs(s, seed=51)
+    ref = run_oracle(s, D, w=w, dy=dy)
+    for parts in (None, [s.N - 1, 1] if s.N > 1 else None):
+        assert rel_l2(_run(s, w, dy, parts), ref) <= 1e-6
+
+
+@pytest.mark.parametrize("s", [SHAPES[1], SHAPES[3], SHAPES[9], SHAPES[13]], ids=_id)
+def test_halo_not_finite(s):
+    """Infinities and NaN come out where, and as, fp32 arithmetic gives them; the other outputs stay exact."""
+    _, w, dy = inputs(s, seed=52)
+    dy[0, -1, 1, 1], dy[-1, 0, -1, -1], dy[0, 0, 0, 0] = -np.inf, np.nan, 3.3e38   # the last: infinite when rounded to bf16
+    got = _run(s, w, dy).astype(np.float64)
+    ref = run_oracle(s, D, w=w, dy=dy)
+    ref = np.where(np.abs(ref) > np.finfo(np.float32).max, np.sign(ref) * np.inf, ref)
+    fine = np.isfinite(ref)
+    assert fine.any() and not fine.all()
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isinf(got), np.isinf(ref))
+    assert rel_l2(got[fine], ref[fine]) <= 1e-6
+
+
+@pytest.mark.parametrize("scale,partner", [(1e-37, 1.0), (1e30, 1.0), (2.0 ** -116, 2.0 ** 30), (2.0 ** -136, 2.0 ** 60)])
+@pytest.mark.parametrize("s", [SHAPES[2], SHAPES[8]], ids=_id)
+def test_halo_range(s, scale, partner):
+    """Operands whose low parts leave bf16's range, and large ones, next to partners that bring the results back."""
+    _, w, dy = inputs(s, seed=53)
+    for a, b in ((scale, partner), (partner, scale)):
+        ws, dys = w * np.float32(a), dy * np.float32(b)
+        assert rel_l2(_run(s, ws, dys), run_oracle(s, D, w=ws, dy=dys)) <= 1e-6
