@@ -45,6 +45,10 @@ hipError_t small_conv(const Dims &d, int op, int b, const void *a, const void *b
 bool halo_pays(const Dims &d, int b);
 hipError_t halo_bwd_data(const Dims &d, int b, const void *dy, const void *w, void *dx, hipStream_t s);
 
+// Forward (x, w, y) and BackwardData (dy, w, dx) of fp32 1x1 layers that keep their input in LDS (conv_pointwise.hip)
+bool pointwise_pays(const Dims &d, int op, int b);
+hipError_t pointwise_conv(const Dims &d, int op, int b, const void *in, const void *w, void *out, hipStream_t s);
+
 // zero-workspace implicit GEMM
 hipError_t implicit_fwd(const Dims &d, int b, const void *x, const void *w, void *y, hipStream_t s);
 hipError_t implicit_bwd_data(const Dims &d, int b, const void *dy, const void *w, void *dx, hipStream_t s);

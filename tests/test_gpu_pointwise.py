@@ -1,0 +1,74 @@
+"""pointwise_kernel (1x1 layers that keep their input in LDS): edges of its tiles of 128 x 128, of its pairs of 16-channel
+steps and of the last round of workgroups, images of a multiple of four pixels and not, values out of range."""
+import numpy as np
+import pytest
+
+from paper_1804_04806_amd import ucd
+from paper_1804_04806_amd.synth import Shape
+from hip_helpers import inputs, rel_l2, run_hip, run_oracle
+
+pytestmark = pytest.mark.gpu
+
+I, F, D = ucd.ALGO_IMPLICIT, ucd.FWD, ucd.BWD_DATA
+
+
+def _layer(n, h, w, few, many, op):
+    """1x1 layer whose `op` reduces over `few` channels into `many`."""
+    return Shape(n, few if op == F else many, h, w, many if op == F else few, 1, 1, 1, 0)
+
+
+CASES = [(21, 14, 14, 17, 129), (21, 13, 15, 32, 256), (5, 29, 29, 33, 257), (9, 22, 21, 48, 200), (6, 26, 26, 159, 140),
+         (21, 14, 14, 160, 385), (63, 13, 10, 100, 100), (43, 28, 28, 20, 300), (42, 28, 29, 64, 130), (1, 64, 63, 96, 1000)]
+
+
+def _run(s, op, x, w, dy, parts=None):
+    assert parts or "gemm_kernel_split_pointwise" in ucd.ucd_describe_micro(ucd.layer(s), op, I, s.N)[0]
+    return run_hip(s, op, [(I, b) for b in parts or [s.N]], x=x, w=w, dy=dy)
+
+
+@pytest.mark.parametrize("op", (F, D))
+@pytest.mark.parametrize("case", CASES, ids=str)
+def test_pointwise_edges(case, op):
+    s = _layer(*case, op)
+    x, w, dy = inputs(s, seed=61)
+    ref = run_oracle(s, op, x=x, w=w, dy=dy)
+    for parts in (None, [1, s.N - 1] if s.N > 1 else None):
+        assert rel_l2(_run(s, op, x, w, dy, parts), ref) <= 1e-6
+
+
+@pytest.mark.parametrize("op", (F, D))
+@pytest.mark.parametrize("case", [CASES[1], CASES[2], CASES[7]], ids=str)
+def test_pointwise_not_finite(case, op):
+    """Infinities and NaN come out where, and as, fp32 arithmetic gives them; the other outputs stay exact."""
+    s = _layer(*case, op)
+    x, w, dy = inputs(s, seed=62)
+    t = x if op == F else dy
+    t[0, -1, 1, 1], t[-1, 0, -1, -1], t[0, 0, 0, 0] = -np.inf, np.nan, 3.3e38   # the last: infinite when rounded to bf16
+    got = _run(s, op, x, w, dy).astype(np.float64)
+    ref = run_oracle(s, op, x=x, w=w, dy=dy)
+    ref = np.where(np.abs(ref) > np.finfo(np.float32).max, np.sign(ref) * np.inf, ref)
+    fine = np.isfinite(ref)
+    assert fine.any() and not fine.all()
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isinf(got), np.isinf(ref))
+    assert rel_l2(got[fine], ref[fine]) <= 1e-6
+
+
+@pytest.mark.parametrize("op", (F, D))
+@pytest.mark.parametrize("scale,partner", [(1e-37, 1.0), (1e30, 1.0), (2.0 ** -116, 2.0 ** 30), (2.0 ** -136, 2.0 ** 60)])
+def test_pointwise_range(scale, partner, op):
+    """Operands whose low parts leave bf16's range, and large ones, next to partners that bring the results back."""
+    s = _layer(*CASES[3], op)
+    x, w, dy = inputs(s, seed=63)
+    for a, b in ((scale, partner), (partner, scale)):
+        xs, ws, dys = x * np.float32(a), w * np.float32(b), dy * np.float32(a)
+        assert rel_l2(_run(s, op, xs, ws, dys), run_oracle(s, op, x=xs, w=ws, dy=dys)) <= 1e-6
+
+
+def test_values_behind_a_filter_row_do_not_reach_it():
+    """The last step of a filter row of 17 channels reads into the next row."""
+    s = _layer(*CASES[0], F)
+    x, w, dy = inputs(s, seed=64)
+    w[3], w[100] = np.inf, np.nan
+    got = _run(s, F, x, w, dy)
+    fine = [k for k in range(s.K) if k not in (3, 100)]
+    assert rel_l2(got[:, fine], run_oracle(s, F, x=x, w=w)[:, fine]) <= 1e-6
