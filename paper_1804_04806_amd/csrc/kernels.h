@@ -49,6 +49,9 @@ hipError_t halo_bwd_data(const Dims &d, int b, const void *dy, const void *w, vo
 bool pointwise_pays(const Dims &d, int op, int b);
 hipError_t pointwise_conv(const Dims &d, int op, int b, const void *in, const void *w, void *out, hipStream_t s);
 
+bool pointwise_bf16_pays(const Dims &d, int op, int b);
+hipError_t pointwise_bf16(const Dims &d, int op, int b, const void *in, const void *w, void *out, hipStream_t s);
+
 // zero-workspace implicit GEMM
 hipError_t implicit_fwd(const Dims &d, int b, const void *x, const void *w, void *y, hipStream_t s);
 hipError_t implicit_bwd_data(const Dims &d, int b, const void *dy, const void *w, void *dx, hipStream_t s);

@@ -1,4 +1,4 @@
-"""pointwise_kernel (1x1 layers that keep their input in LDS): edges of its tiles of 128 x 128, of its pairs of 16-channel
+"""pointwise_kernel and pointwise_bf16_kernel (1x1 layers that keep their input in LDS): edges of its tiles of 128 x 128, of its pairs of 16-channel
 steps and of the last round of workgroups, images of a multiple of four pixels and not, values out of range."""
 import numpy as np
 import pytest
@@ -6,6 +6,7 @@ import pytest
 from paper_1804_04806_amd import ucd
 from paper_1804_04806_amd.synth import Shape
 from hip_helpers import inputs, rel_l2, run_hip, run_oracle
+from test_gpu_bf16 import bf16_inputs, check_bf16_output, run_hip_bf16
 
 pytestmark = pytest.mark.gpu
 
@@ -72,3 +73,39 @@ def test_values_behind_a_filter_row_do_not_reach_it():
     got = _run(s, F, x, w, dy)
     fine = [k for k in range(s.K) if k not in (3, 100)]
     assert rel_l2(got[:, fine], run_oracle(s, F, x=x, w=w)[:, fine]) <= 1e-6
+
+
+# tiles of 128 pixels (the last three: of 256), 64-channel steps, 128 rows; (op,): the kernel takes that operation only
+HALF = [(21, 14, 14, 40, 130), (41, 14, 10, 256, 386), (3, 34, 30, 264, 66), (5, 28, 27, 512, 258), (9, 22, 22, 8, 100),
+        (1, 4, 901, 72, 200), (6, 31, 32, 328, 34), (14, 40, 36, 24, 129, (F,)), (41, 22, 23, 256, 300, ()), (27, 28, 27, 256, 260),
+        (11, 44, 42, 56, 140), (31, 30, 22, 200, 36)]
+
+
+@pytest.mark.parametrize("op", (F, D))
+@pytest.mark.parametrize("case", HALF, ids=str)
+def test_pointwise_bf16_edges(case, op):
+    """Products are exact and summed in fp32: outputs are held to their rounding.  Odd numbers of rows in BackwardData and
+    images of other than a multiple of four pixels stay with the tile GEMMs."""
+    s = _layer(*case[:5], op)
+    bits, (x, w, dy) = bf16_inputs(s, seed=65)
+    ref = run_oracle(s, op, x=x, w=w, dy=dy)
+    kernel = ucd.ucd_describe_micro(ucd.layer(s, dtype=1), op, I, s.N)[0]
+    assert ("gemm_kernel_bf16_pointwise" in kernel) == (op in (case[5] if len(case) > 5 else (F, D))), kernel
+    for parts in [s.N], [1, s.N - 1]:
+        if min(parts) > 0:
+            check_bf16_output(run_hip_bf16(s, op, [(I, b) for b in parts], bits), ref, ucd.OP_NAMES[op])
+
+
+@pytest.mark.parametrize("op", (F, D))
+def test_pointwise_bf16_not_finite(op):
+    """An infinity or a NaN reaches the outputs of its pixel or of its filter row, and no other."""
+    s = _layer(*HALF[0], op)
+    bits, (x, w, dy) = bf16_inputs(s, seed=66)
+    clean = run_hip_bf16(s, op, [(I, s.N)], bits)
+    t = bits[0 if op == F else 2]
+    t[3, 5, 7, 9], t[-1, -1, -1, -1] = 0x7F80, 0x7FC0
+    bits[1][(17, 3) if op == F else (3, 17)] = 0xFF80
+    got = run_hip_bf16(s, op, [(I, s.N)], bits)
+    hit = np.zeros(got.shape, bool)
+    hit[3, :, 7, 9] = hit[-1, :, -1, -1] = hit[:, 17] = True
+    assert not np.isfinite(got[hit]).any() and np.array_equal(got[~hit], clean[~hit])
