@@ -60,14 +60,14 @@ __global__ __launch_bounds__(1024) void gemm_kernel_small(SmallParams<KIND> p)
     // consecutive reduction rows of a lane: four feed four v_mfma_f32_16x16x4_f32, eight one v_mfma_f32_16x16x32_bf16
     constexpr int PL = F32 ? 4 : 8, STEP = 4 * PL;
     constexpr int kBatch = F32 ? 4 : 2;
-    constexpr int LDP = 20;   // row stride of the partial tiles: the four lane groups of a store on different banks
+    constexpr int LDP = 18;   // row stride of the partial tiles: the four lane groups of a store on different banks
     // A from memory four (eight) rows at a time; otherwise it has a table column of its own
     constexpr bool VEC_A = KIND == kSmallFwd;
     constexpr bool TAB_MASK = KIND == kSmallBwdFilter;   // the mask is the row's, the tap the lane's
     __shared__ __attribute__((aligned(16))) uint32_t tab_b[kSmallRows], tab_t[kSmallRows];
     __shared__ __attribute__((aligned(16))) uint32_t tab_a[VEC_A ? 4 : kSmallRows];
     __shared__ __attribute__((aligned(16))) uint32_t tab_w[TAB_MASK && BIG ? kSmallRows : 4];
-    __shared__ __attribute__((aligned(16))) float part[16][16 * LDP];
+    __shared__ __attribute__((aligned(16))) double part[16][16 * LDP];
 
     const SmallPhase &q = p.ph[KIND == kSmallBwdData ? blockIdx.y : 0];
     const int lane = threadIdx.x & 63, l16 = lane & 15, grp = lane >> 4;
@@ -260,12 +260,12 @@ __global__ __launch_bounds__(1024) void gemm_kernel_small(SmallParams<KIND> p)
     }
 
 #pragma unroll
-    for (int i = 0; i < 4; ++i) part[wave][(4 * grp + i) * LDP + l16] = (acc[0][i] + acc[1][i]) + (acc[2][i] + acc[3][i]);
+    for (int i = 0; i < 4; ++i) part[wave][(4 * grp + i) * LDP + l16] = ((double)acc[0][i] + (double)acc[1][i]) + ((double)acc[2][i] + (double)acc[3][i]);
     __syncthreads();
     if (threadIdx.x >= 256) return;
     const int row = (int)threadIdx.x >> 4, col = (int)threadIdx.x & 15;
-    double all = 0;   // one rounding for the 4 to 16 partial sums
-    for (int w = 0; w < waves; ++w) all += (double)part[w][row * LDP + col];
+    double all = 0;   // one rounding for the 16 to 64 partial sums
+    for (int w = 0; w < waves; ++w) all += part[w][row * LDP + col];
     const float sum = (float)all;
     const int mo = m0 + row, jo = j0 + col;
     if (mo >= p.M || jo >= q.N) return;
