@@ -1,4 +1,4 @@
-// Launch of pointwise_kernel and pointwise_bf16_kernel: Forward and BackwardData of 1x1 stride-1 layers.
+// Launch of pointwise_kernel, pointwise_bf16_kernel and pointwise_stream_kernel: Forward and BackwardData of 1x1 stride-1 layers.
 #include "conv_pointwise_bf16.hpp"
 #include "gemm_launch.hpp"
 #include "implicit_common.hpp"
@@ -19,24 +19,43 @@ bool pointwise_pays(const Dims &d, int op, int b)
     return M > 128 ? cols >= 4000 : M > 64 && cols >= 8000 && cols <= 20000;
 }
 
-// bf16: from here on tiles of 256 pixels, up to here of 128, which give the chip twice the workgroups (narrow / wide tiles of
-// one layer below 1.2 to 1.5, above 0.75 to 1.05 by output channels)
-constexpr long kWideCols = 20000;
+// bf16 layers.  Times of the tile GEMMs / of these kernels over 2600 layers of 800 to 800000 pixels; "narrow" and "wide" are
+// pointwise_bf16_kernel with 128 and 256 pixels, up to 512 and 256 input channels, "stream" is pointwise_stream_kernel.
+enum class Bf16Route { kTiles, kNarrow, kWide, kStream };
+constexpr long kWideCols = 20000;   // below, tiles of 256 pixels leave most CUs idle: narrow / wide 1.3, above 0.75 to 1.05
+constexpr int kStreamGroups = 128;  // half the chip
 
-// The same for bf16 tensors, whose tile GEMMs are slower against it.  Time of the tile GEMMs / of this kernel, least and mean
-// over 1200 layers of 800 to 800000 pixels: more than 64 output channels, up to 256 input channels 1.0 / 1.55 (256 -> 1024
-// 14x14 b = 256 77 / 46 us, BackwardData 90 / 50), up to 512 below 20000 pixels 0.98 / 1.6 (320 -> 192 3.0); from there on, with
-// their narrower tiles, 1.07 / 1.2 above 192 output channels, 0.8 / 0.95 up to 128.  33 to 64 output channels 1.0 / 1.2, but
-// 0.66 to 1.05 with no more than 32 input channels in BackwardData.
-bool pointwise_bf16_pays(const Dims &d, int op, int b)
+static long stream_groups(int M, long cols) { return (cols + 255) / 256 * ((M + 127) / 128); }
+
+static Bf16Route bf16_route(const Dims &d, int op, int b)
 {
-    if (d.dtype != 1 || d.R * d.S != 1 || d.sh != 1 || d.sw != 1 || d.ph != 0 || d.pw != 0) return false;
+    if (d.dtype != 1 || d.R * d.S != 1 || d.sh != 1 || d.sw != 1 || d.ph != 0 || d.pw != 0) return Bf16Route::kTiles;
     const int K = op == 0 ? d.C : d.K, M = op == 0 ? d.K : d.C;
     const long cols = (long)b * d.H * d.W;
-    if (d.H * d.W % 4 != 0 || K % 8 != 0 || (op == 1 && M % 2 != 0) || (long)d.H * d.W > 1l << 22) return false;
-    if (M <= 32 || (M <= 64 && K <= 32)) return false;
-    return K <= PointwiseHalfTile<2>::kMaxK || (K <= PointwiseHalfTile<1>::kMaxK && (cols < kWideCols || M > 192));
+    if (d.H * d.W % 4 != 0 || K % 8 != 0 || (op == 1 && M % 2 != 0) || (long)d.H * d.W > 1l << 22) return Bf16Route::kTiles;
+    const bool many = cols >= kWideCols;
+    // up to 32 output channels most of a tile is empty: stream 0.7 to 0.9 against the Forward tile GEMMs above 256 input
+    // channels, 1.05 to 1.5 up to there; BackwardData 0.8 to 1.1 up to 64 input channels, 1.05 to 1.7 above
+    if (M <= 16) return Bf16Route::kTiles;
+    if (M <= 32) {
+        const bool pays = op == 0 ? many && K <= 256 : (many && K > 64) || (K > 256 && cols >= 3000);
+        return pays ? Bf16Route::kStream : Bf16Route::kTiles;
+    }
+    if (op == 1 && M <= 64 && K <= (many ? 16 : 32)) return Bf16Route::kTiles;   // 0.85 to 1.2
+    // beyond LDS: 128 -> 64 us for 2048 -> 256 28x28 b = 64 in BackwardData, whose tile GEMMs gather the filter; Forward 0.75 to
+    // 0.95 with less than half a chip of workgroups or up to 96 output channels, otherwise 1.02 to 1.7 (1024 -> 256 14x14
+    // b = 256 57 / 34 us)
+    if (K > PointwiseHalfTile<1>::kMaxK)
+        return (op == 1 ? cols >= 3000 : M > 96 && stream_groups(M, cols) >= kStreamGroups) ? Bf16Route::kStream : Bf16Route::kTiles;
+    // narrow / stream 1.05 to 1.5 where stream has half a chip of workgroups, 0.6 to 0.95 below
+    if (K > PointwiseHalfTile<2>::kMaxK)
+        return many || stream_groups(M, cols) >= kStreamGroups ? Bf16Route::kStream : Bf16Route::kNarrow;
+    // one tile of up to 256 output channels uses the input once either way: wide / stream 0.95 to 1.2; above 0.9 to 1.1
+    if (!many) return Bf16Route::kNarrow;   // tile GEMMs / narrow 1.0 to 2.9 (256 -> 192 3.0)
+    return M <= 256 ? Bf16Route::kStream : Bf16Route::kWide;   // tile GEMMs / wide 1.2 to 1.8 (256 -> 1024 14x14 b = 256 77 / 46)
 }
+
+bool pointwise_bf16_pays(const Dims &d, int op, int b) { return bf16_route(d, op, b) != Bf16Route::kTiles; }
 
 // pixel tiles that take all tile rows, and how many workgroups share each of the last round's
 static unsigned pointwise_grid(PointwiseParams &p, int mt, int nt)
@@ -104,11 +123,35 @@ static hipError_t launch_bf16(PointwiseParams &p, int op, hipStream_t s)
     return hipGetLastError();
 }
 
+template <int WM>
+static hipError_t launch_stream(const PointwiseParams &a, int op, hipStream_t s)
+{
+    StreamParams p{};
+    p.x = a.x; p.w = a.w; p.y = a.y;
+    p.w_bytes = a.w_bytes; p.x_bytes = a.x_bytes; p.y_bytes = a.y_bytes;
+    p.K = a.K; p.M = a.M; p.px = a.px; p.cols = a.cols;
+    p.w_row = a.w_row; p.w_k = a.w_k; p.div_px = a.div_px;
+    p.m_tiles = (p.M + 128 * WM - 1) / (128 * WM);
+    p.tiles = (p.cols + 255) / 256;
+    if (LaunchLog *log = launch_log()) {
+        log->add(pointwise_text(a, "gemm_kernel_bf16_pointwise_stream", op == 0 ? "forward" : "backward data", 128 * WM, 256));
+        return hipSuccess;
+    }
+    const unsigned grid = (unsigned)((p.tiles + 7) / 8 * 8 * p.m_tiles);
+    if (op == 0) pointwise_stream_kernel<WM, true><<<grid, 768, 0, s>>>(p);
+    else pointwise_stream_kernel<WM, false><<<grid, 768, 0, s>>>(p);
+    return hipGetLastError();
+}
+
 hipError_t pointwise_bf16(const Dims &d, int op, int b, const void *in, const void *w, void *out, hipStream_t s)
 {
     PointwiseParams p = pointwise_params(d, op, b, in, w, out);
-    if (p.K <= PointwiseHalfTile<2>::kMaxK && p.cols >= kWideCols) return launch_bf16<PointwiseHalfTile<2>>(p, op, s);
-    return launch_bf16<PointwiseHalfTile<1>>(p, op, s);
+    switch (bf16_route(d, op, b)) {
+    case Bf16Route::kNarrow: return launch_bf16<PointwiseHalfTile<1>>(p, op, s);
+    case Bf16Route::kWide: return launch_bf16<PointwiseHalfTile<2>>(p, op, s);
+    // tiles of 256 output channels once those of 128 take more than one round: in one round 128 / 256 take 0.87, in more 1.35
+    default: return p.M > 128 && stream_groups(p.M, p.cols) > device_cus() ? launch_stream<2>(p, op, s) : launch_stream<1>(p, op, s);
+    }
 }
 
 }  // namespace ucd

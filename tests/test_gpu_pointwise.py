@@ -1,4 +1,4 @@
-"""pointwise_kernel and pointwise_bf16_kernel (1x1 layers that keep their input in LDS): edges of its tiles of 128 x 128, of its pairs of 16-channel
+"""pointwise_kernel, pointwise_bf16_kernel and pointwise_stream_kernel (1x1 layers that keep their input in LDS): edges of its tiles of 128 x 128, of its pairs of 16-channel
 steps and of the last round of workgroups, images of a multiple of four pixels and not, values out of range."""
 import numpy as np
 import pytest
@@ -77,12 +77,16 @@ def test_values_behind_a_filter_row_do_not_reach_it():
 
 # tiles of 128 pixels (the last three: of 256), 64-channel steps, 128 rows; (op,): the kernel takes that operation only
 HALF = [(21, 14, 14, 40, 130), (41, 14, 10, 256, 386), (3, 34, 30, 264, 66), (5, 28, 27, 512, 258), (9, 22, 22, 8, 100),
-        (1, 4, 901, 72, 200), (6, 31, 32, 328, 34), (14, 40, 36, 24, 129, (F,)), (41, 22, 23, 256, 300, ()), (27, 28, 27, 256, 260),
-        (11, 44, 42, 56, 140), (31, 30, 22, 200, 36)]
+        (1, 4, 901, 72, 200), (6, 31, 32, 328, 34), (14, 40, 36, 24, 261, (F,)), (41, 22, 23, 256, 300, ()), (27, 28, 27, 256, 260),
+        (11, 44, 42, 56, 516)]
+# tiles of 128 or 256 rows and 256 pixels, 32-channel steps in threes, workgroups in eights
+STREAM = [(14, 40, 36, 24, 129, (F,)), (42, 22, 22, 256, 130), (26, 28, 28, 72, 22), (26, 28, 28, 200, 36), (33, 32, 32, 104, 256),
+          (34, 32, 32, 8, 140), (9, 44, 42, 520, 300), (6, 30, 30, 552, 20, (D,)), (3, 34, 30, 1032, 66, (D,)),
+          (65, 28, 18, 264, 140), (9, 30, 28, 320, 1000), (35, 32, 31, 648, 250), (1, 148, 149, 96, 66)]
 
 
 @pytest.mark.parametrize("op", (F, D))
-@pytest.mark.parametrize("case", HALF, ids=str)
+@pytest.mark.parametrize("case", HALF + STREAM, ids=str)
 def test_pointwise_bf16_edges(case, op):
     """Products are exact and summed in fp32: outputs are held to their rounding.  Odd numbers of rows in BackwardData and
     images of other than a multiple of four pixels stay with the tile GEMMs."""
@@ -90,16 +94,18 @@ def test_pointwise_bf16_edges(case, op):
     bits, (x, w, dy) = bf16_inputs(s, seed=65)
     ref = run_oracle(s, op, x=x, w=w, dy=dy)
     kernel = ucd.ucd_describe_micro(ucd.layer(s, dtype=1), op, I, s.N)[0]
-    assert ("gemm_kernel_bf16_pointwise" in kernel) == (op in (case[5] if len(case) > 5 else (F, D))), kernel
+    name = "gemm_kernel_bf16_pointwise_stream<" if case in STREAM else "gemm_kernel_bf16_pointwise<"
+    assert (name in kernel) == (op in (case[5] if len(case) > 5 else (F, D))), kernel
     for parts in [s.N], [1, s.N - 1]:
         if min(parts) > 0:
             check_bf16_output(run_hip_bf16(s, op, [(I, b) for b in parts], bits), ref, ucd.OP_NAMES[op])
 
 
 @pytest.mark.parametrize("op", (F, D))
-def test_pointwise_bf16_not_finite(op):
+@pytest.mark.parametrize("case", [HALF[0], STREAM[3], STREAM[4]], ids=str)
+def test_pointwise_bf16_not_finite(case, op):
     """An infinity or a NaN reaches the outputs of its pixel or of its filter row, and no other."""
-    s = _layer(*HALF[0], op)
+    s = _layer(*case, op)
     bits, (x, w, dy) = bf16_inputs(s, seed=66)
     clean = run_hip_bf16(s, op, [(I, s.N)], bits)
     t = bits[0 if op == F else 2]
