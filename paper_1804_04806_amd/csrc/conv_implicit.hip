@@ -128,6 +128,7 @@ static hipError_t implicit_fwd_t(const Dims &d, int b, const void *x, const void
 hipError_t implicit_fwd(const Dims &d, int b, const void *x, const void *w, void *y, hipStream_t s)
 {
     if (small_pays(d, 0, b)) return small_conv(d, 0, b, x, w, y, 0.f, s);
+    if (pointwise_stream_pays(d, 0, b)) return pointwise_stream(d, 0, b, x, w, y, s);
     if (pointwise_pays(d, 0, b)) return pointwise_conv(d, 0, b, x, w, y, s);
     if (pointwise_bf16_pays(d, 0, b)) return pointwise_bf16(d, 0, b, x, w, y, s);
     return d.dtype == 1 ? implicit_fwd_t<bf16>(d, b, x, w, y, s) : implicit_fwd_t<float>(d, b, x, w, y, s);

@@ -201,6 +201,7 @@ static hipError_t implicit_bwd_data_t(const Dims &d, int b, const void *dy, cons
 hipError_t implicit_bwd_data(const Dims &d, int b, const void *dy, const void *w, void *dx, hipStream_t s)
 {
     if (small_pays(d, 1, b)) return small_conv(d, 1, b, dy, w, dx, 0.f, s);
+    if (pointwise_stream_pays(d, 1, b)) return pointwise_stream(d, 1, b, dy, w, dx, s);
     if (pointwise_pays(d, 1, b)) return pointwise_conv(d, 1, b, dy, w, dx, s);
     if (pointwise_bf16_pays(d, 1, b)) return pointwise_bf16(d, 1, b, dy, w, dx, s);
     if (halo_pays(d, b)) return halo_bwd_data(d, b, dy, w, dx, s);

@@ -1,5 +1,6 @@
 // Launch of pointwise_kernel, pointwise_bf16_kernel and pointwise_stream_kernel: Forward and BackwardData of 1x1 stride-1 layers.
 #include "conv_pointwise_bf16.hpp"
+#include "conv_pointwise_stream.hpp"
 #include "gemm_launch.hpp"
 #include "implicit_common.hpp"
 
@@ -17,6 +18,23 @@ bool pointwise_pays(const Dims &d, int op, int b)
     const long cols = (long)b * d.H * d.W;
     if (K <= 16 || K > PointwiseTile::kMaxK || (long)d.H * d.W > 1l << 22) return false;   // (rows of a tile below 2^31 bytes apart)
     return M > 128 ? cols >= 4000 : M > 64 && cols >= 8000 && cols <= 20000;
+}
+
+// fp32 layers that pointwise_kernel does not take: input channels beyond LDS, or one tile of output channels and many pixels.
+// Tile GEMMs / pointwise_split_stream_kernel over 900 layers of 3000 to 100000 pixels: with 128 workgroups and more, half the chip,
+// Forward 1.1 to 1.6 above 96 output channels (fewer workgroups 0.55 to 1.0, up to 64 channels 0.6 to 1.2); not beyond 256
+// input channels, where tile GEMMs that split their last tiles' sums are more exact by up to 6 % (352 -> 256 14x14 b = 256).
+// BackwardData, whose tile GEMMs run on the fp32 pipe, 1.04 to 2.0 from 96 workgroups and 65 output channels on (512 -> 128
+// 28x28 b = 128 142 / 94 us; 97 beyond 1024 input channels, 0.93 below).  32 input channels and fewer 0.75 to 1.3.
+bool pointwise_stream_pays(const Dims &d, int op, int b)
+{
+    if (d.dtype != 0 || d.R * d.S != 1 || d.sh != 1 || d.sw != 1 || d.ph != 0 || d.pw != 0 || d.H * d.W % 2 != 0) return false;
+    const int K = op == 0 ? d.C : d.K, M = op == 0 ? d.K : d.C;
+    const long cols = (long)b * d.H * d.W;
+    if ((long)d.H * d.W > 1l << 22) return false;
+    if (K <= 32 || pointwise_pays(d, op, b)) return false;
+    const long groups = (cols + 255) / 256 * ((M + 127) / 128);
+    return op == 0 ? M > 96 && K <= 256 && groups >= 128 : M > (K <= 1024 ? 64 : 96) && groups >= 96;
 }
 
 // bf16 layers.  Times of the tile GEMMs / of these kernels over 2600 layers of 800 to 800000 pixels; "narrow" and "wide" are
@@ -107,6 +125,22 @@ hipError_t pointwise_conv(const Dims &d, int op, int b, const void *in, const vo
         if (op == 0) pointwise_kernel<true, false><<<grid, T::THREADS, 0, s>>>(p);
         else pointwise_kernel<false, false><<<grid, T::THREADS, 0, s>>>(p);
     }
+    return hipGetLastError();
+}
+
+hipError_t pointwise_stream(const Dims &d, int op, int b, const void *in, const void *w, void *out, hipStream_t s)
+{
+    PointwiseParams p = pointwise_params(d, op, b, in, w, out);
+    p.m_tiles = (p.M + 127) / 128;
+    p.whole = (p.cols + 255) / 256;
+    p.splits = 1;
+    if (LaunchLog *log = launch_log()) {
+        log->add(pointwise_text(p, "gemm_kernel_split_pointwise_stream", op == 0 ? "forward" : "backward data", 128, 256));
+        return hipSuccess;
+    }
+    const unsigned grid = (unsigned)((p.whole + 7) / 8 * 8 * p.m_tiles);
+    if (op == 0) pointwise_split_stream_kernel<true><<<grid, 768, 0, s>>>(p);
+    else pointwise_split_stream_kernel<false><<<grid, 768, 0, s>>>(p);
     return hipGetLastError();
 }
 

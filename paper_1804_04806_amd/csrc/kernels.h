@@ -49,6 +49,9 @@ hipError_t halo_bwd_data(const Dims &d, int b, const void *dy, const void *w, vo
 bool pointwise_pays(const Dims &d, int op, int b);
 hipError_t pointwise_conv(const Dims &d, int op, int b, const void *in, const void *w, void *out, hipStream_t s);
 
+// the same of layers that stream their input (even images)
+bool pointwise_stream_pays(const Dims &d, int op, int b);
+hipError_t pointwise_stream(const Dims &d, int op, int b, const void *in, const void *w, void *out, hipStream_t s);
 bool pointwise_bf16_pays(const Dims &d, int op, int b);
 hipError_t pointwise_bf16(const Dims &d, int op, int b, const void *in, const void *w, void *out, hipStream_t s);
 

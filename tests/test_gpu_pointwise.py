@@ -1,4 +1,4 @@
-"""pointwise_kernel, pointwise_bf16_kernel and pointwise_stream_kernel (1x1 layers that keep their input in LDS): edges of its tiles of 128 x 128, of its pairs of 16-channel
+"""pointwise_kernel, pointwise_split_stream_kernel, pointwise_bf16_kernel and pointwise_stream_kernel (1x1 layers that keep their input in LDS): edges of its tiles of 128 x 128, of its pairs of 16-channel
 steps and of the last round of workgroups, images of a multiple of four pixels and not, values out of range."""
 import numpy as np
 import pytest
@@ -22,15 +22,21 @@ CASES = [(21, 14, 14, 17, 129), (21, 13, 15, 32, 256), (5, 29, 29, 33, 257), (9,
          (21, 14, 14, 160, 385), (63, 13, 10, 100, 100), (43, 28, 28, 20, 300), (42, 28, 29, 64, 130), (1, 64, 63, 96, 1000)]
 
 
+# the streaming kernel: steps of 16 channels in threes, 128 rows, 256 pixels, workgroups in eights
+STREAM32 = [(42, 28, 28, 33, 97), (21, 28, 28, 161, 200), (43, 27, 28, 249, 129), (10, 28, 29, 176, 500), (42, 28, 28, 256, 100)]
+
+
 def _run(s, op, x, w, dy, parts=None):
     assert parts or "gemm_kernel_split_pointwise" in ucd.ucd_describe_micro(ucd.layer(s), op, I, s.N)[0]
     return run_hip(s, op, [(I, b) for b in parts or [s.N]], x=x, w=w, dy=dy)
 
 
 @pytest.mark.parametrize("op", (F, D))
-@pytest.mark.parametrize("case", CASES, ids=str)
+@pytest.mark.parametrize("case", CASES + STREAM32, ids=str)
 def test_pointwise_edges(case, op):
     s = _layer(*case, op)
+    kernel = ucd.ucd_describe_micro(ucd.layer(s), op, I, s.N)[0]
+    assert ("pointwise_stream" in kernel) == (case in STREAM32), kernel
     x, w, dy = inputs(s, seed=61)
     ref = run_oracle(s, op, x=x, w=w, dy=dy)
     for parts in (None, [1, s.N - 1] if s.N > 1 else None):
@@ -38,7 +44,7 @@ def test_pointwise_edges(case, op):
 
 
 @pytest.mark.parametrize("op", (F, D))
-@pytest.mark.parametrize("case", [CASES[1], CASES[2], CASES[7]], ids=str)
+@pytest.mark.parametrize("case", [CASES[1], CASES[2], CASES[7], STREAM32[0], STREAM32[1]], ids=str)
 def test_pointwise_not_finite(case, op):
     """Infinities and NaN come out where, and as, fp32 arithmetic gives them; the other outputs stay exact."""
     s = _layer(*case, op)
@@ -58,21 +64,23 @@ def test_pointwise_not_finite(case, op):
 @pytest.mark.parametrize("scale,partner", [(1e-37, 1.0), (1e30, 1.0), (2.0 ** -116, 2.0 ** 30), (2.0 ** -136, 2.0 ** 60)])
 def test_pointwise_range(scale, partner, op):
     """Operands whose low parts leave bf16's range, and large ones, next to partners that bring the results back."""
-    s = _layer(*CASES[3], op)
-    x, w, dy = inputs(s, seed=63)
-    for a, b in ((scale, partner), (partner, scale)):
-        xs, ws, dys = x * np.float32(a), w * np.float32(b), dy * np.float32(a)
-        assert rel_l2(_run(s, op, xs, ws, dys), run_oracle(s, op, x=xs, w=ws, dy=dys)) <= 1e-6
+    for case in CASES[3], STREAM32[1]:
+        s = _layer(*case, op)
+        x, w, dy = inputs(s, seed=63)
+        for a, b in ((scale, partner), (partner, scale)):
+            xs, ws, dys = x * np.float32(a), w * np.float32(b), dy * np.float32(a)
+            assert rel_l2(_run(s, op, xs, ws, dys), run_oracle(s, op, x=xs, w=ws, dy=dys)) <= 1e-6
 
 
 def test_values_behind_a_filter_row_do_not_reach_it():
-    """The last step of a filter row of 17 channels reads into the next row."""
-    s = _layer(*CASES[0], F)
-    x, w, dy = inputs(s, seed=64)
-    w[3], w[100] = np.inf, np.nan
-    got = _run(s, F, x, w, dy)
-    fine = [k for k in range(s.K) if k not in (3, 100)]
-    assert rel_l2(got[:, fine], run_oracle(s, F, x=x, w=w)[:, fine]) <= 1e-6
+    """The last step of a filter row of 17 (33) channels reads into the next row."""
+    for case in CASES[0], STREAM32[0]:
+        s = _layer(*case, F)
+        x, w, dy = inputs(s, seed=64)
+        w[3], w[90] = np.inf, np.nan
+        got = _run(s, F, x, w, dy)
+        fine = [k for k in range(s.K) if k not in (3, 90)]
+        assert rel_l2(got[:, fine], run_oracle(s, F, x=x, w=w)[:, fine]) <= 1e-6
 
 
 # tiles of 128 pixels (the last three: of 256), 64-channel steps, 128 rows; (op,): the kernel takes that operation only
