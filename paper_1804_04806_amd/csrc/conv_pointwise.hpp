@@ -41,7 +41,10 @@ __global__ __launch_bounds__(PointwiseTile::THREADS, 3) void pointwise_kernel(Po
     typedef PointwiseTile T;
     constexpr int WM = T::WM, WN = T::WN, MT = T::MT, NT = T::NT;
     __shared__ __attribute__((aligned(16))) char lds[T::LDS];
-    __shared__ uint32_t inexact;   // some operand was not split exactly
+    // Some operand was not split exactly: an input element, or a filter element of tile row mt, which leaves mt + 1 in the
+    // word of its parity.  The multiplying waves look behind a row's last barrier, where the producers are at the next
+    // row's cells already; they come to the row after that, which has the same word again, behind another barrier.
+    __shared__ uint32_t inexact_x, inexact_w[2];
     char *const lds_b = lds + 2 * T::A_BUF;
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, lhi = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -87,12 +90,14 @@ __global__ __launch_bounds__(PointwiseTile::THREADS, 3) void pointwise_kernel(Po
             for (int i = 0; i < 8; ++i) ra[i] = Elem<float>::load(rw, a_off, so + 4u * (uint32_t)(i * p.w_k));
         }
     };
-    auto put_a = [&](int st, float (&ra)[8]) __attribute__((always_inline)) {
+    auto put_a = [&](int mt, int st, float (&ra)[8]) __attribute__((always_inline)) {
+        rest = 0;
         if (ROWS && 16 * st + 16 > p.K) {   // what follows a row's last channel is the next one's first
 #pragma unroll
             for (int i = 0; i < 8; ++i) ra[i] = 16 * st + 8 * a_hi + i < p.K ? ra[i] : 0.f;
         }
         split_cell(lds + (st & 1) * T::A_BUF + a_hi * T::A_HALF + a_row * 16, T::A_PART, ra);
+        if ((rest & 0xFFFFu) != 0) inexact_w[mt & 1] = (uint32_t)mt + 1u;
     };
 
     float ra0[8], ra1[8];
@@ -100,7 +105,7 @@ __global__ __launch_bounds__(PointwiseTile::THREADS, 3) void pointwise_kernel(Po
     auto next = [&]() __attribute__((always_inline)) {
         if (++ls == steps) { ls = 0; ++lm; }
     };
-    if (tid == 0) inexact = 0;
+    if (tid == 0) inexact_x = inexact_w[0] = inexact_w[1] = 0;
     if (producer) {
         load_a(lm, ls, ra0);
         next();
@@ -127,25 +132,22 @@ __global__ __launch_bounds__(PointwiseTile::THREADS, 3) void pointwise_kernel(Po
 #pragma unroll
         for (int i = 0; i < PX; ++i) split_cell(lds_b + st * T::B_STEP + hi * T::B_HALF + (PX * q + i) * 16, T::B_PART, v[i]);
     }
+    if ((rest & 0xFFFFu) != 0) inexact_x = 1;
     if (producer) {
-        put_a(0, ra0);
+        put_a(mt_begin, 0, ra0);
         load_a(lm, ls, ra1);
         next();
         load_a(lm, ls, ra0);
         next();
-    }
-    if ((rest & 0xFFFFu) != 0) inexact = 1;
-    if (producer) {
         __syncthreads();
         for (int mt = mt_begin; mt < mt_end; ++mt)
             for (int st = 0; st < steps; st += 2) {   // the cells of the step after each, loads of two steps in flight
-                put_a(st + 1, ra1);
-                if ((rest & 0xFFFFu) != 0) inexact = 1;
+                put_a(mt, st + 1, ra1);
                 load_a(lm, ls, ra1);
                 next();
                 __syncthreads();
-                put_a(st + 2 < steps ? st + 2 : 0, ra0);
-                if ((rest & 0xFFFFu) != 0) inexact = 1;
+                const bool more = st + 2 < steps;
+                put_a(more ? mt : mt + 1, more ? st + 2 : 0, ra0);
                 load_a(lm, ls, ra0);
                 next();
                 __syncthreads();
@@ -232,7 +234,9 @@ __global__ __launch_bounds__(PointwiseTile::THREADS, 3) void pointwise_kernel(Po
                 }
         const bool redo = !(not_finite == 0.f) || least < ((127u - 104u) << 24) - 1u;
         const int m0 = mt * MT + wm0;
-        if (__builtin_amdgcn_readfirstlane(*(volatile uint32_t *)&inexact) || __builtin_amdgcn_ballot_w64(redo)) {
+        const bool inexact = __builtin_amdgcn_readfirstlane(*(volatile uint32_t *)&inexact_x) != 0 ||
+                             __builtin_amdgcn_readfirstlane(*(volatile uint32_t *)&inexact_w[mt & 1]) == (uint32_t)mt + 1u;
+        if (inexact || __builtin_amdgcn_ballot_w64(redo)) {
 #pragma unroll
             for (int i = 0; i < WM; ++i)
 #pragma unroll

@@ -83,6 +83,24 @@ def test_values_behind_a_filter_row_do_not_reach_it():
         assert rel_l2(got[:, fine], run_oracle(s, F, x=x, w=w)[:, fine]) <= 1e-6
 
 
+# workgroups that walk over one tile row (33 tiles of pixels) and over all four (258)
+@pytest.mark.parametrize("op", (F, D))
+@pytest.mark.parametrize("case", [(21, 14, 14, 160, 385), (168, 14, 14, 32, 385)], ids=str)
+def test_pointwise_recomputes_the_tile_row_of_an_inexact_filter_element(case, op):
+    """One filter element that three bf16 parts do not represent (24 significant bits near 2^-120) sends its 128 output
+    channels to the fp32 instructions, in every run, and no others: these keep the bits they have without it."""
+    s = _layer(*case, op)
+    x, w, dy = inputs(s, seed=67)
+    clean = _run(s, op, x, w, dy)
+    w[(130, 20) if op == F else (20, 130)] = 0xFFFFFF * 2.0 ** -143
+    assert w[(130, 20) if op == F else (20, 130)] != 0
+    runs = [_run(s, op, x, w, dy) for _ in range(4)]
+    assert all(np.array_equal(runs[0], r) for r in runs[1:])
+    assert np.array_equal(runs[0][:, :128], clean[:, :128]) and np.array_equal(runs[0][:, 256:], clean[:, 256:])
+    assert not np.array_equal(runs[0][:, 128:256], clean[:, 128:256])
+    assert rel_l2(runs[0], run_oracle(s, op, x=x, w=w, dy=dy)) <= 1e-6
+
+
 # tiles of 128 pixels (the last three: of 256), 64-channel steps, 128 rows; (op,): the kernel takes that operation only
 HALF = [(21, 14, 14, 40, 130), (41, 14, 10, 256, 386), (3, 34, 30, 264, 66), (5, 28, 27, 512, 258), (9, 22, 22, 8, 100),
         (1, 4, 901, 72, 200), (6, 31, 32, 328, 34), (14, 40, 36, 24, 261, (F,)), (41, 22, 23, 256, 300, ()), (27, 28, 27, 256, 260),
