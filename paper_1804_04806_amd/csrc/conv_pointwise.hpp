@@ -33,6 +33,68 @@ struct PointwiseTile {
     static constexpr int kMaxK = (LDS - 2 * A_BUF) / (2 * B_STEP) * 32;
 };
 
+// A wave's tile on the fp32 instructions, operands straight from memory: `row` is the lane's filter row, load_b(k, b) its
+// pixels' values of input channel k (zero behind the last one).  Eight channels at a time, of which lanes 0-31 hold the first
+// four, in two sets of registers, so that the loads of one have the time of the other's products.  A launch of which
+// everything is computed again takes 1.6 to 2.7 times as long (160 -> 1024 channels 14x14 b = 168: 75 / 190 us; with two
+// channels at a time, one after another, 380).
+template <bool ROWS, int WM, int WN, class LoadB>
+__device__ __forceinline__ void pointwise_fp32(const PointwiseParams &p, __amdgpu_buffer_rsrc_t rw, int row, int lhi, LoadB load_b,
+                                               f32x16 (&acc)[WM][WN])
+{
+    constexpr int kAhead = 2;
+    asm volatile("" : "+v"(row), "+v"(lhi));   // addresses are computed here, not ahead of the caller's loops
+    struct Set { float a[WM][4], b[4][WN]; } set[kAhead];
+    auto load = [&](int k0, Set &s) __attribute__((always_inline)) {
+        const int k = k0 + 4 * lhi;
+#pragma unroll
+        for (int i = 0; i < WM; ++i) {
+            const int r = row + 32 * i;
+            const uint32_t vo = r < p.M && k < p.K ? 4u * (uint32_t)(r * p.w_row + k * p.w_k) : kOob;
+            if constexpr (ROWS) {
+                const f32x4 v = buf_load4(rw, vo);
+                s.a[i][0] = v.x; s.a[i][1] = v.y; s.a[i][2] = v.z; s.a[i][3] = v.w;
+            } else {   // channels past the last one lie behind the filter
+#pragma unroll
+                for (int e = 0; e < 4; ++e) s.a[i][e] = Elem<float>::load(rw, vo, 4u * (uint32_t)(e * p.w_k));
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) load_b(k + e, s.b[e]);
+    };
+    auto multiply = [&](int k0, Set &s) __attribute__((always_inline)) {
+        if (ROWS && k0 + 8 > p.K) {   // what follows a row's last channel is the next one's first
+#pragma unroll
+            for (int i = 0; i < WM; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) s.a[i][e] = k0 + 4 * lhi + e < p.K ? s.a[i][e] : 0.f;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int i = 0; i < WM; ++i)
+#pragma unroll
+                for (int j = 0; j < WN; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(s.a[i][e], s.b[e][j], acc[i][j], 0, 0, 0);
+    };
+#pragma unroll
+    for (int i = 0; i < WM; ++i)
+#pragma unroll
+        for (int j = 0; j < WN; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) load(8 * i, set[i]);
+#pragma unroll 1
+    for (int k0 = 0; k0 < p.K; k0 += 8 * kAhead) {
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i) {
+            multiply(k0 + 8 * i, set[i]);
+            load(k0 + 8 * (i + kAhead), set[i]);
+        }
+    }
+}
+
 // ROWS: the filter is contiguous along the reduction (Forward); otherwise along the output channels (BackwardData).
 // VEC: images of a multiple of four pixels
 template <bool ROWS, bool VEC>
@@ -236,36 +298,20 @@ __global__ __launch_bounds__(PointwiseTile::THREADS, 3) void pointwise_kernel(Po
         const int m0 = mt * MT + wm0;
         const bool inexact = __builtin_amdgcn_readfirstlane(*(volatile uint32_t *)&inexact_x) != 0 ||
                              __builtin_amdgcn_readfirstlane(*(volatile uint32_t *)&inexact_w[mt & 1]) == (uint32_t)mt + 1u;
-        if (inexact || __builtin_amdgcn_ballot_w64(redo)) {
-#pragma unroll
-            for (int i = 0; i < WM; ++i)
-#pragma unroll
-                for (int j = 0; j < WN; ++j)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+        if (__builtin_expect(inexact || __builtin_amdgcn_ballot_w64(redo), 0)) {
             uint32_t vo_b[WN];
 #pragma unroll
             for (int j = 0; j < WN; ++j) {
-                const int col = j0 + wn0 + 32 * j + l32;
+                int col = j0 + wn0 + 32 * j + l32;
+                asm volatile("" : "+v"(col));   // as there
                 uint32_t n, px;
                 p.div_px.divmod((uint32_t)col, n, px);
                 vo_b[j] = col < p.cols ? 4u * (uint32_t)((int)n * p.K * p.px + (int)px) : kOob;
             }
-            for (int k = 0; k < p.K; k += 2) {
-                const bool in = k + lhi < p.K;
-                float a[WM], b[WN];
+            pointwise_fp32<ROWS>(p, rw, m0 + l32, lhi, [&](int k, float (&b)[WN]) __attribute__((always_inline)) {
 #pragma unroll
-                for (int i = 0; i < WM; ++i) {
-                    const int row = m0 + 32 * i + l32;
-                    a[i] = Elem<float>::load(rw, in && row < p.M ? 4u * (uint32_t)(row * p.w_row + (k + lhi) * p.w_k) : kOob, 0);
-                }
-#pragma unroll
-                for (int j = 0; j < WN; ++j) b[j] = Elem<float>::load(rx, in && vo_b[j] != kOob ? vo_b[j] + (uint32_t)(k + lhi) * plane : kOob, 0);
-#pragma unroll
-                for (int i = 0; i < WM; ++i)
-#pragma unroll
-                    for (int j = 0; j < WN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
-            }
+                for (int j = 0; j < WN; ++j) b[j] = Elem<float>::load(rx, k < p.K && vo_b[j] != kOob ? vo_b[j] + (uint32_t)k * plane : kOob, 0);
+            }, acc);
         }
         auto store = [&](auto wholec) __attribute__((always_inline)) {
 #pragma unroll

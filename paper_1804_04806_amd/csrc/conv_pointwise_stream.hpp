@@ -178,28 +178,13 @@ __global__ __launch_bounds__(768, 3) void pointwise_split_stream_kernel(Pointwis
     const int col = j0 + 2 * (wq0 + l32);
     uint32_t n, px;
     p.div_px.divmod((uint32_t)col, n, px);
-    if (__builtin_amdgcn_readfirstlane(*(volatile uint32_t *)&inexact) || __builtin_amdgcn_ballot_w64(redo)) {
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+    if (__builtin_expect(__builtin_amdgcn_readfirstlane(*(volatile uint32_t *)&inexact) || __builtin_amdgcn_ballot_w64(redo), 0)) {
         const uint32_t vo_b = 4u * (uint32_t)((int)n * p.K * p.px + (int)px);
-        for (int k = 0; k < p.K; k += 2) {
-            const bool in = k + lhi < p.K;
-            float a[2];
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int row = m0 + wm0 + 32 * i + l32;
-                a[i] = Elem<float>::load(rw, in && row < p.M ? 4u * (uint32_t)(row * p.w_row + (k + lhi) * p.w_k) : kOob, 0);
-            }
-            const u32x2 b = __builtin_amdgcn_raw_buffer_load_b64(rx, (int)(in && col < p.cols ? vo_b + (uint32_t)(k + lhi) * plane : kOob), 0, 0);
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], __uint_as_float(b[j]), acc[i][j], 0, 0, 0);
-        }
+        pointwise_fp32<ROWS>(p, rw, m0 + wm0 + l32, lhi, [&](int k, float (&b)[2]) __attribute__((always_inline)) {
+            const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rx, (int)(k < p.K && col < p.cols ? vo_b + (uint32_t)k * plane : kOob), 0, 0);
+            b[0] = __uint_as_float(v[0]);
+            b[1] = __uint_as_float(v[1]);
+        }, acc);
     }
     if (col >= p.cols) return;
     const __amdgpu_buffer_rsrc_t ry = make_rsrc_bytes(p.y, 0, p.y_bytes);
