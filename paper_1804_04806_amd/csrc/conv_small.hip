@@ -62,11 +62,18 @@ bool small_pays(const Dims &d, int op, int b)
 }
 
 template <class E, int KIND>
-static void launch(bool big, const SmallParams<kSmallBwdData> &all, dim3 grid, int threads, hipStream_t s)
+static void launch(bool big, bool few, const SmallParams<kSmallBwdData> &all, dim3 grid, int threads, hipStream_t s)
 {
     SmallParams<KIND> p;
     static_cast<SmallHead &>(p) = all;
     for (size_t i = 0; i < sizeof(p.ph) / sizeof(p.ph[0]); ++i) p.ph[i] = all.ph[i];
+    if constexpr (std::is_same<E, float>::value) {
+        if (few) {
+            if (big) gemm_kernel_small<E, KIND, true, true><<<grid, threads, 0, s>>>(p);
+            else gemm_kernel_small<E, KIND, false, true><<<grid, threads, 0, s>>>(p);
+            return;
+        }
+    }
     if (big) gemm_kernel_small<E, KIND, true><<<grid, threads, 0, s>>>(p);
     else gemm_kernel_small<E, KIND, false><<<grid, threads, 0, s>>>(p);
 }
@@ -150,6 +157,7 @@ hipError_t small_conv(const Dims &d, int op, int b, const void *a, const void *b
     }
     const int steps = (kd + step - 1) / step;
     const int waves = steps >= 64 ? 16 : steps >= 24 ? 8 : 4;
+    const bool few = kd <= kSmallFew;
     const dim3 grid((unsigned)(p.tiles_m * ((n + 15) / 16)), (unsigned)phases, (unsigned)splits);
     if (LaunchLog *log = launch_log()) {
         static const char *const kind[3] = {"forward", "backward data", "backward filter"};
@@ -159,13 +167,13 @@ hipError_t small_conv(const Dims &d, int op, int b, const void *a, const void *b
         return hipSuccess;
     }
     if (d.dtype == 1) {
-        if (op == 0) launch<bf16, kSmallFwd>(big, p, grid, 64 * waves, s);
-        else if (op == 1) launch<bf16, kSmallBwdData>(big, p, grid, 64 * waves, s);
-        else launch<bf16, kSmallBwdFilter>(big, p, grid, 64 * waves, s);
+        if (op == 0) launch<bf16, kSmallFwd>(big, false, p, grid, 64 * waves, s);
+        else if (op == 1) launch<bf16, kSmallBwdData>(big, false, p, grid, 64 * waves, s);
+        else launch<bf16, kSmallBwdFilter>(big, false, p, grid, 64 * waves, s);
     } else {
-        if (op == 0) launch<float, kSmallFwd>(big, p, grid, 64 * waves, s);
-        else if (op == 1) launch<float, kSmallBwdData>(big, p, grid, 64 * waves, s);
-        else launch<float, kSmallBwdFilter>(big, p, grid, 64 * waves, s);
+        if (op == 0) launch<float, kSmallFwd>(big, few, p, grid, 64 * waves, s);
+        else if (op == 1) launch<float, kSmallBwdData>(big, few, p, grid, 64 * waves, s);
+        else launch<float, kSmallBwdFilter>(big, few, p, grid, 64 * waves, s);
     }
     return hipGetLastError();
 }

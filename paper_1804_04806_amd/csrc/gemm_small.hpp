@@ -19,6 +19,8 @@ namespace ucd {
 constexpr int kSmallRows = 2560;    // reduction rows per filling of the table
 constexpr int kSmallPhases = 16;
 
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
 enum SmallKind { kSmallFwd, kSmallBwdData, kSmallBwdFilter };
 
 // One GEMM: rows m (A), columns j (B), Kd reduction rows.
@@ -52,7 +54,13 @@ struct SmallParamsT : SmallHead {
 // (a single phase where there is but one: the arguments are written anew for every launch)
 template <int KIND> using SmallParams = SmallParamsT<KIND == kSmallBwdData ? kSmallPhases : 1>;
 
-template <class E, int KIND, bool BIG>
+// FEW: at most kSmallFew reduction rows of fp32, one step of a wave.  The fp32 instructions round every product, which among
+// so few is the larger part of the error (2 to 16 products spread over four accumulators: up to 1.3 times that of the tile
+// kernels, which add them in one chain or split them); 64-bit products and sums leave the rounding of the result: 0.2 to
+// 0.9 times, in the same time (310 layers, 1.00).
+constexpr int kSmallFew = 64;
+
+template <class E, int KIND, bool BIG, bool FEW = false>
 __global__ __launch_bounds__(1024) void gemm_kernel_small(SmallParams<KIND> p)
 {
     constexpr bool F32 = std::is_same<E, float>::value;
@@ -112,6 +120,7 @@ __global__ __launch_bounds__(1024) void gemm_kernel_small(SmallParams<KIND> p)
     f32x4 acc[4];   // one per MFMA of a step: shorter sums, and no MFMA waits for its predecessor
 #pragma unroll
     for (int i = 0; i < 4; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    f64x4 few = {0., 0., 0., 0.};
     const int k_begin = KIND == kSmallBwdFilter ? (int)blockIdx.z * p.k_chunk : 0;
     const int k_end = KIND == kSmallBwdFilter ? min(q.Kd, k_begin + p.k_chunk) : q.Kd;
     for (int base = k_begin; base < k_end; base += kSmallRows) {
@@ -230,7 +239,11 @@ __global__ __launch_bounds__(1024) void gemm_kernel_small(SmallParams<KIND> p)
                     }
                 }
             }
-            if constexpr (F32) {
+            if constexpr (FEW) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    few = __builtin_amdgcn_mfma_f64_16x16x4f64((double)__uint_as_float(g.a[i]), (double)__uint_as_float(g.b[i]), few, 0, 0, 0);
+            } else if constexpr (F32) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
                     acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(g.a[i]), __uint_as_float(g.b[i]), acc[i], 0, 0, 0);
@@ -260,7 +273,10 @@ __global__ __launch_bounds__(1024) void gemm_kernel_small(SmallParams<KIND> p)
     }
 
 #pragma unroll
-    for (int i = 0; i < 4; ++i) part[wave][(4 * grp + i) * LDP + l16] = ((double)acc[0][i] + (double)acc[1][i]) + ((double)acc[2][i] + (double)acc[3][i]);
+    for (int i = 0; i < 4; ++i) {   // a lane's four rows are adjacent, those of a 64-bit MFMA four apart
+        if constexpr (FEW) part[wave][(4 * i + grp) * LDP + l16] = few[i];
+        else part[wave][(4 * grp + i) * LDP + l16] = ((double)acc[0][i] + (double)acc[1][i]) + ((double)acc[2][i] + (double)acc[3][i]);
+    }
     __syncthreads();
     if (threadIdx.x >= 256) return;
     const int row = (int)threadIdx.x >> 4, col = (int)threadIdx.x & 15;

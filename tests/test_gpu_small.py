@@ -67,3 +67,23 @@ def test_values_behind_a_filter_row_do_not_reach_it():
     assert "gemm_kernel_small" in _kernel(s, F)
     assert rel_l2(got[:, fine], run_oracle(s, F, x=x, w=w)[:, fine]) <= 1e-6
     assert not np.isfinite(got[:, [3, 5]]).any()
+
+
+# sums of 1 to 64 products
+FEW = [(Shape(2, c, 7, 9, 20, r, r, 1, r // 2), F) for c, r in ((1, 1), (2, 1), (3, 1), (5, 1), (16, 1), (17, 1), (64, 1), (1, 3), (7, 3), (1, 7))] + \
+      [(Shape(2, 20, 7, 9, k, r, r, st, r // 2), D) for k, r, st in ((1, 1, 1), (2, 1, 1), (15, 1, 1), (33, 1, 1), (63, 1, 1), (2, 3, 1), (7, 3, 1), (16, 3, 2), (4, 7, 2))] + \
+      [(Shape(n, 10, h, w, 20, r, r, st, p), W) for n, h, w, r, st, p in ((1, 1, 1, 1, 1, 0), (1, 1, 2, 1, 1, 0), (1, 3, 3, 3, 1, 1), (1, 4, 4, 1, 1, 0),
+                                                                         (2, 5, 5, 1, 1, 0), (1, 8, 8, 3, 1, 1), (1, 9, 9, 3, 2, 0), (1, 8, 8, 7, 1, 3))]
+
+
+@pytest.mark.parametrize("s,op", FEW, ids=str)
+def test_sums_of_few_products_are_rounded_once(s, op):
+    """Up to 64 products of 48 bits are summed in 64-bit arithmetic: the result is off by half a unit of its last place, and by
+    64 roundings at 2^-53 of the largest partial sum where terms cancel."""
+    x, w, dy = inputs(s, seed=44)
+    assert "gemm_kernel_small" in _kernel(s, op)
+    a, b, rows = {F: (x, w, s.C * s.R * s.S), D: (dy, w, s.K * s.R * s.S), W: (x, dy, s.N * s.P * s.Q)}[op]
+    got, ref = run_hip(s, op, [(I, s.N)], x=x, w=w, dy=dy).astype(np.float64), run_oracle(s, op, x=x, w=w, dy=dy)
+    half = 0.5 * np.spacing(np.abs(ref).astype(np.float32)).astype(np.float64)
+    cancelled = 64 * 2.0 ** -53 * min(rows, 64) * np.abs(a).max() * np.abs(b).max()
+    assert (np.abs(got - ref) <= half * (1 + 1e-6) + cancelled).all()
