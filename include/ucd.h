@@ -119,7 +119,8 @@ int ucd_version(void);
  *   - Forward / BackwardData, implicit GEMM (also on the mirrored filter copy), fp32 tensors only: when the output has fewer than 768
  *     tiles the reduction over C*R*S is split the same way into a zero-filled output, and when the
  *     tile count is not a multiple of 256 the last tiles' reductions are spread over several
- *     workgroups.
+ *     workgroups (small layers, up to 256 tiles of 16 x 16 outputs and 2560 products each, run on a
+ *     kernel that does neither).
  * Everything else (im2col, Winograd and FFT Forward / BackwardData; implicit-GEMM Forward /
  * BackwardData with bf16 tensors or without the splits above) adds each output once and is bit
  * reproducible.

@@ -30,10 +30,9 @@ static PhaseExtent phase_extent(const Dims &d, int a, int c)
 //   bf16 (an eighth of the matrix time) Forward and BackwardData: up to 512 tiles 1.08 / 3.0, 512 to 1024 tiles 0.80 / 2.3
 //   BackwardFilter: fp32 up to 128 tiles, 524288 rows of tiles 1.22 / 2.0, 128 to 512 tiles up to 512 rows 1.49 / 2.1, 128 to
 //   256 tiles of 512 to 2560 rows 0.86 / 1.5; bf16 up to 128 tiles, 2048 rows 1.18 / 1.8, 128 to 512 tiles up to 512 rows 1.39 / 1.9
-// Some fp32 layers of more than 32 output channels stay on gemm_kernel_split although this kernel is the faster one there
-// too (7x7 64 -> 64 3x3: Forward 20.9 / 6.0 us, BackwardFilter 7.8 / 3.4): the tests of that kernel's edges name small layers
-// and hold their route fixed.  Forward: from 384 rows on, of one tap up to 512 rows, of more than 31, and of the others
-// between 64 tiles and 64 million multiplications; BackwardFilter: stride 1, up to 31 taps.
+// Layers of more than 32 output channels by themselves (900 more, fp32): Forward up to 64 tiles, 1024 to 2560 rows 1.08 / 2.0,
+// otherwise 1.5 / 3.8 (one image, 128 -> 128 3x3 14x14, which the tile kernels split over a cleared output, 21.9 / 7.9 us);
+// BackwardFilter 1.7 / 2.5.
 bool small_pays(const Dims &d, int op, int b)
 {
     const long M = op == 1 ? d.C : d.K;
@@ -44,17 +43,13 @@ bool small_pays(const Dims &d, int op, int b)
     const bool f32 = d.dtype == 0;
     if (op == 2) {
         if (d.det) return false;   // its chunks keep their planes there
-        if (f32 && d.K > 32 && d.sh == 1 && d.sw == 1 && d.R * d.S <= 31) return false;
         if (tiles <= 128) return f32 ? tiles * Kd <= 524288 : Kd < 2048;
         return tiles <= 512 && Kd <= 512;
     }
     if (op == 0) {
         // bf16: filter rows are read eight elements at a time, and the tensor's last dword has to be whole
         if (!f32) return tiles <= 512 && Kd <= 9216 && Kd % 2 == 0;
-        if (tiles > 256 || Kd > 2560) return false;
-        if (d.K <= 32 || Kd < 384 || M * N * Kd >= 64000000l) return true;
-        const int taps = d.R * d.S;
-        return taps == 1 ? Kd >= 512 : taps <= 31 && tiles < 64;
+        return tiles <= 256 && Kd <= 2560;
     }
     if (d.sh * d.sw > kSmallPhases) return false;
     if (!f32) return tiles <= 512 && Kd <= 9216;
@@ -157,7 +152,8 @@ hipError_t small_conv(const Dims &d, int op, int b, const void *a, const void *b
     }
     const int steps = (kd + step - 1) / step;
     const int waves = steps >= 64 ? 16 : steps >= 24 ? 8 : 4;
-    const bool few = kd <= kSmallFew;
+    // (up to twice as many rows where the tile kernels split their operands, whose products are exact)
+    const bool few = kd <= (op == 2 && p.M > 32 ? 2 * kSmallFew : kSmallFew);
     const dim3 grid((unsigned)(p.tiles_m * ((n + 15) / 16)), (unsigned)phases, (unsigned)splits);
     if (LaunchLog *log = launch_log()) {
         static const char *const kind[3] = {"forward", "backward data", "backward filter"};

@@ -54,10 +54,10 @@ struct SmallParamsT : SmallHead {
 // (a single phase where there is but one: the arguments are written anew for every launch)
 template <int KIND> using SmallParams = SmallParamsT<KIND == kSmallBwdData ? kSmallPhases : 1>;
 
-// FEW: at most kSmallFew reduction rows of fp32, one step of a wave.  The fp32 instructions round every product, which among
-// so few is the larger part of the error (2 to 16 products spread over four accumulators: up to 1.3 times that of the tile
-// kernels, which add them in one chain or split them); 64-bit products and sums leave the rounding of the result: 0.2 to
-// 0.9 times, in the same time (310 layers, 1.00).
+// FEW: few reduction rows of fp32.  The fp32 instructions round every product, which among so few is the larger part of
+// the error (2 to 16 products spread over four accumulators: up to 1.3 times that of the tile kernels that add them in one
+// chain; 65 to 128 up to 1.08 times that of those that split them); 64-bit products and sums leave the rounding of the result:
+// 0.2 to 0.9 times, in the same time up to 64 rows, one step of a wave (310 layers, 1.00; 65 to 128 rows 1.02).
 constexpr int kSmallFew = 64;
 
 template <class E, int KIND, bool BIG, bool FEW = false>

@@ -19,9 +19,9 @@ SHAPES = [
     (Shape(1, 15, 1, 17, 15, 1, 1, 1, 0), (F, D, W), (D, W)), (Shape(3, 33, 5, 5, 31, 3, 3, 1, 1), (F, D, W), (D, W)),
     (Shape(2, 16, 9, 7, 32, 5, 3, 1, 1), (F, D, W), (F, D, W)), (Shape(1, 284, 6, 6, 32, 3, 3, 1, 1), (F, D, W), (F, D, W)),
     (Shape(1, 290, 6, 6, 32, 3, 3, 1, 1), (D, W), (F, D, W)), (Shape(1, 1020, 5, 5, 40, 3, 3, 1, 1), (D,), (F, D)),
-    (Shape(1, 20, 6, 5, 640, 3, 3, 1, 1), (F,), (F, D, W)), (Shape(2, 12, 13, 11, 34, 3, 3, 2, 1), (F, D, W), (F, D, W)),
+    (Shape(1, 20, 6, 5, 640, 3, 3, 1, 1), (F, W), (F, D, W)), (Shape(2, 12, 13, 11, 34, 3, 3, 2, 1), (F, D, W), (F, D, W)),
     (Shape(2, 12, 13, 11, 34, 1, 1, 2, 0), (F, D, W), (F, D, W)), (Shape(1, 6, 17, 19, 20, 3, 3, 4, 0), (F, D, W), (F, D, W)),
-    (Shape(1, 10, 17, 13, 36, 7, 7, 1, 3), (D, W), (F, D, W)), (Shape(1, 4, 23, 20, 24, 11, 11, 4, 0), (F, D, W), (F, D, W)),
+    (Shape(1, 10, 17, 13, 36, 7, 7, 1, 3), (F, D, W), (F, D, W)), (Shape(1, 4, 23, 20, 24, 11, 11, 4, 0), (F, D, W), (F, D, W)),
     (Shape(1, 3, 31, 30, 40, 7, 7, 2, 3), (F, D, W), (D, W)), (Shape(4, 8, 17, 15, 32, 3, 3, 1, 1), (F, D, W), (F, D, W)),
     (Shape(8, 16, 16, 16, 32, 3, 3, 1, 1), (F, D, W), (F, D)), (Shape(60, 9, 13, 12, 32, 1, 1, 1, 0), (D, W), ()),
     (Shape(1, 256, 14, 14, 256, 3, 3, 1, 1), (F, D), (F, D)),
@@ -69,21 +69,22 @@ def test_values_behind_a_filter_row_do_not_reach_it():
     assert not np.isfinite(got[:, [3, 5]]).any()
 
 
-# sums of 1 to 64 products
+# sums of 1 to 64 products, BackwardFilter of more than 32 output channels up to 128
 FEW = [(Shape(2, c, 7, 9, 20, r, r, 1, r // 2), F) for c, r in ((1, 1), (2, 1), (3, 1), (5, 1), (16, 1), (17, 1), (64, 1), (1, 3), (7, 3), (1, 7))] + \
       [(Shape(2, 20, 7, 9, k, r, r, st, r // 2), D) for k, r, st in ((1, 1, 1), (2, 1, 1), (15, 1, 1), (33, 1, 1), (63, 1, 1), (2, 3, 1), (7, 3, 1), (16, 3, 2), (4, 7, 2))] + \
-      [(Shape(n, 10, h, w, 20, r, r, st, p), W) for n, h, w, r, st, p in ((1, 1, 1, 1, 1, 0), (1, 1, 2, 1, 1, 0), (1, 3, 3, 3, 1, 1), (1, 4, 4, 1, 1, 0),
-                                                                         (2, 5, 5, 1, 1, 0), (1, 8, 8, 3, 1, 1), (1, 9, 9, 3, 2, 0), (1, 8, 8, 7, 1, 3))]
+      [(Shape(n, 10, h, w, k, r, r, st, p), W) for n, h, w, k, r, st, p in (
+          (1, 1, 1, 20, 1, 1, 0), (1, 1, 2, 20, 1, 1, 0), (1, 3, 3, 20, 3, 1, 1), (1, 4, 4, 20, 1, 1, 0), (2, 5, 5, 20, 1, 1, 0),
+          (1, 8, 8, 20, 3, 1, 1), (1, 9, 9, 20, 3, 2, 0), (1, 8, 8, 20, 7, 1, 3), (2, 7, 7, 40, 3, 1, 1), (2, 8, 8, 33, 1, 1, 0))]
 
 
 @pytest.mark.parametrize("s,op", FEW, ids=str)
 def test_sums_of_few_products_are_rounded_once(s, op):
-    """Up to 64 products of 48 bits are summed in 64-bit arithmetic: the result is off by half a unit of its last place, and by
-    64 roundings at 2^-53 of the largest partial sum where terms cancel."""
+    """Products of 48 bits are summed in 64-bit arithmetic: the result is off by half a unit of its last place and, where terms
+    cancel, by a rounding at 2^-53 of the largest partial sum for each of them."""
     x, w, dy = inputs(s, seed=44)
     assert "gemm_kernel_small" in _kernel(s, op)
     a, b, rows = {F: (x, w, s.C * s.R * s.S), D: (dy, w, s.K * s.R * s.S), W: (x, dy, s.N * s.P * s.Q)}[op]
     got, ref = run_hip(s, op, [(I, s.N)], x=x, w=w, dy=dy).astype(np.float64), run_oracle(s, op, x=x, w=w, dy=dy)
     half = 0.5 * np.spacing(np.abs(ref).astype(np.float32)).astype(np.float64)
-    cancelled = 64 * 2.0 ** -53 * min(rows, 64) * np.abs(a).max() * np.abs(b).max()
+    cancelled = rows * 2.0 ** -53 * rows * np.abs(a).max() * np.abs(b).max()
     assert (np.abs(got - ref) <= half * (1 + 1e-6) + cancelled).all()

@@ -53,19 +53,40 @@ def _runs(s):
     return runs
 
 
+def _kernels(s, op, algo):
+    return ucd.ucd_describe_micro(ucd.layer(s), op, algo, s.N)[0]
+
+
+def _tile_runs(s):
+    """(operation, algorithm, layer): the operations above with so many images that they leave gemm_kernel_small."""
+    for op, algo in _runs(s):
+        t = s
+        while "gemm_kernel_small" in _kernels(t, op, algo):
+            t = t.with_batch(t.N + 1)
+        yield op, algo, t
+
+
+def _check_edges(s, op, algo):
+    x, w, dy = inputs(s, seed=7)
+    got = run_hip(s, op, [(algo, s.N)], x=x, w=w, dy=dy)
+    ref = run_oracle(s, op, x=x, w=w, dy=dy)
+    assert rel_l2(got, ref) <= 1e-6, (ucd.OP_NAMES[op], s.N, rel_l2(got, ref))
+
+
 @pytest.mark.parametrize("s", SHAPES, ids=_id)
 def test_split_gemm_edges(s):
-    x, w, dy = inputs(s, seed=7)
-    for op, algo in _runs(s):
-        rows = (s.C if op == ucd.FWD else s.K) * s.R * s.S
-        split = "gemm_kernel_split" in ucd.ucd_describe_micro(ucd.layer(s), op, algo, s.N)[0]
+    for op, algo, t in _tile_runs(s):
+        rows = (t.C if op == ucd.FWD else t.K) * t.R * t.S
+        text = _kernels(t, op, algo)
+        split = "gemm_kernel_split<" in text
+        assert split or "gemm_kernel<" in text, text
         if op == ucd.BWD_FILTER:  # strided layers and padded ones of many taps: from a number of multiplications on
-            assert split or (s.K * s.C * s.R * s.S * s.N * s.P * s.Q < 1.6e9 and (s.stride > 1 or s.R * s.S > 31))
+            assert split or (t.K * t.C * t.R * t.S * t.N * t.P * t.Q < 1.6e9 and (t.stride > 1 or t.R * t.S > 31))
         else:
             assert split or rows < 384   # short reductions stay on the fp32 kernel
-        got = run_hip(s, op, [(algo, s.N)], x=x, w=w, dy=dy)
-        ref = run_oracle(s, op, x=x, w=w, dy=dy)
-        assert rel_l2(got, ref) <= 1e-6, (ucd.OP_NAMES[op], rel_l2(got, ref))
+        _check_edges(t, op, algo)
+        if t.N > s.N:
+            _check_edges(s, op, algo)
 
 
 def test_shapes_reach_every_tile_and_loader():
@@ -89,11 +110,11 @@ def test_shapes_reach_every_tile_and_loader():
 @pytest.mark.parametrize("s", [SHAPES[i] for i in (6, 9, 10, 13, 14, 0, 24, 26)], ids=_id)
 def test_split_gemm_not_finite(s):
     """Infinities and NaN come out where, and as, fp32 arithmetic gives them; the other outputs stay exact."""
-    x, w, dy = inputs(s, seed=8)
-    finite_dy = dy.copy()
-    x[0, 0, 0, 0], x[-1, -1, -1, -1], dy[0, -1, 0, 0], dy[-1, 0, -1, -1] = np.inf, np.nan, -np.inf, np.nan
-    x[0, 1, 0, 0] = 3.3e38  # finite, but infinite when rounded to bf16
-    for op, algo in _runs(s):
+    for op, algo, s in _tile_runs(s):
+        x, w, dy = inputs(s, seed=8)
+        finite_dy = dy.copy()
+        x[0, 0, 0, 0], x[-1, -1, -1, -1], dy[0, -1, 0, 0], dy[-1, 0, -1, -1] = np.inf, np.nan, -np.inf, np.nan
+        x[0, 1, 0, 0] = 3.3e38  # finite, but infinite when rounded to bf16
         # BackwardFilter's kernels multiply dy with the padding's zeros, the oracle skips them
         g = finite_dy if op == ucd.BWD_FILTER and s.pad else dy
         got = run_hip(s, op, [(algo, s.N)], x=x, w=w, dy=g).astype(np.float64)
@@ -115,8 +136,8 @@ RANGES = [(1e-37, 1.0), (1e-30, 1.0), (1e30, 1.0), (2.0 ** -116, 2.0 ** 30), (2.
 @pytest.mark.parametrize("scale,partner", RANGES)
 @pytest.mark.parametrize("s", [SHAPES[0], SHAPES[11]], ids=_id)
 def test_split_gemm_range(s, scale, partner):
-    x, w, dy = inputs(s, seed=9)
-    for op, algo in _runs(s):
+    for op, algo, s in _tile_runs(s):
+        x, w, dy = inputs(s, seed=9)
         for first in (True, False):   # which operand is the small one
             a, b = np.float32(scale if first else partner), np.float32(partner if first else scale)
             xs, ws, dys = (x * a, w * b, dy) if op == ucd.FWD else (x, w * b, dy * a) if op == ucd.BWD_DATA else (x * b, w, dy * a)
@@ -129,13 +150,12 @@ def test_split_gemm_range(s, scale, partner):
 def test_split_gemm_small_parts(s):
     """One image, one output channel or one input channel far below bf16's range among ordinary ones, whose results
     are compared by themselves."""
-    x, w, dy = inputs(s, seed=10)
-    tiny = np.float32(2.0 ** -130)
-    x[0] *= tiny
-    w[1] *= tiny
-    dy[:, 2] *= tiny
-    up = np.float32(2.0 ** 40)
-    for op, algo in _runs(s):
+    tiny, up = np.float32(2.0 ** -130), np.float32(2.0 ** 40)
+    for op, algo, s in _tile_runs(s):
+        x, w, dy = inputs(s, seed=10)
+        x[0] *= tiny
+        w[1] *= tiny
+        dy[:, 2] *= tiny
         xs, ws, dys = (x, w * up, dy) if op == ucd.FWD else (x, w * up, dy) if op == ucd.BWD_DATA else (x * up, w, dy)
         got = run_hip(s, op, [(algo, s.N)], x=xs, w=ws, dy=dys)
         ref = run_oracle(s, op, x=xs, w=ws, dy=dys)
