@@ -35,8 +35,8 @@ sys.path.insert(0, ROOT)
 
 METRIC = "conv ms/iter (fwd+bwdData+bwdFilter) @64MB workspace; TFLOP/s, % MFMA peak"
 FP32_MFMA_PEAK_TFLOPS = 157.3   # MI355X dense fp32 matrix peak: 256 CU x 2.4 GHz x 256 flop/clk/CU
-BF16_MFMA_PEAK_TFLOPS = 2500.0  # dense bf16 matrix peak (16x the fp32 rate); kernels named gemm_kernel_bf16
-SPLIT_PEAK_TFLOPS = BF16_MFMA_PEAK_TFLOPS / 6  # fp32 products as six bf16 ones; kernels named *_split*
+BF16_MFMA_PEAK_TFLOPS = 2500.0  # dense bf16 matrix peak (16x the fp32 rate)
+SPLIT_PEAK_TFLOPS = BF16_MFMA_PEAK_TFLOPS / 6  # fp32 products as six bf16 ones
 WS_LIMIT = 64 << 20
 
 # HBM bytes (fetched + written) per matrix flop of the kernels of the default workload's planned
@@ -247,6 +247,19 @@ def num(v):
     return None if v != v else round(v, 4)
 
 
+GEMM_KERNELS = ("gemm_kernel", "conv_halo_kernel", "pointwise_")   # described with the M, N and K of their GEMM
+
+
+def matrix_peak(name):
+    """TFLOP/s that the matrix instructions of a kernel (as the library describes it) can reach."""
+    kernel = name.split("<")[0]
+    if "_bf16" in kernel or kernel == "pointwise_stream_kernel" or "/bf16" in name:
+        return BF16_MFMA_PEAK_TFLOPS
+    if "_split" in kernel or kernel in ("conv_halo_kernel", "pointwise_kernel"):
+        return SPLIT_PEAK_TFLOPS
+    return FP32_MFMA_PEAK_TFLOPS
+
+
 def gemm_flops(text):
     """MFMA flops the GEMM launches of a micro-batch description issue: 2*M*N*K*batch each."""
     total = 0.0
@@ -254,7 +267,7 @@ def gemm_flops(text):
         part = part.strip()
         if part.startswith(("wino_fused", "wino5_fused")):
             total += float(part.split("gemm_flops=")[1].split()[0])
-        if not part.startswith("gemm_kernel"):
+        if not part.startswith(GEMM_KERNELS):
             continue
         f = dict(kv.split("=") for kv in part.split("> ")[-1].split() if "=" in kv)
         total += 2.0 * int(f["M"]) * int(f["N"]) * int(f["K"]) * int(f["batch"])
@@ -283,7 +296,7 @@ def kernel_class(ucd, desc, op, algo, b):
     parts = [p.strip() for p in text.split(";")]
     helpers = ("fill_zero_kernel", "zero_tiles_kernel", "wino_filter_kernel", "wino_dw_kernel", "mirror_filter_kernel",
                "wino5_filter_kernel", "wino5_dw_kernel", "wino_phase_filter_kernel", "wino_filter_bf16_kernel")
-    main = [p for p in parts if p.startswith(("gemm_kernel", "wino_fused", "wino5_fused"))]
+    main = [p for p in parts if p.startswith(GEMM_KERNELS + ("wino_fused", "wino5_fused"))]
     others = [p for p in parts if p not in main and p not in helpers]
     if len(main) != 1 or others:
         return None
@@ -342,8 +355,7 @@ def dominant_kernel_roofline(torch, ucd, states, plans, ws, reps, traffic_table=
              for k, g in sorted(groups.items(), key=lambda kv: -kv[1]["ms"])]
     name, g = max(groups.items(), key=lambda kv: kv[1]["ms"])
     achieved = g["flops"] / (g["ms"] * 1e-3) / 1e12
-    peak = (BF16_MFMA_PEAK_TFLOPS if name.startswith("gemm_kernel_bf16") else
-            SPLIT_PEAK_TFLOPS if "_split" in name.split("<")[0] else FP32_MFMA_PEAK_TFLOPS)
+    peak = matrix_peak(name)
     roof = {"bound": "mfma", "kernel": name, "achieved": round(achieved, 2), "peak": peak,
             "unit": "TFLOP/s", "frac": round(achieved / peak, 4),
             "traffic": None,

@@ -46,7 +46,7 @@ static hipError_t launch(const Dims &d, int b, const void *dy, const void *w, vo
     const int tiles_n = (p.cols + T::NT - 1) / T::NT;
     const dim3 grid((unsigned)(p.tiles_m * tiles_n), (unsigned)d.sh);
     if (LaunchLog *log = launch_log()) {
-        log->add("gemm_kernel_split_halo<Tile<" + std::to_string(T::MT) + "x" + std::to_string(T::NT) + ">,phases " +
+        log->add("conv_halo_kernel<Tile<" + std::to_string(T::MT) + "x" + std::to_string(T::NT) + ">,phases " +
                  std::to_string(d.sh * T::NPH) + "> tiles=" + std::to_string(grid.x * grid.y) + " splits=1 batch=1 M=" +
                  std::to_string(d.C) + " N=" + std::to_string(p.cols) + " K=" + std::to_string(d.K * d.R * d.S));
         return hipSuccess;

@@ -115,7 +115,7 @@ hipError_t pointwise_conv(const Dims &d, int op, int b, const void *in, const vo
     typedef PointwiseTile T;
     const unsigned grid = pointwise_grid(p, T::MT, T::NT);
     if (LaunchLog *log = launch_log()) {
-        log->add(pointwise_text(p, "gemm_kernel_split_pointwise", op == 0 ? "forward" : "backward data", T::MT, T::NT));
+        log->add(pointwise_text(p, "pointwise_kernel", op == 0 ? "forward" : "backward data", T::MT, T::NT));
         return hipSuccess;
     }
     if (p.px % 4 == 0) {
@@ -135,7 +135,7 @@ hipError_t pointwise_stream(const Dims &d, int op, int b, const void *in, const 
     p.whole = (p.cols + 255) / 256;
     p.splits = 1;
     if (LaunchLog *log = launch_log()) {
-        log->add(pointwise_text(p, "gemm_kernel_split_pointwise_stream", op == 0 ? "forward" : "backward data", 128, 256));
+        log->add(pointwise_text(p, "pointwise_split_stream_kernel", op == 0 ? "forward" : "backward data", 128, 256));
         return hipSuccess;
     }
     const unsigned grid = (unsigned)((p.whole + 7) / 8 * 8 * p.m_tiles);
@@ -149,7 +149,7 @@ static hipError_t launch_bf16(PointwiseParams &p, int op, hipStream_t s)
 {
     const unsigned grid = pointwise_grid(p, T::MT, T::NT);
     if (LaunchLog *log = launch_log()) {
-        log->add(pointwise_text(p, "gemm_kernel_bf16_pointwise", op == 0 ? "forward" : "backward data", T::MT, T::NT));
+        log->add(pointwise_text(p, "pointwise_bf16_kernel", op == 0 ? "forward" : "backward data", T::MT, T::NT));
         return hipSuccess;
     }
     if (op == 0) pointwise_bf16_kernel<T, true><<<grid, T::THREADS, 0, s>>>(p);
@@ -168,7 +168,7 @@ static hipError_t launch_stream(const PointwiseParams &a, int op, hipStream_t s)
     p.m_tiles = (p.M + 128 * WM - 1) / (128 * WM);
     p.tiles = (p.cols + 255) / 256;
     if (LaunchLog *log = launch_log()) {
-        log->add(pointwise_text(a, "gemm_kernel_bf16_pointwise_stream", op == 0 ? "forward" : "backward data", 128 * WM, 256));
+        log->add(pointwise_text(a, "pointwise_stream_kernel", op == 0 ? "forward" : "backward data", 128 * WM, 256));
         return hipSuccess;
     }
     const unsigned grid = (unsigned)((p.tiles + 7) / 8 * 8 * p.m_tiles);

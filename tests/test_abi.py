@@ -250,3 +250,27 @@ def test_small_layers_by_tiles_and_rows():
     # BackwardFilter up to 128 tiles with 4096 rows of each, 512 tiles with 512 rows
     assert all(small(ucd.BWD_FILTER, 1, 16, 28, k) for k in (32, 33, 64)) and small(ucd.BWD_FILTER, 2, 64, 14, 128)
     assert not small(ucd.BWD_FILTER, 8, 64, 28, 33) and not small(ucd.BWD_FILTER, 3, 64, 14, 128)
+
+
+def test_descriptions_name_kernels_of_the_sources():
+    """ucd_describe_micro's names are those of the kernels that a trace of the same call shows."""
+    kernels = set()
+    for name in os.listdir(os.path.join(ROOT, "paper_1804_04806_amd", "csrc")):
+        with open(os.path.join(ROOT, "paper_1804_04806_amd", "csrc", name)) as f:
+            kernels |= set(re.findall(r"__global__[^;{]*?\bvoid\s+(\w+)\(", f.read()))
+    seen = set()
+    for dtype in (0, 1):
+        for n, c, hw, k, r, stride, pad in ((8, 16, 16, 32, 3, 1, 1), (64, 64, 56, 128, 3, 2, 1), (64, 128, 28, 512, 1, 1, 0),
+                                            (64, 512, 28, 128, 1, 1, 0), (64, 3, 224, 64, 7, 2, 3), (64, 96, 27, 256, 5, 1, 2),
+                                            (64, 256, 14, 256, 3, 1, 1), (16, 768, 28, 64, 1, 1, 0), (16, 24, 33, 40, 3, 1, 0)):
+            L = ucd.layer(N=n, C=c, H=hw, W=hw, K=k, R=r, S=r, pad_h=pad, pad_w=pad, stride_h=stride, stride_w=stride, dtype=dtype)
+            for op in range(3):
+                for algo in range(ucd.N_ALGO):
+                    if ucd.ucd_workspace_size(L, op, algo, n) != ucd.WS_NA:
+                        text, launches = ucd.ucd_describe_micro(L, op, algo, n)
+                        parts = [re.match(r"\w+", p.strip()).group(0) for p in text.split(";") if p.strip()]
+                        assert len(parts) == launches, text
+                        seen |= set(parts)
+    assert seen <= kernels, seen - kernels
+    assert seen >= {"conv_halo_kernel", "gemm_kernel_small", "pointwise_kernel", "pointwise_split_stream_kernel",
+                    "pointwise_bf16_kernel", "pointwise_stream_kernel"}, seen

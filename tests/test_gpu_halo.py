@@ -28,7 +28,7 @@ def _id(s):
 
 
 def _run(s, w, dy, parts=None):
-    assert parts or "gemm_kernel_split_halo" in ucd.ucd_describe_micro(ucd.layer(s), D, I, s.N)[0]
+    assert parts or "conv_halo_kernel<" in ucd.ucd_describe_micro(ucd.layer(s), D, I, s.N)[0]
     return run_hip(s, D, [(I, b) for b in parts or [s.N]], w=w, dy=dy)
 
 

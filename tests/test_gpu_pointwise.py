@@ -26,8 +26,12 @@ CASES = [(21, 14, 14, 17, 129), (21, 13, 15, 32, 256), (5, 29, 29, 33, 257), (9,
 STREAM32 = [(42, 28, 28, 33, 97), (21, 28, 28, 161, 200), (43, 27, 28, 249, 129), (10, 28, 29, 176, 500), (42, 28, 28, 256, 100)]
 
 
+def _fp32_kernel(s, op):
+    return ucd.ucd_describe_micro(ucd.layer(s), op, I, s.N)[0].split("<")[0]
+
+
 def _run(s, op, x, w, dy, parts=None):
-    assert parts or "gemm_kernel_split_pointwise" in ucd.ucd_describe_micro(ucd.layer(s), op, I, s.N)[0]
+    assert parts or _fp32_kernel(s, op) in ("pointwise_kernel", "pointwise_split_stream_kernel")
     return run_hip(s, op, [(I, b) for b in parts or [s.N]], x=x, w=w, dy=dy)
 
 
@@ -35,8 +39,7 @@ def _run(s, op, x, w, dy, parts=None):
 @pytest.mark.parametrize("case", CASES + STREAM32, ids=str)
 def test_pointwise_edges(case, op):
     s = _layer(*case, op)
-    kernel = ucd.ucd_describe_micro(ucd.layer(s), op, I, s.N)[0]
-    assert ("pointwise_stream" in kernel) == (case in STREAM32), kernel
+    assert _fp32_kernel(s, op) == ("pointwise_split_stream_kernel" if case in STREAM32 else "pointwise_kernel")
     x, w, dy = inputs(s, seed=61)
     ref = run_oracle(s, op, x=x, w=w, dy=dy)
     for parts in (None, [1, s.N - 1] if s.N > 1 else None):
@@ -101,13 +104,14 @@ def test_pointwise_recomputes_the_tile_row_of_an_inexact_filter_element(case, op
     assert rel_l2(runs[0], run_oracle(s, op, x=x, w=w, dy=dy)) <= 1e-6
 
 
-@pytest.mark.parametrize("s,op,kernel", [(Shape(168, 160, 14, 14, 1024, 1, 1, 1, 0), F, "pointwise"),
-                                         (Shape(64, 256, 28, 28, 1024, 1, 1, 1, 0), D, "stream")], ids=("lds", "stream"))
+@pytest.mark.parametrize("s,op,kernel", [(Shape(168, 160, 14, 14, 1024, 1, 1, 1, 0), F, "pointwise_kernel"),
+                                         (Shape(64, 256, 28, 28, 1024, 1, 1, 1, 0), D, "pointwise_split_stream_kernel")],
+                         ids=("lds", "stream"))
 def test_pointwise_recomputed_tiles_are_not_far_slower(s, op, kernel):
     """With a filter below bf16's range every tile is computed twice, the second time on the fp32 instructions, which
     alone take about 1.5 times the ordinary call: 2.5 and 2.7 times in all, 3.5 are the limit."""
     import torch
-    assert kernel in ucd.ucd_describe_micro(ucd.layer(s), op, I, s.N)[0]
+    assert _fp32_kernel(s, op) == kernel
     plan = ucd.ucd_plan_fixed(ucd.layer(s), op, [(I, s.N)])
     t, w = (torch.randn(shape, device="cuda:0") for shape in (s.x_shape if op == F else s.y_shape, s.w_shape))
     out = torch.empty(s.y_shape if op == F else s.x_shape, device="cuda:0")
@@ -147,8 +151,8 @@ def test_pointwise_bf16_edges(case, op):
     bits, (x, w, dy) = bf16_inputs(s, seed=65)
     ref = run_oracle(s, op, x=x, w=w, dy=dy)
     kernel = ucd.ucd_describe_micro(ucd.layer(s, dtype=1), op, I, s.N)[0]
-    name = "gemm_kernel_bf16_pointwise_stream<" if case in STREAM else "gemm_kernel_bf16_pointwise<"
-    assert (name in kernel) == (op in (case[5] if len(case) > 5 else (F, D))), kernel
+    name = "pointwise_stream_kernel<" if case in STREAM else "pointwise_bf16_kernel<"
+    assert kernel.startswith(name) == (op in (case[5] if len(case) > 5 else (F, D))), kernel
     for parts in [s.N], [1, s.N - 1]:
         if min(parts) > 0:
             check_bf16_output(run_hip_bf16(s, op, [(I, b) for b in parts], bits), ref, ucd.OP_NAMES[op])
