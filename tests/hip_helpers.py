@@ -1,13 +1,41 @@
 """Shared helpers of the GPU parity tests: run the HIP path through the C-ABI binding on torch
 device buffers and return numpy results; run the oracle on the same bits."""
+from dataclasses import dataclass
+
 import numpy as np
 
 from oracle import conv as oc
 from paper_1804_04806_amd import synth, ucd
 
 
+@dataclass(frozen=True)
+class RectShape(synth.Shape):
+    """A layer whose rows have `stride` and `pad`, its columns strides and paddings of their own."""
+    stride_w: int = 1
+    pad_w: int = 0
+
+    @property
+    def Q(self):
+        return (self.W + 2 * self.pad_w - self.S) // self.stride_w + 1
+
+
+def rect(n, c, h, w, k, r, s, strides, pads):
+    return RectShape(n, c, h, w, k, r, s, strides[0], pads[0], "", strides[1], pads[1])
+
+
+def _columns(s):
+    return getattr(s, "stride_w", s.stride), getattr(s, "pad_w", s.pad)
+
+
+def desc_of(s, dtype=0):
+    stride_w, pad_w = _columns(s)
+    return ucd.layer(N=s.N, C=s.C, H=s.H, W=s.W, K=s.K, R=s.R, S=s.S, stride_h=s.stride, stride_w=stride_w, pad_h=s.pad,
+                     pad_w=pad_w, dtype=dtype)
+
+
 def oracle_layer(s):
-    return oc.Layer(s.N, s.C, s.H, s.W, s.K, s.R, s.S, s.stride, s.stride, s.pad, s.pad)
+    stride_w, pad_w = _columns(s)
+    return oc.Layer(s.N, s.C, s.H, s.W, s.K, s.R, s.S, s.stride, stride_w, s.pad, pad_w)
 
 
 def rel_l2(got, ref):
@@ -81,7 +109,7 @@ def run_hip(s, op, micro, x=None, w=None, dy=None, beta=0.0, dw0=None, poison=Tr
     region behind it must stay untouched); inputs are numpy float32 arrays. Returns numpy float32."""
     import torch
     dev = torch.device("cuda:0")
-    desc = ucd.layer(s)
+    desc = desc_of(s)
     plan = ucd.ucd_plan_fixed(desc, op, micro)
     need = plan.ws_bytes
     guarded = GuardedWorkspace(need)

@@ -15,7 +15,7 @@ import pytest
 
 from paper_1804_04806_amd import synth, ucd
 from paper_1804_04806_amd.synth import Shape
-from hip_helpers import GuardedWorkspace, inputs, l2_tol, rel_l2, run_oracle
+from hip_helpers import GuardedWorkspace, desc_of, inputs, l2_tol, rel_l2, run_oracle
 
 pytestmark = pytest.mark.gpu
 
@@ -57,7 +57,7 @@ def dev_bf16(bits):
 def run_hip_bf16(s, op, micro, bits, beta=0.0, dw0=None):
     import torch
     dev = torch.device("cuda:0")
-    desc = ucd.layer(s, dtype=1)
+    desc = desc_of(s, dtype=1)
     plan = ucd.ucd_plan_fixed(desc, op, micro)
     need = plan.ws_bytes
     guarded = GuardedWorkspace(need)   # exactly the plan's bytes, a guard region behind them

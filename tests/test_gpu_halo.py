@@ -1,11 +1,12 @@
 """conv_halo_kernel (BackwardData over a window in LDS): edges of its tiles of channels and positions, chunks of 16 channels
-that the last one does not fill, column blocks, tiles over several images, paddings of either parity, values out of range."""
+that the last one does not fill, column blocks, tiles over several images, paddings of either parity, strides and paddings of
+rows and columns that differ, values out of range, equal bits in every run."""
 import numpy as np
 import pytest
 
 from paper_1804_04806_amd import ucd
 from paper_1804_04806_amd.synth import Shape
-from hip_helpers import inputs, rel_l2, run_hip, run_oracle
+from hip_helpers import desc_of, inputs, rect, rel_l2, run_hip, run_oracle
 
 pytestmark = pytest.mark.gpu
 
@@ -28,7 +29,7 @@ def _id(s):
 
 
 def _run(s, w, dy, parts=None):
-    assert parts or "conv_halo_kernel<" in ucd.ucd_describe_micro(ucd.layer(s), D, I, s.N)[0]
+    assert parts or "conv_halo_kernel<" in ucd.ucd_describe_micro(desc_of(s), D, I, s.N)[0]
     return run_hip(s, D, [(I, b) for b in parts or [s.N]], w=w, dy=dy)
 
 
@@ -38,6 +39,36 @@ def test_halo_edges(s):
     ref = run_oracle(s, D, w=w, dy=dy)
     for parts in (None, [s.N - 1, 1] if s.N > 1 else None):
         assert rel_l2(_run(s, w, dy, parts), ref) <= 1e-6
+
+
+# rows and columns of different strides and paddings: (1, 2), (2, 1), (3, 2), (3, 1), (4, 2); filters as wide as they are not high
+RECT = [rect(60, 24, 14, 15, 100, 3, 3, (1, 2), (1, 0)), rect(101, 100, 20, 21, 20, 3, 3, (2, 1), (0, 1)),
+        rect(6, 63, 29, 31, 65, 3, 3, (3, 2), (1, 2)), rect(70, 120, 28, 23, 40, 4, 3, (3, 1), (2, 0)),
+        rect(9, 40, 25, 22, 49, 5, 5, (1, 2), (2, 1)), rect(12, 33, 31, 40, 150, 4, 5, (4, 2), (0, 2)),
+        rect(7, 70, 33, 35, 20, 2, 3, (2, 2), (0, 1)), rect(37, 51, 45, 29, 77, 3, 5, (1, 1), (1, 2)),
+        rect(85, 120, 23, 22, 36, 5, 3, (1, 1), (0, 2)), rect(61, 56, 29, 26, 17, 3, 5, (2, 1), (1, 0))]
+
+
+@pytest.mark.parametrize("s", RECT, ids=str)
+def test_halo_rows_and_columns_differ(s):
+    _, w, dy = inputs(s, seed=54)
+    ref = run_oracle(s, D, w=w, dy=dy)
+    for parts in (None, [1, s.N - 1]):
+        assert rel_l2(_run(s, w, dy, parts), ref) <= 1e-6
+
+
+@pytest.mark.parametrize("det", (0, 1))
+@pytest.mark.parametrize("s", [SHAPES[0], SHAPES[9], SHAPES[12], RECT[2]], ids=str)
+def test_halo_gives_the_same_bits_in_every_run(s, det):
+    """Also with a part of the tiles recomputed (one image holds a value below bf16's range)."""
+    _, w, dy = inputs(s, seed=55)
+    dy[0, 1, 1, 1] = 0xFFFFFF * 2.0 ** -143
+    prev = ucd.ucd_set_deterministic(det)
+    try:
+        runs = [_run(s, w, dy) for _ in range(3)]
+    finally:
+        ucd.ucd_set_deterministic(prev)
+    assert all(np.array_equal(runs[0], r) for r in runs[1:])
 
 
 @pytest.mark.parametrize("s", [SHAPES[1], SHAPES[3], SHAPES[9], SHAPES[13]], ids=_id)

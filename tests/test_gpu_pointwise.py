@@ -1,12 +1,13 @@
 """pointwise_kernel, pointwise_split_stream_kernel, pointwise_bf16_kernel and pointwise_stream_kernel (1x1 layers that keep their input in LDS): edges of its tiles of 128 x 128, of its pairs of 16-channel
-steps and of the last round of workgroups, images of a multiple of four pixels and not, values out of range."""
+steps and of the last round of workgroups, images of a multiple of four pixels and not, values out of range, equal bits in every
+run, tensors on any element."""
 import numpy as np
 import pytest
 
 from paper_1804_04806_amd import ucd
 from paper_1804_04806_amd.synth import Shape
 from hip_helpers import inputs, rel_l2, run_hip, run_oracle
-from test_gpu_bf16 import bf16_inputs, check_bf16_output, run_hip_bf16
+from test_gpu_bf16 import bf16_inputs, check_bf16_output, dev_bf16, run_hip_bf16
 
 pytestmark = pytest.mark.gpu
 
@@ -44,6 +45,34 @@ def test_pointwise_edges(case, op):
     ref = run_oracle(s, op, x=x, w=w, dy=dy)
     for parts in (None, [1, s.N - 1] if s.N > 1 else None):
         assert rel_l2(_run(s, op, x, w, dy, parts), ref) <= 1e-6
+
+
+# BackwardData takes the streaming kernel for any number of input channels: one chain per sum
+@pytest.mark.parametrize("case", [(33, 28, 28, 512, 128), (42, 22, 22, 1000, 130), (33, 28, 28, 1500, 97), (64, 14, 14, 2048, 256),
+                                  (27, 31, 30, 4090, 100)], ids=str)
+def test_pointwise_long_reductions(case):
+    """A sum is rounded once per 16 channels: at 4090 of them a random walk of 256 steps at 2^-25 of the sums, 5e-7 of the
+    result; the fp32 instructions, which round once per two, 1.5e-6."""
+    s = _layer(*case, D)
+    assert _fp32_kernel(s, D) == "pointwise_split_stream_kernel"
+    _, w, dy = inputs(s, seed=68)
+    assert rel_l2(_run(s, D, None, w, dy), run_oracle(s, D, w=w, dy=dy)) <= 1e-6
+
+
+@pytest.mark.parametrize("det", (0, 1))
+@pytest.mark.parametrize("op", (F, D))
+@pytest.mark.parametrize("case", [CASES[4], CASES[9], STREAM32[1], STREAM32[3]], ids=str)
+def test_pointwise_gives_the_same_bits_in_every_run(case, op, det):
+    """Also with a part of the tiles recomputed (one image holds a value below bf16's range)."""
+    s = _layer(*case, op)
+    x, w, dy = inputs(s, seed=69)
+    (x if op == F else dy)[0, 1, 1, 1] = 0xFFFFFF * 2.0 ** -143
+    prev = ucd.ucd_set_deterministic(det)
+    try:
+        runs = [_run(s, op, x, w, dy) for _ in range(3)]
+    finally:
+        ucd.ucd_set_deterministic(prev)
+    assert all(np.array_equal(runs[0], r) for r in runs[1:])
 
 
 @pytest.mark.parametrize("op", (F, D))
@@ -172,3 +201,48 @@ def test_pointwise_bf16_not_finite(case, op):
     hit = np.zeros(got.shape, bool)
     hit[3, :, 7, 9] = hit[-1, :, -1, -1] = hit[:, 17] = True
     assert not np.isfinite(got[hit]).any() and np.array_equal(got[~hit], clean[~hit])
+
+
+@pytest.mark.parametrize("det", (0, 1))
+@pytest.mark.parametrize("op", (F, D))
+@pytest.mark.parametrize("case", [HALF[1], HALF[9], STREAM[1], STREAM[10]], ids=str)
+def test_pointwise_bf16_gives_the_same_bits_in_every_run(case, op, det):
+    s = _layer(*case[:5], op)
+    bits, _ = bf16_inputs(s, seed=67)
+    prev = ucd.ucd_set_deterministic(det)
+    try:
+        runs = [run_hip_bf16(s, op, [(I, s.N)], bits) for _ in range(3)]
+    finally:
+        ucd.ucd_set_deterministic(prev)
+    assert all(np.array_equal(runs[0], r) for r in runs[1:])
+
+
+@pytest.mark.parametrize("op", (F, D))
+@pytest.mark.parametrize("dtype,case", [(1, HALF[0]), (1, HALF[1]), (1, HALF[6]), (1, HALF[10]), (1, STREAM[1]), (1, STREAM[2]), (1, STREAM[5]),
+                                        (1, STREAM[10]), (0, CASES[0]), (0, CASES[2]), (0, CASES[5]), (0, STREAM32[0]), (0, STREAM32[4])], ids=str)
+def test_pointwise_tensors_on_any_element(case, op, dtype):
+    """Tensors have to be aligned to their element size only: inputs, filter and output one element behind an aligned
+    address give the bits of aligned ones, and the elements before and behind the output stay."""
+    import torch
+    s = _layer(*case[:5], op)
+    kind = torch.bfloat16 if dtype else torch.float32
+    if dtype:
+        bits, _ = bf16_inputs(s, seed=68)
+        ref = run_hip_bf16(s, op, [(I, s.N)], bits)
+    else:
+        bits = inputs(s, seed=68)
+        ref = _run(s, op, *bits)
+
+    def shifted(b):
+        t = torch.full((b.size + 64,), 3.0, dtype=kind, device="cuda:0")
+        t[1:1 + b.size] = (dev_bf16(b) if dtype else torch.from_numpy(b).to("cuda:0")).flatten()
+        return t
+
+    a, w = shifted(bits[0 if op == F else 2]), shifted(bits[1])
+    out = torch.full((ref.size + 64,), 3.0, dtype=kind, device="cuda:0")
+    plan = ucd.ucd_plan_fixed(ucd.layer(s, dtype=dtype), op, [(I, s.N)])
+    run = ucd.ucd_conv_fwd if op == F else ucd.ucd_conv_bwd_data
+    run(plan, a[1:], w[1:], out[1:], None, 0)
+    got = out.float().cpu().numpy()
+    assert np.array_equal(got[1:1 + ref.size], ref.ravel())
+    assert got[0] == 3.0 and (got[1 + ref.size:] == 3.0).all()

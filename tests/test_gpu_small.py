@@ -5,7 +5,7 @@ import pytest
 
 from paper_1804_04806_amd import ucd
 from paper_1804_04806_amd.synth import Shape
-from hip_helpers import inputs, rel_l2, run_hip, run_oracle
+from hip_helpers import desc_of, inputs, rect, rel_l2, run_hip, run_oracle
 from test_gpu_bf16 import bf16_inputs, check_bf16_output, run_hip_bf16
 
 pytestmark = pytest.mark.gpu
@@ -29,7 +29,7 @@ SHAPES = [
 
 
 def _kernel(s, op, dtype=0):
-    return ucd.ucd_describe_micro(ucd.layer(s, dtype=dtype), op, I, s.N)[0]
+    return ucd.ucd_describe_micro(desc_of(s, dtype), op, I, s.N)[0]
 
 
 @pytest.mark.parametrize("s,f32,bf16", SHAPES, ids=lambda v: str(v) if isinstance(v, Shape) else "")
@@ -55,6 +55,28 @@ def test_small_layers(s, f32, bf16):
                 assert rel_l2(got, ref) <= 1e-6
             else:
                 check_bf16_output(got, ref, ucd.OP_NAMES[op])
+
+
+RECT = [rect(2, 12, 13, 11, 34, 3, 3, (1, 2), (1, 0)), rect(2, 10, 12, 15, 20, 3, 3, (2, 1), (0, 2)),
+        rect(1, 8, 19, 17, 24, 5, 3, (3, 2), (2, 1)), rect(1, 6, 18, 21, 20, 3, 5, (1, 4), (0, 3)),
+        rect(3, 5, 14, 13, 17, 2, 3, (4, 4), (1, 0)), rect(1, 4, 22, 19, 24, 7, 5, (2, 3), (3, 0)),
+        rect(2, 9, 10, 11, 33, 1, 3, (1, 2), (0, 1)), rect(1, 10, 13, 16, 36, 7, 6, (1, 2), (1, 2))]
+
+
+@pytest.mark.parametrize("s", RECT, ids=str)
+def test_small_layers_rows_and_columns_differ(s):
+    x, w, dy = inputs(s, seed=45)
+    for op in (F, D, W):
+        assert "gemm_kernel_small" in _kernel(s, op)
+        assert rel_l2(run_hip(s, op, [(I, s.N)], x=x, w=w, dy=dy), run_oracle(s, op, x=x, w=w, dy=dy)) <= 1e-6, op
+    bits, (x, w, dy) = bf16_inputs(s, seed=46)
+    for op in (D, W):
+        assert "gemm_kernel_small" in _kernel(s, op, 1)
+        got, ref = run_hip_bf16(s, op, [(I, s.N)], bits), run_oracle(s, op, x=x, w=w, dy=dy)
+        if op == W:
+            assert rel_l2(got, ref) <= 1e-6
+        else:
+            check_bf16_output(got, ref, ucd.OP_NAMES[op])
 
 
 def test_values_behind_a_filter_row_do_not_reach_it():
