@@ -248,7 +248,9 @@ void ucd_bench_clear(void);
  * ucd_bench_save writes every cached timing to a text file; ucd_bench_load merges a file into
  * the cache (*n_loaded, may be NULL, receives the number of timings read) and refuses, with
  * UCD_E_UNSUPPORTED, a file taken on a different device than the current one (a process without
- * a GPU accepts any file).  ucd_bench_put injects one timing by hand.  Host only. */
+ * a GPU accepts any file).  Timings of a file that another version of the library wrote (other
+ * kernels) serve ucd_plan_cached; ucd_plan and ucd_plan_wd, which have the device at hand, take them
+ * again.  ucd_bench_put injects one timing by hand.  Host only. */
 int ucd_bench_save(const char *path);
 int ucd_bench_load(const char *path, int *n_loaded);
 int ucd_bench_put(const ucd_layer_t *layer, int op, int algo, int b, uint64_t t_ns);

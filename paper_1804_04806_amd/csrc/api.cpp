@@ -225,8 +225,15 @@ int run_plan(const ucd_plan_t *plan, int op, const void *a_, const void *bsrc_, 
 
 // ---- benchmark cache ------------------------------------------------------------------------
 typedef std::tuple<int, int, int, int, int, int, int, int, int, int, int, int, int, int> BenchKey;
-std::map<BenchKey, uint64_t> g_cache;
+// A timing from a file that another version of the library wrote was taken with other kernels: planning from the cache alone
+// uses it, planning on the device takes it again.
+struct Timing {
+    uint64_t ns;
+    bool stale;
+};
+std::map<BenchKey, Timing> g_cache;
 std::mutex g_cache_mu;
+constexpr int kVersion = 102;   // goes up with every change of the kernels' times
 
 BenchKey key_of(const ucd_layer_t *L, int op, int algo, int b)
 {
@@ -235,19 +242,21 @@ BenchKey key_of(const ucd_layer_t *L, int op, int algo, int b)
                     L->dtype + (g_deterministic.load() != 0 ? 16 : 0), op, algo, b);
 }
 
-bool cache_get(const BenchKey &k, uint64_t &t)
+bool cache_get(const BenchKey &k, uint64_t &t, bool stale_too = true)
 {
     std::lock_guard<std::mutex> g(g_cache_mu);
     auto it = g_cache.find(k);
-    if (it == g_cache.end()) return false;
-    t = it->second;
+    if (it == g_cache.end() || (it->second.stale && !stale_too)) return false;
+    t = it->second.ns;
     return true;
 }
 
-void cache_put(const BenchKey &k, uint64_t t)
+void cache_put(const BenchKey &k, uint64_t t, bool stale = false)
 {
     std::lock_guard<std::mutex> g(g_cache_mu);
-    g_cache[k] = t;
+    auto it = g_cache.find(k);
+    if (stale && it != g_cache.end() && !it->second.stale) return;
+    g_cache[k] = Timing{t, stale};
 }
 
 struct Events {
@@ -324,7 +333,7 @@ int bench_kernel(const ucd_layer_t *L, int op, size_t limit, int policy, void *x
             if (need > limit) continue;
             const BenchKey k = key_of(L, op, a, b);
             uint64_t ns;
-            if (!cache_get(k, ns)) {
+            if (!cache_get(k, ns, false)) {
                 if (!spun) {
                     // A GPU that has sat idle (while the host prepared tensors, say) runs its first
                     // kernels at a low clock: timings taken then came out 5-15 % too long, and since
@@ -442,7 +451,7 @@ const char *ucd_strerror(int status)
     }
 }
 
-int ucd_version(void) { return 101; }
+int ucd_version(void) { return kVersion; }
 
 int ucd_set_deterministic(int on)
 {
@@ -695,7 +704,8 @@ int ucd_bench_put(const ucd_layer_t *layer, int op, int algo, int b, uint64_t t_
     });
 }
 
-// File format: one header line "ucd-bench 1 <device>", then one line of 15 integers per timing:
+// File format: one header line "ucd-bench 1 <device> [library version]" (the version where every timing is this library's),
+// then one line of 15 integers per timing:
 // C H W K R S stride_h stride_w pad_h pad_w dtype op algo b ns.
 static std::string device_tag()
 {
@@ -717,14 +727,16 @@ int ucd_bench_save(const char *path)
         if (!path) return UCD_E_NULLPTR;
         FILE *f = std::fopen(path, "w");
         if (!f) return UCD_E_INVALID;
-        std::fprintf(f, "ucd-bench 1 %s\n", device_tag().c_str());
         std::lock_guard<std::mutex> g(g_cache_mu);
+        bool stale = false;
+        for (const auto &kv : g_cache) stale = stale || kv.second.stale;
+        std::fprintf(f, "ucd-bench 1 %s%s\n", device_tag().c_str(), stale ? "" : (" " + std::to_string(kVersion)).c_str());
         for (const auto &kv : g_cache) {
             const BenchKey &k = kv.first;
             std::fprintf(f, "%d %d %d %d %d %d %d %d %d %d %d %d %d %d %llu\n", std::get<0>(k), std::get<1>(k),
                          std::get<2>(k), std::get<3>(k), std::get<4>(k), std::get<5>(k), std::get<6>(k), std::get<7>(k),
                          std::get<8>(k), std::get<9>(k), std::get<10>(k), std::get<11>(k), std::get<12>(k), std::get<13>(k),
-                         (unsigned long long)kv.second);
+                         (unsigned long long)kv.second.ns);
         }
         const bool ok = std::fclose(f) == 0;
         return ok ? UCD_OK : UCD_E_INVALID;
@@ -737,9 +749,10 @@ int ucd_bench_load(const char *path, int *n_loaded)
         if (!path) return UCD_E_NULLPTR;
         FILE *f = std::fopen(path, "r");
         if (!f) return UCD_E_INVALID;
-        char magic[32] = {0}, dev[128] = {0};
-        int ver = 0;
-        if (std::fscanf(f, "%31s %d %127s", magic, &ver, dev) != 3 || std::strcmp(magic, "ucd-bench") != 0 || ver != 1) {
+        char line[256] = {0}, magic[32] = {0}, dev[128] = {0};
+        int ver = 0, library = 0;
+        if (!std::fgets(line, sizeof(line), f) || std::sscanf(line, "%31s %d %127s %d", magic, &ver, dev, &library) < 3 ||
+            std::strcmp(magic, "ucd-bench") != 0 || ver != 1) {
             std::fclose(f);
             return UCD_E_INVALID;
         }
@@ -765,7 +778,7 @@ int ucd_bench_load(const char *path, int *n_loaded)
                             (uint64_t)ns});
         }
         std::fclose(f);
-        for (const auto &r : rows) cache_put(r.first, r.second);
+        for (const auto &r : rows) cache_put(r.first, r.second, library != kVersion);
         if (n_loaded) *n_loaded = (int)rows.size();
         return UCD_OK;
     });

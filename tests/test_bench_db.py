@@ -78,3 +78,31 @@ def test_put_validation():
     for args in ((ucd.FWD, ucd.N_ALGO, 1, 10), (5, 0, 1, 10), (ucd.FWD, 0, 0, 10), (ucd.FWD, 0, 1, 0)):
         with pytest.raises(ucd.UcdError):
             ucd.ucd_bench_put(L, *args)
+
+
+def test_timings_of_another_library_version_are_marked_as_such(tmp_path):
+    """They serve planning from the cache, do not displace timings of this version, and a file that holds any does not
+    claim to be of this version."""
+    L = ucd.layer(N=4, C=8, H=9, W=9, K=8, R=3, S=3)
+    path = tmp_path / "bench.txt"
+
+    def header():
+        return path.read_text().splitlines()[0].split()
+
+    ucd.ucd_bench_clear()
+    t = fill(L, ucd.FWD, 4, 5)
+    ucd.ucd_bench_save(path)
+    assert header()[:2] == ["ucd-bench", "1"] and header()[3] == str(ucd.ucd_version())
+    device = header()[2]
+    rows = path.read_text().splitlines()[1:]
+    for other in ([], ["101"]):
+        path.write_text(" ".join(["ucd-bench", "1", device] + other) + "\n" + "\n".join(rows) + "\n")
+        ucd.ucd_bench_clear()
+        assert ucd.ucd_bench_load(path) == len(rows) and ucd.ucd_bench_table(L, ucd.FWD, 4)[0] == t
+        ucd.ucd_plan_cached(L, ucd.FWD, 1 << 20, ucd.POLICY_ALL)
+        ucd.ucd_bench_put(L, ucd.FWD, ucd.ALGO_IMPLICIT, 2, 77)
+        ucd.ucd_bench_load(path)
+        assert ucd.ucd_bench_table(L, ucd.FWD, 4)[0][ucd.ALGO_IMPLICIT][2] == 77
+        ucd.ucd_bench_save(path)
+        assert len(header()) == 3
+    ucd.ucd_bench_clear()

@@ -194,6 +194,27 @@ def test_benchmark_db_roundtrip_on_device(tmp_path):
     torch.cuda.synchronize()
 
 
+def test_planning_on_the_device_takes_timings_of_another_library_version_again(tmp_path):
+    import torch
+    s = Shape(8, 32, 12, 12, 48, 3, 3, 1, 1, "db")
+    desc = ucd.layer(s)
+    _, (xd, wd, dyd) = device_buffers(s)
+    ws = torch.empty(4, dtype=torch.float32, device=xd.device)
+    y = torch.empty(s.y_shape, device=xd.device)
+    path = tmp_path / "bench.txt"
+    ucd.ucd_bench_clear()
+    ucd.ucd_bench_put(desc, ucd.FWD, ucd.ALGO_IMPLICIT, 8, 123456789)
+    ucd.ucd_bench_save(path)
+    header, row = path.read_text().splitlines()
+    for version, kept in ((str(ucd.ucd_version()), True), ("101", False), ("", False)):
+        path.write_text(" ".join(header.split()[:3] + [version]) + "\n" + row + "\n")
+        ucd.ucd_bench_clear()
+        assert ucd.ucd_bench_load(path) == 1
+        ucd.ucd_plan(desc, ucd.FWD, 0, ucd.POLICY_UNDIVIDED, xd, wd, y, ws)
+        assert (ucd.ucd_bench_table(desc, ucd.FWD, 8)[0][ucd.ALGO_IMPLICIT][8] == 123456789) == kept
+    ucd.ucd_bench_clear()
+
+
 def test_table_times_predict_a_configuration_run_in_sequence():
     """The benchmark step times a micro-batch the way a configuration runs it (back to back, on
     consecutive samples, after a clock spin-up), so the sum of table entries must predict the
