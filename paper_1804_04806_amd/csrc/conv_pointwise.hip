@@ -6,9 +6,13 @@
 
 namespace ucd {
 
+// Two rows of tiles, few input channels, and outputs of 200 MB and more, beyond the last-level cache: tile GEMMs / pointwise_kernel
+// 0.84 to 0.98, pointwise_split_stream_kernel alike (48 -> 160 56x56 b = 128 113 / 128 us).
+static bool thin_and_large(int K, int M, long cols) { return M > 128 && M <= 192 && K <= 48 && cols * M >= 50000000l; }
+
 // Where it is the faster one: its input channels fit LDS and are enough that the products outweigh the stores, and its
 // pixels give most CUs a workgroup.  Time of the tile GEMMs / of this kernel over 430 layers, least and mean, more than 128
-// output channels: 17 to 160 input channels and 4000 pixels or more 0.99 / 1.24 (128 -> 512 28x28 b = 128 131 / 94 us, 160 ->
+// output channels: 17 to 160 input channels and 4000 pixels or more 0.96 / 1.24 (128 -> 512 28x28 b = 128 131 / 94 us, 160 ->
 // 1024 up to 1.77), 800 to 4000 pixels 0.87 to 1.6, 16 channels 0.82 / 1.0.  Up to 128 output channels the input is used once:
 // 8000 to 20000 pixels, a single round, 1.04 / 1.36, more 0.83 to 1.28.
 bool pointwise_pays(const Dims &d, int op, int b)
@@ -17,6 +21,7 @@ bool pointwise_pays(const Dims &d, int op, int b)
     const int K = op == 0 ? d.C : d.K, M = op == 0 ? d.K : d.C;
     const long cols = (long)b * d.H * d.W;
     if (K <= 16 || K > PointwiseTile::kMaxK || (long)d.H * d.W > 1l << 22) return false;   // (rows of a tile below 2^31 bytes apart)
+    if (thin_and_large(K, M, cols)) return false;
     return M > 128 ? cols >= 4000 : M > 64 && cols >= 8000 && cols <= 20000;
 }
 
@@ -26,14 +31,18 @@ bool pointwise_pays(const Dims &d, int op, int b)
 // input channels, where tile GEMMs that split their last tiles' sums are more exact by up to 6 % (352 -> 256 14x14 b = 256).
 // BackwardData, whose tile GEMMs run on the fp32 pipe, 1.04 to 2.0 from 96 workgroups and 65 output channels on (512 -> 128
 // 28x28 b = 128 142 / 94 us; 97 beyond 1024 input channels, 0.93 below).  32 input channels and fewer 0.75 to 1.3.
+// BackwardData of up to 96 output channels from more than 256, the second round of workgroups less than a quarter full: 0.91 to
+// 0.99 (otherwise 1.0 to 1.6).
 bool pointwise_stream_pays(const Dims &d, int op, int b)
 {
     if (d.dtype != 0 || d.R * d.S != 1 || d.sh != 1 || d.sw != 1 || d.ph != 0 || d.pw != 0 || d.H * d.W % 2 != 0) return false;
     const int K = op == 0 ? d.C : d.K, M = op == 0 ? d.K : d.C;
     const long cols = (long)b * d.H * d.W;
     if ((long)d.H * d.W > 1l << 22) return false;
-    if (K <= 32 || pointwise_pays(d, op, b)) return false;
+    if (K <= 32 || pointwise_pays(d, op, b) || thin_and_large(K, M, cols)) return false;
     const long groups = (cols + 255) / 256 * ((M + 127) / 128);
+    const long cus = device_cus();
+    if (op == 1 && M <= 96 && K > 256 && groups > cus && 4 * groups < 5 * cus) return false;
     return op == 0 ? M > 96 && K <= 256 && groups >= 128 : M > (K <= 1024 ? 64 : 96) && groups >= 96;
 }
 
@@ -44,6 +53,23 @@ constexpr long kWideCols = 20000;   // below, tiles of 256 pixels leave most CUs
 constexpr int kStreamGroups = 128;  // half the chip
 
 static long stream_groups(int M, long cols) { return (cols + 255) / 256 * ((M + 127) / 128); }
+
+// Up to 64 output channels half or more of a streaming workgroup's rows are padding: a round of workgroups (one per CU) costs
+// it what the tile GEMMs take for about 0.7 to 1 rounds of pixels, so that both its number of rounds and how full the last one
+// is decide.  Tile GEMMs / stream over 2100 layers of 16000 to 800000 pixels, least and mean:
+//   Forward, up to 32 channels from up to 32 0.97 / 1.14, up to 64 from up to 128 0.97 / 1.22 in any number of rounds
+//   others: one round 1.0 / 1.25 (up to 32 from up to 256, up to 64 from up to 512), two rounds, the second more than half full (from
+//   up to 128 a third) 0.97 / 1.05, otherwise 0.66 / 0.87 (256 -> 32 28x28 b = 84: 11.2 / 16.1 us)
+//   BackwardData: up to two rounds 0.95 / 1.2; more, up to 32 channels 0.73 / 0.88, up to 64 from up to 320 0.84 / 0.96, from
+//   more 0.94 / 1.05
+static bool stream_few_rows_pays(int op, int M, int K, long cols)
+{
+    const double rounds = (double)((cols + 255) / 256) / device_cus();
+    if (op == 1) return rounds <= 2 ? K > 128 || rounds <= 1 || rounds > 1.5 || M > 32 : M > 32 && K > 320;
+    if (K <= (M <= 32 ? 32 : 128)) return true;
+    if (K > (M <= 32 ? 256 : 512)) return false;
+    return rounds <= 1 || (rounds <= 2 && rounds > (K <= 128 ? 1.3 : 1.5));
+}
 
 static Bf16Route bf16_route(const Dims &d, int op, int b)
 {
@@ -56,9 +82,10 @@ static Bf16Route bf16_route(const Dims &d, int op, int b)
     // channels, 1.05 to 1.5 up to there; BackwardData 0.8 to 1.1 up to 64 input channels, 1.05 to 1.7 above
     if (M <= 16) return Bf16Route::kTiles;
     if (M <= 32) {
-        const bool pays = op == 0 ? many && K <= 256 : (many && K > 64) || (K > 256 && cols >= 3000);
-        return pays ? Bf16Route::kStream : Bf16Route::kTiles;
+        const bool pays = op == 0 ? many : (many && K > 64) || (K > 256 && cols >= 3000);
+        return pays && stream_few_rows_pays(op, M, K, cols) ? Bf16Route::kStream : Bf16Route::kTiles;
     }
+    if (M <= 64 && many && !stream_few_rows_pays(op, M, K, cols)) return Bf16Route::kTiles;
     if (op == 1 && M <= 64 && K <= (many ? 16 : 32)) return Bf16Route::kTiles;   // 0.85 to 1.2
     // beyond LDS: 128 -> 64 us for 2048 -> 256 28x28 b = 64 in BackwardData, whose tile GEMMs gather the filter; Forward 0.75 to
     // 0.95 with less than half a chip of workgroups or up to 96 output channels, otherwise 1.02 to 1.7 (1024 -> 256 14x14

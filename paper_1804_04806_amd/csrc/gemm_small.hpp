@@ -6,7 +6,8 @@
 // each), or split it over workgroups that add into an output which another launch has to clear first.  Here a tile is one
 // MFMA of 16x16, so that the chip gets a workgroup per CU, and the waves of a workgroup divide the reduction: each
 // loads its operands straight from memory into MFMA order, two batches of kBatch steps in flight, with no barrier until the
-// partial sums meet in LDS, in a fixed order.  No atomics, no zero fill, one launch (all stride phases of a BackwardData).
+// partial sums meet in LDS, in a fixed order.  Forward and BackwardData (all stride phases) are one launch without atomics or
+// a zero fill; a BackwardFilter of 512 reduction rows and more adds chunks of its sums to a cleared dw with atomics.
 //
 // Addresses.  An element's offset is a part that depends on the tile position (one register per lane) plus one that
 // depends on the reduction row; the latter, and which taps it stands for, are computed once per workgroup into an LDS

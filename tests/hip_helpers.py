@@ -146,3 +146,27 @@ def run_oracle(s, op, x=None, w=None, dy=None, beta=0.0, dw0=None):
 
 def inputs(s, seed=0, idx=0):
     return synth.make_x(s, seed, idx), synth.make_w(s, seed, idx), synth.make_dy(s, seed, idx)
+
+
+def recomputed_time_ratio(s, op):
+    """Time of an implicit-GEMM launch whose filter lies below bf16's range, so that every tile is computed a second time on
+    the fp32 instructions, over its ordinary time (best of six runs of five launches)."""
+    import torch
+    plan = ucd.ucd_plan_fixed(desc_of(s), op, [(ucd.ALGO_IMPLICIT, s.N)])
+    t, w = (torch.randn(shape, device="cuda:0") for shape in (s.x_shape if op == ucd.FWD else s.y_shape, s.w_shape))
+    out = torch.empty(s.y_shape if op == ucd.FWD else s.x_shape, device="cuda:0")
+    run = ucd.ucd_conv_fwd if op == ucd.FWD else ucd.ucd_conv_bwd_data
+    ms = []
+    for scale in (1.0, 2.0 ** -120):
+        w *= scale
+        best = float("inf")
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(5):
+                run(plan, t, w, out, None, 0)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b))
+        ms.append(best)
+    return ms[1] / ms[0]

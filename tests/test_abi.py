@@ -274,3 +274,18 @@ def test_descriptions_name_kernels_of_the_sources():
     assert seen <= kernels, seen - kernels
     assert seen >= {"conv_halo_kernel", "gemm_kernel_small", "pointwise_kernel", "pointwise_split_stream_kernel",
                     "pointwise_bf16_kernel", "pointwise_stream_kernel"}, seen
+
+
+def test_bf16_1x1_layers_of_few_output_channels_by_rounds_of_workgroups():
+    """The streaming kernel's tiles are mostly padding there: layers with one more round of few workgroups, or many rounds,
+    run on the tile GEMMs."""
+    def stream(op, n, few, many):
+        L = ucd.layer(N=n, C=many if op == ucd.FWD else few, H=28, W=28, K=few if op == ucd.FWD else many, R=1, S=1, dtype=1)
+        return "pointwise_stream_kernel" in ucd.ucd_describe_micro(L, op, ucd.ALGO_IMPLICIT, n)[0]
+    # 65536 pixels are a round: b = 83 fills the first, 84 begins the second, 160 fills most of it, 168 begins the third
+    assert [stream(ucd.FWD, n, 32, 256) for n in (50, 83, 84, 110, 160, 168, 336)] == [True, True, False, False, True, False, False]
+    assert [stream(ucd.FWD, n, 32, 128) for n in (83, 84, 110, 168)] == [True, False, True, False]
+    assert [stream(ucd.FWD, n, 64, 512) for n in (83, 84, 160, 168)] == [True, False, True, False]
+    assert all(stream(ucd.FWD, n, 64, 128) for n in (83, 84, 168, 336)) and all(stream(ucd.FWD, n, 32, 32) for n in (83, 84, 336))
+    assert [stream(ucd.BWD_DATA, n, 32, 256) for n in (83, 84, 160, 168)] == [True, True, True, False]
+    assert [stream(ucd.BWD_DATA, n, 64, 256) for n in (84, 168)] == [True, False] and stream(ucd.BWD_DATA, 168, 64, 640)

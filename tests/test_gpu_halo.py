@@ -6,7 +6,7 @@ import pytest
 
 from paper_1804_04806_amd import ucd
 from paper_1804_04806_amd.synth import Shape
-from hip_helpers import desc_of, inputs, rect, rel_l2, run_hip, run_oracle
+from hip_helpers import desc_of, inputs, recomputed_time_ratio, rect, rel_l2, run_hip, run_oracle
 
 pytestmark = pytest.mark.gpu
 
@@ -93,3 +93,10 @@ def test_halo_range(s, scale, partner):
     for a, b in ((scale, partner), (partner, scale)):
         ws, dys = w * np.float32(a), dy * np.float32(b)
         assert rel_l2(_run(s, ws, dys), run_oracle(s, D, w=ws, dy=dys)) <= 1e-6
+
+
+def test_halo_recomputed_tiles_are_not_far_slower():
+    """1.9 times the ordinary call (114 us against 217), 3 are the limit."""
+    s = Shape(128, 64, 56, 56, 128, 3, 3, 2, 1)
+    assert "conv_halo_kernel<" in ucd.ucd_describe_micro(ucd.layer(s), D, I, s.N)[0]
+    assert recomputed_time_ratio(s, D) <= 3
