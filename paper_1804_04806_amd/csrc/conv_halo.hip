@@ -69,8 +69,13 @@ static auto with_tile(const Dims &d, F f)
 // Where it is the faster one.  Measured over 470 layers (1 to 128 images of 7x7 to 150x150, 16 to 512 channels, filters of
 // 3x3 to 7x7), time of the implicit GEMMs otherwise taken / of this kernel, least and mean:
 //   column stride 2: 3 columns 1.6 / 2.4, 5 columns 1.4 / 2.2 (128 -> 64 3x3/2 56x56 b = 128: 224 / 124 us, 256 -> 96 5x5/2
-//   28x28 b = 64 237 / 71).  With 16 input channels three quarters of a tile's rows are padding, 0.96 and 0.8; 5 columns in
-//   fewer than 48 workgroups of more than 160 channels, which the implicit GEMM splits, 0.66 to 0.91.
+//   28x28 b = 64 237 / 71).  With 16 input channels three quarters of a tile's rows are padding, 0.96 and 0.8.  A workgroup
+//   walks over all channels of dy, which takes a launch that leaves CUs idle as long as a full one, where the implicit GEMM
+//   splits the reduction: 900 layers more, by the outputs in full workgroups' worth of them:
+//     3 columns: up to 384 channels 1.4 / 2.0; 512 from 26 workgroups on 1.0 / 1.4, 768 from 77 1.16 / 1.7, 1024 from 128 1.4 / 1.9,
+//     2048 from 150 1.35 / 1.8; with fewer 0.25 to 0.96 (1024 -> 256 14x14 b = 1: 83 / 167 us)
+//     5 columns: up to 160 channels 1.5 / 1.9; 256 from 48 on 1.07 / 1.8, 384 from 64 and 512 from 85 1.3 / 2.0, 768 from 96
+//     1.36 / 2.0; with fewer 0.48 to 1.2
 //   column stride 1, by filled part of the last round of workgroups times useful part of a tile's rows: from 0.5 on 1.29 /
 //   1.6 (384 -> 384 3x3 13x13 b = 256: 923 / 512; as the Winograd kernel 410), 0.38 1.1 to 1.4, 0.25 0.65 to 1.2
 // Filters of 7 columns: their operands and window do not fit LDS together often enough.
@@ -83,7 +88,11 @@ bool halo_pays(const Dims &d, int b)
         HaloParams p{};
         if (!halo_params<T>(d, b, p)) return false;
         const long wgs = (long)p.tiles_m * ((p.cols + T::NT - 1) / T::NT) * d.sh;
-        if (T::NPH == 2) return T::S == 3 || wgs >= 48 || d.K <= 160;
+        if (T::NPH == 2) {
+            const double full = (double)d.C * b * d.H * d.W / (T::MT * T::NT * T::NPH);
+            if (T::S == 3) return full >= (d.K > 1134 ? 150 : (d.K - 384) / 5);
+            return d.K <= 160 || full >= (d.K < 288 ? 48 : d.K > 576 ? 96 : d.K / 6);
+        }
         const long slots = (T::THREADS == 256 ? 2l : 1l) * device_cus();
         return 2.0 * wgs * d.C >= (double)((wgs + slots - 1) / slots * slots) * p.tiles_m * T::MT;
     });

@@ -30,7 +30,7 @@ bool pointwise_pays(const Dims &d, int op, int b)
 // Forward 1.1 to 1.6 above 96 output channels (fewer workgroups 0.55 to 1.0, up to 64 channels 0.6 to 1.2); not beyond 256
 // input channels, where tile GEMMs that split their last tiles' sums are more exact by up to 6 % (352 -> 256 14x14 b = 256).
 // BackwardData, whose tile GEMMs run on the fp32 pipe, 1.04 to 2.0 from 96 workgroups and 65 output channels on (512 -> 128
-// 28x28 b = 128 142 / 94 us; 97 beyond 1024 input channels, 0.93 below).  32 input channels and fewer 0.75 to 1.3.
+// 28x28 b = 128 142 / 94 us; 97 beyond 1024 input channels, 0.93 below; 128 workgroups beyond 2048, 0.90 with 98).  32 input channels and fewer 0.75 to 1.3.
 // BackwardData of up to 96 output channels from more than 256, the second round of workgroups less than a quarter full: 0.91 to
 // 0.99 (otherwise 1.0 to 1.6).
 bool pointwise_stream_pays(const Dims &d, int op, int b)
@@ -43,7 +43,7 @@ bool pointwise_stream_pays(const Dims &d, int op, int b)
     const long groups = (cols + 255) / 256 * ((M + 127) / 128);
     const long cus = device_cus();
     if (op == 1 && M <= 96 && K > 256 && groups > cus && 4 * groups < 5 * cus) return false;
-    return op == 0 ? M > 96 && K <= 256 && groups >= 128 : M > (K <= 1024 ? 64 : 96) && groups >= 96;
+    return op == 0 ? M > 96 && K <= 256 && groups >= 128 : M > (K <= 1024 ? 64 : 96) && groups >= (K <= 2048 ? 96 : 128);
 }
 
 // bf16 layers.  Times of the tile GEMMs / of these kernels over 2600 layers of 800 to 800000 pixels; "narrow" and "wide" are
