@@ -293,11 +293,14 @@ def test_bf16_1x1_layers_of_few_output_channels_by_rounds_of_workgroups():
 
 def test_strided_backward_data_of_many_channels_and_few_pixels_splits_the_reduction():
     """conv_halo_kernel walks over all channels in one workgroup: only with enough pixels to fill the chip that way."""
-    def halo(n, c, hw, k, r):
-        L = ucd.layer(N=n, C=c, H=hw, W=hw, K=k, R=r, S=r, pad_h=r // 2, pad_w=r // 2, stride_h=2, stride_w=2)
+    def halo(n, c, hw, k, r, stride_h=2):
+        L = ucd.layer(N=n, C=c, H=hw, W=hw, K=k, R=r, S=r, pad_h=r // 2, pad_w=r // 2, stride_h=stride_h, stride_w=2)
         return "conv_halo_kernel" in ucd.ucd_describe_micro(L, ucd.BWD_DATA, ucd.ALGO_IMPLICIT, n)[0]
     assert all(halo(4, 256, 14, 384, 3) == halo(n, 256, 28, k, 3) == True for n, k in ((4, 256), (8, 512), (16, 1024), (16, 2048)))
     assert not any(halo(n, 256, 14, 1024, 3) for n in (1, 2, 8)) and not any(halo(n, 512, 14, 2048, 3) for n in (1, 8, 16))
-    assert [halo(n, 128, 28, 768, 3) for n in (8, 12, 16)] == [False, False, True]
-    assert [halo(n, 96, 28, 256, 5) for n in (10, 20, 21)] == [False, False, True] and halo(4, 96, 28, 160, 5)
+    assert [halo(n, 128, 28, 768, 3) for n in (4, 8, 16)] == [False, False, True]
+    assert [halo(n, 96, 28, 512, 5) for n in (4, 24, 40)] == [False, False, True] and halo(4, 96, 28, 160, 5)
     assert [halo(n, 128, 28, 768, 5) for n in (24, 32)] == [False, True]
+    # a row stride of 1: more filter rows per workgroup, fewer launches of the other kernels
+    assert [halo(n, 128, 28, 384, 3, 1) for n in (1, 8, 24)] == [False, False, True] and halo(8, 128, 28, 64, 3, 1)
+    assert [halo(n, 96, 28, 96, 5, 1) for n in (4, 24)] == [False, True]
