@@ -32,7 +32,8 @@ bool pointwise_pays(const Dims &d, int op, int b)
 // BackwardData, whose tile GEMMs run on the fp32 pipe, 1.04 to 2.0 from 96 workgroups and 65 output channels on (512 -> 128
 // 28x28 b = 128 142 / 94 us; 97 beyond 1024 input channels, 0.93 below; 128 workgroups beyond 2048, 0.90 with 98).  32 input channels and fewer 0.75 to 1.3.
 // BackwardData of up to 96 output channels from more than 256, the second round of workgroups less than a quarter full: 0.91 to
-// 0.99 (otherwise 1.0 to 1.6).
+// 0.99 (otherwise 1.0 to 1.6).  Both lines only where the tile GEMMs may split their last tiles' sums: in reproducible mode 1.03 to
+// 1.8 on the layers beyond them (752 -> 2328 28x28 b = 5: 267 / 150 us).
 bool pointwise_stream_pays(const Dims &d, int op, int b)
 {
     if (d.dtype != 0 || d.R * d.S != 1 || d.sh != 1 || d.sw != 1 || d.ph != 0 || d.pw != 0 || d.H * d.W % 2 != 0) return false;
@@ -42,8 +43,9 @@ bool pointwise_stream_pays(const Dims &d, int op, int b)
     if (K <= 32 || pointwise_pays(d, op, b) || thin_and_large(K, M, cols)) return false;
     const long groups = (cols + 255) / 256 * ((M + 127) / 128);
     const long cus = device_cus();
-    if (op == 1 && M <= 96 && K > 256 && groups > cus && 4 * groups < 5 * cus) return false;
-    return op == 0 ? M > 96 && K <= 256 && groups >= 128 : M > (K <= 1024 ? 64 : 96) && groups >= (K <= 2048 ? 96 : 128);
+    if (op == 0) return M > 96 && K <= 256 && groups >= 128;
+    if (!d.det && M <= 96 && K > 256 && groups > cus && 4 * groups < 5 * cus) return false;
+    return M > (K <= 1024 ? 64 : 96) && groups >= (K <= 2048 || d.det ? 96 : 128);
 }
 
 // bf16 layers.  Times of the tile GEMMs / of these kernels over 2600 layers of 800 to 800000 pixels; "narrow" and "wide" are

@@ -304,3 +304,18 @@ def test_strided_backward_data_of_many_channels_and_few_pixels_splits_the_reduct
     # a row stride of 1: more filter rows per workgroup, fewer launches of the other kernels
     assert [halo(n, 128, 28, 384, 3, 1) for n in (1, 8, 24)] == [False, False, True] and halo(8, 128, 28, 64, 3, 1)
     assert [halo(n, 96, 28, 96, 5, 1) for n in (4, 24)] == [False, True]
+
+
+def test_reproducible_mode_keeps_layers_whose_reduction_the_other_kernels_would_split():
+    """1x1 BackwardData: the implicit GEMMs are the faster ones there only where they may split a sum."""
+    deep = ucd.layer(N=18, C=224, H=28, W=28, K=2344, R=1, S=1)
+    second_round = ucd.layer(N=201, C=80, H=20, W=20, K=1016, R=1, S=1)
+    prev = ucd.ucd_set_deterministic(0)
+    try:
+        for det in (0, 1):
+            ucd.ucd_set_deterministic(det)
+            for layer, kernel in ((deep, "pointwise_split_stream_kernel<"), (second_round, "pointwise_split_stream_kernel<")):
+                text, _ = ucd.ucd_describe_micro(layer, ucd.BWD_DATA, ucd.ALGO_IMPLICIT, layer.N)
+                assert (kernel in text) == bool(det), (det, text)
+    finally:
+        ucd.ucd_set_deterministic(prev)
