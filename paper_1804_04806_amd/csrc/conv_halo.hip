@@ -1,4 +1,6 @@
 // Launch of conv_halo_kernel: BackwardData of fp32 layers.
+#include <cmath>
+
 #include "conv_halo.hpp"
 #include "gemm_launch.hpp"
 #include "implicit_common.hpp"
@@ -67,26 +69,26 @@ static auto with_tile(const Dims &d, F f)
     return d.S == 3 ? f(Strided<3, 0>{}) : f(Strided<5, 0>{});
 }
 // Column stride 2: a workgroup walks over all channels of dy and all filter rows of its phase, which takes a launch that leaves
-// CUs idle as long as a full one; the implicit GEMMs split their reductions there.  Times in us as measured: of a round of
-// workgroups, by channels and filter rows; of the implicit GEMMs, a launch per phase with chunks of 512 to 1023 rows
-// and the layer's operations at 74 (3 columns) and 95 TFLOP/s.  From 150 workgroups' worth of outputs on they take longer whatever the layer.
-static bool strided_pays(const Dims &d, int b, int tile_outputs)
+// CUs idle as long as a full one; the implicit GEMMs split their reductions there, but not in reproducible mode nor with merged
+// phases.  Time in us as measured over the layers of implicit_bwd_data_us (model / measured 0.71 to 1.31, 0.82 to 1.17 in 98 of
+// 100): two workgroups share a CU with 3 columns, one at a time has it with 5.  Where the two are within a tenth of each other
+// this kernel, which adds no parts of a sum by atomics.
+static bool strided_pays(const Dims &d, int b, long wgs)
 {
     const int rows = (d.R + d.sh - 1) / d.sh;
-    const double here = 3 + d.K * (d.S == 3 ? 0.07 * rows + 0.028 : 0.155 * rows);
-    const double outputs = (double)d.C * b * d.H * d.W;
-    const long reduction = (long)d.K * rows * ((d.S + 1) / 2), chunks = reduction < 512 ? 1 : reduction / 512;
-    const double implicit = 0.039 * (double)(reduction / chunks) * d.sh * d.sw +
-                            (d.S == 3 ? 2.7e-8 : 2.1e-8) * outputs * d.K * d.R * d.S / (d.sh * d.sw);
-    return outputs >= 150.0 * tile_outputs || here <= implicit;
+    const double cus = (double)wgs / device_cus(), more = (d.S == 3 ? cus : std::ceil(cus)) - 1;
+    const double here = d.S == 3 ? 8.2 + d.K * (0.067 * rows + 0.031) * (1 + 0.92 * (more > 0 ? more : 0))
+                                 : 12.4 + d.K * (0.14 * rows + 0.032) * (1 + 1.04 * (more > 0 ? more : 0));
+    return here <= 1.1 * implicit_bwd_data_us(d, b);
 }
 
 // Where it is the faster one.  Measured over 470 layers (1 to 128 images of 7x7 to 150x150, 16 to 512 channels, filters of
 // 3x3 to 7x7), time of the implicit GEMMs otherwise taken / of this kernel, least and mean:
 //   column stride 2: 3 columns 1.6 / 2.4, 5 columns 1.4 / 2.2 (128 -> 64 3x3/2 56x56 b = 128: 224 / 124 us, 256 -> 96 5x5/2
-//   28x28 b = 64 237 / 71).  With 16 input channels three quarters of a tile's rows are padding, 0.96 and 0.8.  Over 3000
-//   layers of 1 to 256 images, 64 to 2048 channels and strides of 1 to 4 rows, on the line that strided_pays draws, 0.89 / 2.1;
-//   without it 0.25 (2048 -> 64 3x3/2 14x14 b = 4: 87 / 344 us)
+//   28x28 b = 64 237 / 71).  With 16 input channels three quarters of a tile's rows are padding, 0.96 and 0.8.  Over 1041 more
+//   layers of 1 to 256 images, 17 to 1024 -> 16 to 2048 channels and strides of 1 to 4 rows, where strided_pays is true (815) 0.75 /
+//   2.4, four below 0.9 (reproducible mode 934, 0.84 / 2.7); where it is false this kernel / the others 0.69 / 1.3 (eleven
+//   below 0.9), 6.9 at most (31 -> 1574 3x3 13x19 stride (1, 2) b = 8: 374 / 54 us)
 //   column stride 1, by filled part of the last round of workgroups times useful part of a tile's rows: from 0.5 on 1.29 /
 //   1.6 (384 -> 384 3x3 13x13 b = 256: 923 / 512; as the Winograd kernel 410), 0.38 1.1 to 1.4, 0.25 0.65 to 1.2
 // Filters of 7 columns: their operands and window do not fit LDS together often enough.
@@ -99,7 +101,7 @@ bool halo_pays(const Dims &d, int b)
         HaloParams p{};
         if (!halo_params<T>(d, b, p)) return false;
         const long wgs = (long)p.tiles_m * ((p.cols + T::NT - 1) / T::NT) * d.sh;
-        if (T::NPH == 2) return strided_pays(d, b, T::MT * T::NT * T::NPH);
+        if (T::NPH == 2) return strided_pays(d, b, wgs);
         const long slots = (T::THREADS == 256 ? 2l : 1l) * device_cus();
         return 2.0 * wgs * d.C >= (double)((wgs + slots - 1) / slots * slots) * p.tiles_m * T::MT;
     });

@@ -103,6 +103,46 @@ static hipError_t implicit_bwd_data_bf16_vec(const Dims &d, int b, const void *d
                  : launch_gemm<L::template FilterKLane, RunNLaneMaskedBig, EpiNCHWT<bf16>, true>(pa, pb, pe, g, s);
 }
 
+static void phase_shape(const Dims &d, int a, int c, int &h0, int &w0, int &Hh, int &Ww, int &Ra, int &Sc)
+{
+    h0 = ((a - d.ph) % d.sh + d.sh) % d.sh;
+    w0 = ((c - d.pw) % d.sw + d.sw) % d.sw;
+    Hh = h0 < d.H ? (d.H - h0 + d.sh - 1) / d.sh : 0;
+    Ww = w0 < d.W ? (d.W - w0 + d.sw - 1) / d.sw : 0;
+    Ra = a < d.R ? (d.R - a + d.sh - 1) / d.sh : 0;
+    Sc = c < d.S ? (d.S - c + d.sw - 1) / d.sw : 0;
+}
+
+// Time in us of the launches below (fp32), as measured: a workgroup's reduction rows follow one another, and beyond one
+// workgroup per CU the rows of all share its matrix pipes; both go with the size of the tile.  1700 strided layers (1 to 128
+// images of 7x7 to 112x112, 17 to 1024 -> 32 to 2048 channels, 3 to 7 filter rows, 3 and 5 columns, row strides 1 to 4), both
+// modes: model / measured within a fifth in four of five (least 0.5, most 2).
+double implicit_bwd_data_us(const Dims &d, int b)
+{
+    auto launch_us = [](int M, int N, int Kd, int splits) {
+        const TilePick t = pick_tile(M, N, true, splits);
+        const double size = t.bm * t.bn / 16384., more = (double)t.blocks(M, N, splits) / device_cus() - 1;
+        return 5.9 + Kd / splits * (0.012 + size * (0.088 + 0.12 * (more > 0 ? more : 0)));
+    };
+    if (const int f = merged_phase_factor(d)) {
+        const int Hb = (d.H - 1 + d.ph) / (f * d.sh) + 1, Wb = (d.W - 1 + d.pw) / (f * d.sw) + 1;
+        const int U = (d.R + d.sh - 1) / d.sh + f - 1, V = (d.S + d.sw - 1) / d.sw + f - 1;
+        return launch_us(d.C * f * d.sh * f * d.sw, b * Hb * Wb, d.K * U * V, 1);
+    }
+    double us = 0;
+    bool any_split = false;
+    for (int a = 0; a < d.sh; ++a)
+        for (int c = 0; c < d.sw; ++c) {
+            int h0, w0, Hh, Ww, Ra, Sc;
+            phase_shape(d, a, c, h0, w0, Hh, Ww, Ra, Sc);
+            if (Hh == 0 || Ww == 0 || Ra == 0 || Sc == 0) continue;
+            const int splits = output_splits(d.C, b * Hh * Ww, d.K * Ra * Sc, !d.det);
+            any_split = any_split || splits > 1;
+            us += launch_us(d.C, b * Hh * Ww, d.K * Ra * Sc, splits);
+        }
+    return us + (any_split ? 3.5 : 0);
+}
+
 // Stride phases: input pixels h with (h + ph) % sh == a are reached only by filter rows
 // r = a, a + sh, ...; within a phase the gather is a dense stride-1 correlation with the
 // sub-sampled, index-reversed filter.  Pixels of a phase with no tap get zeros (Kd = 0).
@@ -120,19 +160,11 @@ static hipError_t implicit_bwd_data_t(const Dims &d, int b, const void *dy, cons
     if (const int f = merged_phase_factor(d)) return implicit_bwd_data_merged<E>(d, b, dy, w, dx, f, s);
     // phases whose GEMM has too few tiles split their reduction (atomics); dx is zero-filled once
     // if any phase does
-    auto phase_shape = [&](int a, int c, int &h0, int &w0, int &Hh, int &Ww, int &Ra, int &Sc) {
-        h0 = ((a - d.ph) % d.sh + d.sh) % d.sh;
-        w0 = ((c - d.pw) % d.sw + d.sw) % d.sw;
-        Hh = h0 < d.H ? (d.H - h0 + d.sh - 1) / d.sh : 0;
-        Ww = w0 < d.W ? (d.W - w0 + d.sw - 1) / d.sw : 0;
-        Ra = a < d.R ? (d.R - a + d.sh - 1) / d.sh : 0;
-        Sc = c < d.S ? (d.S - c + d.sw - 1) / d.sw : 0;
-    };
     bool any_split = false;
     for (int a = 0; a < d.sh; ++a)
         for (int c = 0; c < d.sw; ++c) {
             int h0, w0, Hh, Ww, Ra, Sc;
-            phase_shape(a, c, h0, w0, Hh, Ww, Ra, Sc);
+            phase_shape(d, a, c, h0, w0, Hh, Ww, Ra, Sc);
             if (Hh && Ww && Ra && Sc && output_splits(d.C, b * Hh * Ww, d.K * Ra * Sc, F32 && !d.det) > 1) any_split = true;
         }
     if (any_split) {
@@ -142,7 +174,7 @@ static hipError_t implicit_bwd_data_t(const Dims &d, int b, const void *dy, cons
     for (int a = 0; a < d.sh; ++a)
         for (int c = 0; c < d.sw; ++c) {
             int h0, w0, Hh, Ww, Ra, Sc;
-            phase_shape(a, c, h0, w0, Hh, Ww, Ra, Sc);
+            phase_shape(d, a, c, h0, w0, Hh, Ww, Ra, Sc);
             if (Hh == 0 || Ww == 0) continue;
             GemmShape g{d.C, b * Hh * Ww, d.K * Ra * Sc};
             if (any_split && g.Kd == 0) continue;  // dx is already zero there

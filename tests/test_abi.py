@@ -296,25 +296,33 @@ def test_strided_backward_data_of_many_channels_and_few_pixels_splits_the_reduct
     def halo(n, c, hw, k, r, stride_h=2):
         L = ucd.layer(N=n, C=c, H=hw, W=hw, K=k, R=r, S=r, pad_h=r // 2, pad_w=r // 2, stride_h=stride_h, stride_w=2)
         return "conv_halo_kernel" in ucd.ucd_describe_micro(L, ucd.BWD_DATA, ucd.ALGO_IMPLICIT, n)[0]
-    assert all(halo(4, 256, 14, 384, 3) == halo(n, 256, 28, k, 3) == True for n, k in ((4, 256), (8, 512), (16, 1024), (16, 2048)))
-    assert not any(halo(n, 256, 14, 1024, 3) for n in (1, 2, 8)) and not any(halo(n, 512, 14, 2048, 3) for n in (1, 8, 16))
-    assert [halo(n, 128, 28, 768, 3) for n in (4, 8, 16)] == [False, False, True]
-    assert [halo(n, 96, 28, 512, 5) for n in (4, 24, 40)] == [False, False, True] and halo(4, 96, 28, 160, 5)
-    assert [halo(n, 128, 28, 768, 5) for n in (24, 32)] == [False, True]
+    assert halo(4, 256, 14, 384, 3) and all(halo(n, 256, 28, k, 3) for n, k in ((4, 256), (8, 512), (16, 1024), (16, 2048)))
+    assert not any(halo(n, 256, 14, 1024, 3) for n in (1, 2, 8)) and not any(halo(n, 512, 14, 2048, 3) for n in (1, 8))
+    assert [halo(n, 128, 28, 768, 3) for n in (1, 4, 24)] == [False, False, True]
+    assert halo(40, 96, 28, 512, 5) and halo(4, 96, 28, 160, 5) and halo(32, 128, 28, 768, 5) and not halo(1, 512, 14, 1024, 5)
     # a row stride of 1: more filter rows per workgroup, fewer launches of the other kernels
     assert [halo(n, 128, 28, 384, 3, 1) for n in (1, 8, 24)] == [False, False, True] and halo(8, 128, 28, 64, 3, 1)
-    assert [halo(n, 96, 28, 96, 5, 1) for n in (4, 24)] == [False, True]
+    assert halo(4, 96, 28, 96, 5, 1) and halo(24, 96, 28, 96, 5, 1)
+    # few channels, all phases in one launch that splits no sum: 853 us against 386 (17x17, 5x3), or with few products 12 against 20
+    def few(n, c, hw, k, r, s, stride_h):
+        L = ucd.layer(N=n, C=c, H=hw, W=hw, K=k, R=r, S=s, pad_h=r // 2, pad_w=s // 2, stride_h=stride_h, stride_w=2)
+        return "conv_halo_kernel" in ucd.ucd_describe_micro(L, ucd.BWD_DATA, ucd.ALGO_IMPLICIT, n)[0]
+    assert few(1, 20, 17, 1703, 5, 3, 2) and few(5, 19, 83, 890, 5, 3, 2) and few(10, 21, 34, 1364, 4, 3, 2)
+    assert not few(3, 20, 75, 58, 3, 5, 3) and not few(34, 19, 27, 36, 4, 5, 3)
 
 
 def test_reproducible_mode_keeps_layers_whose_reduction_the_other_kernels_would_split():
-    """1x1 BackwardData: the implicit GEMMs are the faster ones there only where they may split a sum."""
+    """Strided and 1x1 BackwardData: the implicit GEMMs are the faster ones there only where they may split a sum."""
+    strided = ucd.layer(N=1, C=256, H=14, W=14, K=1024, R=3, S=3, pad_h=1, pad_w=1, stride_h=2, stride_w=2)
+    wide = ucd.layer(N=1, C=512, H=14, W=14, K=1024, R=5, S=5, pad_h=2, pad_w=2, stride_h=2, stride_w=2)
     deep = ucd.layer(N=18, C=224, H=28, W=28, K=2344, R=1, S=1)
     second_round = ucd.layer(N=201, C=80, H=20, W=20, K=1016, R=1, S=1)
     prev = ucd.ucd_set_deterministic(0)
     try:
         for det in (0, 1):
             ucd.ucd_set_deterministic(det)
-            for layer, kernel in ((deep, "pointwise_split_stream_kernel<"), (second_round, "pointwise_split_stream_kernel<")):
+            for layer, kernel in ((strided, "conv_halo_kernel<"), (wide, "conv_halo_kernel<"),
+                                  (deep, "pointwise_split_stream_kernel<"), (second_round, "pointwise_split_stream_kernel<")):
                 text, _ = ucd.ucd_describe_micro(layer, ucd.BWD_DATA, ucd.ALGO_IMPLICIT, layer.N)
                 assert (kernel in text) == bool(det), (det, text)
     finally:
