@@ -324,31 +324,29 @@ __global__ __launch_bounds__(512, 2) void wino_fused_split_kernel(FusedParams p)
                 };
                 static_for<6>(one);
             };
+            // The patch that the half step before loaded is transformed first, so that the next one's loads, into the
+            // same registers, are in flight for 18 of the 24 MFMAs (with the loads in the last group, behind the
+            // transform's own registers, they had 5: 384 -> 384 13x13 b = 256 423 us against 412 now, 64 -> 64 56x56 322
+            // against 312, phases of 11x11 stride 4 433 against 405).
             read_v(vr, q, 1);
             group(acc[q][0][0], a0, b0, [&](int m) __attribute__((always_inline)) {
-                if (m >= 2) b1.pair(m - 2, vv, rest);
                 if (m == 0) finish_patch();
                 if (m == 1) column_transform();
+                if (m >= 2) b1.pair(m - 2, vv, rest);
+                if (m >= 2) put_row(vw, q, m - 2);
             });
             group(acc[q][0][1], a0, b1, [&](int m) __attribute__((always_inline)) {
+                if (m < 4) fetch_row(q == 0 ? c0 + kWsC : c0 + 2 * kWsC, q ^ 1, m);
                 if (m < 4) a1.pair(m, ur[1], rest);
                 if (m == 4) fetch_u(c_next, q ^ 1, 1);
-                if (m == 4) put_row(vw, q, 0);
-                if (m == 5) put_row(vw, q, 1);
             });
             group(acc[q][1][0], a1, b0, [&](int m) __attribute__((always_inline)) {
-                if (m == 0) put_row(vw, q, 2);
-                if (m == 1) put_row(vw, q, 3);
                 if (m >= 2) a0.pair(m - 2, ur[0], rest);
                 if (m == 5) fetch_u(c0 + kWsC, q, 0);
             });
             if (q == 1) __syncthreads();   // the next step's V is complete, and this step's has been read
             read_v(q == 0 ? vr : vw, q ^ 1, 0);
             group(acc[q][1][1], a1, b1, [&](int m) __attribute__((always_inline)) {
-                if (m < 2) {
-                    fetch_row(q == 0 ? c0 + kWsC : c0 + 2 * kWsC, q ^ 1, 2 * m);
-                    fetch_row(q == 0 ? c0 + kWsC : c0 + 2 * kWsC, q ^ 1, 2 * m + 1);
-                }
                 if (m >= 2) b0.pair(m - 2, vv, rest);
             });
         };
