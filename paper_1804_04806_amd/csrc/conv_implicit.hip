@@ -131,6 +131,7 @@ hipError_t implicit_fwd(const Dims &d, int b, const void *x, const void *w, void
     if (pointwise_stream_pays(d, 0, b)) return pointwise_stream(d, 0, b, x, w, y, s);
     if (pointwise_pays(d, 0, b)) return pointwise_conv(d, 0, b, x, w, y, s);
     if (pointwise_bf16_pays(d, 0, b)) return pointwise_bf16(d, 0, b, x, w, y, s);
+    if (window_pays(d, 0, b)) return window_conv(d, 0, b, x, w, y, s);
     return d.dtype == 1 ? implicit_fwd_t<bf16>(d, b, x, w, y, s) : implicit_fwd_t<float>(d, b, x, w, y, s);
 }
 

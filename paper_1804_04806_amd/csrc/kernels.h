@@ -56,6 +56,11 @@ hipError_t pointwise_stream(const Dims &d, int op, int b, const void *in, const 
 bool pointwise_bf16_pays(const Dims &d, int op, int b);
 hipError_t pointwise_bf16(const Dims &d, int op, int b, const void *in, const void *w, void *out, hipStream_t s);
 
+// Forward (x, w, y) and BackwardData (dy, w, dx) of 3x3 stride-1 layers with bf16 tensors over a window in LDS
+// (conv_window.hip), zero workspace
+bool window_pays(const Dims &d, int op, int b);
+hipError_t window_conv(const Dims &d, int op, int b, const void *in, const void *w, void *out, hipStream_t s);
+
 // zero-workspace implicit GEMM
 hipError_t implicit_fwd(const Dims &d, int b, const void *x, const void *w, void *y, hipStream_t s);
 hipError_t implicit_bwd_data(const Dims &d, int b, const void *dy, const void *w, void *dx, hipStream_t s);
