@@ -61,6 +61,10 @@ hipError_t pointwise_bf16(const Dims &d, int op, int b, const void *in, const vo
 bool window_pays(const Dims &d, int op, int b);
 hipError_t window_conv(const Dims &d, int op, int b, const void *in, const void *w, void *out, hipStream_t s);
 
+// BackwardFilter of 3x3 stride-1 layers with bf16 tensors, all taps at once (filter_window.hip), zero workspace, fp32 atomics
+bool filter_window_pays(const Dims &d, int b);
+hipError_t filter_window(const Dims &d, int b, const void *x, const void *dy, float *dw, float beta, hipStream_t s);
+
 // zero-workspace implicit GEMM
 hipError_t implicit_fwd(const Dims &d, int b, const void *x, const void *w, void *y, hipStream_t s);
 hipError_t implicit_bwd_data(const Dims &d, int b, const void *dy, const void *w, void *dx, hipStream_t s);
