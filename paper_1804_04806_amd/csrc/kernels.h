@@ -46,6 +46,10 @@ double implicit_bwd_data_us(const Dims &d, int b);   // of the implicit GEMMs th
 bool halo_pays(const Dims &d, int b);
 hipError_t halo_bwd_data(const Dims &d, int b, const void *dy, const void *w, void *dx, hipStream_t s);
 
+// BackwardData of layers with few input channels over a window in LDS (conv_few.hip), zero workspace
+bool few_pays(const Dims &d, int b);
+hipError_t few_bwd_data(const Dims &d, int b, const void *dy, const void *w, void *dx, hipStream_t s);
+
 // Forward (x, w, y) and BackwardData (dy, w, dx) of fp32 1x1 layers that keep their input in LDS (conv_pointwise.hip)
 bool pointwise_pays(const Dims &d, int op, int b);
 hipError_t pointwise_conv(const Dims &d, int op, int b, const void *in, const void *w, void *out, hipStream_t s);
