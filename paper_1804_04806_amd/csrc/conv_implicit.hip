@@ -128,6 +128,7 @@ static hipError_t implicit_fwd_t(const Dims &d, int b, const void *x, const void
 hipError_t implicit_fwd(const Dims &d, int b, const void *x, const void *w, void *y, hipStream_t s)
 {
     if (small_pays(d, 0, b)) return small_conv(d, 0, b, x, w, y, 0.f, s);
+    if (rows_pays(d, b)) return rows_fwd(d, b, x, w, y, s);
     if (pointwise_stream_pays(d, 0, b)) return pointwise_stream(d, 0, b, x, w, y, s);
     if (pointwise_pays(d, 0, b)) return pointwise_conv(d, 0, b, x, w, y, s);
     if (pointwise_bf16_pays(d, 0, b)) return pointwise_bf16(d, 0, b, x, w, y, s);

@@ -50,6 +50,10 @@ hipError_t halo_bwd_data(const Dims &d, int b, const void *dy, const void *w, vo
 bool few_pays(const Dims &d, int b);
 hipError_t few_bwd_data(const Dims &d, int b, const void *dy, const void *w, void *dx, hipStream_t s);
 
+// Forward of layers with few input channels over windows of image rows in LDS (conv_rows.hip), zero workspace
+bool rows_pays(const Dims &d, int b);
+hipError_t rows_fwd(const Dims &d, int b, const void *x, const void *w, void *y, hipStream_t s);
+
 // Forward (x, w, y) and BackwardData (dy, w, dx) of fp32 1x1 layers that keep their input in LDS (conv_pointwise.hip)
 bool pointwise_pays(const Dims &d, int op, int b);
 hipError_t pointwise_conv(const Dims &d, int op, int b, const void *in, const void *w, void *out, hipStream_t s);
