@@ -18,7 +18,7 @@ OUT = os.path.join(HERE, "libucd.so")
 OBJ_DIR = os.path.join(ROOT, "_build")
 
 SOURCES = ["api.cpp", "planner.cpp", "conv_implicit.hip", "conv_implicit_bwd_data.hip",
-           "conv_implicit_bwd_filter.hip", "conv_small.hip", "conv_halo.hip", "conv_window.hip", "conv_few.hip", "conv_rows.hip", "filter_window.hip", "conv_pointwise.hip",
+           "conv_implicit_bwd_filter.hip", "conv_small.hip", "conv_halo.hip", "conv_window.hip", "conv_few.hip", "conv_rows.hip", "filter_window.hip", "filter_few.hip", "conv_pointwise.hip",
            "conv_im2col.hip", "conv_winograd.hip", "conv_winograd5.hip", "conv_fft.hip", "mfma_probe.hip"]
 
 # packed fp32 instructions are switched off on purpose (they have mis-computed on the test machines)

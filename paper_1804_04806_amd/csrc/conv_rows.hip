@@ -95,6 +95,8 @@ static int pick(const Dims &d, int b)
 {
     if (d.C > 16 || d.crs() < (d.dtype == 1 ? 100 : 60)) return 0;
     const int wm = d.K <= 32 ? 1 : (d.K + 95) / 96 * 96 < (d.K + 63) / 64 * 64 ? 3 : 2;
+    // blocks of eight columns and more fill up less than half of them: too few positions are, before the grid is worked out
+    if (1.5 * b * d.P * d.Q < 256. * (d.dtype == 1 ? 8 : 3) * (device_cus() / ((d.K + 32 * wm - 1) / (32 * wm)) - 1)) return 0;
     RowsParams p{};
     if (!(wm == 1 ? rows_grid<RowsTile<E, 1>>(d, b, p) : wm == 2 ? rows_grid<RowsTile<E, 2>>(d, b, p) : rows_grid<RowsTile<E, 3>>(d, b, p))) return 0;
     if ((long)p.tiles_n < (d.dtype == 1 ? 8l : 3l) * per_row(p) || (d.dtype == 1 && p.tiles_m > 1)) return 0;

@@ -73,6 +73,10 @@ hipError_t window_conv(const Dims &d, int op, int b, const void *in, const void 
 bool filter_window_pays(const Dims &d, int b);
 hipError_t filter_window(const Dims &d, int b, const void *x, const void *dy, float *dw, float beta, hipStream_t s);
 
+// BackwardFilter of layers with few input channels, all filter elements at once (filter_few.hip), zero workspace, fp32 atomics
+bool filter_few_pays(const Dims &d, int b);
+hipError_t filter_few(const Dims &d, int b, const void *x, const void *dy, float *dw, float beta, hipStream_t s);
+
 // zero-workspace implicit GEMM
 hipError_t implicit_fwd(const Dims &d, int b, const void *x, const void *w, void *y, hipStream_t s);
 hipError_t implicit_bwd_data(const Dims &d, int b, const void *dy, const void *w, void *dx, hipStream_t s);
