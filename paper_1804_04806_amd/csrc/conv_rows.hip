@@ -46,7 +46,7 @@ static double tile_cycles(const RowsParams &p)
 template <class T>
 static bool rows_grid(const Dims &d, int b, RowsParams &best)
 {
-    if (d.R < d.sh) return false;
+    if (d.R < d.sh || !offsets_in_reach(T::MT, (long)d.esize() * d.P * d.Q)) return false;   // stores of rows past the last one
     double least = 1e30;
     for (int nb = 1; nb == 1 || (d.Q + nb - 1) / nb >= 8; ++nb) {
         RowsParams p{};

@@ -39,6 +39,11 @@ inline int device_cus()
     }
     return v;
 }
+
+// Loads and stores of elements that do not exist take the offset kOob (2^31) and the scalar offset of their row all the same: whether those of
+// `rows` rows, row_bytes apart, keep the sum below 2^32, where the range check has it as it is.
+inline bool offsets_in_reach(long rows, long row_bytes) { return (rows - 1) * row_bytes < 1l << 31; }
+
 constexpr int kTailMinSteps = 8;    // a tail workgroup's run has at least this many reduction steps (of BK rows)
 constexpr int kTailMaxTiles = 224;  // a last round fuller than this is left alone
 
