@@ -208,7 +208,7 @@ __global__ __launch_bounds__(512, 2) void conv_few_kernel(FewParams p)
                 next_a();
                 if (last) {
                     put_b((c + 1) & 1);
-                    load_b(c + 2);
+                    if (c + 2 < chunks) load_b(c + 2);
                 }
             };
             if (early) stage();

@@ -240,7 +240,7 @@ __global__ __launch_bounds__(T::THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
                     load_a(lc, lg);
                     if (last && c + 1 < chunks) {
                         put_b((c + 1) & 1);
-                        load_b(c + 2);
+                        if (c + 2 < chunks) load_b(c + 2);
                     }
                 };
                 if (early) stage();

@@ -17,6 +17,7 @@ static bool window_params(const Dims &d, int b, WindowParams &p)
         p.Ci = d.K; p.Hi = d.P; p.Wi = d.Q; p.Co = d.C; p.Ho = d.H; p.Wo = d.W; p.ph = 2 - d.ph; p.pw = 2 - d.pw;
     }
     if (p.ph < 0 || p.ph > 2 || p.pw < 0 || p.pw > 2 || p.Wi < 4) return false;
+    if (!offsets_in_reach((p.Ci + kWinC - 1) / kWinC * kWinC - 8, 2l * p.Hi * p.Wi)) return false;   // loads of channels past the last one
     // as few blocks of columns as the window's size in LDS and its 512 runs of four pixels allow
     for (p.nb = (p.Wo + 61) / 62;; ++p.nb) {
         p.Wc = (p.Wo + p.nb - 1) / p.nb;

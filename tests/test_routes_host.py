@@ -14,3 +14,14 @@ def test_rows_kernel_keeps_the_offsets_of_its_stores_below_32_bits():
         assert "conv_rows_kernel" not in described(ucd.FWD, n, c, h, h, k, r, r, (stride, stride))
     for n, c, h, k, r, stride in ((1, 3, 5600, 58, 7, 2), (1, 4, 4100, 26, 4, 1)):
         assert "conv_rows_kernel" in described(ucd.FWD, n, c, h, h, k, r, r, (stride, stride))
+
+
+def test_loads_of_channels_past_the_last_one_keep_their_offsets_below_32_bits():
+    """The same for the channels that fill up a chunk: planes such that the chunk's last one begins at 2^31 and more."""
+    for op in (ucd.FWD, ucd.BWD_DATA):
+        assert "conv_window_kernel" not in described(op, 1, 2, 12500, 12500, 2, 3, 3, pads=(1, 1), dtype=1)
+        assert "conv_window_kernel" in described(op, 1, 2, 12000, 12000, 2, 3, 3, pads=(1, 1), dtype=1)
+    for pad, kernel in ((150, False), (1, True)):   # planes of 95 MB and of 17
+        assert ("conv_few_kernel" in described(ucd.BWD_DATA, 1, 3, 64, 1 << 16, 17, 5, 5, pads=(pad, 1))) == kernel
+    for pad, kernel in ((560, False), (1, True)):   # 294 MB
+        assert ("conv_halo_kernel" in described(ucd.BWD_DATA, 1, 64, 64, 1 << 16, 1, 3, 3, pads=(pad, 1))) == kernel
