@@ -17,7 +17,9 @@ static bool rows_blocks(const Dims &d, int b, int nb, RowsParams &p)
     p.nb = nb;
     p.Wc = (d.Q + p.nb - 1) / p.nb;
     if (p.nb > 1 && d.sw % 2) p.Wc += p.Wc & 1;   // blocks begin on even columns
-    p.pitch = ((p.Wc - 1) * d.sw + 4 * p.SQ + 1) / 2 * 2;
+    const long pitch = ((p.Wc - 1l) * d.sw + 4 * p.SQ + 1) / 2 * 2;
+    if (pitch > 1024 * T::NB) return false;   // (as integers its window has no size any more)
+    p.pitch = (int)pitch;
     const int rows = (T::NT - 2) / p.Wc + 2, segments = (rows - 2) / d.P + 2;   // of positions, and virtual images they lie in
     p.rows = d.sh * rows + segments * (d.R - d.sh);
     const int elements = d.C * p.rows * p.pitch;

@@ -25,3 +25,9 @@ def test_loads_of_channels_past_the_last_one_keep_their_offsets_below_32_bits():
         assert ("conv_few_kernel" in described(ucd.BWD_DATA, 1, 3, 64, 1 << 16, 17, 5, 5, pads=(pad, 1))) == kernel
     for pad, kernel in ((560, False), (1, True)):   # 294 MB
         assert ("conv_halo_kernel" in described(ucd.BWD_DATA, 1, 64, 64, 1 << 16, 1, 3, 3, pads=(pad, 1))) == kernel
+
+
+def test_rows_kernel_with_windows_of_two_thousand_million_elements():
+    """Rows of 2^23 pixels: the size of a window with all of their columns begins at 2^31."""
+    for w in (8388606, 8388607, 8388608, 8388610):
+        assert "conv_rows_kernel" not in described(ucd.FWD, 1, 16, 1, w, 31, 8, 4, pads=(4, 0))
