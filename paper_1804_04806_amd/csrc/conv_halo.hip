@@ -1,4 +1,5 @@
 // Launch of conv_halo_kernel: BackwardData of fp32 layers.
+#include <algorithm>
 #include <cmath>
 
 #include "conv_halo.hpp"
@@ -19,7 +20,8 @@ static bool halo_params(const Dims &d, int b, HaloParams &p)
     const int Gw = (d.W + T::NPH - 1) / T::NPH;
     // as few blocks of columns as the window's size in LDS allows
     const int U = (d.R + d.sh - 1) / d.sh;
-    for (p.nb = (Gw + 31) / 32;; ++p.nb) {
+    for (int widest = 32;;) {
+        p.nb = (Gw + widest - 1) / widest;
         p.Wc = (Gw + p.nb - 1) / p.nb;
         if (p.Wc < 4 && p.nb > 1) return false;
         p.pitch = p.Wc + T::kSpan;
@@ -27,6 +29,9 @@ static bool halo_params(const Dims &d, int b, HaloParams &p)
         p.cells = (rows + segments * (U - 1)) * p.pitch;
         while (p.cells % 16 < 4 || p.cells % 16 > 12) ++p.cells;   // the halves on other banks
         if (p.cells <= T::kMaxCells) break;
+        // narrower blocks hold as many rows or more: the next to try is as wide as the window of these rows may be
+        widest = std::min(p.Wc - 1, T::kMaxCells / (rows + segments * (U - 1)) - T::kSpan);
+        if (widest < 4) return false;
     }
     p.images = b * p.nb;
     const long cols = (long)p.images * p.Gh * p.Wc;

@@ -128,11 +128,12 @@ static hipError_t implicit_fwd_t(const Dims &d, int b, const void *x, const void
 hipError_t implicit_fwd(const Dims &d, int b, const void *x, const void *w, void *y, hipStream_t s)
 {
     if (small_pays(d, 0, b)) return small_conv(d, 0, b, x, w, y, 0.f, s);
-    if (rows_pays(d, b)) return rows_fwd(d, b, x, w, y, s);
+    hipError_t e;
+    if (rows_fwd(d, b, x, w, y, s, e)) return e;
     if (pointwise_stream_pays(d, 0, b)) return pointwise_stream(d, 0, b, x, w, y, s);
     if (pointwise_pays(d, 0, b)) return pointwise_conv(d, 0, b, x, w, y, s);
     if (pointwise_bf16_pays(d, 0, b)) return pointwise_bf16(d, 0, b, x, w, y, s);
-    if (window_pays(d, 0, b)) return window_conv(d, 0, b, x, w, y, s);
+    if (window_conv(d, 0, b, x, w, y, s, e)) return e;
     return d.dtype == 1 ? implicit_fwd_t<bf16>(d, b, x, w, y, s) : implicit_fwd_t<float>(d, b, x, w, y, s);
 }
 

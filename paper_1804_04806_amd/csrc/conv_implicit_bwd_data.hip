@@ -236,8 +236,8 @@ hipError_t implicit_bwd_data(const Dims &d, int b, const void *dy, const void *w
     if (pointwise_stream_pays(d, 1, b)) return pointwise_stream(d, 1, b, dy, w, dx, s);
     if (pointwise_pays(d, 1, b)) return pointwise_conv(d, 1, b, dy, w, dx, s);
     if (pointwise_bf16_pays(d, 1, b)) return pointwise_bf16(d, 1, b, dy, w, dx, s);
-    if (window_pays(d, 1, b)) return window_conv(d, 1, b, dy, w, dx, s);
-    if (few_pays(d, b)) return few_bwd_data(d, b, dy, w, dx, s);
+    hipError_t e;
+    if (window_conv(d, 1, b, dy, w, dx, s, e) || few_bwd_data(d, b, dy, w, dx, s, e)) return e;
     if (halo_pays(d, b)) return halo_bwd_data(d, b, dy, w, dx, s);
     return d.dtype == 1 ? implicit_bwd_data_t<bf16>(d, b, dy, w, dx, s) : implicit_bwd_data_t<float>(d, b, dy, w, dx, s);
 }

@@ -227,8 +227,8 @@ hipError_t implicit_bwd_filter(const Dims &d, int b, const void *x, const void *
                                float *ws, hipStream_t s)
 {
     if (small_pays(d, 2, b)) return small_conv(d, 2, b, x, dy, dw, beta, s);
-    if (filter_window_pays(d, b)) return filter_window(d, b, x, dy, dw, beta, s);
-    if (filter_few_pays(d, b)) return filter_few(d, b, x, dy, dw, beta, s);
+    hipError_t e;
+    if (filter_window(d, b, x, dy, dw, beta, s, e) || filter_few(d, b, x, dy, dw, beta, s, e)) return e;
     return d.dtype == 1 ? implicit_bwd_filter_t<bf16>(d, b, x, dy, dw, beta, ws, s)
                         : implicit_bwd_filter_t<float>(d, b, x, dy, dw, beta, ws, s);
 }

@@ -44,17 +44,26 @@ static double tile_cycles(const RowsParams &p)
     return 4000 + 70. * ((p.pairs + 511) / 512) * 2 + p.steps * (T::F32 ? 192 : 32) * T::WM * 2;
 }
 
-// The blocks of columns with which that is least over the launch: narrow ones keep more of a window's rows, and of its columns fewer.
+// The blocks of columns with which that is least over the launch: narrow ones keep more of a window's rows, and of its columns fewer.  Of those
+// as wide as each other the fewest; none wider than a tile, whose windows hold columns that it does not read, nor than a window of 2 R rows per
+// channel may be.
 template <class T>
 static bool rows_grid(const Dims &d, int b, RowsParams &best)
 {
     if (d.R < d.sh || !offsets_in_reach(T::MT, (long)d.esize() * d.P * d.Q)) return false;   // stores of rows past the last one
+    const int room = 512 * T::NB / (d.C * d.R) - 4 * ((d.S + (d.pw & 1) + 3) / 4);
+    if (room < 0) return false;
     double least = 1e30;
-    for (int nb = 1; nb == 1 || (d.Q + nb - 1) / nb >= 8; ++nb) {
+    for (int widest = std::min(std::max(T::NT, d.Q < 2 * T::NT ? d.Q : 0), room / d.sw + 1);;) {
+        const int nb = (d.Q + widest - 1) / widest, Wc = (d.Q + nb - 1) / nb;
+        if (nb > 1 && Wc < 8) break;
         RowsParams p{};
-        if (!rows_blocks<T>(d, b, nb, p)) continue;
-        const double cycles = tile_cycles<T>(p) * p.cols;
-        if (cycles < least) { least = cycles; best = p; }
+        if (rows_blocks<T>(d, b, nb, p)) {
+            const double cycles = tile_cycles<T>(p) * p.cols;
+            if (cycles < least) { least = cycles; best = p; }
+        }
+        widest = Wc - 1;
+        if (widest < 1) break;
     }
     return least < 1e30;
 }
@@ -62,10 +71,8 @@ static bool rows_grid(const Dims &d, int b, RowsParams &best)
 static int per_row(const RowsParams &p) { return std::max(1, std::min(p.tiles_n, device_cus() / p.tiles_m)); }
 
 template <class T>
-static hipError_t launch(const Dims &d, int b, const void *x, const void *w, void *y, hipStream_t s)
+static hipError_t launch(const Dims &d, int b, const void *x, const void *w, void *y, hipStream_t s, RowsParams &p)
 {
-    RowsParams p{};
-    if (!rows_grid<T>(d, b, p)) return hipErrorInvalidValue;
     p.C = d.C; p.H = d.H; p.W = d.W; p.K = d.K; p.P = d.P; p.Q = d.Q; p.R = d.R; p.S = d.S; p.CRS = d.crs();
     p.sh = d.sh; p.sw = d.sw; p.ph = d.ph; p.pw = d.pw;
     p.div_wc = FastDiv(p.Wc); p.div_p = FastDiv(d.P); p.div_nb = FastDiv(p.nb); p.div_half = FastDiv(p.pitch / 2);
@@ -93,34 +100,32 @@ static hipError_t launch(const Dims &d, int b, const void *x, const void *w, voi
 // multiplications for the same window): eight tiles and 100 products 1.29, 1.18 at least; six tiles 1.06; three 0.79; more than one row
 // tile 0.87.  Of 112 other layers that it takes 1.38 and 1.04 (bf16 1.38 and 1.22).
 template <class E>
-static int pick(const Dims &d, int b)
+static int pick(const Dims &d, int b, RowsParams &p)
 {
     if (d.C > 16 || d.crs() < (d.dtype == 1 ? 100 : 60)) return 0;
     const int wm = d.K <= 32 ? 1 : (d.K + 95) / 96 * 96 < (d.K + 63) / 64 * 64 ? 3 : 2;
     // blocks of eight columns and more fill up less than half of them: too few positions are, before the grid is worked out
     if (1.5 * b * d.P * d.Q < 256. * (d.dtype == 1 ? 8 : 3) * (device_cus() / ((d.K + 32 * wm - 1) / (32 * wm)) - 1)) return 0;
-    RowsParams p{};
     if (!(wm == 1 ? rows_grid<RowsTile<E, 1>>(d, b, p) : wm == 2 ? rows_grid<RowsTile<E, 2>>(d, b, p) : rows_grid<RowsTile<E, 3>>(d, b, p))) return 0;
     if ((long)p.tiles_n < (d.dtype == 1 ? 8l : 3l) * per_row(p) || (d.dtype == 1 && p.tiles_m > 1)) return 0;
     return 4.0 * d.crs() * d.K > 3.0 * (16.0 * p.steps) * (32.0 * wm * p.tiles_m) ? wm : 0;
 }
 
-bool rows_pays(const Dims &d, int b) { return (d.dtype == 1 ? pick<bf16>(d, b) : pick<float>(d, b)) > 0; }
-
 template <class E>
-static hipError_t rows_fwd_t(const Dims &d, int b, const void *x, const void *w, void *y, hipStream_t s)
+static bool rows_fwd_t(const Dims &d, int b, const void *x, const void *w, void *y, hipStream_t s, hipError_t &e)
 {
-    switch (pick<E>(d, b)) {
-    case 1: return launch<RowsTile<E, 1>>(d, b, x, w, y, s);
-    case 2: return launch<RowsTile<E, 2>>(d, b, x, w, y, s);
-    case 3: return launch<RowsTile<E, 3>>(d, b, x, w, y, s);
+    RowsParams p{};
+    switch (pick<E>(d, b, p)) {
+    case 1: e = launch<RowsTile<E, 1>>(d, b, x, w, y, s, p); return true;
+    case 2: e = launch<RowsTile<E, 2>>(d, b, x, w, y, s, p); return true;
+    case 3: e = launch<RowsTile<E, 3>>(d, b, x, w, y, s, p); return true;
     }
-    return hipErrorInvalidValue;
+    return false;
 }
 
-hipError_t rows_fwd(const Dims &d, int b, const void *x, const void *w, void *y, hipStream_t s)
+bool rows_fwd(const Dims &d, int b, const void *x, const void *w, void *y, hipStream_t s, hipError_t &e)
 {
-    return d.dtype == 1 ? rows_fwd_t<bf16>(d, b, x, w, y, s) : rows_fwd_t<float>(d, b, x, w, y, s);
+    return d.dtype == 1 ? rows_fwd_t<bf16>(d, b, x, w, y, s, e) : rows_fwd_t<float>(d, b, x, w, y, s, e);
 }
 
 }  // namespace ucd

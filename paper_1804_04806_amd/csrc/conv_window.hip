@@ -18,8 +18,10 @@ static bool window_params(const Dims &d, int b, WindowParams &p)
     }
     if (p.ph < 0 || p.ph > 2 || p.pw < 0 || p.pw > 2 || p.Wi < 4) return false;
     if (!offsets_in_reach((p.Ci + kWinC - 1) / kWinC * kWinC - 8, 2l * p.Hi * p.Wi)) return false;   // loads of channels past the last one
-    // as few blocks of columns as the window's size in LDS and its 512 runs of four pixels allow
-    for (p.nb = (p.Wo + 61) / 62;; ++p.nb) {
+    // As few blocks of columns as the window's size in LDS and its 512 runs of four pixels allow.  Narrower blocks hold as many rows or
+    // more: after one that does not fit, the next to try is as wide as the window of its rows may be.
+    for (int widest = 62;;) {
+        p.nb = (p.Wo + widest - 1) / widest;
         p.Wc = (p.Wo + p.nb - 1) / p.nb;
         if (p.Wc < 4 && p.nb > 1) return false;
         p.runs = (p.Wc + 2 + 3) / 4;
@@ -28,6 +30,8 @@ static bool window_params(const Dims &d, int b, WindowParams &p)
         p.rows = rows + more * (2 - p.ph) + 2;
         p.cells = p.rows * p.pitch;
         if (p.cells <= T::kMaxCells && 2 * p.rows * p.runs <= 512) break;
+        widest = std::min(p.Wc - 1, 4 * std::min(256 / p.rows, (T::kMaxCells / p.rows - 1) / 4) - 2);
+        if (widest < 4) return false;
     }
     p.images = b * p.nb;
     const long cols = (long)p.images * p.Ho * p.Wc;
@@ -40,10 +44,8 @@ static bool window_params(const Dims &d, int b, WindowParams &p)
 }
 
 template <class T>
-static hipError_t launch(const Dims &d, int b, const void *in, const void *w, void *out, hipStream_t s)
+static hipError_t launch(const Dims &d, int b, const void *in, const void *w, void *out, hipStream_t s, WindowParams &p)
 {
-    WindowParams p{};
-    if (!window_params<T>(d, b, p)) return hipErrorInvalidValue;
     p.in = in; p.in_bytes = T::OP == 0 ? xbytes(d, b) : ybytes(d, b);
     p.w = w; p.w_bytes = wbytes(d);
     p.out = out; p.out_bytes = T::OP == 0 ? ybytes(d, b) : xbytes(d, b);
@@ -66,53 +68,48 @@ static hipError_t launch(const Dims &d, int b, const void *in, const void *w, vo
 struct WindowPick {
     int tile = -1;
     double us = 1e30;
+    WindowParams p;
 };
 
 template <class T>
-static void consider(const Dims &d, int b, int tile, double start, double chunk, WindowPick &best)
+static void consider(const Dims &d, int b, int cus, int tile, double start, double chunk, WindowPick &best)
 {
     WindowParams p{};
     if (!window_params<T>(d, b, p)) return;
-    const double wgs = (double)p.tiles_m * ((p.cols + T::NT - 1) / T::NT), cus = device_cus();
+    const double wgs = (double)p.tiles_m * ((p.cols + T::NT - 1) / T::NT);
     const double rounds = T::kPair ? 0.6 * std::ceil(wgs / cus) + 0.4 * std::max(1., wgs / cus) : std::ceil(wgs / cus);
     const double us = (T::kPair ? 3.5 : 0.) + rounds * (start + chunk * ((p.Ci + kWinC - 1) / kWinC));
-    if (us < best.us) { best.us = us; best.tile = tile; }
-}
-
-template <int OP>
-static WindowPick pick(const Dims &d, int b)
-{
-    WindowPick best;
-    consider<WindowTile<OP, 4, 2, 8>>(d, b, 0, 12., 3.2, best);
-    consider<WindowTile<OP, 2, 2, 8>>(d, b, 1, 5.4, 2.1, best);
-    consider<WindowTile<OP, 2, 1, 8>>(d, b, 2, 4.1, 1.57, best);
-    consider<WindowTile<OP, 1, 1, 8>>(d, b, 3, 0.5, 1.13, best);
-    return best;
-}
-
-template <int OP>
-static hipError_t launch_pick(const Dims &d, int b, const void *in, const void *w, void *out, hipStream_t s)
-{
-    switch (pick<OP>(d, b).tile) {
-    case 0: return launch<WindowTile<OP, 4, 2, 8>>(d, b, in, w, out, s);
-    case 1: return launch<WindowTile<OP, 2, 2, 8>>(d, b, in, w, out, s);
-    case 2: return launch<WindowTile<OP, 2, 1, 8>>(d, b, in, w, out, s);
-    case 3: return launch<WindowTile<OP, 1, 1, 8>>(d, b, in, w, out, s);
-    }
-    return hipErrorInvalidValue;
+    if (us < best.us) { best.us = us; best.tile = tile; best.p = p; }
 }
 
 // Wherever a tile's window fits: rows of four pixels and more (a run is loaded from inside its row), padding of up to two.  An odd
 // number of channels would let the last run of the filter end in half a word, which reads as zero behind the tensor.
-bool window_pays(const Dims &d, int op, int b)
+template <int OP>
+static bool window_conv_op(const Dims &d, int b, const void *in, const void *w, void *out, hipStream_t s, hipError_t &e)
 {
     if (d.dtype != 1 || d.R != 3 || d.S != 3 || d.sh != 1 || d.sw != 1 || d.C % 2) return false;
-    return (op == 0 ? pick<0>(d, b) : pick<1>(d, b)).tile >= 0;
+    typedef WindowTile<OP, 4, 2, 8> T0;
+    typedef WindowTile<OP, 2, 2, 8> T1;
+    typedef WindowTile<OP, 2, 1, 8> T2;
+    typedef WindowTile<OP, 1, 1, 8> T3;
+    WindowPick best{};
+    const int cus = device_cus();
+    consider<T0>(d, b, cus, 0, 12., 3.2, best);
+    consider<T1>(d, b, cus, 1, 5.4, 2.1, best);
+    consider<T2>(d, b, cus, 2, 4.1, 1.57, best);
+    consider<T3>(d, b, cus, 3, 0.5, 1.13, best);
+    switch (best.tile) {
+    case 0: e = launch<T0>(d, b, in, w, out, s, best.p); return true;
+    case 1: e = launch<T1>(d, b, in, w, out, s, best.p); return true;
+    case 2: e = launch<T2>(d, b, in, w, out, s, best.p); return true;
+    case 3: e = launch<T3>(d, b, in, w, out, s, best.p); return true;
+    }
+    return false;
 }
 
-hipError_t window_conv(const Dims &d, int op, int b, const void *in, const void *w, void *out, hipStream_t s)
+bool window_conv(const Dims &d, int op, int b, const void *in, const void *w, void *out, hipStream_t s, hipError_t &e)
 {
-    return op == 0 ? launch_pick<0>(d, b, in, w, out, s) : launch_pick<1>(d, b, in, w, out, s);
+    return op == 0 ? window_conv_op<0>(d, b, in, w, out, s, e) : window_conv_op<1>(d, b, in, w, out, s, e);
 }
 
 }  // namespace ucd

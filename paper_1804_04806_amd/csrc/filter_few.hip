@@ -43,12 +43,16 @@ static bool few_blocks(const Dims &d, int b, FilterFewParams &best)
 {
     double least = 1e30;
     const int across = (d.Q + 7) / 8;
-    for (int nb = 1; nb <= across; ++nb) {
+    // of blocks as wide as each other the fewest; none wider than a window of 2 R rows may be, whose phases have 4 gw pairs and more
+    for (int gw = std::min(across, T::kMaxElements / (16 * d.R * d.sw)); gw >= 1;) {
+        const int nb = (across + gw - 1) / gw;
+        gw = (across + nb - 1) / nb;
         FilterFewParams p{};
-        const int gw = (across + nb - 1) / nb;
-        if (!few_groups<T>(d, b, gw, p)) continue;
-        const double cycles = (double)p.tiles * (2000. + 60. * ((p.pairs + 511) / 512) + 700. / gw);
-        if (cycles < least) { least = cycles; best = p; }
+        if (few_groups<T>(d, b, gw, p)) {
+            const double cycles = (double)p.tiles * (2000. + 60. * ((p.pairs + 511) / 512) + 700. / gw);
+            if (cycles < least) { least = cycles; best = p; }
+        }
+        --gw;
     }
     return least < 1e30;
 }
@@ -57,10 +61,8 @@ template <class T>
 static int splits_of(const FilterFewParams &p) { return std::max(1, std::min(p.tiles, device_cus() / (p.k_blocks * p.c_blocks))); }
 
 template <class T>
-static hipError_t launch(const Dims &d, int b, const void *x, const void *dy, float *dw, hipStream_t s)
+static hipError_t launch(const Dims &d, int b, const void *x, const void *dy, float *dw, hipStream_t s, FilterFewParams &p)
 {
-    FilterFewParams p{};
-    if (!few_blocks<T>(d, b, p)) return hipErrorInvalidValue;
     p.C = d.C; p.H = d.H; p.W = d.W; p.K = d.K; p.P = d.P; p.Q = d.Q; p.R = d.R; p.S = d.S; p.CRS = d.crs();
     p.sh = d.sh; p.sw = d.sw; p.ph = d.ph; p.pw = d.pw;
     p.div_gw = FastDiv(p.gw); p.div_p = FastDiv(d.P); p.div_nb = FastDiv(p.nb); p.div_len = FastDiv(d.sh * (d.P - 1) + d.R);
@@ -85,11 +87,10 @@ typedef FilterFewTile<2, 3, 2> Wide;
 
 // Whether tile T has enough pixels per workgroup and few enough products that are padding.
 template <class T>
-static bool fills(const Dims &d, int b, int pixels, double share)
+static bool fills(const Dims &d, int b, int pixels, double share, FilterFewParams &p)
 {
     // the least that few_blocks could come to, before it is asked
     if ((double)b * d.P * d.Q < (double)pixels * (device_cus() / (((d.K + T::MT - 1) / T::MT) * d.C))) return false;
-    FilterFewParams p{};
     if (!few_blocks<T>(d, b, p) || (double)b * d.P * d.Q < (double)pixels * splits_of<T>(p)) return false;
     return (double)d.K * d.crs() >= share * ((double)p.k_blocks * T::MT) * (p.c_blocks * 32. * T::NJ);
 }
@@ -100,19 +101,15 @@ static bool fills(const Dims &d, int b, int pixels, double share)
 // time / this kernel's is 1.79 in the geometric mean of 35 with up to 32 output channels, 1000 pixels and two fifths of the products
 // real, 1.00 at least; 1.31 of 7 with more channels, 3200 pixels and four fifths real, 1.19 at least (2000 pixels 0.94, seven tenths 0.92).  Of 130
 // other layers that it takes none is below 1.00.  (A strided window does not fit beside the 256 pixels of Narrow's tiles.)
-bool filter_few_pays(const Dims &d, int b)
+bool filter_few(const Dims &d, int b, const void *x, const void *dy, float *dw, float beta, hipStream_t s, hipError_t &e)
 {
     if (d.dtype != 0 || d.det || d.C > 16 || d.R * d.S == 1 || d.K > 64) return false;
-    return d.K <= 32 ? fills<Narrow>(d, b, 1000, 0.4) : fills<Wide>(d, b, 3200, 0.8);
-}
-
-hipError_t filter_few(const Dims &d, int b, const void *x, const void *dy, float *dw, float beta, hipStream_t s)
-{
-    if (beta == 0.f) {
-        const hipError_t e = fill_zero(dw, (size_t)d.K * d.crs(), s);
-        if (e != hipSuccess) return e;
-    }
-    return d.K <= 32 ? launch<Narrow>(d, b, x, dy, dw, s) : launch<Wide>(d, b, x, dy, dw, s);
+    FilterFewParams p{};
+    if (!(d.K <= 32 ? fills<Narrow>(d, b, 1000, 0.4, p) : fills<Wide>(d, b, 3200, 0.8, p))) return false;
+    e = hipSuccess;
+    if (beta == 0.f) e = fill_zero(dw, (size_t)d.K * d.crs(), s);
+    if (e == hipSuccess) e = d.K <= 32 ? launch<Narrow>(d, b, x, dy, dw, s, p) : launch<Wide>(d, b, x, dy, dw, s, p);
+    return true;
 }
 
 }  // namespace ucd

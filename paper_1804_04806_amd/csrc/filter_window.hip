@@ -39,30 +39,33 @@ static void filter_window_params(const Dims &d, int b, FilterWindowParams &p)
 // gemm_kernel_bf16q / of this kernel 1.31 in the geometric mean, 1.00 at least; 16 Gflop 0.85, 12 0.78: the atomics outweigh
 // the rest), from 8 where they are not (74 layers, gemm_kernel_bf16, 1.51 and 1.13; 6 Gflop 0.89).  Rows of four pixels and
 // more, because they are loaded in fours from inside the row.
-bool filter_window_pays(const Dims &d, int b)
+static bool filter_window_pays(const Dims &d, int b)
 {
     if (d.dtype != 1 || d.det || d.R != 3 || d.S != 3 || d.sh != 1 || d.sw != 1 || d.W < 4 || d.Q < 4 || d.ph > 2 || d.pw > 2) return false;
     return 2. * d.K * d.crs() * ((double)b * d.P * d.Q) >= (d.P * d.Q % 4 == 0 ? 20e9 : 8e9);
 }
 
-hipError_t filter_window(const Dims &d, int b, const void *x, const void *dy, float *dw, float beta, hipStream_t s)
+bool filter_window(const Dims &d, int b, const void *x, const void *dy, float *dw, float beta, hipStream_t s, hipError_t &e)
 {
+    if (!filter_window_pays(d, b)) return false;
     FilterWindowParams p{};
     filter_window_params(d, b, p);
     p.x = x; p.dy = dy; p.dw = dw;
     if (beta == 0.f) {
-        const hipError_t e = fill_zero(dw, (size_t)d.K * d.crs(), s);
-        if (e != hipSuccess) return e;
+        e = fill_zero(dw, (size_t)d.K * d.crs(), s);
+        if (e != hipSuccess) return true;
     }
     const long blocks = (long)p.k_blocks * p.c_blocks, splits = (p.units + p.per_wg - 1) / p.per_wg;
     if (LaunchLog *log = launch_log()) {
         log->add("filter_window_kernel<Tile<" + std::to_string(Tile4::KT) + "x" + std::to_string(9 * Tile4::CT) + ">> tiles=" + std::to_string(blocks) +
                  " splits=" + std::to_string(splits) + " batch=1 M=" + std::to_string(d.K) + " N=" + std::to_string(d.crs()) +
                  " K=" + std::to_string(b * d.P * d.Q));
-        return hipSuccess;
+        e = hipSuccess;
+        return true;
     }
     filter_window_kernel<Tile4><<<(unsigned)(blocks * splits), 512, 0, s>>>(p);
-    return hipGetLastError();
+    e = hipGetLastError();
+    return true;
 }
 
 }  // namespace ucd

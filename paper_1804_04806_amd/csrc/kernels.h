@@ -46,13 +46,17 @@ double implicit_bwd_data_us(const Dims &d, int b);   // of the implicit GEMMs th
 bool halo_pays(const Dims &d, int b);
 hipError_t halo_bwd_data(const Dims &d, int b, const void *dy, const void *w, void *dx, hipStream_t s);
 
-// BackwardData of layers with few input channels over a window in LDS (conv_few.hip), zero workspace
-bool few_pays(const Dims &d, int b);
-hipError_t few_bwd_data(const Dims &d, int b, const void *dy, const void *w, void *dx, hipStream_t s);
-
-// Forward of layers with few input channels over windows of image rows in LDS (conv_rows.hip), zero workspace
-bool rows_pays(const Dims &d, int b);
-hipError_t rows_fwd(const Dims &d, int b, const void *x, const void *w, void *y, hipStream_t s);
+// The kernels for windows in LDS below, zero workspace: false where another kernel is the one to take; otherwise they have launched, or not, and e says so.
+// BackwardData of layers with few input channels over a window in LDS (conv_few.hip)
+bool few_bwd_data(const Dims &d, int b, const void *dy, const void *w, void *dx, hipStream_t s, hipError_t &e);
+// Forward of layers with few input channels over windows of image rows in LDS (conv_rows.hip)
+bool rows_fwd(const Dims &d, int b, const void *x, const void *w, void *y, hipStream_t s, hipError_t &e);
+// Forward (x, w, y) and BackwardData (dy, w, dx) of 3x3 stride-1 layers with bf16 tensors over a window in LDS (conv_window.hip)
+bool window_conv(const Dims &d, int op, int b, const void *in, const void *w, void *out, hipStream_t s, hipError_t &e);
+// BackwardFilter of 3x3 stride-1 layers with bf16 tensors, all taps at once (filter_window.hip), fp32 atomics
+bool filter_window(const Dims &d, int b, const void *x, const void *dy, float *dw, float beta, hipStream_t s, hipError_t &e);
+// BackwardFilter of layers with few input channels, all filter elements at once (filter_few.hip), fp32 atomics
+bool filter_few(const Dims &d, int b, const void *x, const void *dy, float *dw, float beta, hipStream_t s, hipError_t &e);
 
 // Forward (x, w, y) and BackwardData (dy, w, dx) of fp32 1x1 layers that keep their input in LDS (conv_pointwise.hip)
 bool pointwise_pays(const Dims &d, int op, int b);
@@ -63,19 +67,6 @@ bool pointwise_stream_pays(const Dims &d, int op, int b);
 hipError_t pointwise_stream(const Dims &d, int op, int b, const void *in, const void *w, void *out, hipStream_t s);
 bool pointwise_bf16_pays(const Dims &d, int op, int b);
 hipError_t pointwise_bf16(const Dims &d, int op, int b, const void *in, const void *w, void *out, hipStream_t s);
-
-// Forward (x, w, y) and BackwardData (dy, w, dx) of 3x3 stride-1 layers with bf16 tensors over a window in LDS
-// (conv_window.hip), zero workspace
-bool window_pays(const Dims &d, int op, int b);
-hipError_t window_conv(const Dims &d, int op, int b, const void *in, const void *w, void *out, hipStream_t s);
-
-// BackwardFilter of 3x3 stride-1 layers with bf16 tensors, all taps at once (filter_window.hip), zero workspace, fp32 atomics
-bool filter_window_pays(const Dims &d, int b);
-hipError_t filter_window(const Dims &d, int b, const void *x, const void *dy, float *dw, float beta, hipStream_t s);
-
-// BackwardFilter of layers with few input channels, all filter elements at once (filter_few.hip), zero workspace, fp32 atomics
-bool filter_few_pays(const Dims &d, int b);
-hipError_t filter_few(const Dims &d, int b, const void *x, const void *dy, float *dw, float beta, hipStream_t s);
 
 // zero-workspace implicit GEMM
 hipError_t implicit_fwd(const Dims &d, int b, const void *x, const void *w, void *y, hipStream_t s);
