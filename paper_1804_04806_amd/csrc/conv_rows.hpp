@@ -20,8 +20,6 @@
 
 namespace ucd {
 
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-
 constexpr int kRowsQuads = 128;   // quads of a filter, at most
 constexpr int kRowsMost = 256;    // rows of a window, all channels
 constexpr int kRowsLds = 163840 - 512 - 4 * kRowsQuads - 8 * kRowsMost;
@@ -55,6 +53,7 @@ __global__ __launch_bounds__(512, 2) void conv_rows_kernel(RowsParams p)
     constexpr int WM = T::WM, MT = T::MT, NT = T::NT, PARTS = T::PARTS, NB = T::NB, EB = (int)Elem<E>::kBytes;
     __shared__ __attribute__((aligned(16))) char lds[kRowsLds];
     __shared__ __attribute__((aligned(16))) int b_tab[kRowsQuads], row_tab[2 * kRowsMost];
+    __shared__ int again;   // bf16: a sum of the tile is not finite
     char *const win = lds + p.steps * T::A_STEP;
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, lhi = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wn0 = wave * 32;
@@ -137,7 +136,7 @@ __global__ __launch_bounds__(512, 2) void conv_rows_kernel(RowsParams p)
         row_tab[2 * tid + 1] = ok ? (int)cb * p.Wc * p.sw - p.pw - p.delta : -(1 << 30);
     };
     const bool whole = p.W % 2 == 0;   // no pair of pixels ends behind its row
-    auto load_b = [&](float (&rb)[NB][2]) __attribute__((always_inline)) {
+    auto load_b = [&](uint32_t (&rb)[NB][2]) __attribute__((always_inline)) {   // as they lie in memory
 #pragma unroll
         for (int x = 0; x < NB; ++x) {
             if (512 * x >= p.pairs) break;
@@ -149,15 +148,21 @@ __global__ __launch_bounds__(512, 2) void conv_rows_kernel(RowsParams p)
             const uint32_t off = (unsigned)col < (unsigned)p.W ? (uint32_t)EB * (uint32_t)(at + col) : kOob;
             if (F32 && whole) {
                 const u32x2 v = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(rin, (int)off, 0, 0));
-                rb[x][0] = __uint_as_float(v[0]);
-                rb[x][1] = __uint_as_float(v[1]);
+                rb[x][0] = v[0];
+                rb[x][1] = v[1];
             } else {
-                rb[x][0] = Elem<E>::load(rin, off, 0u);
-                rb[x][1] = Elem<E>::load(rin, col + 1 < p.W ? off + EB : kOob, 0u);
+                const int next = (int)(col + 1 < p.W ? off + EB : kOob);
+                if constexpr (F32) {
+                    rb[x][0] = __builtin_amdgcn_raw_buffer_load_b32(rin, (int)off, 0, 0);
+                    rb[x][1] = __builtin_amdgcn_raw_buffer_load_b32(rin, next, 0, 0);
+                } else {
+                    rb[x][0] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rin, (int)off, 0, 0);
+                    rb[x][1] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rin, next, 0, 0);
+                }
             }
         }
     };
-    auto put_b = [&](auto fp32c, const float (&rb)[NB][2]) __attribute__((always_inline)) {
+    auto put_b = [&](auto fp32c, const uint32_t (&rb)[NB][2]) __attribute__((always_inline)) {
         constexpr bool FP32 = fp32c;
 #pragma unroll
         for (int x = 0; x < NB; ++x) {
@@ -165,26 +170,27 @@ __global__ __launch_bounds__(512, 2) void conv_rows_kernel(RowsParams p)
             const int e = tid + 512 * x;
             if (e >= p.pairs) break;
             if constexpr (FP32) {
-                *reinterpret_cast<f32x2 *>(win + 8 * e) = f32x2{rb[x][0], rb[x][1]};
+                *reinterpret_cast<u32x2 *>(win + 8 * e) = u32x2{rb[x][0], rb[x][1]};
             } else if constexpr (F32) {
                 uint32_t h, m, l;
-                split_pair(rb[x][0], rb[x][1], h, m, l, rest);
+                split_pair(__uint_as_float(rb[x][0]), __uint_as_float(rb[x][1]), h, m, l, rest);
                 *reinterpret_cast<uint32_t *>(win + 4 * e) = h;
                 *reinterpret_cast<uint32_t *>(win + p.b_part + 4 * e) = m;
                 *reinterpret_cast<uint32_t *>(win + 2 * p.b_part + 4 * e) = l;
             } else {
-                *reinterpret_cast<uint32_t *>(win + 4 * e) = __builtin_amdgcn_perm(__float_as_uint(rb[x][1]), __float_as_uint(rb[x][0]), 0x07060302u);
+                *reinterpret_cast<uint32_t *>(win + 4 * e) = __builtin_amdgcn_perm(rb[x][1], rb[x][0], 0x05040100u);
             }
         }
     };
 
     rest = 0;
+    if (!F32) again = 0;
     put_filter(std::false_type{});
     put_rows(first);
     const bool plain = F32 && __syncthreads_or((rest & 0xFFFFu) != 0);   // a filter that the parts do not hold
     if (plain) put_filter(std::true_type{});
     if (!F32) __syncthreads();
-    float rb[NB][2];
+    uint32_t rb[NB][2];
     load_b(rb);
     __syncthreads();   // row_tab is written again
     rest = 0;
@@ -230,7 +236,16 @@ __global__ __launch_bounds__(512, 2) void conv_rows_kernel(RowsParams p)
 #pragma unroll
             for (int e = 0; e < 16; ++e) { acc[i][e] = 0.f; low[i][e] = 0.f; }
         const char *const pa = lds + (lhi * MT + l32) * 16;
-        auto step = [&](int s) __attribute__((always_inline)) {
+        // which of a quad's four taps there are
+        auto taps_of = [&](int quad) __attribute__((always_inline)) {
+            uint32_t cr, sq, there = 0;
+            p.div_sq.divmod((uint32_t)quad, cr, sq);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) there |= quad < p.quads && (unsigned)(4 * (int)sq - p.delta + e) < (unsigned)p.S ? 1u << e : 0u;
+            return there;
+        };
+        auto step = [&](auto exact, int s) __attribute__((always_inline)) {
+            constexpr bool EXACT = exact;   // pixels under taps that are not there, which meet a zero, are zeros too
             const int o0 = b_tab[4 * s + 2 * lhi], o1 = b_tab[4 * s + 2 * lhi + 1];
             u32x4 va[WM][PARTS], vb[PARTS];
 #pragma unroll
@@ -248,6 +263,11 @@ __global__ __launch_bounds__(512, 2) void conv_rows_kernel(RowsParams p)
                         d0 = __builtin_amdgcn_alignbit(d1, d0, shift);
                         d1 = __builtin_amdgcn_alignbit(d2, d1, shift);
                     }
+                    if constexpr (EXACT) {
+                        const uint32_t there = taps_of(4 * s + 2 * lhi + h);
+                        d0 &= (there & 1 ? 0xFFFFu : 0u) | (there & 2 ? 0xFFFF0000u : 0u);
+                        d1 &= (there & 4 ? 0xFFFFu : 0u) | (there & 8 ? 0xFFFF0000u : 0u);
+                    }
                     vb[pl][2 * h] = d0;
                     vb[pl][2 * h + 1] = d1;
                 }
@@ -262,13 +282,12 @@ __global__ __launch_bounds__(512, 2) void conv_rows_kernel(RowsParams p)
         };
 #pragma unroll
         for (int s = 0; s < 4 * WM; ++s) {
-            if (s < p.steps) step(s);
+            if (s < p.steps) step(std::false_type{}, s);
 #pragma unroll
             for (int e = 0; e < 4; ++e) store(s >> 2, 4 * (s & 3) + e);
         }
 #pragma unroll 1
-        for (int s = 4 * WM; s < p.steps; ++s) step(s);
-        bool redo = !F32;   // whether sums may be other than finite
+        for (int s = 4 * WM; s < p.steps; ++s) step(std::false_type{}, s);
         if constexpr (F32) {
             // not finite, or below 2^-104 and not zero (see conv_halo.hpp)
             float not_finite = 0.f;
@@ -282,14 +301,14 @@ __global__ __launch_bounds__(512, 2) void conv_rows_kernel(RowsParams p)
                     not_finite = fmaf(y, 0.f, not_finite);
                     least = min(least, (__float_as_uint(y) << 1) - 1u);
                 }
-            redo = __syncthreads_or(plain || (rest & 0xFFFFu) != 0 || !(not_finite == 0.f) || least < ((127u - 104u) << 24) - 1u);
+            const bool redo = __syncthreads_or(plain || (rest & 0xFFFFu) != 0 || !(not_finite == 0.f) || least < ((127u - 104u) << 24) - 1u);
             if (redo) {   // the tile once more, on the fp32 instructions, operands as they are
-                float again[NB][2];
+                uint32_t once_more[NB][2];
                 if (!plain) put_filter(std::true_type{});
                 put_rows(n);
                 __syncthreads();
-                load_b(again);
-                put_b(std::true_type{}, again);
+                load_b(once_more);
+                put_b(std::true_type{}, once_more);
                 __syncthreads();
 #pragma unroll
                 for (int i = 0; i < WM; ++i)
@@ -300,12 +319,14 @@ __global__ __launch_bounds__(512, 2) void conv_rows_kernel(RowsParams p)
                     const int o0 = b_tab[4 * s + 2 * lhi], o1 = b_tab[4 * s + 2 * lhi + 1];
 #pragma unroll
                     for (int h = 0; h < 2; ++h) {
+                        const uint32_t there = taps_of(4 * s + 2 * lhi + h);
                         f32x4 va[WM];
 #pragma unroll
                         for (int i = 0; i < WM; ++i) va[i] = *reinterpret_cast<const f32x4 *>(pa + s * T::A_STEP + i * 512 + h * T::A_PART);
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
-                            const float b = *reinterpret_cast<const float *>(win + 4 * (cell + (h ? o1 : o0) + e));
+                            float b = *reinterpret_cast<const float *>(win + 4 * (cell + (h ? o1 : o0) + e));
+                            b = there >> e & 1 ? b : 0.f;
 #pragma unroll
                             for (int i = 0; i < WM; ++i) acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(va[i][e], b, acc[i], 0, 0, 0);
                         }
@@ -315,7 +336,23 @@ __global__ __launch_bounds__(512, 2) void conv_rows_kernel(RowsParams p)
                 if (!plain) put_filter(std::false_type{});
             }
         } else {
+            float sums[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int i = 0; i < WM; ++i)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) sums[e & 3] = fmaf(acc[i][e], 0.f, sums[e & 3]);
+            if (!(sums[0] + sums[1] + (sums[2] + sums[3]) == 0.f)) again = 1;
             __syncthreads();
+            if (again) {   // the tile once more
+#pragma unroll
+                for (int i = 0; i < WM; ++i)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) acc[i][e] = 0.f;
+#pragma unroll 1
+                for (int s = 0; s < p.steps; ++s) step(std::true_type{}, s);
+                __syncthreads();
+                again = 0;
+            }
         }
         rest = 0;
         if (n + stride < p.tiles_n) put_b(std::false_type{}, rb);
@@ -324,37 +361,6 @@ __global__ __launch_bounds__(512, 2) void conv_rows_kernel(RowsParams p)
         load_b(rb);
 
         const bool in = jo < p.cols && q < p.Q;
-        // a tap that is not there is a zero in the products above, and one with an infinity is no zero: sums that are not finite are taken
-        // again, tap by tap
-        bool finite = true;
-        if (redo)
-#pragma unroll
-            for (int i = 0; i < WM; ++i)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) finite &= fabsf(acc[i][e]) < __builtin_inff();
-        if (in && !finite)
-#pragma unroll 1
-            for (int ie = 0; ie < 16 * WM; ++ie) {
-                const int k = m0 + 32 * (ie >> 4) + 8 * ((ie & 15) >> 2) + 4 * lhi + (ie & 3);
-                if (k >= p.K) continue;
-                float sum = 0.f;
-                for (int c = 0; c < p.C; ++c)
-                    for (int r = 0; r < p.R; ++r) {
-                        const int h = (int)t * p.sh - p.ph + r;
-                        if ((unsigned)h >= (unsigned)p.H) continue;
-                        for (int s = 0; s < p.S; ++s) {
-                            const int w = q * p.sw - p.pw + s;
-                            if ((unsigned)w >= (unsigned)p.W) continue;
-                            sum = fmaf(Elem<E>::load(rin, (uint32_t)EB * (uint32_t)((((int)img * p.C + c) * p.H + h) * p.W + w), 0u),
-                                       Elem<E>::load(rw, (uint32_t)EB * (uint32_t)(k * p.CRS + (c * p.R + r) * p.S + s), 0u), sum);
-                        }
-                    }
-#pragma unroll
-                for (int i = 0; i < WM; ++i)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e)
-                        if (16 * i + e == ie && !(fabsf(acc[i][e]) < __builtin_inff())) acc[i][e] = sum;
-            }
         done_at = in ? (uint32_t)EB * (uint32_t)((((int)img * p.K + m0 + 4 * lhi) * p.P + (int)t) * p.Q + q) : kOob;
 #pragma unroll
         for (int i = 0; i < WM; ++i)

@@ -144,8 +144,58 @@ def run_oracle(s, op, x=None, w=None, dy=None, beta=0.0, dw0=None):
     return oc.conv_bwd_filter(L, x, dy, beta=beta, dw=dw0)
 
 
+def run_oracle_zeros(s, op, x=None, w=None, dy=None):
+    """The oracle with the padding (BackwardData: what surrounds dy) as zeros in the tensors: an infinity that meets one is a NaN, as in the
+    kernels, where the oracle leaves such products out."""
+    sw, pw = _columns(s)
+    if op == ucd.BWD_DATA:
+        a = [s.R + s.pad, s.S + pw]
+        dy = np.pad(dy, ((0, 0), (0, 0), (a[0], a[0]), (a[1], a[1])))
+        h, v = (s.P + 2 * a[0] - 1) * s.stride + s.R, (s.Q + 2 * a[1] - 1) * sw + s.S
+        dx = oc.conv_bwd_data(oc.Layer(s.N, s.C, h, v, s.K, s.R, s.S, s.stride, sw, 0, 0), dy, w)
+        top, left = a[0] * s.stride + s.pad, a[1] * sw + pw
+        return dx[:, :, top:top + s.H, left:left + s.W]
+    x = np.pad(x, ((0, 0), (0, 0), (s.pad, s.pad), (pw, pw)))
+    L = oc.Layer(s.N, s.C, s.H + 2 * s.pad, s.W + 2 * pw, s.K, s.R, s.S, s.stride, sw, 0, 0)
+    return oc.conv_fwd(L, x, w) if op == ucd.FWD else oc.conv_bwd_filter(L, x, dy)
+
+
+def check_specials(got, ref, bound):
+    """Infinities and NaN where, and as, they are in ref, and the other values within bound of it."""
+    fine = np.isfinite(ref)
+    assert fine.any() and not fine.all()
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isposinf(got), np.isposinf(ref))
+    assert np.array_equal(np.isneginf(got), np.isneginf(ref))
+    assert rel_l2(got[fine], ref[fine]) <= bound
+
+
 def inputs(s, seed=0, idx=0):
     return synth.make_x(s, seed, idx), synth.make_w(s, seed, idx), synth.make_dy(s, seed, idx)
+
+
+def not_finite_time_ratio(s, op, dtype):
+    """Time of an implicit-GEMM launch on tensors that hold nothing but infinities and NaN, over its ordinary time: the larger of the two for
+    the data and for the filter (best of four runs of three launches)."""
+    import torch
+    plan = ucd.ucd_plan_fixed(desc_of(s, dtype=dtype), op, [(ucd.ALGO_IMPLICIT, s.N)])
+    kind = torch.bfloat16 if dtype else torch.float32
+    t, w = (torch.randn(shape, device="cuda:0").to(kind) for shape in (s.x_shape if op == ucd.FWD else s.y_shape, s.w_shape))
+    out = torch.empty(s.y_shape if op == ucd.FWD else s.x_shape, device="cuda:0", dtype=kind)
+    run = ucd.ucd_conv_fwd if op == ucd.FWD else ucd.ucd_conv_bwd_data
+
+    def best(t, w):
+        ms = float("inf")
+        for _ in range(4):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(3):
+                run(plan, t, w, out, None, 0)
+            b.record()
+            torch.cuda.synchronize()
+            ms = min(ms, a.elapsed_time(b))
+        return ms
+    plain, inf = best(t, w), float("inf")
+    return max(best(t2, w2) for t2, w2 in ((t * inf, w), (t * float("nan"), w), (t, w * inf), (t, w * float("nan")))) / plain
 
 
 def recomputed_time_ratio(s, op):
