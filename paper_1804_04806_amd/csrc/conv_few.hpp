@@ -38,17 +38,15 @@ struct FewParams {
     FastDiv div_wc, div_hb, div_nb, div_pitch, div_span, div_v, div_block, div_vsw;
 };
 
-template <class E>
-__global__ __launch_bounds__(512, 2) void conv_few_kernel(FewParams p)
+// The tile from position j0 on; AGAIN: whose sums the split operands do not hold.  True: it has to be done again.
+template <class E, bool AGAIN>
+__device__ __forceinline__ bool few_tile(const FewParams &p, int j0, char *lds, int *tab)
 {
     constexpr bool F32 = std::is_same<E, float>::value;
     constexpr int PARTS = F32 ? 3 : 1, NA = (kFewPairs * 64 + 511) / 512, NB = 3, EB = (int)Elem<E>::kBytes;
-    __shared__ __attribute__((aligned(16))) char lds[kFewLds];
-    __shared__ int tab[kFewTaps];
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, lhi = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wn0 = (wave & 3) * 64, wr = wave >> 2;
-    const int j0 = (int)xcd_order(blockIdx.x, gridDim.x) * kFewN;
 
     const __amdgpu_buffer_rsrc_t rin = make_rsrc_bytes(p.in, 0, p.in_bytes), rw = make_rsrc_bytes(p.w, 0, p.w_bytes),
                                  rout = make_rsrc_bytes(p.out, 0, p.out_bytes);
@@ -89,30 +87,45 @@ __global__ __launch_bounds__(512, 2) void conv_few_kernel(FewParams p)
     }
     // the filter: a thread takes eight channels of a tap and row
     uint32_t a_off[NA];
+    int r0, s0, a_row;   // of its row: the filter's element under tap (0, 0), and where it lies; negative: no such row
+    {
+        uint32_t c, a, ah, aw;
+        p.div_block.divmod((uint32_t)(tid & 31), c, a);
+        p.div_vsw.divmod(a, ah, aw);
+        r0 = (int)c < p.C ? (int)ah - p.sh * (p.fh - 1) : -(1 << 20);
+        s0 = (int)aw - p.sw * (p.fw - 1);
+        a_row = (int)c * p.R * p.S;
+    }
     auto place_a = [&](int g) __attribute__((always_inline)) {
 #pragma unroll
         for (int x = 0; x < NA; ++x) {
-            const int e = tid + 512 * x, m = e & 31, tap = 2 * (g * p.pairs + (e >> 6)) + (e >> 5 & 1);
-            uint32_t u, v, c, a, ah, aw;
+            const int e = tid + 512 * x, tap = 2 * (g * p.pairs + (e >> 6)) + (e >> 5 & 1);
+            uint32_t u, v;
             p.div_v.divmod((uint32_t)tap, u, v);
-            p.div_block.divmod((uint32_t)m, c, a);
-            p.div_vsw.divmod(a, ah, aw);
-            const int r = (int)ah + p.sh * ((int)u - p.fh + 1), s = (int)aw + p.sw * ((int)v - p.fw + 1);
-            const bool ok = (int)c < p.C && tap < p.taps && (unsigned)r < (unsigned)p.R && (unsigned)s < (unsigned)p.S;
-            a_off[x] = ok ? (uint32_t)EB * (uint32_t)(((int)c * p.R + r) * p.S + s) : kOob;
+            const int r = r0 + p.sh * (int)u, s = s0 + p.sw * (int)v;
+            const bool ok = tap < p.taps && (unsigned)r < (unsigned)p.R && (unsigned)s < (unsigned)p.S;
+            a_off[x] = ok ? (uint32_t)EB * (uint32_t)(a_row + r * p.S + s) : kOob;
         }
     };
     place_a(0);
-    // this lane's positions: the cell of the last tap
-    int col_cell[2];
+    // this lane's positions: the cell of the last tap; of the one that it stores, image and first pixel
+    int col_cell[2], n = -1, h0 = 0, w0 = 0;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-        const int j = min(j0 + wn0 + 32 * i + l32, p.cols - 1);
-        uint32_t g, u, v, t;
-        p.div_wc.divmod((uint32_t)j, g, u);
+        const int j = j0 + wn0 + 32 * i + l32;
+        uint32_t g, u, v, t, img, cb;
+        p.div_wc.divmod((uint32_t)min(j, p.cols - 1), g, u);
         p.div_hb.divmod(g, v, t);
+        p.div_nb.divmod(v, img, cb);
         const int row = (int)v == v0 ? p.fh * ((int)t - t0) : len0 + ((int)v - v0 - 1) * len + p.fh * (int)t;
         col_cell[i] = (row * p.pitch + (int)u) * 16;
+        const int w = p.vsw * ((int)cb * p.Wc + (int)u);
+        if (i == wr) {
+            // a position behind the last one of its row belongs to the next block or to none
+            n = j < p.cols && w < p.W + p.pw ? (int)img : -1;
+            h0 = p.vsh * (int)t - p.ph;
+            w0 = w - p.pw;
+        }
     }
 
     f32x16 acc[2], low[2];
@@ -120,19 +133,32 @@ __global__ __launch_bounds__(512, 2) void conv_few_kernel(FewParams p)
     const int chunks = (p.K + kFewC - 1) / kFewC, steps = chunks * p.groups;
     const uint32_t in_plane = (uint32_t)EB * (uint32_t)(p.P * p.Q);
 
-    auto pass = [&](auto fp32c) __attribute__((always_inline)) {
-        constexpr bool FP32 = fp32c;   // operands as they are, on the fp32 instructions: cells of eight floats
+    // How the sums are made.  kSplit: as above.  kPlain: fp32 operands as they are, on the fp32 instructions, in cells of eight floats.
+    // A tap that is not there is a zero in a tile's rows, and that times an infinity is no zero.  So when sums are not finite, elements of dy that
+    // are not either count as 1 or -1 in the second time (bf16: kFinite), and two more passes find the sums that they belong to, on bf16
+    // instructions: kSigns adds up the signs of their products with the filter (0 if a product is NaN), kNumber their number, over the taps that
+    // there are.  The sum is infinite if all signs are equal, else NaN; where there are none it stands.
+    enum { kSplit, kPlain, kFinite, kSigns, kNumber };
+    int mode = kSplit;
+    bool odd = false;  // dy is not finite
+    auto load_bits = [](__amdgpu_buffer_rsrc_t r, uint32_t vo, uint32_t so) __attribute__((always_inline)) -> uint32_t {
+        if constexpr (F32) return __builtin_amdgcn_raw_buffer_load_b32(r, (int)vo, (int)so, 0);
+        else return (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(r, (int)vo, (int)so, 0);
+    };
+    auto pass = [&](auto first) __attribute__((always_inline)) {   // first: kSplit or kPlain, or as mode says
+        constexpr int FIRST = first;
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int e = 0; e < 16; ++e) { acc[j][e] = 0.f; low[j][e] = 0.f; }
-        float ra[NA][8], rb[NB][8];
+        uint32_t ra[NA][8], rb[NB][8];   // as they lie in memory
+        auto value = [](uint32_t v) __attribute__((always_inline)) { return __uint_as_float(F32 ? v : v << 16); };
         auto load_a = [&](int c) __attribute__((always_inline)) {
 #pragma unroll
             for (int x = 0; x < NA; ++x)
 #pragma unroll
                 for (int i = 0; i < 8; ++i)   // channels past the last one lie behind the filter and read as zero
-                    ra[x][i] = Elem<E>::load(rw, a_off[x], (uint32_t)EB * (uint32_t)((kFewC * c + i) * p.CRS));
+                    ra[x][i] = load_bits(rw, a_off[x], (uint32_t)EB * (uint32_t)((kFewC * c + i) * p.CRS));
         };
         auto load_b = [&](int c) __attribute__((always_inline)) {
 #pragma unroll
@@ -140,39 +166,45 @@ __global__ __launch_bounds__(512, 2) void conv_few_kernel(FewParams p)
                 if (512 * x >= p.cells) break;
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
-                    uint32_t vo = b_off[x];
-                    if (kFewC * (c + 1) > p.K) vo = kFewC * c + i < p.K ? vo : kOob;   // channels past the last one are the next image's
-                    rb[x][i] = Elem<E>::load(rin, vo, (uint32_t)(kFewC * c + i) * in_plane);
+                    // channels past the last one are the next image's: an offset behind the tensor, also if added to kOob
+                    const int k = kFewC * c + i;
+                    rb[x][i] = load_bits(rin, b_off[x], k < p.K ? (uint32_t)k * in_plane : 0x7FFFFFF0u);
                 }
             }
         };
-        auto put = [&](char *dst, int part, const float (&v)[8]) __attribute__((always_inline)) {
-            if constexpr (FP32) {   // two rows of 16 bytes in the first two parts' places
-                const f32x4 x = {v[0], v[1], v[2], v[3]}, y = {v[4], v[5], v[6], v[7]};
-                *reinterpret_cast<f32x4 *>(dst) = x;
-                *reinterpret_cast<f32x4 *>(dst + part) = y;
-            } else if constexpr (F32) {
+        auto put = [&](char *dst, int part, const uint32_t (&d)[8]) __attribute__((always_inline)) {
+            if constexpr (F32 && FIRST == kSplit) {
                 u32x4 c[3];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     uint32_t h, m, l;
-                    split_pair(v[2 * i], v[2 * i + 1], h, m, l, rest);
+                    split_pair(__uint_as_float(d[2 * i]), __uint_as_float(d[2 * i + 1]), h, m, l, rest);
                     c[0][i] = h; c[1][i] = m; c[2][i] = l;
                 }
 #pragma unroll
                 for (int pl = 0; pl < 3; ++pl) *reinterpret_cast<u32x4 *>(dst + pl * part) = c[pl];
+            } else if constexpr (F32 && FIRST == kPlain) {   // two rows of 16 bytes in the first two parts' places
+                *reinterpret_cast<u32x4 *>(dst) = u32x4{d[0], d[1], d[2], d[3]};
+                *reinterpret_cast<u32x4 *>(dst + part) = u32x4{d[4], d[5], d[6], d[7]};
             } else {
                 u32x4 c;
 #pragma unroll
-                for (int i = 0; i < 4; ++i)   // widened bf16: the high halves
-                    c[i] = __builtin_amdgcn_perm(__float_as_uint(v[2 * i + 1]), __float_as_uint(v[2 * i]), 0x07060302u);
+                for (int i = 0; i < 4; ++i)   // bf16: the low halves; fp32 signs and numbers: the high ones
+                    c[i] = __builtin_amdgcn_perm(d[2 * i + 1], d[2 * i], F32 ? 0x07060302u : 0x05040100u);
                 *reinterpret_cast<u32x4 *>(dst) = c;
             }
         };
+        auto bits = [](float v) __attribute__((always_inline)) { return F32 ? __float_as_uint(v) : __float_as_uint(v) >> 16; };   // of values that bf16 holds
         auto put_a = [&](int buf) __attribute__((always_inline)) {
 #pragma unroll
             for (int x = 0; x < NA; ++x) {
                 const int e = tid + 512 * x;
+                if constexpr (FIRST > kPlain) if (mode >= kSigns)
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        const float v = value(ra[x][i]);
+                        ra[x][i] = bits(mode == kNumber ? a_off[x] != kOob : v > 0.f ? 1.f : v < 0.f ? -1.f : 0.f);
+                    }
                 if (e < p.pairs * 64) put(lds + buf * a_buf + e * 16, a_part, ra[x]);
             }
         };
@@ -180,6 +212,15 @@ __global__ __launch_bounds__(512, 2) void conv_few_kernel(FewParams p)
 #pragma unroll
             for (int x = 0; x < NB; ++x) {
                 const int e = tid + 512 * x;
+                if constexpr (FIRST != kSplit)
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        const float v = value(rb[x][i]), one = copysignf(1.f, v);
+                        const bool finite = fabsf(v) < __builtin_inff();
+                        if (e < p.cells) odd |= !finite;
+                        if (mode < kSigns) rb[x][i] = finite ? rb[x][i] : bits(one);
+                        else rb[x][i] = bits(finite ? 0.f : mode == kNumber ? 1.f : v != v ? 0.f : one);
+                    }
                 if (e < p.cells) put(lds_b + buf * b_buf + e * 16, b_part, rb[x]);
             }
         };
@@ -214,32 +255,45 @@ __global__ __launch_bounds__(512, 2) void conv_few_kernel(FewParams p)
             if (early) stage();
             const char *pa = lds + (s & 1) * a_buf + lane * 16, *pb = lds_b + (c & 1) * b_buf;
             const int *pt = tab + 2 * g * p.pairs + lhi;
-            for (int i = wr; i < p.pairs; i += 2) {
+            auto read = [&](int i, int pl, u32x4 (&va)[PARTS], u32x4 (&vb)[PARTS][2]) __attribute__((always_inline)) {
                 const int off = pt[2 * i];
-                u32x4 va[PARTS], vb[PARTS][2];
+                va[pl] = *reinterpret_cast<const u32x4 *>(pa + i * 1024 + pl * a_part);
 #pragma unroll
-                for (int pl = 0; pl < (FP32 ? 2 : PARTS); ++pl) {
-                    va[pl] = *reinterpret_cast<const u32x4 *>(pa + i * 1024 + pl * a_part);
+                for (int j = 0; j < 2; ++j) vb[pl][j] = *reinterpret_cast<const u32x4 *>(pb + col_cell[j] + off + pl * b_part);
+            };
+            auto product = [&](u32x4 a, u32x4 b, f32x16 &d) __attribute__((always_inline)) {
+                d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), d, 0, 0, 0);
+            };
+            if constexpr (F32 && FIRST == kSplit) {
+                for (int i = wr; i < p.pairs; i += 2) {
+                    u32x4 va[PARTS], vb[PARTS][2];
 #pragma unroll
-                    for (int j = 0; j < 2; ++j) vb[pl][j] = *reinterpret_cast<const u32x4 *>(pb + col_cell[j] + off + pl * b_part);
+                    for (int pl = 0; pl < PARTS; ++pl) read(i, pl, va, vb);
+                    constexpr int PL_A[6] = {0, 2, 1, 1, 0, 0}, PL_B[6] = {0, 0, 1, 0, 1, 2};
+#pragma unroll
+                    for (int m = 0; m < 6; ++m)
+#pragma unroll
+                        for (int j = 0; j < 2; ++j) product(va[PL_A[m] % PARTS], vb[PL_B[m] % PARTS][j], m == 0 ? acc[j] : low[j]);
                 }
-                if constexpr (FP32) {
+            } else if constexpr (F32 && FIRST == kPlain) {
+#pragma unroll 1
+                for (int i = wr; i < p.pairs; i += 2) {
+                    u32x4 va[PARTS], vb[PARTS][2];
+#pragma unroll
+                    for (int pl = 0; pl < 2; ++pl) read(i, pl % PARTS, va, vb);
 #pragma unroll
                     for (int e = 0; e < 8; ++e)
 #pragma unroll
                         for (int j = 0; j < 2; ++j)
-                            acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(va[e >> 2][e & 3]), __uint_as_float(vb[e >> 2][j][e & 3]),
-                                                                          acc[j], 0, 0, 0);
-                } else {
-                    constexpr int PL_A[6] = {0, 2, 1, 1, 0, 0}, PL_B[6] = {0, 0, 1, 0, 1, 2};
+                            acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(va[(e >> 2) % PARTS][e & 3]),
+                                                                          __uint_as_float(vb[(e >> 2) % PARTS][j][e & 3]), acc[j], 0, 0, 0);
+                }
+            } else {
+                for (int i = wr; i < p.pairs; i += 2) {
+                    u32x4 va[PARTS], vb[PARTS][2];
+                    read(i, 0, va, vb);
 #pragma unroll
-                    for (int m = 0; m < (F32 ? 6 : 1); ++m)
-#pragma unroll
-                        for (int j = 0; j < 2; ++j) {
-                            f32x16 &d = m == 0 ? acc[j] : low[j];
-                            d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, va[PL_A[m]]),
-                                                                        __builtin_bit_cast(bf16x8, vb[PL_B[m]][j]), d, 0, 0, 0);
-                        }
+                    for (int j = 0; j < 2; ++j) product(va[0], vb[0][j], acc[j]);
                 }
             }
             if (!early) stage();
@@ -247,71 +301,78 @@ __global__ __launch_bounds__(512, 2) void conv_few_kernel(FewParams p)
             __syncthreads();
         }
     };
-    pass(std::false_type{});
-
-    if constexpr (F32) {
-        // not finite, or below 2^-104 and not zero (see conv_halo.hpp)
-        float not_finite = 0.f;
-        uint32_t least = 0xFFFFFFFFu;
+    // the waves of a pair give each other one of the two tiles
+    auto halves = [&](float (&y)[16]) __attribute__((always_inline)) {
+        float *give = reinterpret_cast<float *>(lds) + wave * 1024 + lane, *take = reinterpret_cast<float *>(lds) + (wave ^ 4) * 1024 + lane;
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int e = 0; e < 16; ++e) give[64 * e] = wr ? acc[0][e] : acc[1][e];
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < 16; ++e) y[e] = (wr ? acc[1][e] : acc[0][e]) + take[64 * e];
+    };
+    typedef std::integral_constant<int, kSplit> Split;
+    typedef std::integral_constant<int, kPlain> Plain;
+    typedef std::integral_constant<int, kFinite> Other;
+    float y[16];
+    int &flag = *reinterpret_cast<int *>(lds + kFewLds - 16);   // (only split operands reach so far)
+    if constexpr (!AGAIN) {
+        if (!F32) flag = 0;
+        pass(Split{});
+        if constexpr (F32) {
+            // not finite, or below 2^-104 and not zero (see conv_halo.hpp)
+            float not_finite = 0.f;
+            uint32_t least = 0xFFFFFFFFu;
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const float v = acc[j][e] + low[j][e];
+                    acc[j][e] = v;
+                    not_finite = fmaf(v, 0.f, not_finite);
+                    least = min(least, (__float_as_uint(v) << 1) - 1u);
+                }
+            if (__syncthreads_or((rest & 0xFFFFu) != 0 || !(not_finite == 0.f) || least < ((127u - 104u) << 24) - 1u)) return true;
+        } else {
+            float sums[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) sums[e & 3] = fmaf(acc[j][e], 0.f, sums[e & 3]);
+            if (!(sums[0] + sums[1] + (sums[2] + sums[3]) == 0.f)) flag = 1;
+            __syncthreads();
+            if (flag) return true;
+        }
+        halves(y);
+    } else {
+        mode = F32 ? kPlain : kFinite;
+        flag = 0;
+        if constexpr (F32) {
+            pass(Plain{});
+            halves(y);
+            mode = kSigns;
+        }
+        float sign[16];
+#pragma unroll 1
+        for (; mode <= kNumber; ++mode) {
+            if (mode == kSigns) {
+                if (odd) flag = 1;
+                __syncthreads();
+                if (!__builtin_amdgcn_readfirstlane(flag)) break;
+            }
+            __syncthreads();
+            pass(Other{});
+            float z[16];
+            halves(z);
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
-                const float v = acc[j][e] + low[j][e];
-                acc[j][e] = v;
-                not_finite = fmaf(v, 0.f, not_finite);
-                least = min(least, (__float_as_uint(v) << 1) - 1u);
+                if (mode == kFinite) y[e] = z[e];
+                else if (mode == kSigns) sign[e] = z[e];
+                else if (z[e] != 0.f) y[e] = fabsf(sign[e]) == z[e] ? y[e] + copysignf(__builtin_inff(), sign[e]) : __builtin_nanf("");
             }
-        const bool redo = (rest & 0xFFFFu) != 0 || !(not_finite == 0.f) || least < ((127u - 104u) << 24) - 1u;
-        if (__syncthreads_or(redo)) pass(std::true_type{});
+        }
     }
 
-    // the waves of a pair give each other one of the two tiles
-    float *give = reinterpret_cast<float *>(lds) + wave * 1024 + lane, *take = reinterpret_cast<float *>(lds) + (wave ^ 4) * 1024 + lane;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) give[64 * e] = wr ? acc[0][e] : acc[1][e];
-    __syncthreads();
-    float y[16];
-#pragma unroll
-    for (int e = 0; e < 16; ++e) y[e] = (wr ? acc[1][e] : acc[0][e]) + take[64 * e];
-
-    const int jo = j0 + wn0 + 32 * wr + l32;
-    if (jo >= p.cols) return;
-    uint32_t gr, uw, v, t, n, cb;
-    p.div_wc.divmod((uint32_t)jo, gr, uw);
-    p.div_hb.divmod(gr, v, t);
-    p.div_nb.divmod(v, n, cb);
-    const int h0 = p.vsh * (int)t - p.ph, w0 = p.vsw * ((int)cb * p.Wc + (int)uw) - p.pw;
-    // a position behind the last one of its row belongs to the next block or to none
-    if ((int)(cb * p.Wc + uw) * p.vsw >= p.W + p.pw) return;
-    // A tap that is not there is a zero in the products above, and one with an infinity is no zero: sums that are not finite are taken
-    // again, tap by tap
-    bool finite = true;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) finite &= fabsf(y[e]) < __builtin_inff();
-    if (!finite)
-#pragma unroll 1
-        for (int e = 0; e < 16; ++e) {
-            uint32_t c, a, ah, aw;
-            p.div_block.divmod((uint32_t)(8 * (e >> 2) + 4 * lhi + (e & 3)), c, a);
-            p.div_vsw.divmod(a, ah, aw);
-            const int h = h0 + (int)ah + p.ph, w = w0 + (int)aw + p.pw;   // of the padded image
-            if ((int)c >= p.C) break;
-            float sum = 0.f;
-            for (int r = h % p.sh; r < p.R; r += p.sh) {
-                if (h < r || (h - r) / p.sh >= p.P) continue;
-                for (int s = w % p.sw; s < p.S; s += p.sw) {
-                    if (w < s || (w - s) / p.sw >= p.Q) continue;
-                    const uint32_t at = (uint32_t)EB * (uint32_t)(((int)n * p.K * p.P + (h - r) / p.sh) * p.Q + (w - s) / p.sw);
-                    const uint32_t tap = (uint32_t)EB * (uint32_t)(((int)c * p.R + r) * p.S + s);
-                    for (int k = 0; k < p.K; ++k)
-                        sum = fmaf(Elem<E>::load(rin, at, (uint32_t)k * in_plane), Elem<E>::load(rw, tap, (uint32_t)EB * (uint32_t)(k * p.CRS)), sum);
-                }
-            }
-#pragma unroll
-            for (int i = 0; i < 16; ++i)
-                if (i == e && !(fabsf(y[i]) < __builtin_inff())) y[i] = sum;
-        }
+    if (n < 0) return false;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const int m = 8 * q + 4 * lhi;
@@ -321,7 +382,7 @@ __global__ __launch_bounds__(512, 2) void conv_few_kernel(FewParams p)
             p.div_vsw.divmod(a, ah, aw);
             const int h = h0 + (int)ah, w = w0 + (int)aw;
             if ((int)c >= p.C || (unsigned)h >= (unsigned)p.H) continue;
-            const uint32_t off = 4u * (uint32_t)((((int)n * p.C + (int)c) * p.H + h) * p.W + w);
+            const uint32_t off = 4u * (uint32_t)(((n * p.C + (int)c) * p.H + h) * p.W + w);
             if (w >= 0 && w + 3 < p.W) {
                 const u32x4 d = {__float_as_uint(y[4 * q]), __float_as_uint(y[4 * q + 1]), __float_as_uint(y[4 * q + 2]), __float_as_uint(y[4 * q + 3])};
                 __builtin_amdgcn_raw_buffer_store_b128(d, rout, (int)off, 0, 0);
@@ -342,6 +403,31 @@ __global__ __launch_bounds__(512, 2) void conv_few_kernel(FewParams p)
             }
         }
     }
+    return false;
+}
+
+// A function of its own, so that its registers are not missing in the other one; it reads the kernel's parameters again.
+template <class E>
+static __device__ __attribute__((noinline)) void few_again(uint32_t args_lo, uint32_t args_hi, int j0, __attribute__((address_space(3))) char *lds,
+                                                           __attribute__((address_space(3))) int *tab)
+{
+    typedef const __attribute__((address_space(4))) uint32_t *Words;
+    const Words from = (Words)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)args_hi) << 32 | (uint32_t)__builtin_amdgcn_readfirstlane((int)args_lo));
+    struct { uint32_t w[sizeof(FewParams) / 4]; } t;
+#pragma unroll
+    for (size_t i = 0; i < sizeof(FewParams) / 4; ++i) t.w[i] = from[i];
+    few_tile<E, true>(__builtin_bit_cast(FewParams, t), __builtin_amdgcn_readfirstlane(j0), (char *)lds, (int *)tab);
+}
+
+template <class E>
+__global__ __launch_bounds__(512, 2) void conv_few_kernel(FewParams p)
+{
+    __shared__ __attribute__((aligned(16))) char lds[kFewLds];
+    __shared__ int tab[kFewTaps];
+    const int j0 = (int)xcd_order(blockIdx.x, gridDim.x) * kFewN;
+    if (!few_tile<E, false>(p, j0, lds, tab)) return;
+    const uint64_t args = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
+    few_again<E>((uint32_t)args, (uint32_t)(args >> 32), j0, (__attribute__((address_space(3))) char *)lds, (__attribute__((address_space(3))) int *)tab);
 }
 
 }  // namespace ucd

@@ -8,7 +8,7 @@ import numpy as np
 import pytest
 
 from paper_1804_04806_amd import ucd
-from hip_helpers import desc_of, inputs, rect, rel_l2, run_hip, run_oracle
+from hip_helpers import check_specials, desc_of, inputs, rect, rel_l2, run_hip, run_oracle, run_oracle_zeros
 
 pytestmark = pytest.mark.gpu
 
@@ -65,6 +65,16 @@ def test_few_channels_not_finite(s):
     assert fine.any() and not fine.all()
     assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isinf(got), np.isinf(ref))
     assert rel_l2(got[fine], ref[fine]) <= 5e-6
+
+
+@pytest.mark.parametrize("s", [NARROW[0], NARROW[2], NARROW[3], WIDE[2], WIDE[3], WIDE[6]], ids=str)
+def test_few_channels_dy_not_finite(s):
+    """The same of dy: in the middle, beside the padding (a zero that an infinity meets there is a NaN, as in the GEMMs) and where a row ends inside
+    a group of eight pixels; the other output channels stay exact.  Together with one of x."""
+    x, _, dy = inputs(s, seed=105)
+    dy[0, 2, s.P // 2, s.Q // 2], dy[1, -1, -1, -1], dy[2, 5, 0, 0], dy[-1, 7, s.P // 2, -1] = np.inf, -np.inf, np.nan, np.inf
+    x[1, 0, 0, 0] = np.inf
+    check_specials(run_hip(s, D, [(I, s.N)], x=x, dy=dy).astype(np.float64), run_oracle_zeros(s, D, x=x, dy=dy), 5e-6)
 
 
 @pytest.mark.parametrize("dtype, s", [(0, rect(16, 3, 61, 59, 32, 7, 7, (2, 2), (0, 0))), (0, rect(256, 3, 227, 227, 96, 11, 11, (4, 4), (0, 0))),
