@@ -90,7 +90,7 @@ static bool few_pays(const Dims &d, int b, FewParams &p)
 {
     if (d.C > 16 || d.R < d.sh || d.S < d.sw || d.R * d.S == 1 || (long)d.H * d.W > 1l << 22) return false;
     if (d.dtype == 1 && d.R * d.S <= 9 && d.K < 48) return false;
-    if (!few_pick(d, b, p)) return false;
+    if (!offsets_in_reach(d.K + 2 * kFewC, (long)d.esize() * d.crs()) || !few_pick(d, b, p)) return false;   // loads of the filter's channels past the last one
     return d.dtype == 1 || d.det || d.sh * d.sw > 1 || p.cols > 127 * kFewN;
 }
 

@@ -102,6 +102,7 @@ bool halo_pays(const Dims &d, int b)
     if (d.dtype != 0 || (d.S != 3 && d.S != 5) || d.sw > 2 || d.R < d.sh) return false;
     if (d.C <= 16 || (long)d.H * d.W > 1l << 22) return false;   // (rows of a tile below 2^31 bytes apart)
     if (!offsets_in_reach((d.K + kHaloC - 1) / kHaloC * kHaloC - 8, 4l * d.P * d.Q)) return false;   // loads of channels past the last one
+    if (!offsets_in_reach(d.K + 2 * kHaloC, 4l * d.crs())) return false;                                                             // and of the filter's
     return with_tile(d, [&](auto t) {
         typedef decltype(t) T;
         HaloParams p{};
