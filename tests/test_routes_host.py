@@ -51,5 +51,5 @@ def test_loads_of_the_filter_past_its_last_channel_keep_their_offsets_below_32_b
     """Filters of close to 2 GB, of which the channels that fill up two chunks would begin behind 2^31."""
     for k, kernel in ((58240, False), (58000, True)):
         assert ("conv_halo_kernel" in described(ucd.BWD_DATA, 1, 1024, 90, 90, k, 3, 3, pads=(1, 1))) == kernel
-    for k, kernel in ((116490, False), (112000, True)):
+    for k, kernel in ((116494, False), (112000, True)):
         assert ("conv_few_kernel" in described(ucd.BWD_DATA, 1, 16, 60, 60, k, 18, 16, (2, 1), (9, 8))) == kernel
