@@ -1,4 +1,4 @@
-// Launch of gemm_kernel_split_few: BackwardFilter of layers with few input channels.
+// Launch of filter_few_kernel: BackwardFilter of layers with few input channels.
 #include <algorithm>
 
 #include "filter_few.hpp"
@@ -73,12 +73,12 @@ static hipError_t launch(const Dims &d, int b, const void *x, const void *dy, fl
     p.dw = dw;
     const long blocks = (long)p.k_blocks * p.c_blocks, splits = splits_of<T>(p);
     if (LaunchLog *log = launch_log()) {
-        log->add("gemm_kernel_split_few<Tile<" + std::to_string(T::MT) + "x" + std::to_string(32 * T::NJ) + ">> tiles=" + std::to_string(blocks) +
+        log->add("filter_few_kernel<Tile<" + std::to_string(T::MT) + "x" + std::to_string(32 * T::NJ) + ">> tiles=" + std::to_string(blocks) +
                  " splits=" + std::to_string(splits) + " batch=1 M=" + std::to_string(d.K) + " N=" + std::to_string(d.crs()) +
                  " K=" + std::to_string(b * d.P * d.Q));
         return hipSuccess;
     }
-    gemm_kernel_split_few<T><<<(unsigned)(blocks * splits), 512, 0, s>>>(p);
+    filter_few_kernel<T><<<(unsigned)(blocks * splits), 512, 0, s>>>(p);
     return hipGetLastError();
 }
 

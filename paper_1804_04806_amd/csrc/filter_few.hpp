@@ -47,7 +47,7 @@ struct FilterFewTile {
 };
 
 template <class T>
-__global__ __launch_bounds__(512, 2) void gemm_kernel_split_few(FilterFewParams p)
+__global__ __launch_bounds__(512, 2) void filter_few_kernel(FilterFewParams p)
 {
     constexpr int WQ = T::WQ, NJ = T::NJ, MT = T::MT, G = T::G, PARTS = T::PARTS, NX = T::NX;
     __shared__ __attribute__((aligned(16))) char lds[T::LDS];

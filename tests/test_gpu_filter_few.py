@@ -1,4 +1,4 @@
-"""gemm_kernel_split_few (BackwardFilter of layers with few input channels, all filter elements of a block of channels at once): strides 1 to 4 and
+"""filter_few_kernel (BackwardFilter of layers with few input channels, all filter elements of a block of channels at once): strides 1 to 4 and
 rows and columns apart, odd and even taps, rows of dy that end inside a group of eight pixels, channels in one and in several
 blocks, 32 and 64 output channels per tile and fewer, blocks of columns, tiles over several images, accumulation, values out of the split's
 range and values that are not finite, layers that it does not take.
@@ -28,7 +28,7 @@ def described(s, dtype):
 
 @pytest.mark.parametrize("s", NARROW + WIDE, ids=str)
 def test_few_channels(s):
-    assert "gemm_kernel_split_few" in described(s, 0)
+    assert "filter_few_kernel" in described(s, 0)
     x, _, dy = inputs(s, seed=101)
     ref = run_oracle(s, D, x=x, dy=dy)
     assert rel_l2(run_hip(s, D, [(I, s.N)], x=x, dy=dy), ref) <= 3e-6
@@ -81,4 +81,4 @@ def test_few_channels_dy_not_finite(s):
                                       (0, rect(128, 17, 112, 112, 32, 7, 7, (2, 2), (3, 3))), (1, NARROW[0]), (0, rect(200, 3, 224, 224, 32, 7, 7, (2, 2), (3, 3))), (0, rect(256, 3, 112, 112, 64, 3, 3, (1, 1), (1, 1)))],
                          ids=str)
 def test_layers_that_it_does_not_take(dtype, s):
-    assert "gemm_kernel_split_few" not in described(s, dtype)
+    assert "filter_few_kernel" not in described(s, dtype)
