@@ -82,8 +82,9 @@ static void consider(const Dims &d, int b, int cus, int tile, double start, doub
     if (us < best.us) { best.us = us; best.tile = tile; best.p = p; }
 }
 
-// Wherever a tile's window fits: rows of four pixels and more (a run is loaded from inside its row), padding of up to two.  An odd
-// number of channels would let the last run of the filter end in half a word, which reads as zero behind the tensor.
+// Wherever a tile's window fits: rows of four pixels and more (a run is loaded from inside its row), padding of up to two.  With an odd
+// number of channels every other row of the filter begins in the middle of a word (BackwardData: every other channel of it), and the last
+// word that holds elements ends behind the tensor, which the range check, by whole words, lets read as zero.
 template <int OP>
 static bool window_conv_op(const Dims &d, int b, const void *in, const void *w, void *out, hipStream_t s, hipError_t &e)
 {
