@@ -50,6 +50,7 @@ static bool few_grid(const Dims &d, int b, int fh, int fw, FewParams &p)
 // Time in us: whole rounds of workgroups, one per CU, of a start and, per chunk of eight channels, the pairs of taps multiplied, a step's filter
 // cells and the window's cells.  Fitted to 813 launches (1 to 256 images of 7x7 to 227x227, 1 to 32 channels in, 16 to 512 out, filters of 3x3
 // to 11x11, strides 1, 2 and 4), standard deviation 6 % fp32 and 5 % bf16; the block so chosen takes 1.01 times the best one's time in the mean.
+// Of 3000 launches of the kernel as it is now the model is 1.05 (fp32) and 1.1 times the time, standard deviation 7 and 10 %.
 static double few_us(const Dims &d, const FewParams &p, long cus)
 {
     const long wgs = (p.cols + kFewN - 1) / kFewN, rounds = (wgs + cus - 1) / cus;
@@ -58,7 +59,7 @@ static double few_us(const Dims &d, const FewParams &p, long cus)
     return (f32 ? 1.2 : 1.8) + rounds * ((f32 ? 6.3 : 5.3) + chunks * (p.groups * ((f32 ? 0.2 : 0.048) * p.pairs + 0.7) + (f32 ? 0.3 : 0.34) * p.cells / 512));
 }
 
-static bool few_pick(const Dims &d, int b, FewParams &best)
+static double few_pick(const Dims &d, int b, FewParams &best)   // its time
 {
     const bool f32 = d.dtype == 0;
     const int chunks = (d.K + kFewC - 1) / kFewC, cus = device_cus();
@@ -78,19 +79,22 @@ static bool few_pick(const Dims &d, int b, FewParams &best)
             const double us = few_us(d, p, cus);
             if (us <= least) { least = us; best = p; }
         }
-    return least < 1e30;
+    return least;
 }
 
-// Up to 16 input channels, filters whose every stride phase has a tap.  fp32 layers of stride 1 whose launch has fewer than 128 workgroups split
-// their reductions in the implicit GEMMs (not in reproducible mode); bf16 layers of up to nine taps and 47 output channels are
-// bound by memory either way.  Of 372 other layers drawn as above the implicit GEMMs' time / this kernel's is 2.2 in the
-// geometric mean, 0.91 at least, two below 0.97 (3 -> 64 7x7/2 224x224 b = 128: 818 -> 432 us, bf16 482 -> 280; 3 -> 64 7x7 112x112 b = 64 1759 -> 526;
-// 3 -> 64 11x11 64x64 b = 32 810 -> 430); where it is not taken for its workgroups 0.75 to 0.09.
+// Up to 16 input channels, filters whose every stride phase has a tap, where the model of the implicit GEMMs comes to 1.15 times this kernel's.
+// fp32 layers of stride 1 whose launch has fewer than 128 workgroups split their reductions there (not in reproducible mode: where
+// it was not taken for them 0.75 to 0.09); bf16 layers of up to nine taps and 47 output channels are bound by memory either way.  Of 1500 layers drawn
+// at random that it takes (1 to 256 images of 7x7 to 227x600, 1 to 1024 channels out, filters of 2x2 to 11x11, strides 1 to 4) their time / this
+// kernel's is 2.3 in the geometric mean, 0.90 at least, one below 0.97; of 1390 that the models leave to them it would be 0.8, 0.27 at least (few
+// output channels, filters no larger than the stride: 6 -> 39 2x2/2 100x218 b = 60 30 us against 70).  3 -> 64 7x7/2 224x224 b = 128:
+// 865 -> 407 us, bf16 486 -> 232; 3 -> 64 7x7 112x112 b = 64 1737 -> 520; 3 -> 64 11x11 64x64 b = 32 810 -> 430.
 static bool few_pays(const Dims &d, int b, FewParams &p)
 {
     if (d.C > 16 || d.R < d.sh || d.S < d.sw || d.R * d.S == 1 || (long)d.H * d.W > 1l << 22) return false;
     if (d.dtype == 1 && d.R * d.S <= 9 && d.K < 48) return false;
-    if (!offsets_in_reach(d.K + 2 * kFewC, (long)d.esize() * d.crs()) || !few_pick(d, b, p)) return false;   // loads of the filter's channels past the last one
+    if (!offsets_in_reach(d.K + 2 * kFewC, (long)d.esize() * d.crs())) return false;   // loads of the filter's channels past the last one
+    if (1.15 * few_pick(d, b, p) > implicit_bwd_data_us(d, b)) return false;
     return d.dtype == 1 || d.det || d.sh * d.sw > 1 || p.cols > 127 * kFewN;
 }
 

@@ -113,30 +113,34 @@ static void phase_shape(const Dims &d, int a, int c, int &h0, int &w0, int &Hh, 
     Sc = c < d.S ? (d.S - c + d.sw - 1) / d.sw : 0;
 }
 
-// Time in us of the launches below (fp32), as measured: a workgroup's reduction rows follow one another, and beyond one
+// Time in us of the launches below, as measured: a workgroup's reduction rows follow one another, and beyond one
 // workgroup per CU the rows of all share its matrix pipes; both go with the size of the tile.  1700 strided layers (1 to 128
 // images of 7x7 to 112x112, 17 to 1024 -> 32 to 2048 channels, 3 to 7 filter rows, 3 and 5 columns, row strides 1 to 4), both
-// modes: model / measured within a fifth in four of five (least 0.5, most 2).
+// modes: model / measured within a fifth in four of five (least 0.5, most 2); 2000 layers of 1 to 16 -> 1 to 1024 channels 0.7 to 1.2 in four of five.
+// bf16: 1020 layers of 1 to 16 channels, standard deviation 12 % (0.7 to 1.25).
 double implicit_bwd_data_us(const Dims &d, int b)
 {
-    auto launch_us = [](int M, int N, int Kd, int splits) {
+    const bool bf = d.dtype == 1;
+    const int cus = device_cus();
+    auto launch_us = [&](int M, int N, int Kd, int splits) {
         const TilePick t = pick_tile(M, N, true, splits);
-        const double size = t.bm * t.bn / 16384., more = (double)t.blocks(M, N, splits) / device_cus() - 1;
+        const double size = t.bm * t.bn / 16384., more = (double)t.blocks(M, N, splits) / cus - 1;
+        if (bf) return 1.9 + Kd * (0.022 + size * (0.03 + 0.043 * (more > 0 ? more : 0))) + 1.5e-6 * M * N;
         return 5.9 + Kd / splits * (0.012 + size * (0.088 + 0.12 * (more > 0 ? more : 0)));
     };
     if (const int f = merged_phase_factor(d)) {
         const int Hb = (d.H - 1 + d.ph) / (f * d.sh) + 1, Wb = (d.W - 1 + d.pw) / (f * d.sw) + 1;
         const int U = (d.R + d.sh - 1) / d.sh + f - 1, V = (d.S + d.sw - 1) / d.sw + f - 1;
-        return launch_us(d.C * f * d.sh * f * d.sw, b * Hb * Wb, d.K * U * V, 1);
+        return (bf ? 2.8 : 0) + launch_us(d.C * f * d.sh * f * d.sw, b * Hb * Wb, d.K * U * V, 1);
     }
-    double us = 0;
+    double us = bf ? 2.8 : 0;
     bool any_split = false;
     for (int a = 0; a < d.sh; ++a)
         for (int c = 0; c < d.sw; ++c) {
             int h0, w0, Hh, Ww, Ra, Sc;
             phase_shape(d, a, c, h0, w0, Hh, Ww, Ra, Sc);
             if (Hh == 0 || Ww == 0 || Ra == 0 || Sc == 0) continue;
-            const int splits = output_splits(d.C, b * Hh * Ww, d.K * Ra * Sc, !d.det);
+            const int splits = output_splits(d.C, b * Hh * Ww, d.K * Ra * Sc, !bf && !d.det);
             any_split = any_split || splits > 1;
             us += launch_us(d.C, b * Hh * Ww, d.K * Ra * Sc, splits);
         }

@@ -42,7 +42,7 @@ bool small_pays(const Dims &d, int op, int b);
 hipError_t small_conv(const Dims &d, int op, int b, const void *a, const void *bsrc, void *out, float beta, hipStream_t s);
 
 // BackwardData of fp32 layers over a window in LDS (conv_halo.hip), zero workspace
-double implicit_bwd_data_us(const Dims &d, int b);   // of the implicit GEMMs themselves, fp32
+double implicit_bwd_data_us(const Dims &d, int b);   // of the implicit GEMMs themselves
 bool halo_pays(const Dims &d, int b);
 hipError_t halo_bwd_data(const Dims &d, int b, const void *dy, const void *w, void *dx, hipStream_t s);
 

@@ -17,10 +17,10 @@ D, I = ucd.BWD_DATA, ucd.ALGO_IMPLICIT
 
 # (n, c, h, w, k, r, s, strides, pads)
 STRIDED = [rect(9, 3, 45, 61, 37, 7, 7, (2, 2), (3, 3)), rect(30, 3, 30, 29, 50, 7, 7, (2, 2), (0, 0)), rect(40, 1, 33, 34, 51, 11, 11, (4, 4), (0, 2)),
-           rect(12, 2, 40, 130, 60, 5, 5, (2, 2), (2, 1)), rect(70, 4, 23, 21, 49, 3, 3, (2, 2), (1, 1)), rect(25, 8, 26, 27, 63, 5, 3, (2, 2), (0, 1)),
+           rect(12, 2, 40, 130, 60, 5, 5, (2, 2), (2, 1)), rect(70, 4, 23, 21, 49, 3, 3, (2, 2), (1, 1)), rect(25, 8, 26, 27, 63, 7, 5, (2, 2), (0, 1)),
            rect(16, 3, 38, 40, 55, 7, 5, (3, 1), (2, 2)), rect(16, 5, 36, 41, 48, 4, 7, (1, 2), (1, 3)), rect(3, 1, 150, 200, 52, 6, 6, (2, 3), (5, 0)),
-           rect(90, 2, 17, 16, 57, 9, 8, (4, 4), (3, 3)), rect(700, 7, 9, 8, 65, 5, 5, (2, 2), (2, 2)), rect(60, 3, 113, 114, 17, 7, 7, (2, 2), (3, 3)),
-           rect(60, 2, 110, 115, 21, 7, 7, (2, 2), (2, 3))]
+           rect(90, 2, 40, 39, 57, 13, 15, (4, 4), (3, 3)), rect(1400, 7, 9, 8, 65, 5, 5, (2, 2), (2, 2)), rect(60, 3, 113, 114, 17, 7, 7, (2, 2), (3, 3)),
+           rect(60, 2, 110, 115, 53, 7, 7, (2, 2), (2, 3))]
 PLAIN = [rect(24, 3, 112, 113, 21, 7, 7, (1, 1), (3, 3)), rect(140, 16, 25, 23, 33, 3, 3, (1, 1), (1, 1)), rect(60, 1, 60, 130, 18, 5, 4, (1, 1), (0, 3)),
          rect(100, 3, 44, 40, 19, 11, 11, (1, 1), (5, 5)), rect(500, 9, 13, 12, 40, 3, 5, (1, 1), (2, 2)), rect(33, 2, 64, 300, 17, 3, 3, (1, 1), (1, 0))]
 
@@ -103,6 +103,7 @@ def test_few_channels_not_finite_time(s, dtype):
 
 
 @pytest.mark.parametrize("s", [rect(9, 17, 45, 61, 37, 7, 7, (2, 2), (3, 3)), rect(9, 3, 45, 61, 37, 1, 7, (2, 2), (0, 3)),
-                               rect(9, 3, 45, 61, 37, 1, 1, (1, 1), (0, 0)), rect(4, 3, 30, 31, 200, 7, 7, (1, 1), (3, 3))], ids=str)
+                               rect(9, 3, 45, 61, 37, 1, 1, (1, 1), (0, 0)), rect(4, 3, 30, 31, 200, 7, 7, (1, 1), (3, 3)), rect(48, 5, 136, 248, 35, 2, 2, (2, 2), (1, 1)),
+                               rect(90, 2, 17, 16, 57, 9, 8, (4, 4), (3, 3)), rect(12, 1, 214, 214, 1, 11, 11, (1, 1), (5, 5))], ids=str)
 def test_layers_that_it_does_not_take(s):
     assert "conv_few_kernel" not in described(s, 0)
