@@ -85,10 +85,15 @@ static void consider(const Dims &d, int b, int cus, int tile, double start, doub
 // Wherever a tile's window fits: rows of four pixels and more (a run is loaded from inside its row), padding of up to two.  With an odd
 // number of channels every other row of the filter begins in the middle of a word (BackwardData: every other channel of it), and the last
 // word that holds elements ends behind the tensor, which the range check, by whole words, lets read as zero.
+// Of few channels most of a chunk is zeros, and the element-wise GEMM, which stops at the last one, is as fast or faster (time of it / of
+// this kernel): up to 8 channels in Forward 1.04 in the mean of 152 layers, 0.67 at least, where rows are not as long as the image's; where they
+// are, the GEMM with vector loads 1.88 and 1.34 (172 layers); BackwardData of up to 4 channels 1.04 and 0.70 (278 layers), of 5 to 8 1.28 and
+// 0.97 (87) up to 16 M pixels of dx, 0.88 at least beyond.  With 9 and 10 1.3 to 1.5, 0.99 at least.
 template <int OP>
 static bool window_conv_op(const Dims &d, int b, const void *in, const void *w, void *out, hipStream_t s, hipError_t &e)
 {
     if (d.dtype != 1 || d.R != 3 || d.S != 3 || d.sh != 1 || d.sw != 1 || d.C % 2) return false;
+    if (OP == 0 ? d.C <= 8 && d.Q != d.W : d.K <= 4 || (d.K <= 8 && (double)b * d.C * d.H * d.W >= 16e6)) return false;
     typedef WindowTile<OP, 4, 2, 8> T0;
     typedef WindowTile<OP, 2, 2, 8> T1;
     typedef WindowTile<OP, 2, 1, 8> T2;
