@@ -38,11 +38,14 @@ static void filter_window_params(const Dims &d, int b, FilterWindowParams &p)
 // From 20 Gflop on where images are whole runs of four pixels (113 layers of 1 to 256 images of 7x7 to 227x227 and 9 to 1024 channels, time of
 // gemm_kernel_bf16q / of this kernel 1.31 in the geometric mean, 1.00 at least; 16 Gflop 0.85, 12 0.78: the atomics outweigh
 // the rest), from 8 where they are not (74 layers, gemm_kernel_bf16, 1.51 and 1.13; 6 Gflop 0.89).  Rows of four pixels and
-// more, because they are loaded in fours from inside the row.
+// more, because they are loaded in fours from inside the row.  Where less than three fifths of the units' 4 x 8 pixels are dy's, gemm_kernel_bf16q
+// loses nothing to padding: 13 layers 1.09, 0.82 at least; gemm_kernel_bf16 is the slower one there too (37 layers, 1.41 and 0.99).  Of 960 other
+// layers that it takes 1.55, two below 0.92 (9 Gflop).
 static bool filter_window_pays(const Dims &d, int b)
 {
     if (d.dtype != 1 || d.det || d.R != 3 || d.S != 3 || d.sh != 1 || d.sw != 1 || d.W < 4 || d.Q < 4 || d.ph > 2 || d.pw > 2) return false;
-    return 2. * d.K * d.crs() * ((double)b * d.P * d.Q) >= (d.P * d.Q % 4 == 0 ? 20e9 : 8e9);
+    const double flops = 2. * d.K * d.crs() * ((double)b * d.P * d.Q), units = (d.P + 3) / 4 * 4. * ((d.Q + 7) / 8 * 8.);
+    return d.P * d.Q % 4 == 0 ? flops >= 20e9 && d.P * d.Q >= 0.6 * units : flops >= 8e9;
 }
 
 bool filter_window(const Dims &d, int b, const void *x, const void *dy, float *dw, float beta, hipStream_t s, hipError_t &e)
