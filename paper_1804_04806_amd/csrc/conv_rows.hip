@@ -98,7 +98,9 @@ static hipError_t launch(const Dims &d, int b, const void *x, const void *w, voi
 // kernel's is 0.85 to 1.7 in fp32 from three tiles per workgroup on; with three quarters of the products real and sums of 60 products, 1.41 in the
 // geometric mean of 37 and 1.17 at least, with fewer of either 0.96 and 0.87, below two tiles down to 0.54.  bf16 (a sixth of the
 // multiplications for the same window): eight tiles and 100 products 1.29, 1.18 at least; six tiles 1.06; three 0.79; more than one row
-// tile 0.87.  Of 112 other layers that it takes 1.38 and 1.04 (bf16 1.38 and 1.22).
+// tile 0.87.  The tile GEMMs hold the 16 taps of 4x4 filters without a rest: under a column stride 1.04 and 0.77 (55 layers); and with many row
+// tiles few workgroups share the columns: from six on, a last round of less than 0.85 of them 1.18 and 0.86 (55 layers).  Of 600 other layers
+// that it takes 1.32 and 0.89, six below 0.97.
 template <class E>
 static int pick(const Dims &d, int b, RowsParams &p)
 {
@@ -108,6 +110,9 @@ static int pick(const Dims &d, int b, RowsParams &p)
     if (1.5 * b * d.P * d.Q < 256. * (d.dtype == 1 ? 8 : 3) * (device_cus() / ((d.K + 32 * wm - 1) / (32 * wm)) - 1)) return 0;
     if (!(wm == 1 ? rows_grid<RowsTile<E, 1>>(d, b, p) : wm == 2 ? rows_grid<RowsTile<E, 2>>(d, b, p) : rows_grid<RowsTile<E, 3>>(d, b, p))) return 0;
     if ((long)p.tiles_n < (d.dtype == 1 ? 8l : 3l) * per_row(p) || (d.dtype == 1 && p.tiles_m > 1)) return 0;
+    if (d.dtype == 0 && d.R == 4 && d.S == 4 && d.sw > 1) return 0;
+    const int per = per_row(p), rounds = (p.tiles_n + per - 1) / per;
+    if (p.tiles_m > 5 && p.tiles_n < 0.85 * per * rounds) return 0;
     return 4.0 * d.crs() * d.K > 3.0 * (16.0 * p.steps) * (32.0 * wm * p.tiles_m) ? wm : 0;
 }
 

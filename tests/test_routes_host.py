@@ -20,9 +20,8 @@ def test_rows_kernel_keeps_the_offsets_of_its_stores_below_32_bits():
 
 def test_loads_of_channels_past_the_last_one_keep_their_offsets_below_32_bits():
     """The same for the channels that fill up a chunk: planes such that the chunk's last one begins at 2^31 and more."""
-    for op in (ucd.FWD, ucd.BWD_DATA):
-        assert "conv_window_kernel" not in described(op, 1, 2, 12500, 12500, 2, 3, 3, pads=(1, 1), dtype=1)
-        assert "conv_window_kernel" in described(op, 1, 2, 12000, 12000, 2, 3, 3, pads=(1, 1), dtype=1)
+    assert "conv_window_kernel" not in described(ucd.FWD, 1, 2, 12500, 12500, 2, 3, 3, pads=(1, 1), dtype=1)
+    assert "conv_window_kernel" in described(ucd.FWD, 1, 2, 12000, 12000, 2, 3, 3, pads=(1, 1), dtype=1)
     for pad, kernel in ((560, False), (1, True)):   # planes of 294 MB and of 17
         assert ("conv_halo_kernel" in described(ucd.BWD_DATA, 1, 64, 64, 1 << 16, 1, 3, 3, pads=(pad, 1))) == kernel
 
@@ -53,3 +52,20 @@ def test_loads_of_the_filter_past_its_last_channel_keep_their_offsets_below_32_b
         assert ("conv_halo_kernel" in described(ucd.BWD_DATA, 1, 1024, 90, 90, k, 3, 3, pads=(1, 1))) == kernel
     for k, kernel in ((116494, False), (112000, True)):
         assert ("conv_few_kernel" in described(ucd.BWD_DATA, 1, 16, 60, 60, k, 18, 16, (2, 1), (9, 8))) == kernel
+
+
+def test_layers_that_the_tile_gemms_are_faster_on():
+    """Few channels, reductions or pixels that leave a window kernel's tiles mostly empty; beside each a layer of its kind that is taken."""
+    def takes(kernel, *a, **k):
+        return kernel in described(*a, **k)
+    for dtype in (0, 1):   # BackwardData: filters no larger than the stride, few output channels
+        assert not takes("conv_few_kernel", ucd.BWD_DATA, 48, 5, 136, 248, 70, 2, 2, (2, 2), (1, 1), dtype=dtype)
+        assert not takes("conv_few_kernel", ucd.BWD_DATA, 12, 1, 214, 214, 1, 11, 11, pads=(5, 5), dtype=dtype)
+        assert takes("conv_few_kernel", ucd.BWD_DATA, 48, 3, 136, 248, 70, 7, 7, (2, 2), (3, 3), dtype=dtype)
+    assert not takes("conv_window_kernel", ucd.FWD, 59, 4, 172, 67, 36, 3, 3, dtype=1) and takes("conv_window_kernel", ucd.FWD, 59, 4, 172, 67, 36, 3, 3, pads=(1, 1), dtype=1)
+    assert takes("conv_window_kernel", ucd.FWD, 59, 10, 172, 67, 36, 3, 3, dtype=1)
+    for k, w, taken in ((3, 27, False), (6, 27, False), (6, 4, True), (9, 27, True)):
+        assert takes("conv_window_kernel", ucd.BWD_DATA, 203, 68, 95, w, k, 3, 3, pads=(0, 1), dtype=1) == taken
+    assert not takes("filter_window_kernel", ucd.BWD_FILTER, 20, 799, 141, 6, 502, 3, 3, dtype=1) and takes("filter_window_kernel", ucd.BWD_FILTER, 20, 799, 141, 7, 502, 3, 3, dtype=1)
+    for s, k, taken in ((4, 64, False), (5, 64, True), (5, 700, False)):
+        assert takes("conv_rows_kernel", ucd.FWD, 36, 5, 69, 69, k, 4, s, (2, 3), (2, 2)) == taken
