@@ -67,5 +67,7 @@ def test_layers_that_the_tile_gemms_are_faster_on():
     for k, w, taken in ((3, 27, False), (6, 27, False), (6, 4, True), (9, 27, True)):
         assert takes("conv_window_kernel", ucd.BWD_DATA, 203, 68, 95, w, k, 3, 3, pads=(0, 1), dtype=1) == taken
     assert not takes("filter_window_kernel", ucd.BWD_FILTER, 20, 799, 141, 6, 502, 3, 3, dtype=1) and takes("filter_window_kernel", ucd.BWD_FILTER, 20, 799, 141, 7, 502, 3, 3, dtype=1)
-    for s, k, taken in ((4, 64, False), (5, 64, True), (5, 700, False)):
-        assert takes("conv_rows_kernel", ucd.FWD, 36, 5, 69, 69, k, 4, s, (2, 3), (2, 2)) == taken
+    for r, sw, taken in ((4, 2, False), (4, 1, True), (5, 2, True)):
+        assert takes("conv_rows_kernel", ucd.FWD, 100, 5, 100, 100, 64, r, 4, (2, sw), (2, 2)) == taken
+    for n, taken in ((4, False), (5, True)):
+        assert takes("conv_rows_kernel", ucd.FWD, n, 3, 130, 147, 640, 11, 7, (2, 2), (5, 3)) == taken
