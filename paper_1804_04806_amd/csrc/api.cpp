@@ -233,7 +233,7 @@ struct Timing {
 };
 std::map<BenchKey, Timing> g_cache;
 std::mutex g_cache_mu;
-constexpr int kVersion = 105;   // goes up with every change of the kernels' times
+constexpr int kVersion = 106;   // goes up with every change of the kernels' times
 
 BenchKey key_of(const ucd_layer_t *L, int op, int algo, int b)
 {
