@@ -177,9 +177,10 @@ __global__ __launch_bounds__(512, T::kPair ? 4 : 2) void conv_window_kernel(Wind
                 u32x2 keep = {0xFFFFFFFFu, 0xFFFFFFFFu};
                 const bool tail = kWinC * (c + 1) > p.Ci;   // behind the last channel the next row begins
                 if (tail) {
+                    // (channels are even; without the masks of an odd rest the kernel is compiled to be 3 % slower)
                     const int left = p.Ci - kWinC * c - 4 * q;
-                    keep[0] = left >= 2 ? 0xFFFFFFFFu : 0u;   // (channels are even)
-                    keep[1] = left >= 4 ? 0xFFFFFFFFu : 0u;
+                    keep[0] = left >= 2 ? 0xFFFFFFFFu : left == 1 ? 0xFFFFu : 0u;
+                    keep[1] = left >= 4 ? 0xFFFFFFFFu : left == 3 ? 0xFFFFu : 0u;
                 }
                 dst += (q >> 1) * T::A_HALF + (m ^ ((q >> 1) << 3)) * 16 + (q & 1) * 8;
 #pragma unroll
