@@ -13,9 +13,11 @@
 // 64 positions, so that an operand of the filter serves two tiles (with 32 positions and all pairs LDS alone would take as long as the MFMAs), and the
 // two sums meet at the end.
 //
-// 3 -> 64 7x7/2 224x224 b = 128: 818 us as tile GEMMs of merged phases on the fp32 instructions, 432 with this; its MFMAs alone, with three
-// quarters of the rows and 61 % of the taps real, would be 180.  39 % of the matrix pipe's cycles are MFMAs, with 5.9 other vector instructions
-// each (the split of the window's cells, half of them, and of the filter's); operands read a pair ahead made it 3 % slower.
+// 3 -> 64 7x7/2 224x224 b = 128: 807 us as tile GEMMs of merged phases on the fp32 instructions, 413 with this (bf16 482, 231); its MFMAs
+// alone, with three quarters of the rows and 61 % of the taps real, would be 180.  37 % of the matrix pipe's cycles are MFMAs, with 6.0 other vector
+// instructions each (the split of the window's cells, half of them, and of the filter's); operands read a pair ahead made it 3 % slower.
+// What a tile of which not all sums are finite or in range needs besides is a function of its own: in the kernel itself its
+// scalar registers were spilled in the loop, 3 to 13 % of the time.
 #pragma once
 #include "gemm_split.hpp"
 

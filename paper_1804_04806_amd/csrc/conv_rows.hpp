@@ -10,7 +10,7 @@
 // positions (which run over images, blocks of Wc columns, rows, columns of the block).  Of these it keeps one window with all channels; the
 // next one's pixels are on their way to registers while it multiplies, and are split into its place between two barriers.
 //
-// 3 -> 64 7x7/2 224x224 b = 128: 355 us as tile GEMMs on the fp32 instructions, 237 with this; 42 % of the matrix pipe's cycles are MFMAs.  Its
+// 3 -> 64 7x7/2 224x224 b = 128: 357 us as tile GEMMs on the fp32 instructions, 223 with this (bf16 170, 107); 42 % of the matrix pipe's cycles are MFMAs.  Its
 // memory alone (411 of 488 MB are stores) would take 93 at a copy's rate, its MFMAs, 16 % on zeros, 97.  What is left is that a CU's
 // eight waves multiply, split and store together: sums stored while the next tile is multiplied (284 to 249 us against storing
 // them at the tile's end, 246 and 258 with twice and four times the stores per step), narrow blocks of columns (249 to 237).  Two

@@ -12,8 +12,8 @@
 // that the filter's sums, the larger part of which are registers, are held once per share of the groups and meet at the end, in LDS and
 // then by atomics.  LDS holds two tiles: one is multiplied while the next is split into place and the one after is on its way.
 //
-// 3 -> 64 7x7/2 224x224 b = 128: 437 us as tile GEMMs (397 in two micro-batches), 280 with this; its MFMAs, 8 % on columns that do not exist, would
-// take 98, its bytes 93.  What is left is 7.5 vector instructions per MFMA (the splits, and x's addresses) and LDS, where an operand's 32
+// 3 -> 64 7x7/2 224x224 b = 128: 385 us as tile GEMMs, 266 with this; its MFMAs, 8 % on columns that do not exist, would
+// take 98, its bytes 93.  What is left is 7.4 vector instructions per MFMA (the splits, and x's addresses) and LDS, where an operand's 32
 // columns meet 2.2 times on a bank.  A window row has an odd number of pairs per phase for that: 3 -> 64 7x7 120x120 b = 73 with
 // three groups to a block 238 -> 182 us.  Waves that stage at different ends of a tile made it 3 % slower, and x's addresses
 // kept in registers, which then spill, 11 %.
