@@ -88,7 +88,7 @@ static double few_pick(const Dims &d, int b, FewParams &best)   // its time
 // at random that it takes (1 to 256 images of 7x7 to 227x600, 1 to 1024 channels out, filters of 2x2 to 11x11, strides 1 to 4) their time / this
 // kernel's is 2.3 in the geometric mean, 0.90 at least, one below 0.97; of 1390 that the models leave to them it would be 0.8, 0.27 at least (few
 // output channels, filters no larger than the stride: 6 -> 39 2x2/2 100x218 b = 60 30 us against 70).  3 -> 64 7x7/2 224x224 b = 128:
-// 807 -> 413 us, bf16 482 -> 231; 3 -> 64 7x7 112x112 b = 64 1760 -> 520; 3 -> 64 11x11 64x64 b = 32 809 -> 428.
+// 807 -> 413 us, bf16 482 -> 225; 3 -> 64 7x7 112x112 b = 64 1760 -> 508; 3 -> 64 11x11 64x64 b = 32 809 -> 428.
 static bool few_pays(const Dims &d, int b, FewParams &p)
 {
     if (d.C > 16 || d.R < d.sh || d.S < d.sw || d.R * d.S == 1 || (long)d.H * d.W > 1l << 22) return false;

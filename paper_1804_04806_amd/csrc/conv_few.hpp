@@ -13,11 +13,11 @@
 // 64 positions, so that an operand of the filter serves two tiles (with 32 positions and all pairs LDS alone would take as long as the MFMAs), and the
 // two sums meet at the end.
 //
-// 3 -> 64 7x7/2 224x224 b = 128: 807 us as tile GEMMs of merged phases on the fp32 instructions, 413 with this (bf16 482, 231); its MFMAs
+// 3 -> 64 7x7/2 224x224 b = 128: 807 us as tile GEMMs of merged phases on the fp32 instructions, 413 with this (bf16 482, 225); its MFMAs
 // alone, with three quarters of the rows and 61 % of the taps real, would be 180.  37 % of the matrix pipe's cycles are MFMAs, with 6.0 other vector
 // instructions each (the split of the window's cells, half of them, and of the filter's); operands read a pair ahead made it 3 % slower.
-// What a tile of which not all sums are finite or in range needs besides is a function of its own: in the kernel itself its
-// scalar registers were spilled in the loop, 3 to 13 % of the time.
+// A tile of which not all sums are finite or in range is begun anew, with parameters read again, so that nothing of it is live in the loop
+// of the others, whose scalar registers are all in use (3 to 13 % of the time when they were spilled there).
 #pragma once
 #include "gemm_split.hpp"
 
@@ -333,7 +333,7 @@ __device__ __forceinline__ bool few_tile(const FewParams &p, int j0, char *lds, 
                     not_finite = fmaf(v, 0.f, not_finite);
                     least = min(least, (__float_as_uint(v) << 1) - 1u);
                 }
-            if (__syncthreads_or((rest & 0xFFFFu) != 0 || !(not_finite == 0.f) || least < ((127u - 104u) << 24) - 1u)) return true;
+            if (__builtin_expect(__syncthreads_or((rest & 0xFFFFu) != 0 || !(not_finite == 0.f) || least < ((127u - 104u) << 24) - 1u), 0)) return true;
         } else {
             float sums[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -342,7 +342,7 @@ __device__ __forceinline__ bool few_tile(const FewParams &p, int j0, char *lds, 
                 for (int e = 0; e < 16; ++e) sums[e & 3] = fmaf(acc[j][e], 0.f, sums[e & 3]);
             if (!(sums[0] + sums[1] + (sums[2] + sums[3]) == 0.f)) flag = 1;
             __syncthreads();
-            if (flag) return true;
+            if (__builtin_expect(flag, 0)) return true;
         }
         halves(y);
     } else {
@@ -408,17 +408,17 @@ __device__ __forceinline__ bool few_tile(const FewParams &p, int j0, char *lds, 
     return false;
 }
 
-// A function of its own, so that its registers are not missing in the other one; it reads the kernel's parameters again.
-template <class E>
-static __device__ __attribute__((noinline)) void few_again(uint32_t args_lo, uint32_t args_hi, int j0, __attribute__((address_space(3))) char *lds,
-                                                           __attribute__((address_space(3))) int *tab)
+struct FewWords { uint32_t w[sizeof(FewParams) / 4]; };
+// The kernel's parameters, read again
+__device__ __forceinline__ FewParams few_args()
 {
     typedef const __attribute__((address_space(4))) uint32_t *Words;
-    const Words from = (Words)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)args_hi) << 32 | (uint32_t)__builtin_amdgcn_readfirstlane((int)args_lo));
-    struct { uint32_t w[sizeof(FewParams) / 4]; } t;
+    Words from = (Words)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(from));
+    FewWords t;
 #pragma unroll
     for (size_t i = 0; i < sizeof(FewParams) / 4; ++i) t.w[i] = from[i];
-    few_tile<E, true>(__builtin_bit_cast(FewParams, t), __builtin_amdgcn_readfirstlane(j0), (char *)lds, (int *)tab);
+    return __builtin_bit_cast(FewParams, t);
 }
 
 template <class E>
@@ -427,9 +427,20 @@ __global__ __launch_bounds__(512, 2) void conv_few_kernel(FewParams p)
     __shared__ __attribute__((aligned(16))) char lds[kFewLds];
     __shared__ int tab[kFewTaps];
     const int j0 = (int)xcd_order(blockIdx.x, gridDim.x) * kFewN;
-    if (!few_tile<E, false>(p, j0, lds, tab)) return;
-    const uint64_t args = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
-    few_again<E>((uint32_t)args, (uint32_t)(args >> 32), j0, (__attribute__((address_space(3))) char *)lds, (__attribute__((address_space(3))) int *)tab);
+    // The parameters in registers one by one: as they are loaded, sixteen at a time, they are also kept and spilled sixteen at a time.
+    FewWords t = __builtin_bit_cast(FewWords, p);
+#pragma unroll
+    for (uint32_t &w : t.w) {
+        uint32_t own;
+        asm volatile("s_mov_b32 %0, %1" : "=s"(own) : "s"(w));
+        w = own;
+    }
+    FewParams q = __builtin_bit_cast(FewParams, t);
+    q.in = p.in; q.w = p.w; q.out = p.out;
+    if (__builtin_expect(!few_tile<E, false>(q, j0, lds, tab), 1)) return;
+    int again = j0;
+    asm volatile("" : "+s"(again));
+    few_tile<E, true>(few_args(), again, lds, tab);
 }
 
 }  // namespace ucd
