@@ -316,7 +316,8 @@ __device__ __forceinline__ bool few_tile(const FewParams &p, int j0, char *lds, 
     typedef std::integral_constant<int, kPlain> Plain;
     typedef std::integral_constant<int, kFinite> Other;
     float y[16];
-    int &flag = *reinterpret_cast<int *>(lds + kFewLds - 16);   // (only split operands reach so far)
+    // (Only split operands reach so far.  A word for each of the two ways: a wave may begin the second while others read the first's.)
+    int &flag = *reinterpret_cast<int *>(lds + kFewLds - (AGAIN ? 12 : 16));
     if constexpr (!AGAIN) {
         if (!F32) flag = 0;
         pass(Split{});
